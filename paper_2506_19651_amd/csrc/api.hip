@@ -278,7 +278,7 @@ static int32_t auto_splits(const pevlm_layout *lay, const pevlm_heads *h)
     const int32_t tile_rows = tile_rows_of(h, true);
     const int32_t G = h->n_q_heads / h->n_kv_heads;
     // workgroups per split: one per (row tile, head); the bf16 kernel takes tiles of <= 64 rows
-    // for 2 or 4 heads of a KV group at once
+    // for 2 or 4 heads of a KV group at once, the fp32 kernel two heads
     int64_t units = 0, max_len = 0, min_len = INT64_MAX;
     for (int32_t s = 0; s < lay->num_seqs; ++s) {
         if (lay->query_len[s] == 0) continue;
@@ -287,7 +287,7 @@ static int32_t auto_splits(const pevlm_layout *lay, const pevlm_heads *h)
         for (int32_t r0 = 0; r0 < lay->query_len[s]; r0 += tile_rows) {
             int32_t rows = std::min(tile_rows, lay->query_len[s] - r0);
             int32_t hpw = 1;
-            if (h->dtype == PEVLM_BF16 && G > 1 && !h->kv_head_of_q) hpw = rows <= 32 ? 4 : (rows <= 64 ? 2 : 1);
+            if (G > 1 && !h->kv_head_of_q) hpw = h->dtype == PEVLM_F32 ? 2 : rows <= 32 ? 4 : (rows <= 64 ? 2 : 1);
             units += (int64_t)h->n_kv_heads * ((G + hpw - 1) / hpw);
         }
     }
@@ -298,7 +298,9 @@ static int32_t auto_splits(const pevlm_layout *lay, const pevlm_heads *h)
     // a badly filled round, or sequences of very different length (every sequence gets the same
     // number of splits, so the long ones set the pace): take two rounds of finer pieces
     if (want * units * 4 < slots * 3 || 2 * min_len < max_len) want = (2 * slots) / units;
-    const int64_t cap = std::max<int64_t>(1, max_len / 768);
+    // the fp32 kernel's workgroups are finer (16 rows, two key tiles per wavefront at 256 keys): 0.052 ms for 64
+    // question rows over 2.4 K keys at 3 splits, 0.047 ms at 8
+    const int64_t cap = std::max<int64_t>(1, max_len / (h->dtype == PEVLM_F32 ? 256 : 768));
     return (int32_t)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, cap), PEVLM_MAX_SPLITS));
 }
 
@@ -549,7 +551,7 @@ static pevlm_status prefill_impl(const void *q, const void *k, const void *v, vo
     p.n_kv_heads = heads->n_kv_heads;
     p.scale = scale_of(heads);
     hipError_t e = heads->dtype == PEVLM_BF16 ? launch_attn_bf16(p, heads->head_dim, false, hs)
-                                                : launch_attn_f32(p, heads->head_dim, false, hs);
+                                                : launch_attn_f32(p, heads->head_dim, false, compute_units(), hs);
     if (e != hipSuccess) return hip_fail(e, "block-prefill launch");
     return PEVLM_OK;
 }
@@ -778,7 +780,7 @@ static pevlm_status query_impl(const void *q, const void *k, const void *v, void
     p.n_kv_heads = heads->n_kv_heads;
     p.scale = scale_of(heads);
     hipError_t e = heads->dtype == PEVLM_BF16 ? launch_attn_bf16(p, heads->head_dim, true, hs)
-                                              : launch_attn_f32(p, heads->head_dim, true, hs);
+                                              : launch_attn_f32(p, heads->head_dim, true, compute_units(), hs);
     if (e != hipSuccess) return hip_fail(e, "query split launch");
     MergeParams m;
     m.part_acc = acc; m.part_ml = ml; m.qrow_of_compact = qrow; m.out = out; m.lse = lse;

@@ -374,7 +374,7 @@ hipError_t launch_fp8_quantise(const void *q, const void *k, const void *v, int6
                                float q_factor, const pevlm_work_item *key_tiles, int32_t n_key_tiles, uint32_t *kv_amax, float *q_scales,
                                uint8_t *q_codes, uint8_t *k_tiles, uint8_t *v_tiles, int32_t compute_units, hipStream_t stream);
 hipError_t launch_attn_fp8(const Fp8Params &p, int32_t D, hipStream_t stream);
-hipError_t launch_attn_f32(const AttnParams &p, int32_t D, bool partial, hipStream_t stream);
+hipError_t launch_attn_f32(const AttnParams &p, int32_t D, bool partial, int32_t compute_units, hipStream_t stream);
 hipError_t launch_attn_bf16(const AttnParams &p, int32_t D, bool partial, hipStream_t stream);  // p.rope_tab selects the fused variant
 hipError_t launch_merge(const MergeParams &p, hipStream_t stream);
 hipError_t launch_probe_mfma(float *sink, int32_t workgroups, int32_t iters, hipStream_t stream);
