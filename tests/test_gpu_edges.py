@@ -34,3 +34,19 @@ def test_fp32_kernel_edges(oracle, name, Hq, Hkv, D, seqs, splits):
     print(name, error_stats(got, want))
     assert np.max(np.abs(got - want)) <= F32_TOL
     assert np.max(np.abs(to_host_f32(r["lse"]) - want_lse)) <= 1e-4
+
+
+@pytest.mark.parametrize("splits", [2, 3, 7, 8, 9, 16, 33, 63, 64])
+@pytest.mark.parametrize("dtype,Hq,Hkv,D", [("f32", 3, 1, 64), ("f32", 3, 1, 128), ("bf16", 6, 2, 64), ("bf16", 5, 5, 128)])
+def test_merge_of_any_number_of_splits(oracle, dtype, Hq, Hkv, D, splits):
+    """1-64 splits of question rows, more of them than key tiles included (splits without a key)."""
+    w = W.Workload(f"merge{splits}", 32, dtype, Hq, Hkv, D, 1.0e4, [(30, 70, 200, 9), (0, 1, 0, 3), (5, 600, 1200, 33)], 0.5)
+    data = W.generate(w)
+    r = run_path(w, data, num_splits=splits, want_lse=True)
+    want, want_lse = oracle.forward(data["q"], data["k"], data["v"], oracle_layout(oracle, w), w.rope_base)
+    st = error_stats(to_host_f32(r["out"]), want)
+    lse_err = np.max(np.abs(to_host_f32(r["lse"]) - want_lse))
+    if dtype == "f32":
+        assert st["max_abs"] <= F32_TOL and lse_err <= 1e-4, st
+    else:
+        assert st["max_abs"] <= 2e-2 and st["mean_abs"] <= 2e-3 and lse_err <= 2e-2, st
