@@ -155,6 +155,49 @@ static void fill_table(const pevlm_layout *lay, int32_t s0, int32_t n, const int
     }
 }
 
+// The same for a launch that forms its items itself (mode 1: prefill, 2: question); returns false (mode 0: the
+// list is built first) for more sequences or workgroups than that pays for.
+static bool fill_inline_items(const pevlm_layout *lay, int32_t mode, int64_t workgroups, int32_t tile_rows, int32_t num_splits,
+                              int32_t total_q_rows, const Restrict &r, InlineItems *t)
+{
+    memset(t, 0, sizeof *t);
+    if (lay->num_seqs > kInlineSeqs || workgroups > kInlineWorkgroups) return false;
+    SeqTable tab;
+    fill_table(lay, 0, lay->num_seqs, nullptr, &tab, r);
+    t->mode = mode;
+    t->num_seqs = lay->num_seqs;
+    t->tile_rows = tile_rows;
+    t->total_q_rows = total_q_rows;
+    t->windowed = tab.windowed;
+    t->num_splits = num_splits;
+    t->splits_rcp = reciprocal_of(num_splits);
+    int32_t items = 0, rows = 0;
+    for (int32_t i = 0; i < lay->num_seqs; ++i) {
+        const int32_t S = tab.sink[i], B = tab.block[i], C = tab.ctx[i], Q = tab.query[i];
+        t->start[i] = tab.start[i];
+        t->sink[i] = S;
+        t->block[i] = B;
+        t->ctx[i] = C;
+        t->query[i] = Q;
+        t->item_base[i] = items;
+        if (mode == 1) {
+            t->sink_items[i] = tab.sel_sink ? ceil_div(S, tile_rows) : 0;
+            t->first_block[i] = tab.sel_first[i];
+            t->per_block[i] = ceil_div(B, tile_rows);
+            t->per_block_rcp[i] = reciprocal_of(t->per_block[i]);
+            items += prefill_items_of_seq_sel(S, B, C, tile_rows, tab.sel_first[i], tab.sel_count[i], tab.sel_sink);
+        } else {
+            t->qrow_base[i] = rows;
+            t->win_start[i] = tab.win_start[i];
+            t->split_len[i] = tab.windowed ? split_len_of_seq(S + C + Q - tab.win_start[i], num_splits - 1, kKeyTile)
+                                           : split_len_of_seq(S + C + Q, num_splits, kKeyTile);
+            items += query_tiles_of_seq(Q, tile_rows) * num_splits;
+            rows += Q;
+        }
+    }
+    return true;
+}
+
 static int64_t count_prefill_items(const pevlm_layout *lay, int32_t tile_rows, const Restrict &r = Restrict())
 {
     int64_t n = 0;
@@ -520,22 +563,24 @@ static pevlm_status prefill_impl(const void *q, const void *k, const void *v, vo
                                          true, rope_base, ax.pos_ids, ax.sec0, ax.sec01, rope_tab, hs);
         if (e != hipSuccess) return hip_fail(e, "mrope launch");
     }
+    const bool inlined = fill_inline_items(layout, 1, n_items * heads->n_q_heads, tile_rows, 0, 0, sel, &p.inline_items);
     int32_t offset = 0;
     for (int32_t s0 = 0; s0 < layout->num_seqs; s0 += kMaxSeqsPerLaunch) {
+        if (inlined && !fuse_rope) break;
         SeqTable tab;
         int32_t n = std::min(kMaxSeqsPerLaunch, layout->num_seqs - s0);
         fill_table(layout, s0, n, pos_offset, &tab, sel);
         for (int32_t i = 0; i < n; ++i)
             tab.item_base[i + 1] = tab.item_base[i] + prefill_items_of_seq_sel(tab.sink[i], tab.block[i], tab.ctx[i], tile_rows,
                                                                                tab.sel_first[i], tab.sel_count[i], tab.sel_sink);
-        if (tab.item_base[n] > 0) {
+        if (tab.item_base[n] > 0 && !inlined) {
             hipError_t e = launch_build_prefill_items(tab, tile_rows, items, offset, hs);
             if (e != hipSuccess) return hip_fail(e, "work-list builder launch");
         }
         if (fuse_rope && !(ax.pos_ids && rotate_k)) {  // table entries = packed rows of this chunk's sequences
             hipError_t e = rotate_k ? launch_rope(nullptr, const_cast<void *>(k), tab, heads->n_q_heads, heads->n_kv_heads,
                                                   heads->head_dim, true, rope_base, rope_tab, hs)
-                                    : launch_rope_table(rope_tab, nullptr, tab, heads->head_dim, rope_base,
+                                    : launch_rope_table(rope_tab, false, tab, heads->head_dim, rope_base,
                                                         layout->cu_seqlens[s0], layout->cu_seqlens[s0 + n], ax.pos_ids, T,
                                                         ax.sec0, ax.sec01, hs);
             if (e != hipSuccess) return hip_fail(e, "rope table launch");
@@ -746,8 +791,11 @@ static pevlm_status query_impl(const void *q, const void *k, const void *v, void
     float *ml = (float *)(ws + plan.off_ml);
     float *acc = (float *)(ws + plan.off_acc);
     float *rope_tab = (float *)(ws + plan.off_rope);
+    const bool inlined = fill_inline_items(layout, 2, plan.n_items * heads->n_q_heads, plan.tile_rows, plan.num_splits,
+                                           (int32_t)plan.total_q, sel, &p.inline_items);
     int32_t item_offset = 0, qrow_base = 0;
     for (int32_t s0 = 0; s0 < layout->num_seqs; s0 += kMaxSeqsPerLaunch) {
+        if (inlined && !fuse_rope) break;
         SeqTable tab;
         int32_t n = std::min(kMaxSeqsPerLaunch, layout->num_seqs - s0);
         fill_table(layout, s0, n, pos_offset, &tab, sel);
@@ -758,11 +806,11 @@ static pevlm_status query_impl(const void *q, const void *k, const void *v, void
             qrow_base += tab.query[i];
         }
         if (tab.item_base[n] > 0) {
-            hipError_t e = launch_build_query_items(tab, plan.tile_rows, plan.num_splits, (int32_t)plan.total_q,
-                                                    kKeyTile, items, item_offset, qrow, hs);
+            hipError_t e = inlined ? hipSuccess : launch_build_query_items(tab, plan.tile_rows, plan.num_splits, (int32_t)plan.total_q,
+                                                                           kKeyTile, items, item_offset, qrow, hs);
             if (e != hipSuccess) return hip_fail(e, "query work-list builder launch");
-            if (fuse_rope) {  // table entries = compact question rows of this chunk (mapped through qrow)
-                e = launch_rope_table(rope_tab, qrow, tab, heads->head_dim, rope_base, entry_begin, qrow_base, ax.pos_ids,
+            if (fuse_rope) {  // table entries = compact question rows of this chunk
+                e = launch_rope_table(rope_tab, true, tab, heads->head_dim, rope_base, entry_begin, qrow_base, ax.pos_ids,
                                       layout->cu_seqlens[layout->num_seqs], ax.sec0, ax.sec01, hs);
                 if (e != hipSuccess) return hip_fail(e, "rope table launch");
             }
@@ -779,11 +827,16 @@ static pevlm_status query_impl(const void *q, const void *k, const void *v, void
     p.n_q_heads = heads->n_q_heads;
     p.n_kv_heads = heads->n_kv_heads;
     p.scale = scale_of(heads);
-    hipError_t e = heads->dtype == PEVLM_BF16 ? launch_attn_bf16(p, heads->head_dim, true, hs)
-                                              : launch_attn_f32(p, heads->head_dim, true, compute_units(), hs);
+    // a single split is the whole softmax: the attention kernel writes the rows itself and nothing is merged
+    const bool partial = plan.num_splits > 1;
+    p.out = out;
+    p.lse = lse;
+    hipError_t e = heads->dtype == PEVLM_BF16 ? launch_attn_bf16(p, heads->head_dim, partial, hs)
+                                              : launch_attn_f32(p, heads->head_dim, partial, compute_units(), hs);
     if (e != hipSuccess) return hip_fail(e, "query split launch");
+    if (!partial) return PEVLM_OK;
     MergeParams m;
-    m.part_acc = acc; m.part_ml = ml; m.qrow_of_compact = qrow; m.out = out; m.lse = lse;
+    m.part_acc = acc; m.part_ml = ml; m.qrow_of_compact = inlined ? nullptr : qrow; m.seqs = p.inline_items; m.out = out; m.lse = lse;
     m.total_q_rows = (int32_t)plan.total_q;
     m.num_splits = plan.num_splits;
     m.n_q_heads = heads->n_q_heads;

@@ -48,7 +48,13 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
     // ends on short items has a shorter tail
     const int32_t item_idx = p.n_items - 1 - rest % p.n_items;
     const int32_t hs = (rest / p.n_items) * heads_inner + inner;
-    const pevlm_work_item it = p.items[item_idx];
+    pevlm_work_item it;
+    if (p.inline_items.mode) {
+        it = inline_item(p.inline_items, item_idx);
+        if (hs == 0 && threadIdx.x == 0) p.items[item_idx] = it;
+    } else {
+        it = p.items[item_idx];
+    }
     // With the default head map (query head h on KV head h / G, schedule order = head order) both
     // indices are plain arithmetic; the tables live in kernel-argument memory and looking them up
     // costs two dependent memory round trips before the first query row can be requested.

@@ -369,7 +369,13 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(AttnParams p, int32_t 
     const int32_t group = outer / p.n_items, j = outer % p.n_items;
     const int32_t full = p.n_items / stride * stride;  // items dealt out in `stride` runs; the few others come last
     const int32_t idx = p.n_items - 1 - (j < full ? j % (full / stride) * stride + j / (full / stride) : j);
-    const pevlm_work_item it = p.items[idx];
+    pevlm_work_item it;
+    if (p.inline_items.mode) {
+        it = inline_item(p.inline_items, idx);
+        if (group == 0 && u == 0 && threadIdx.x == 0) p.items[idx] = it;
+    } else {
+        it = p.items[idx];
+    }
     if (pairs) {
         const int32_t G = p.n_q_heads / p.n_kv_heads;
         const int32_t h[2] = {p.heads.head_order[group * G + 2 * u], p.heads.head_order[group * G + (2 * u + 1 < G ? 2 * u + 1 : 2 * u)]};

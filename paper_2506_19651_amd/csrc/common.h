@@ -282,6 +282,93 @@ __host__ __device__ inline pevlm_work_item query_item_window(int32_t start, int3
 }
 
 // ------------------------------------------------------------------------------------------
+// Work items formed by the attention kernel itself.  A launch of its own for the list costs 4-5 us, as
+// much as a small attention kernel; evaluating the closed form costs each workgroup a few hundred cycles
+// of scalar arithmetic.  So launches of at most kInlineWorkgroups over at most kInlineSeqs sequences carry
+// the table (it is short enough not to lengthen the kernel arguments noticeably) and larger ones read the list.
+// ------------------------------------------------------------------------------------------
+constexpr int32_t kInlineSeqs = 4;
+constexpr int32_t kInlineWorkgroups = 8192;
+struct InlineItems {
+    int32_t mode;  // 0: read the list, 1: prefill items, 2: question items
+    int32_t num_seqs, tile_rows, total_q_rows, windowed;
+    int32_t num_splits;
+    uint32_t splits_rcp;                                                // for / num_splits
+    int32_t start[kInlineSeqs], sink[kInlineSeqs], block[kInlineSeqs], ctx[kInlineSeqs], query[kInlineSeqs];
+    int32_t item_base[kInlineSeqs];
+    int32_t sink_items[kInlineSeqs], first_block[kInlineSeqs], per_block[kInlineSeqs];  // prefill: selected sink items, first block, items of a block
+    uint32_t per_block_rcp[kInlineSeqs];                                // for / per_block
+    int32_t qrow_base[kInlineSeqs], win_start[kInlineSeqs], split_len[kInlineSeqs];     // question
+};
+
+// n / d as a multiplication: exact while n * d < 2^32
+inline uint32_t reciprocal_of(int32_t d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
+__device__ inline int32_t div_by(int32_t n, uint32_t rcp) { return rcp ? (int32_t)__umulhi((uint32_t)n, rcp) : n; }
+
+// Item idx of the launch: prefill_item_sel, query_item or query_item_window of its sequence, with every quotient
+// that does not depend on idx taken on the host (an integer division costs a wavefront some 40 instructions).
+__device__ inline pevlm_work_item inline_item(const InlineItems &t, int32_t idx)
+{
+    int32_t s = 0;
+#pragma unroll
+    for (int32_t i = 1; i < kInlineSeqs; ++i)
+        if (i < t.num_seqs && idx >= t.item_base[i]) s = i;
+    const int32_t k = idx - t.item_base[s], start = t.start[s], S = t.sink[s], C = t.ctx[s];
+    pevlm_work_item it;
+    it.seq = s;
+    it.full_start = start;
+    if (t.mode == 1) {
+        const int32_t j = k - t.sink_items[s];
+        const bool in_sink = j < 0;
+        const int32_t b = div_by(in_sink ? 0 : j, t.per_block_rcp[s]);
+        const int32_t block = t.first_block[s] + b;
+        const int32_t r0 = (in_sink ? k : j - b * t.per_block[s]) * t.tile_rows;
+        const int32_t rs = in_sink ? 0 : S + block * t.block[s];                                               // region of the rows
+        const int32_t len = in_sink ? S : (C - block * t.block[s] < t.block[s] ? C - block * t.block[s] : t.block[s]);
+        it.reserved = 0;
+        it.q_start = start + rs + r0;
+        it.q_rows = len - r0 < t.tile_rows ? len - r0 : t.tile_rows;
+        it.full_len = in_sink ? 0 : S;
+        it.diag_start = start + rs;
+        it.diag_len = r0 + it.q_rows;
+        return it;
+    }
+    const int32_t tile = div_by(k, t.splits_rcp), split = k - tile * t.num_splits;
+    const int32_t r0 = tile * t.tile_rows, qb = S + C;
+    it.q_start = start + qb + r0;
+    it.q_rows = t.query[s] - r0 < t.tile_rows ? t.query[s] - r0 : t.tile_rows;
+    it.reserved = split * t.total_q_rows + t.qrow_base[s] + r0;
+    if (t.windowed && split == 0) {
+        it.full_len = S;
+        it.diag_start = start + qb;
+        it.diag_len = 0;
+        return it;
+    }
+    const int32_t last_key = qb + r0 + it.q_rows;
+    int32_t lo = t.windowed ? t.win_start[s] + (split - 1) * t.split_len[s] : split * t.split_len[s], hi = lo + t.split_len[s];
+    hi = hi < last_key ? hi : last_key;
+    lo = lo < hi ? lo : hi;
+    const int32_t full_hi = hi < qb ? hi : qb, full_lo = lo < full_hi ? lo : full_hi;
+    int32_t diag_lo = lo > qb ? lo : qb;
+    diag_lo = diag_lo < hi ? diag_lo : hi;
+    it.full_start = start + full_lo;
+    it.full_len = full_hi - full_lo;
+    it.diag_start = start + diag_lo;
+    it.diag_len = hi - diag_lo;
+    return it;
+}
+
+// packed row of the compact question row r
+__device__ inline int32_t inline_question_row(const InlineItems &t, int32_t r)
+{
+    int32_t s = 0;
+#pragma unroll
+    for (int32_t i = 1; i < kInlineSeqs; ++i)
+        if (i < t.num_seqs && r >= t.qrow_base[i]) s = i;
+    return t.start[s] + t.sink[s] + t.ctx[s] + r - t.qrow_base[s];
+}
+
+// ------------------------------------------------------------------------------------------
 // Kernel parameter blocks
 // ------------------------------------------------------------------------------------------
 struct AttnParams {
@@ -290,10 +377,11 @@ struct AttnParams {
     float *lse;                     // final mode: [T][Hq] or nullptr
     float *part_acc;                // partial mode: [slots][Hq][D] unnormalised weighted values
     float *part_ml;                 // partial mode: [slots][Hq][2] (running max of raw scores, sum)
-    const pevlm_work_item *items;
+    pevlm_work_item *items;         // read, or (inline_items.mode != 0) written by the workgroups of the first head
     int32_t n_items;
     int32_t n_q_heads, n_kv_heads;
     float scale;                    // softmax scale
+    InlineItems inline_items;
     // fused query rotation (bf16 kernels): q holds un-rotated queries and rope_tab (cos, sin) pairs
     // [entries][head_dim/2]; the entry of a row is its packed row (rope_compact_rows == 0) or its
     // compact question row (item.reserved % rope_compact_rows + row in tile).  NULL: q is rotated.
@@ -339,7 +427,8 @@ struct Fp8Params {
 
 struct MergeParams {
     const float *part_acc, *part_ml;
-    const int32_t *qrow_of_compact;  // [total_q_rows] packed row of each compact question row
+    const int32_t *qrow_of_compact;  // [total_q_rows] packed row of each compact question row, or NULL: from `seqs`
+    InlineItems seqs;
     void *out;
     float *lse;
     int32_t total_q_rows, num_splits, n_q_heads, head_dim;
@@ -359,7 +448,8 @@ hipError_t launch_build_query_items(const SeqTable &tab, int32_t tile_rows, int3
 hipError_t launch_rope(void *q, void *k, const SeqTable &tab, int32_t Hq, int32_t Hkv, int32_t D, bool bf16,
                        double rope_base, float *table, hipStream_t stream);
 // pos3 != NULL: three-axis ids [3][T] (device) with sections [0, sec0), [sec0, sec01), [sec01, D/2)
-hipError_t launch_rope_table(float *table, const int32_t *row_of_entry, const SeqTable &tab, int32_t D, double rope_base,
+// question: entries are the compact question rows of the chunk's sequences, otherwise packed rows
+hipError_t launch_rope_table(float *table, bool question, const SeqTable &tab, int32_t D, double rope_base,
                              int32_t entry_begin, int32_t entry_end, const int32_t *pos3, int64_t T, int32_t sec0, int32_t sec01,
                              hipStream_t stream);
 hipError_t launch_rope_mrope(void *q, void *k, int64_t T, int32_t Hq, int32_t Hkv, int32_t D, bool bf16, double rope_base,

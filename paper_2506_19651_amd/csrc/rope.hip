@@ -119,11 +119,11 @@ __global__ __launch_bounds__(256) void rope_kernel(void *q, void *k, SeqTable ta
 }
 
 // cos/sin table for the query rotation fused into the bf16 attention kernel: entry e holds, for
-// every pair index i, (cos, sin) of the angle of packed row row_of_entry[e] (e itself when
-// row_of_entry is NULL).  Same arithmetic as rope_kernel, so a query rotated from the table gets the
+// every pair index i, (cos, sin) of the angle of packed row e (of the e-th question row of the batch when
+// `question` is set).  Same arithmetic as rope_kernel, so a query rotated from the table gets the
 // bits pevlm_rope_seq would have stored.  One thread per (entry, 8 pair indices).
 template <int D>
-__global__ __launch_bounds__(256) void rope_table_kernel(float2 *table, const int32_t *row_of_entry, SeqTable tab, RopeFreq fr,
+__global__ __launch_bounds__(256) void rope_table_kernel(float2 *table, int32_t question, SeqTable tab, RopeFreq fr,
                                                          int32_t entry_begin, int32_t entry_end, const int32_t *pos3, int64_t T,
                                                          int32_t sec0, int32_t sec01)
 {
@@ -131,7 +131,12 @@ __global__ __launch_bounds__(256) void rope_table_kernel(float2 *table, const in
     const int32_t e = entry_begin + (blockIdx.x * 256 + threadIdx.x) / LANES_PER_ENTRY;
     if (e >= entry_end) return;
     const int32_t i0 = (threadIdx.x % LANES_PER_ENTRY) * 8;
-    const int32_t row = row_of_entry ? row_of_entry[e] : e;
+    int32_t row = e;
+    if (question) {
+        int32_t s = 0;
+        while (s + 1 < tab.num_seqs && e >= tab.qrow_base[s + 1]) ++s;
+        row = tab.start[s] + tab.sink[s] + tab.ctx[s] + e - tab.qrow_base[s];
+    }
     double pos_axis[3];
     if (pos3) {  // three position axes: pair index i takes the id of the axis whose section holds it
 #pragma unroll
@@ -153,7 +158,7 @@ __global__ __launch_bounds__(256) void rope_table_kernel(float2 *table, const in
     }
 }
 
-hipError_t launch_rope_table(float *table, const int32_t *row_of_entry, const SeqTable &tab, int32_t D, double rope_base,
+hipError_t launch_rope_table(float *table, bool question, const SeqTable &tab, int32_t D, double rope_base,
                              int32_t entry_begin, int32_t entry_end, const int32_t *pos3, int64_t T, int32_t sec0, int32_t sec01,
                              hipStream_t stream)
 {
@@ -162,8 +167,8 @@ hipError_t launch_rope_table(float *table, const int32_t *row_of_entry, const Se
     for (int i = 0; i < 64; ++i) fr.inv_freq[i] = i < D / 2 ? pow(rope_base, -2.0 * (double)i / (double)D) : 0.0;
     const int32_t per_block = 256 / (D / 16);
     dim3 grid((entry_end - entry_begin + per_block - 1) / per_block);
-    if (D == 128) hipLaunchKernelGGL((rope_table_kernel<128>), grid, dim3(256), 0, stream, (float2 *)table, row_of_entry, tab, fr, entry_begin, entry_end, pos3, T, sec0, sec01);
-    else hipLaunchKernelGGL((rope_table_kernel<64>), grid, dim3(256), 0, stream, (float2 *)table, row_of_entry, tab, fr, entry_begin, entry_end, pos3, T, sec0, sec01);
+    if (D == 128) hipLaunchKernelGGL((rope_table_kernel<128>), grid, dim3(256), 0, stream, (float2 *)table, question ? 1 : 0, tab, fr, entry_begin, entry_end, pos3, T, sec0, sec01);
+    else hipLaunchKernelGGL((rope_table_kernel<64>), grid, dim3(256), 0, stream, (float2 *)table, question ? 1 : 0, tab, fr, entry_begin, entry_end, pos3, T, sec0, sec01);
     return hipGetLastError();
 }
 

@@ -150,7 +150,8 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeParams p)
     }
     if (sub != 0) return;
     const float inv = 1.f / denom;
-    const int32_t row = p.qrow_of_compact[unit / p.n_q_heads];
+    const int32_t cr = (int32_t)(unit / p.n_q_heads);
+    const int32_t row = p.qrow_of_compact ? p.qrow_of_compact[cr] : inline_question_row(p.seqs, cr);
     const int32_t h = (int32_t)(unit % p.n_q_heads);
     const int64_t o = ((int64_t)row * p.n_q_heads + h) * D + d4;
     if (p.is_bf16) {

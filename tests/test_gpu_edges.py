@@ -50,3 +50,37 @@ def test_merge_of_any_number_of_splits(oracle, dtype, Hq, Hkv, D, splits):
         assert st["max_abs"] <= F32_TOL and lse_err <= 1e-4, st
     else:
         assert st["max_abs"] <= 2e-2 and st["mean_abs"] <= 2e-3 and lse_err <= 2e-2, st
+
+
+@pytest.mark.parametrize("n_seqs", [1, 4, 5])
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("bf16", 128)])
+@pytest.mark.parametrize("splits", [1, 4])
+def test_items_formed_in_the_kernel_or_read_from_the_list(oracle, dtype, D, n_seqs, splits):
+    """Up to four sequences the attention kernel forms its work items itself, beyond that it reads a built list; the
+    workspace holds the enumeration either way.  One split writes the rows directly, several are merged."""
+    seqs = [(20, 50, 130, 7), (0, 33, 90, 0), (3, 1, 0, 40), (70, 64, 64, 1), (9, 200, 150, 12)][:n_seqs]
+    w = W.Workload(f"inline{n_seqs}", 33, dtype, 4, 2, D, 1.0e4, seqs, 0.5)
+    data = W.generate(w)
+    lay, heads = layout_heads(w)
+    q, k, v = to_device(data["q"]), to_device(data["k"]), to_device(data["v"])
+    out = torch.full_like(q, float("nan"))
+    lse = torch.full((w.total_tokens, 4), float("nan"), device=DEV)
+    offs = [11 * i for i in range(n_seqs)]
+    P.pevlm_rope_seq(q, k, lay, heads, w.rope_base, offs)
+    ws_p = P.pevlm_block_prefill_attn(q, k, v, out, lay, heads, lse=lse)
+    ws_q = P.pevlm_query_attn(q, k, v, out, lay, heads, num_splits=splits, lse=lse)
+    torch.cuda.synchronize()
+    for ws, host in ((ws_p, P.pevlm_prefill_worklist_host(lay, P.pevlm_prefill_tile_rows(heads))),
+                     (ws_q, P.pevlm_query_worklist_host(lay, P.pevlm_query_tile_rows(heads), splits))):
+        want_list = b"".join(bytes(it) for it in host)
+        assert ws.cpu().numpy()[:len(want_list)].tobytes() == want_list
+    want, want_lse = oracle.forward(data["q"], data["k"], data["v"], oracle_layout(oracle, w), w.rope_base, pos_offset=offs)
+    st = error_stats(to_host_f32(out), want)
+    lse_err = np.max(np.abs(to_host_f32(lse) - want_lse))
+    assert st["max_abs"] <= (F32_TOL if dtype == "f32" else 2e-2) and lse_err <= (1e-4 if dtype == "f32" else 2e-2), st
+    if dtype == "bf16":  # the question rows with their rotation folded in: the same bits
+        q_raw, out2 = to_device(data["q"]), torch.zeros_like(out)
+        P.pevlm_query_attn_rope(q_raw, k, v, out2, lay, heads, w.rope_base, offs, num_splits=splits)
+        for lo, (S, _B, C, Q) in zip(lay.cu, seqs):
+            a = int(lo) + S + C
+            assert torch.equal(out2[a:a + Q].view(torch.int16), out[a:a + Q].view(torch.int16))
