@@ -32,25 +32,24 @@ STREAM_US_PER_ITEM = 3.48
 STREAM_US_PER_TILE = 1.778
 US_PER_WORKGROUP = 6.1
 US_PER_WORKGROUP_TILE = 1.865
-_TILE_ROWS, _KEY_TILE = 128, 64
+_TILE_ROWS, _KEY_TILE, _PAIRS = 128, 64, 128
 
 
 def prefill_work(layout: Layout, heads: Heads):
     """(workgroups, workgroup key tiles) of the one-item-per-workgroup kernel, from the same host
-    enumeration the library offers (items of <= 64 rows are taken for 2 or 4 heads of a KV group by
-    one workgroup)."""
+    enumeration the library offers: 128 (row, query head) pairs of an item and KV head per workgroup (one
+    head at a time under a head map), which stages the tiles up to its own last row."""
     from .binding import pevlm_prefill_worklist_host
 
-    G = heads.n_q_heads // heads.n_kv_heads
-    packs = G > 1 and heads.map is None
+    G = heads.n_q_heads // heads.n_kv_heads if heads.map is None else 1
+    groups = heads.n_q_heads // G
     n_wg = n_tiles = 0
     for it in pevlm_prefill_worklist_host(layout, _TILE_ROWS):
-        tiles = -(-it.full_len // _KEY_TILE) + -(-it.diag_len // _KEY_TILE)
-        groups32 = -(-it.q_rows // 32)
-        hpw = (4 if groups32 <= 1 else 2 if groups32 <= 2 else 1) if packs else 1
-        wgs = heads.n_kv_heads * -(-G // hpw)
-        n_wg += wgs
-        n_tiles += wgs * tiles
+        pairs, full = it.q_rows * G, -(-it.full_len // _KEY_TILE)
+        for first in range(0, pairs, _PAIRS):
+            last_row = it.q_start + (min(first + _PAIRS, pairs) - 1) // G
+            n_wg += groups
+            n_tiles += groups * (full + (last_row - it.diag_start) // _KEY_TILE + 1)
     return n_wg, n_tiles
 
 

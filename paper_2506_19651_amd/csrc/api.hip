@@ -208,6 +208,21 @@ static int64_t count_prefill_items(const pevlm_layout *lay, int32_t tile_rows, c
     return n;
 }
 
+// rows of the longest work item: of the block-prefill call, of the question call
+static int32_t max_prefill_rows(const pevlm_layout *lay, int32_t tile_rows, const Restrict &r)
+{
+    int32_t n = 0;
+    for (int32_t s = 0; s < lay->num_seqs; ++s) {
+        if (r.with_sink) n = std::max(n, lay->sink_len[s]);
+        if (lay->ctx_len[s] > 0 && (!r.num_blocks || r.num_blocks[s] > 0)) n = std::max(n, std::min(lay->block_len[s], lay->ctx_len[s]));
+    }
+    return std::min(n, tile_rows);
+}
+static int32_t max_query_rows(const pevlm_layout *lay, int32_t tile_rows)
+{
+    return std::min(tile_rows, *std::max_element(lay->query_len, lay->query_len + lay->num_seqs));
+}
+
 static int64_t count_query_tiles(const pevlm_layout *lay, int32_t tile_rows)
 {
     int64_t n = 0;
@@ -312,39 +327,83 @@ static int32_t compute_units()
     return have;
 }
 
-// Split count when the caller leaves it to the library: the split kernel keeps two workgroups per
-// compute unit, so the number of workgroups (row tiles x heads x splits) is brought as close as
-// possible to one or two full rounds of 2 x CUs from below, with no split of the longest sequence shorter than 768 keys (measured sweet spots: 18 splits at
-// 64K tokens x 28 heads, 8 at 100K x 2 tiles x 32 heads).
-static int32_t auto_splits(const pevlm_layout *lay, const pevlm_heads *h)
+// Split count when the caller leaves it to the library.
+//
+// fp32: workgroups (16 rows x two heads x split) are brought as close as possible to one or two full rounds of 2
+// x CUs from below, with at least 256 keys per split (64 question rows over 2.4 K keys: 0.047 ms at 8
+// splits, 0.052 ms at 3).
+//
+// bf16: the count with the least predicted time.  A workgroup (128 (row, head) pairs x split) takes 6 us plus a
+// time per key tile that depends on how full the compute units are, workgroups run in rounds of two per
+// compute unit, and every split adds partials to write and merge.  Fitted to a sweep over 26 (heads,
+// layout, question) points x 15 counts from 1 to 64, 1 K to 100 K keys, 1 to 256 rows: the picked count is within
+// 1 % of the best one's time on average, 4 % at worst; "one or two full rounds, at least 768 keys" was up
+// to twice as slow on short contexts (1124 keys: 13 us at 18 splits, 26 us at 1).
+static int32_t auto_splits_f32(const pevlm_layout *lay, const pevlm_heads *h)
 {
-    const int32_t tile_rows = tile_rows_of(h, true);
-    const int32_t G = h->n_q_heads / h->n_kv_heads;
-    // workgroups per split: one per (row tile, head); the bf16 kernel takes tiles of <= 64 rows
-    // for 2 or 4 heads of a KV group at once, the fp32 kernel two heads
+    const int32_t G = h->n_q_heads / h->n_kv_heads, hpw = G > 1 && !h->kv_head_of_q ? 2 : 1;
     int64_t units = 0, max_len = 0, min_len = INT64_MAX;
     for (int32_t s = 0; s < lay->num_seqs; ++s) {
         if (lay->query_len[s] == 0) continue;
-        max_len = std::max<int64_t>(max_len, (int64_t)lay->cu_seqlens[s + 1] - lay->cu_seqlens[s]);
-        min_len = std::min<int64_t>(min_len, (int64_t)lay->cu_seqlens[s + 1] - lay->cu_seqlens[s]);
-        for (int32_t r0 = 0; r0 < lay->query_len[s]; r0 += tile_rows) {
-            int32_t rows = std::min(tile_rows, lay->query_len[s] - r0);
-            int32_t hpw = 1;
-            if (G > 1 && !h->kv_head_of_q) hpw = h->dtype == PEVLM_F32 ? 2 : rows <= 32 ? 4 : (rows <= 64 ? 2 : 1);
-            units += (int64_t)h->n_kv_heads * ((G + hpw - 1) / hpw);
-        }
+        const int64_t len = (int64_t)lay->cu_seqlens[s + 1] - lay->cu_seqlens[s];
+        max_len = std::max(max_len, len);
+        min_len = std::min(min_len, len);
+        units += (int64_t)ceil_div(lay->query_len[s], kTileRowsF32) * h->n_kv_heads * ceil_div(G, hpw);
     }
     if (units == 0) return 1;
     const int64_t slots = 2 * (int64_t)compute_units();
-    int64_t want = slots / units;                      // one round
-    if (want < 1) want = 1;
+    int64_t want = std::max<int64_t>(1, slots / units);  // one round
     // a badly filled round, or sequences of very different length (every sequence gets the same
     // number of splits, so the long ones set the pace): take two rounds of finer pieces
     if (want * units * 4 < slots * 3 || 2 * min_len < max_len) want = (2 * slots) / units;
-    // the fp32 kernel's workgroups are finer (16 rows, two key tiles per wavefront at 256 keys): 0.052 ms for 64
-    // question rows over 2.4 K keys at 3 splits, 0.047 ms at 8
-    const int64_t cap = std::max<int64_t>(1, max_len / (h->dtype == PEVLM_F32 ? 256 : 768));
-    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, cap), PEVLM_MAX_SPLITS));
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, max_len / 256), PEVLM_MAX_SPLITS));
+}
+
+static int32_t auto_splits(const pevlm_layout *lay, const pevlm_heads *h, const Restrict &sel = Restrict())
+{
+    if (h->dtype == PEVLM_F32) return auto_splits_f32(lay, h);
+    const int32_t G = equal_head_groups(h) ? h->n_q_heads / h->n_kv_heads : 1, groups = h->n_q_heads / G;
+    const bool windowed = sel.window_blocks != nullptr;
+    const double cus = compute_units(), slots = 2 * cus;
+    const double tile_one = h->head_dim == 128 ? 1.0 : 0.75;   // us per key tile, up to one workgroup per compute unit
+    const double tile_some = h->head_dim == 128 ? 1.25 : 0.95;  // ... some compute units with two
+    const double tile_full = h->head_dim == 128 ? 1.68 : 1.2;   // ... all with two
+    const double partial_us = (double)total_query_rows(lay) * h->n_q_heads * (h->head_dim + 2) * 4 / 2.5e6;  // one split's partials, written and read
+    int32_t best = 1, asking = 0;
+    double best_us = 0;
+    for (int32_t s = 0; s < lay->num_seqs; ++s) asking += lay->query_len[s] > 0;
+    if (asking == 0) return 1;
+    for (int32_t n = windowed ? 2 : 1; n <= PEVLM_MAX_SPLITS; n += n < 20 ? 1 : (n < 32 ? 2 : 4)) {
+        double wgs = 0, sum_us = 0, longest_tiles = 0;
+        for (int32_t s = 0; s < lay->num_seqs; ++s) {
+            const int32_t Q = lay->query_len[s];
+            if (Q == 0) continue;
+            int32_t keys = lay->cu_seqlens[s + 1] - lay->cu_seqlens[s], cuts = n;
+            if (windowed) {  // the sink is a split of its own
+                const int32_t hidden = sel.window_blocks[s] < 0 ? 0 : std::max(0, blocks_of(lay, s) - sel.window_blocks[s]);
+                keys -= lay->sink_len[s] + (int32_t)std::min<int64_t>((int64_t)hidden * lay->block_len[s], lay->ctx_len[s]);
+                cuts = n - 1;
+            }
+            const int32_t len = split_len_of_seq(keys, cuts, kKeyTile), used = ceil_div(keys, len) + (windowed ? 1 : 0);
+            const double tiles = windowed ? std::max(len, lay->sink_len[s]) / (double)kKeyTile : len / (double)kKeyTile;
+            const double units = (double)groups * ((Q / 128) * G + ceil_div(Q % 128 * G, 128));
+            wgs += units * used;
+            sum_us += units * used * (6 + tile_full * tiles);
+            longest_tiles = std::max(longest_tiles, tiles);
+        }
+        double us;
+        const double longest = 6 + tile_full * longest_tiles;
+        if (asking == 1) {
+            const double full = floor(wgs / slots), rest = wgs - full * slots;
+            us = full * longest;
+            if (rest > 0) us += 6 + longest_tiles * (rest <= cus ? tile_one : tile_some + (tile_full - tile_some) * (rest - cus) / cus);
+        } else {  // lengths differ: an even load plus half of the longest piece at the end
+            us = std::max(longest, sum_us / slots + 0.5 * longest);
+        }
+        if (n > 1) us += 4 + n * (partial_us + 0.04);
+        if (best_us == 0 || us < best_us) { best_us = us; best = n; }
+    }
+    return best;
 }
 
 // bytes of the (cos, sin) table of the fused query rotation: head_dim/2 pairs of floats per entry
@@ -356,14 +415,18 @@ struct QueryPlan {
     size_t off_items, off_qrow, off_ml, off_acc, off_rope, bytes;
 };
 
+// sel: the call's window if it is known; the workspace is sized without it, for any window
 static QueryPlan plan_query(const pevlm_layout *lay, const pevlm_heads *h, int32_t num_splits, bool fuse_rope = false,
-                            bool windowed = false)
+                            bool windowed = false, const Restrict &sel = Restrict())
 {
     QueryPlan p;
     p.tile_rows = tile_rows_of(h, true);
     p.num_splits = num_splits > 0 ? num_splits : auto_splits(lay, h);
     // with a window the sink is a split of its own, the rest of the keys takes at least one more
-    if (windowed) p.num_splits = std::min(PEVLM_MAX_SPLITS, std::max(2, p.num_splits + (num_splits > 0 ? 0 : 1)));
+    if (windowed) {
+        p.num_splits = std::min(PEVLM_MAX_SPLITS, std::max(2, p.num_splits + (num_splits > 0 ? 0 : 1)));
+        if (num_splits == 0 && sel.window_blocks) p.num_splits = std::min(p.num_splits, std::max(2, auto_splits(lay, h, sel)));
+    }
     p.total_q = total_query_rows(lay);
     p.n_items = count_query_tiles(lay, p.tile_rows) * p.num_splits;
     size_t off = 0;
@@ -592,6 +655,7 @@ static pevlm_status prefill_impl(const void *q, const void *k, const void *v, vo
     p.rope_compact_rows = 0;
     p.items = items;
     p.n_items = (int32_t)n_items;
+    p.max_item_rows = max_prefill_rows(layout, tile_rows, sel);
     p.n_q_heads = heads->n_q_heads;
     p.n_kv_heads = heads->n_kv_heads;
     p.scale = scale_of(heads);
@@ -778,7 +842,7 @@ static pevlm_status query_impl(const void *q, const void *k, const void *v, void
     if (fuse_rope && heads->dtype != PEVLM_BF16)
         return fail(PEVLM_ERR_UNSUPPORTED, "the fused query rotation exists for bf16 tensors only");
     if (fuse_rope && !(rope_base > 0.0)) return fail(PEVLM_ERR_INVALID_ARG, "rope_base must be positive");
-    QueryPlan plan = plan_query(layout, heads, num_splits, fuse_rope, sel.window_blocks != nullptr);
+    QueryPlan plan = plan_query(layout, heads, num_splits, fuse_rope, sel.window_blocks != nullptr, sel);
     if (plan.total_q == 0) return PEVLM_OK;
     if (plan.n_items * heads->n_q_heads > 0x3fffffff) return fail(PEVLM_ERR_UNSUPPORTED, "too many work items");
     if (!workspace || workspace_bytes < plan.bytes || ((uintptr_t)workspace & 255))
@@ -824,6 +888,7 @@ static pevlm_status query_impl(const void *q, const void *k, const void *v, void
     p.part_ml = ml;
     p.items = items;
     p.n_items = (int32_t)plan.n_items;
+    p.max_item_rows = max_query_rows(layout, plan.tile_rows);
     p.n_q_heads = heads->n_q_heads;
     p.n_kv_heads = heads->n_kv_heads;
     p.scale = scale_of(heads);

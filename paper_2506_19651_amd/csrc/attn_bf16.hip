@@ -4,8 +4,8 @@
 // own-block key range up to the diagonal, nothing else) and, in partial mode, the split-KV question
 // attention (Eq. 5).
 //
-// Tiling.  A workgroup of 4 wavefronts owns one work item (<= 128 query rows of one head); wave w
-// owns rows 32w..32w+31; two workgroups share a compute unit (two wavefronts per SIMD).  Keys are
+// Tiling.  A workgroup of 4 wavefronts owns 128 (query row, head) pairs of one work item (<= 128 query rows)
+// and KV head; wave w owns pairs 32w..32w+31; two workgroups share a compute unit (two wavefronts per SIMD).  Keys are
 // staged 64 at a time in LDS (K and V tiles, XOR-swizzled 16-byte chunks, direct global->LDS loads,
 // two stages each).  Scores are formed transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16: in
 // the accumulator layout a lane then holds 16 keys of ONE query (column = lane % 32), so the softmax
@@ -25,7 +25,7 @@
 //
 // Variants: PARTIAL writes un-normalised fp32 partials (question attention, merged afterwards);
 // ROPEQ rotates the query rows in registers from a (cos, sin) table instead of expecting rotated
-// queries; items of <= 64 rows are taken for 2 or 4 heads of a KV group by one workgroup.
+// queries.
 #include "attn_bf16_tile.h"
 #include "rope_math.h"
 
@@ -33,53 +33,51 @@ namespace pevlm {
 
 // ROPEQ: q holds un-rotated queries; each wavefront rotates its 32 rows once, right after loading
 // them, from the (cos, sin) table of the call (the sequential positions of Sec. "Position Encoding").
-// One work item for one head (or several heads of a KV group, see below): `logical` indexes
-// (KV head group, item, head in group).
+//
+// The rows of an item and the query heads of a KV group form one list of (row, head) pairs, head fastest; a
+// workgroup takes 128 consecutive pairs, a wavefront 32.  So a wavefront's MFMA columns are filled whatever
+// the number of rows (1 question row x 7 heads: one wavefront instead of seven with one column each; K and V are
+// then read once per KV head), and the pairs of a workgroup lie within 128/G + 1 rows of each other: it stages
+// the tiles up to its own last row, not up to the item's.  `logical` indexes (KV head group, item,
+// workgroup of the item); where heads are not in equal groups every head is a group of its own.  Against one head
+// per wavefront group (two or four heads together for items of <= 64 or <= 32 rows): question of 20 rows x 28/4
+// heads over 65 K keys 60 -> 45 us at the same 64 splits, block prefill of 16 K tokens 210 -> 208 us, 100 K
+// tokens in blocks of 3136 with the rotation folded in 3.40 -> 3.28 ms.
 template <int D, bool PARTIAL, bool ROPEQ>
-__device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, int32_t heads_inner, int32_t pack_heads,
-                                          int32_t identity_map, uint8_t *lds_k, uint8_t *lds_v)
+__device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, const HeadGroups &hg, uint8_t *lds_k, uint8_t *lds_v)
 {
     using C = TileCfg<D>;
     constexpr int KT = C::KT, ROWB = C::ROWB, CH = C::CH, NLD = C::NLD, KSTEPS = C::KSTEPS, DBLK = C::DBLK;
     constexpr int VSW = C::VSW, TILEB = C::TILEB, RPI = C::RPI;
-    const int32_t inner = logical % heads_inner;
-    const int32_t rest = logical / heads_inner;
+    const int32_t inner = logical % hg.wgs_per_item;
+    const int32_t rest = logical / hg.wgs_per_item;
     // last item first: within a context block the later tiles are the longer ones, and a launch that
     // ends on short items has a shorter tail
     const int32_t item_idx = p.n_items - 1 - rest % p.n_items;
-    const int32_t hs = (rest / p.n_items) * heads_inner + inner;
+    const int32_t group = rest / p.n_items, G = hg.heads_per_group;
     pevlm_work_item it;
     if (p.inline_items.mode) {
         it = inline_item(p.inline_items, item_idx);
-        if (hs == 0 && threadIdx.x == 0) p.items[item_idx] = it;
+        if (group == 0 && inner == 0 && threadIdx.x == 0) p.items[item_idx] = it;
     } else {
         it = p.items[item_idx];
     }
-    // With the default head map (query head h on KV head h / G, schedule order = head order) both
-    // indices are plain arithmetic; the tables live in kernel-argument memory and looking them up
-    // costs two dependent memory round trips before the first query row can be requested.
-    const int32_t g = identity_map ? rest / p.n_items
-                                   : __builtin_amdgcn_readfirstlane((int32_t)p.heads.kv_of_q[p.heads.head_order[hs]]);  // workgroup-uniform
+    const int32_t n_pairs = it.q_rows * G, pair0 = inner * 128;
+    if (pair0 >= n_pairs) return;  // an item with fewer rows than the launch's longest
+    // With the default head map (query head h on KV head h / G) the indices are plain arithmetic; the tables
+    // live in kernel-argument memory and looking them up costs two dependent memory round trips before the
+    // first query row can be requested.
+    const int32_t g = hg.identity ? group : __builtin_amdgcn_readfirstlane((int32_t)p.heads.kv_of_q[p.heads.head_order[group * G]]);
     const int32_t Hq = p.n_q_heads, Hkv = p.n_kv_heads;
 
     const int32_t tid = threadIdx.x, lane = tid & 63;
     const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Short items (<= 64 rows: small question blocks, tails of context blocks) would leave
-    // wavefronts idle.  When the query heads of a KV group are scheduled next to each other, such an
-    // item is taken for 2 or 4 heads of the group at once (they need the same K/V tiles): wave w
-    // then owns row group w % wph of head slot inner + w / wph, and the workgroups of the other head
-    // slots leave at once.
-    const int32_t groups32 = (it.q_rows + 31) >> 5;
-    const int32_t wph = groups32 <= 1 ? 1 : (groups32 <= 2 ? 2 : 4);  // wavefronts per head
-    const int32_t hpw = pack_heads ? 4 / wph : 1;                     // heads per workgroup
-    if (hpw > 1 && (inner % hpw) != 0) return;
-    const int32_t slot = hpw > 1 ? inner + wave / wph : inner;
-    const bool head_ok = slot < heads_inner;
-    const int32_t h = identity_map ? hs - inner + (head_ok ? slot : inner)
-                                   : __builtin_amdgcn_readfirstlane((int32_t)p.heads.head_order[hs - inner + (head_ok ? slot : inner)]);  // wavefront-uniform
-    const int32_t rg = hpw > 1 ? wave % wph : wave;  // this wave's group of 32 rows
     const int32_t l32 = lane & 31, g32 = lane >> 5;
     const uint16_t *Q = (const uint16_t *)p.q, *K = (const uint16_t *)p.k, *V = (const uint16_t *)p.v;
+    // pair -> (row of the item, query head)
+#define PEVLM_PAIR(v, row, head)                                                                  \
+    const int32_t row = div_by(v, hg.group_rcp);                                                  \
+    const int32_t head = hg.identity ? group * G + ((v) - row * G) : (int32_t)p.heads.head_order[group * G + ((v) - row * G)]
 
     LaneOff L;
     L.g32 = g32;
@@ -89,21 +87,23 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
     L.v_ch_lo = ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
     L.v_swz = (lane >> 2) & VSW;
 
-    // ---- this lane's query row ----
-    const int32_t row_in_tile = rg * 32 + l32;
-    const bool row_valid = head_ok && row_in_tile < it.q_rows;
-    const int32_t my_row = it.q_start + (row_in_tile < it.q_rows ? row_in_tile : it.q_rows - 1);
-    const bool wave_active = head_ok && rg * 32 < it.q_rows;
-    const int32_t wr_lo = it.q_start + rg * 32;
-    const int32_t wr_hi = it.q_start + ((rg * 32 + 31 < it.q_rows) ? rg * 32 + 31 : it.q_rows - 1);
+    // ---- this lane's query row and head, and the rows of the wavefront and of the workgroup
+    const int32_t wave_pair0 = pair0 + wave * 32;
+    const bool wave_active = wave_pair0 < n_pairs;
+    const bool pair_valid = wave_pair0 + l32 < n_pairs;
+    const int32_t my_pair = pair_valid ? wave_pair0 + l32 : n_pairs - 1;
+    PEVLM_PAIR(my_pair, row_in_item, my_head);
+    const int32_t my_row = it.q_start + row_in_item;
+    const int32_t wr_lo = it.q_start + div_by(wave_active ? wave_pair0 : n_pairs - 1, hg.group_rcp);
+    const int32_t wr_hi = it.q_start + div_by(wave_pair0 + 31 < n_pairs ? wave_pair0 + 31 : n_pairs - 1, hg.group_rcp);
+    const int32_t wg_hi = it.q_start + div_by(pair0 + 127 < n_pairs ? pair0 + 127 : n_pairs - 1, hg.group_rcp);
 
     // (cos, sin) of this lane's row for the fused query rotation: fetched first, so that the loads
     // are in flight together with the Q rows
     f32x4 rope_cs[ROPEQ ? KSTEPS / 2 : 1][4];
     if (ROPEQ) {
         int64_t entry = my_row;
-        if (p.rope_compact_rows > 0)
-            entry = it.reserved % p.rope_compact_rows + (row_in_tile < it.q_rows ? row_in_tile : it.q_rows - 1);
+        if (p.rope_compact_rows > 0) entry = it.reserved % p.rope_compact_rows + row_in_item;
         const f32x4 *tab = reinterpret_cast<const f32x4 *>(p.rope_tab + entry * D) + g32 * 4;
 #pragma unroll
         for (int kk = 0; kk < KSTEPS / 2; ++kk)
@@ -119,14 +119,15 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
     uint8_t *const wave_slice = (wave < 2 ? lds_k : lds_v) + TILEB + (wave & 1) * WSLICE;
     const uint32_t wave_slice_addr = (wave < 2 ? lds_k_addr : lds_v_addr) + TILEB + (wave & 1) * WSLICE;
 
+    // tiles the workgroup stages, and tiles this wave computes: all fully visible ones, and the causal ones
+    // that start at or before its last row (the rest is masked for every row)
     const int32_t n_full_tiles = (it.full_len + KT - 1) / KT;
     const int32_t n_diag_tiles = (it.diag_len + KT - 1) / KT;
-    const int32_t n_tiles = n_full_tiles + n_diag_tiles;
-    // tiles this wave computes: all fully visible ones, and the causal ones that start at or before
-    // its last row (the rest is masked for every row of the wave)
+    const int32_t wg_diag = wg_hi >= it.diag_start ? (wg_hi - it.diag_start) / KT + 1 : 0;
+    const int32_t n_tiles = n_full_tiles + (wg_diag < n_diag_tiles ? wg_diag : n_diag_tiles);
     int32_t n_w = 0;
     if (wave_active) {
-        int32_t nd = wr_hi >= it.diag_start ? (wr_hi - it.diag_start) / KT + 1 : 0;
+        const int32_t nd = wr_hi >= it.diag_start ? (wr_hi - it.diag_start) / KT + 1 : 0;
         n_w = n_full_tiles + (nd < n_diag_tiles ? nd : n_diag_tiles);
     }
 
@@ -221,13 +222,49 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
         PEVLM_ISSUE_K(0);
         PEVLM_ISSUE_V(0);
     }
+    // Walk of a lane over the wavefront's pairs, RPI at a time: byte offset of the pair's row from the item's first
+    // one, advanced without a division (an integer product costs as much as four additions).
+    const uint32_t row_bytes = (uint32_t)(Hq * ROWB), step_bytes = (uint32_t)hg.step_rows * row_bytes + (uint32_t)(hg.step_heads * ROWB);
+    const int64_t item_off = ((int64_t)it.q_start * Hq + group * G) * D;  // elements; with the default head map
+#define PEVLM_PAIR_WALK_BEGIN()                                              \
+    int32_t walk_v = wave_pair0 + lane / CH, walk_h;                          \
+    uint32_t walk_off;                                                        \
+    {                                                                         \
+        const int32_t r_ = div_by(walk_v, hg.group_rcp);                      \
+        walk_h = walk_v - r_ * G;                                             \
+        walk_off = (uint32_t)r_ * row_bytes + (uint32_t)(walk_h * ROWB);      \
+    }
+#define PEVLM_PAIR_WALK_NEXT()                                               \
+    do {                                                                      \
+        walk_v += RPI;                                                        \
+        walk_h += hg.step_heads;                                              \
+        walk_off += step_bytes;                                               \
+        if (walk_h >= G) {                                                    \
+            walk_h -= G;                                                      \
+            walk_off += row_bytes - (uint32_t)(G * ROWB);                     \
+        }                                                                     \
+    } while (0)
+    if (hg.identity) {
+        const int32_t last_row = div_by(n_pairs - 1, hg.group_rcp);
+        const uint32_t last_off = (uint32_t)last_row * row_bytes + (uint32_t)((n_pairs - 1 - last_row * G) * ROWB);
+        const uint16_t *qbase = uniform_ptr(Q + item_off);
+        PEVLM_PAIR_WALK_BEGIN();
 #pragma unroll
-    for (int j = 0; j < WSLICE / 1024; ++j) {
-        const int32_t rl = j * RPI + lane / CH, cpos = lane % CH;
-        int32_t r = rg * 32 + rl;
-        r = r < it.q_rows ? r : it.q_rows - 1;
-        load_lds_16(Q + ((int64_t)(it.q_start + r) * Hq + h) * D + ((cpos ^ (rl & (CH - 1))) << 3),
-                    wave_slice_addr + j * 1024);
+        for (int j = 0; j < WSLICE / 1024; ++j) {
+            const int32_t rl = j * RPI + lane / CH;
+            const uint32_t off = walk_off < last_off ? walk_off : last_off;  // pairs past the item repeat its last one
+            load_lds_16_base(qbase, off + (uint32_t)(((lane % CH) ^ (rl & (CH - 1))) << 4), wave_slice_addr + j * 1024);
+            PEVLM_PAIR_WALK_NEXT();
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < WSLICE / 1024; ++j) {
+            const int32_t rl = j * RPI + lane / CH, cpos = lane % CH;
+            const int32_t v = wave_pair0 + rl < n_pairs ? wave_pair0 + rl : n_pairs - 1;
+            PEVLM_PAIR(v, r, h);
+            load_lds_16(Q + ((int64_t)(it.q_start + r) * Hq + h) * D + ((cpos ^ (rl & (CH - 1))) << 3),
+                        wave_slice_addr + j * 1024);
+        }
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
     asm volatile("" ::: "memory");
@@ -373,9 +410,9 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
     // ---- epilogue ----
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     if (PARTIAL) {
-        if (!row_valid) return;
-        const int64_t slot = (int64_t)it.reserved + row_in_tile;
-        float *acc = p.part_acc + (slot * Hq + h) * D;
+        if (!pair_valid) return;
+        const int64_t slot = ((int64_t)it.reserved + row_in_item) * Hq + my_head;
+        float *acc = p.part_acc + slot * D;
 #pragma unroll
         for (int b = 0; b < DBLK; ++b)
 #pragma unroll
@@ -385,8 +422,8 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
                 *reinterpret_cast<f32x4 *>(acc + d) = v4;
             }
         if (g32 == 0) {
-            p.part_ml[(slot * Hq + h) * 2] = m_ref / c_log2;  // back to raw score units (-inf stays)
-            p.part_ml[(slot * Hq + h) * 2 + 1] = l_tot;
+            p.part_ml[slot * 2] = m_ref / c_log2;  // back to raw score units (-inf stays)
+            p.part_ml[slot * 2 + 1] = l_tot;
         }
     } else {
         // O^T fragments -> wave-private LDS slice (row-major bf16, swizzled), then whole-row 16-byte
@@ -409,14 +446,26 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         uint16_t *const obase = (uint16_t *)p.out;
+        if (hg.identity) {
+            uint8_t *const ob = (uint8_t *)(obase + item_off);
+            PEVLM_PAIR_WALK_BEGIN();
 #pragma unroll
-        for (int j = 0; j < WSLICE / 1024; ++j) {
-            const int32_t rl = j * RPI + lane / CH, cpos = lane % CH;
-            const uint4 val = *reinterpret_cast<const uint4 *>(oslice + rl * ROWB + ((cpos ^ (rl & (CH - 1))) << 4));
-            if (head_ok && rg * 32 + rl < it.q_rows)
-                *reinterpret_cast<uint4 *>(obase + ((int64_t)(it.q_start + rg * 32 + rl) * Hq + h) * D + cpos * 8) = val;
+            for (int j = 0; j < WSLICE / 1024; ++j) {
+                const int32_t rl = j * RPI + lane / CH, cpos = lane % CH;
+                const uint4 val = *reinterpret_cast<const uint4 *>(oslice + rl * ROWB + ((cpos ^ (rl & (CH - 1))) << 4));
+                if (walk_v < n_pairs) *reinterpret_cast<uint4 *>(ob + (walk_off + (uint32_t)(cpos << 4))) = val;
+                PEVLM_PAIR_WALK_NEXT();
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < WSLICE / 1024; ++j) {
+                const int32_t rl = j * RPI + lane / CH, cpos = lane % CH, v = wave_pair0 + rl;
+                const uint4 val = *reinterpret_cast<const uint4 *>(oslice + rl * ROWB + ((cpos ^ (rl & (CH - 1))) << 4));
+                PEVLM_PAIR(v, r, h);
+                if (v < n_pairs) *reinterpret_cast<uint4 *>(obase + ((int64_t)(it.q_start + r) * Hq + h) * D + cpos * 8) = val;
+            }
         }
-        if (p.lse && g32 == 0 && row_valid) p.lse[(int64_t)my_row * Hq + h] = (m_ref + __log2f(l_tot)) * 0.69314718056f;
+        if (p.lse && g32 == 0 && pair_valid) p.lse[(int64_t)my_row * Hq + my_head] = (m_ref + __log2f(l_tot)) * 0.69314718056f;
     }
 }
 
@@ -424,33 +473,36 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
 // with its own L2); every XCD gets one contiguous run of logical ids so that the heads of a GQA
 // group working on the same context block share that XCD's L2.
 template <int D, bool PARTIAL, bool ROPEQ>
-__global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnParams p, int32_t n_logical, int32_t heads_inner, int32_t pack_heads,
-                                                           int32_t identity_map)
+__global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnParams p, int32_t n_logical, HeadGroups hg)
 {
     __shared__ __attribute__((aligned(1024))) uint8_t lds_k[2 * TileCfg<D>::TILEB];
     __shared__ __attribute__((aligned(1024))) uint8_t lds_v[2 * TileCfg<D>::TILEB];
     const int32_t per_xcd = gridDim.x >> 3;
     const int32_t logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (logical >= n_logical) return;
-    attn_item<D, PARTIAL, ROPEQ>(p, logical, heads_inner, pack_heads, identity_map, lds_k, lds_v);
+    attn_item<D, PARTIAL, ROPEQ>(p, logical, hg, lds_k, lds_v);
 }
 
 hipError_t launch_attn_bf16(const AttnParams &p, int32_t D, bool partial, hipStream_t stream)
 {
-    // heads that share a KV head are scheduled next to each other when the groups are uniform
-    int32_t G = p.n_q_heads / p.n_kv_heads;
-    bool uniform = true;
-    for (int32_t i = 0; i < p.n_q_heads; ++i)
+    // heads that share a KV head are taken together when the groups are equal
+    const int32_t G = p.n_q_heads / p.n_kv_heads;
+    bool uniform = true, identity = true;
+    for (int32_t i = 0; i < p.n_q_heads; ++i) {
         if (p.heads.kv_of_q[p.heads.head_order[i]] != i / G) uniform = false;
-    int32_t heads_inner = uniform ? G : p.n_q_heads;
-    int32_t identity = uniform ? 1 : 0;  // query head h on KV head h / G, scheduled in head order
-    for (int32_t i = 0; i < p.n_q_heads; ++i)
-        if (p.heads.head_order[i] != i || p.heads.kv_of_q[i] != i / G) identity = 0;
-    int32_t pack = (uniform && G > 1) ? 1 : 0;  // short items are taken for several heads of a KV group at once
-    int32_t n_logical = p.n_items * p.n_q_heads;
-    dim3 grid((n_logical + 7) / 8 * 8), block(256);
-#define PEVLM_ATTN_LAUNCH(DD, PP, RR) \
-    hipLaunchKernelGGL((attn_bf16_kernel<DD, PP, RR>), grid, block, 0, stream, p, n_logical, heads_inner, pack, identity)
+        if (p.heads.head_order[i] != i || p.heads.kv_of_q[i] != i / G) identity = false;
+    }
+    HeadGroups hg;
+    hg.heads_per_group = uniform ? G : 1;
+    hg.group_rcp = reciprocal_of(hg.heads_per_group);
+    hg.identity = uniform && identity;
+    const int32_t rows_per_load = 512 / D;  // rows one wavefront-wide 16-byte-per-lane load covers
+    hg.step_rows = rows_per_load / hg.heads_per_group;
+    hg.step_heads = rows_per_load % hg.heads_per_group;
+    hg.wgs_per_item = ceil_div(p.max_item_rows * hg.heads_per_group, 128);
+    const int32_t n_logical = p.n_items * hg.wgs_per_item * (uniform ? p.n_kv_heads : p.n_q_heads);
+    const dim3 grid((n_logical + 7) / 8 * 8), block(256);
+#define PEVLM_ATTN_LAUNCH(DD, PP, RR) hipLaunchKernelGGL((attn_bf16_kernel<DD, PP, RR>), grid, block, 0, stream, p, n_logical, hg)
     const bool rope = p.rope_tab != nullptr;
     if (D == 128) {
         if (partial) { if (rope) PEVLM_ATTN_LAUNCH(128, true, true); else PEVLM_ATTN_LAUNCH(128, true, false); }

@@ -378,7 +378,7 @@ struct AttnParams {
     float *part_acc;                // partial mode: [slots][Hq][D] unnormalised weighted values
     float *part_ml;                 // partial mode: [slots][Hq][2] (running max of raw scores, sum)
     pevlm_work_item *items;         // read, or (inline_items.mode != 0) written by the workgroups of the first head
-    int32_t n_items;
+    int32_t n_items, max_item_rows; // items, rows of the longest of them
     int32_t n_q_heads, n_kv_heads;
     float scale;                    // softmax scale
     InlineItems inline_items;
@@ -388,6 +388,15 @@ struct AttnParams {
     const float *rope_tab;
     int32_t rope_compact_rows;
     HeadTable heads;
+};
+
+// how the bf16 kernel deals the query heads out over workgroups
+struct HeadGroups {
+    int32_t heads_per_group;  // query heads taken together (those of a KV head, or 1 where the groups differ)
+    uint32_t group_rcp;       // for / heads_per_group
+    int32_t identity;         // query head h is on KV head h / heads_per_group
+    int32_t wgs_per_item;     // workgroups of 128 (row, head) pairs per item and group
+    int32_t step_rows, step_heads;  // the pairs that one wavefront-wide load covers, as rows and heads
 };
 
 struct StreamParams {

@@ -84,3 +84,25 @@ def test_items_formed_in_the_kernel_or_read_from_the_list(oracle, dtype, D, n_se
         for lo, (S, _B, C, Q) in zip(lay.cu, seqs):
             a = int(lo) + S + C
             assert torch.equal(out2[a:a + Q].view(torch.int16), out[a:a + Q].view(torch.int16))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,hmap", [(7, 1, None), (6, 2, None), (4, 4, None), (9, 3, [0, 1, 2] * 3), (5, 1, None), (40, 1, None),
+                                         (4, 2, [0, 0, 0, 1])], ids=["g7", "g3", "g1", "g3map", "g5", "g40", "unequal"])
+@pytest.mark.parametrize("Q", [1, 4, 5, 18, 19, 33, 128, 131])
+def test_row_head_pairs_fill_wavefronts(oracle, Hq, Hkv, hmap, Q, D):
+    """128 (row, head) pairs per workgroup, 32 per wavefront: row counts on both sides of a full wavefront and a full
+    workgroup, groups that do not divide 32, head maps; sink and block rows under the one-item kernel too."""
+    w = W.Workload(f"pairs{Q}", 34, "bf16", Hq, Hkv, D, 1.0e4, [(Q, 150, 210, Q), (0, 1, 0, 2)], 0.5)
+    data = W.generate(w)
+    prev = P.pevlm_set_prefill_kernel("classic")
+    try:
+        r = run_path(w, data, kv_head_of_q=hmap, want_lse=True)
+    finally:
+        P.pevlm_set_prefill_kernel(prev)
+    want, want_lse = oracle.forward(data["q"], data["k"], data["v"], oracle_layout(oracle, w), w.rope_base, kv_head_of_q=hmap)
+    got = to_host_f32(r["out"])
+    assert np.isfinite(got).all()
+    st = error_stats(got, want)
+    assert st["max_abs"] <= 2e-2 and st["mean_abs"] <= 2e-3 and st["max_rel_l2"] <= 3e-2, st
+    assert np.max(np.abs(to_host_f32(r["lse"]) - want_lse)) <= 2e-2
