@@ -17,9 +17,9 @@ struct RopeFreq {
 template <bool WIDE>
 __device__ __forceinline__ void rope_cos_sin(double pos, double inv_freq, float &c, float &s)
 {
-    const double two_pi = 6.283185307179586476925286766559;
+    const double two_pi = 6.283185307179586476925286766559, turns = 0.15915494309189533576888376337251;  // 1 / two_pi
     const double theta = pos * inv_freq;
-    const double r = fma(-two_pi, rint(theta / two_pi), theta);
+    const double r = fma(-two_pi, rint(theta * turns), theta);
     if (WIDE) {
         double sd, cd;
         sincos(r, &sd, &cd);

@@ -106,3 +106,25 @@ def test_row_head_pairs_fill_wavefronts(oracle, Hq, Hkv, hmap, Q, D):
     st = error_stats(got, want)
     assert st["max_abs"] <= 2e-2 and st["mean_abs"] <= 2e-3 and st["max_rel_l2"] <= 3e-2, st
     assert np.max(np.abs(to_host_f32(r["lse"]) - want_lse)) <= 2e-2
+
+
+@pytest.mark.parametrize("tokens", [1, 33, 700, 5500, 16500])
+@pytest.mark.parametrize("dtype,Hq,Hkv,D", [("bf16", 5, 1, 128), ("bf16", 14, 2, 64), ("f32", 3, 3, 64), ("f32", 9, 1, 128)])
+def test_rope_heads_shared_between_workgroups(oracle, dtype, Hq, Hkv, D, tokens):
+    """Few tokens: the heads of a token are dealt out over several workgroups; from 512 workgroups on one takes all."""
+    w = W.Workload(f"rope{tokens}", 35, dtype, Hq, Hkv, D, 1.0e6, [(tokens, 1, 0, 0)], 0.5)
+    data = W.generate(w)
+    lay, heads = layout_heads(w)
+    pos = oracle.positions(oracle_layout(oracle, w)) + 123456
+    for which in ("both", "q", "k"):
+        q, k = to_device(data["q"]), to_device(data["k"])
+        P.pevlm_rope_seq(None if which == "k" else q, None if which == "q" else k, lay, heads, w.rope_base, [123456])
+        torch.cuda.synchronize()
+        for name, t in (("q", q), ("k", k)):
+            got, raw = to_host_f32(t), W.as_float32(data[name])
+            if which not in ("both", name):
+                assert np.array_equal(got, raw)
+                continue
+            want = oracle.rope(data[name], pos, w.rope_base)
+            # one rounding to the storage type (2^-8 relative in bf16, 2^-23 in fp32) on top of fp32 arithmetic
+            assert np.all(np.abs(got - want) <= (2.0 ** -8 if dtype == "bf16" else 2.0 ** -22) * np.abs(want) + 1e-6)
