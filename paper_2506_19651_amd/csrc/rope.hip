@@ -159,13 +159,27 @@ __global__ __launch_bounds__(256) void rope_table_kernel(float2 *table, int32_t 
     }
 }
 
+// rope_base^(-2i/D): 64 powers cost more than a kernel launch's share of the call, and a program asks for one or
+// two (D, base) again and again: each thread keeps the last one it asked for
+static const RopeFreq &frequencies(int32_t D, double rope_base)
+{
+    static thread_local RopeFreq fr;
+    static thread_local int32_t have_d = 0;
+    static thread_local double have_base = 0.0;
+    if (have_d != D || have_base != rope_base) {
+        for (int i = 0; i < 64; ++i) fr.inv_freq[i] = i < D / 2 ? pow(rope_base, -2.0 * (double)i / (double)D) : 0.0;
+        have_d = D;
+        have_base = rope_base;
+    }
+    return fr;
+}
+
 hipError_t launch_rope_table(float *table, bool question, const SeqTable &tab, int32_t D, double rope_base,
                              int32_t entry_begin, int32_t entry_end, const int32_t *pos3, int64_t T, int32_t sec0, int32_t sec01,
                              hipStream_t stream)
 {
     if (entry_end <= entry_begin) return hipSuccess;
-    RopeFreq fr;
-    for (int i = 0; i < 64; ++i) fr.inv_freq[i] = i < D / 2 ? pow(rope_base, -2.0 * (double)i / (double)D) : 0.0;
+    const RopeFreq &fr = frequencies(D, rope_base);
     const int32_t per_block = 256 / (D / 16);
     dim3 grid((entry_end - entry_begin + per_block - 1) / per_block);
     if (D == 128) hipLaunchKernelGGL((rope_table_kernel<128>), grid, dim3(256), 0, stream, (float2 *)table, question ? 1 : 0, tab, fr, entry_begin, entry_end, pos3, T, sec0, sec01);
@@ -173,18 +187,12 @@ hipError_t launch_rope_table(float *table, bool question, const SeqTable &tab, i
     return hipGetLastError();
 }
 
-static void fill_freq(RopeFreq &fr, int32_t D, double rope_base)
-{
-    for (int i = 0; i < 64; ++i) fr.inv_freq[i] = i < D / 2 ? pow(rope_base, -2.0 * (double)i / (double)D) : 0.0;
-}
-
 template <bool MROPE>
 static hipError_t launch_rope_any(void *q, void *k, const SeqTable &tab, int32_t Hq, int32_t Hkv, int32_t D, bool bf16,
                                   double rope_base, int32_t row_begin, int32_t row_end, const int32_t *pos3, int64_t T,
                                   int32_t sec0, int32_t sec01, float *table, hipStream_t stream)
 {
-    RopeFreq fr;
-    fill_freq(fr, D, rope_base);
+    const RopeFreq &fr = frequencies(D, rope_base);
     if (row_end <= row_begin) return hipSuccess;
     int32_t tokens_per_block = 256 / (D / 16);
     // heads per workgroup: all of them from 512 workgroups on, below that as few as it takes to have 512, at least 4
