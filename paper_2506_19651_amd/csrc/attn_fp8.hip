@@ -55,13 +55,20 @@ __device__ __forceinline__ int32_t pack2(float a, float b, int32_t old)
 {
     return __builtin_amdgcn_cvt_pk_fp8_f32(a, b, old, HIGH);
 }
+// four fp32 values -> four codes; both halves of the word are written, so what it held before does not matter
+// (a word started from 0 costs a move per pair of conversions)
+__device__ __forceinline__ int32_t pack4(float a, float b, float c, float d)
+{
+    int32_t v;
+    asm("" : "=v"(v));
+    return pack2<true>(c, d, pack2<false>(a, b, v));
+}
 __device__ __forceinline__ i32x4v quantise16(const float (&x)[16], float inv_scale)
 {
     i32x4v r;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        int32_t v = pack2<false>(x[4 * w] * inv_scale, x[4 * w + 1] * inv_scale, 0);
-        r[w] = pack2<true>(x[4 * w + 2] * inv_scale, x[4 * w + 3] * inv_scale, v);
+        r[w] = pack4(x[4 * w] * inv_scale, x[4 * w + 1] * inv_scale, x[4 * w + 2] * inv_scale, x[4 * w + 3] * inv_scale);
     }
     return r;
 }
@@ -81,6 +88,50 @@ template <int CPR>
 __host__ __device__ __forceinline__ int32_t swizzled_chunk(int32_t r, int32_t c)
 {
     return c ^ ((r / (16 / CPR)) % CPR);
+}
+
+// One k-step of the scores of 64 keys x 32 rows: s[kc] = c + K Q^T with the block exponents of K and Q, c the
+// start values (FIRST) or s[kc].  Written as instructions because both chunks start from the same 16 registers:
+// left to the compiler the start values are copied for one of the chunks on every tile.  The wait states after the
+// LAST step cover the 16-pass results for whatever reads them next; between two steps a chunk's MFMAs are one
+// MFMA (64 cycles) apart, which the chained accumulator needs no wait for.
+template <bool FIRST, bool LAST>
+__device__ __forceinline__ void score_step(const i32x8 &k0, const i32x8 &k1, const i32x8 &q, const f32x16 &start, int32_t k_exp8,
+                                           int32_t q_exp8, f32x16 (&s)[2])
+{
+#define PEVLM_SCORE(dst, kreg, creg) "v_mfma_scale_f32_32x32x64_f8f6f4 " dst ", " kreg ", %4, " creg ", %6, %7 op_sel_hi:[0,0,0]\n\t"
+#define PEVLM_RESULT_WAIT "s_nop 15\n\ts_nop 3"
+    if (FIRST && LAST)
+        asm volatile(PEVLM_SCORE("%0", "%2", "%5") PEVLM_SCORE("%1", "%3", "%5") PEVLM_RESULT_WAIT
+                     : "=&v"(s[0]), "=&v"(s[1]) : "v"(k0), "v"(k1), "v"(q), "v"(start), "v"(k_exp8), "v"(q_exp8));
+    else if (FIRST)
+        asm volatile(PEVLM_SCORE("%0", "%2", "%5") PEVLM_SCORE("%1", "%3", "%5")
+                     : "=&v"(s[0]), "=&v"(s[1]) : "v"(k0), "v"(k1), "v"(q), "v"(start), "v"(k_exp8), "v"(q_exp8));
+    else
+        asm volatile(PEVLM_SCORE("%0", "%2", "%0") PEVLM_SCORE("%1", "%3", "%1") PEVLM_RESULT_WAIT
+                     : "+v"(s[0]), "+v"(s[1]) : "v"(k0), "v"(k1), "v"(q), "i"(0), "v"(k_exp8), "v"(q_exp8));
+#undef PEVLM_SCORE
+#undef PEVLM_RESULT_WAIT
+}
+
+// maximum of 8 values without the quieting moves that plain fmaxf puts in front of values it cannot prove canonical
+__device__ __forceinline__ float max8(float a, float b, float c, float d, float e, float f, float g, float h)
+{
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3\n\tv_max3_f32 %0, %0, %4, %5\n\tv_max3_f32 %0, %0, %6, %7\n\tv_max_f32 %0, %0, %8"
+        : "=&v"(r) : "v"(a), "v"(b), "v"(c), "v"(d), "v"(e), "v"(f), "v"(g), "v"(h));
+    return r;
+}
+// maximum over the 64 keys of the tile for this lane's row (both lanes of a row end up with it)
+__device__ __forceinline__ float row_max_grouped(const f32x16 (&s)[2])
+{
+    const float m0 = max8(s[0][0], s[0][1], s[0][2], s[0][3], s[0][4], s[0][5], s[0][6], s[0][7]);
+    const float m1 = max8(s[0][8], s[0][9], s[0][10], s[0][11], s[0][12], s[0][13], s[0][14], s[0][15]);
+    const float m2 = max8(s[1][0], s[1][1], s[1][2], s[1][3], s[1][4], s[1][5], s[1][6], s[1][7]);
+    const float m3 = max8(s[1][8], s[1][9], s[1][10], s[1][11], s[1][12], s[1][13], s[1][14], s[1][15]);
+    const float mx = fmaxf(max3f(m0, m1, m2), m3);
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
 }
 
 }  // namespace
@@ -266,8 +317,8 @@ __global__ __launch_bounds__(256, 3) void attn_fp8_kernel(Fp8Params p)
     const int32_t work = (int32_t)(blockIdx.x & 7) * per_xcd + (int32_t)(blockIdx.x >> 3);
     if ((int32_t)(blockIdx.x >> 3) >= per_xcd || work >= n_work) return;
     const Fp8Item it = p.items[work / p.n_q_heads];
-    const int32_t head = p.heads.head_order[work % p.n_q_heads];
-    const int32_t g = p.heads.kv_of_q[head];
+    const int32_t head = __builtin_amdgcn_readfirstlane((int32_t)p.heads.head_order[work % p.n_q_heads]);
+    const int32_t g = __builtin_amdgcn_readfirstlane((int32_t)p.heads.kv_of_q[head]);
     const int32_t Hq = p.n_q_heads, Hkv = p.n_kv_heads;
 
     const int32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -331,18 +382,14 @@ __global__ __launch_bounds__(256, 3) void attn_fp8_kernel(Fp8Params p)
         if (t >= n_w) continue;
         const uint8_t *tk = lds + (t & 1) * TILEB, *tv = lds + (2 + (t & 1)) * TILEB;
         // ---- S^T = K Q^T: rows = keys of the chunk, columns = this wavefront's query rows
-#pragma unroll
-        for (int kc = 0; kc < 2; ++kc) {
-            const int32_t r = kc * 32 + l32;
-#pragma unroll
-            for (int kk = 0; kk < KQ; ++kk) {
-                const int32_t c0 = kk * 4 + g32 * 2;
-                const i32x4v a = *reinterpret_cast<const i32x4v *>(tk + r * D + swizzled_chunk<CPR>(r, c0) * 16);
-                const i32x4v b = *reinterpret_cast<const i32x4v *>(tk + r * D + swizzled_chunk<CPR>(r, c0 + 1) * 16);
-                const i32x8 kf = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-                s[kc] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kf, qf[kk], kk == 0 ? start : s[kc], 0, 0, 0, k_exp8, 0, q_exp8);
-            }
-        }
+        auto read_k = [&](int kk, int kc) {
+            const int32_t r = kc * 32 + l32, c0 = kk * 4 + g32 * 2;
+            const i32x4v a = *reinterpret_cast<const i32x4v *>(tk + r * D + swizzled_chunk<CPR>(r, c0) * 16);
+            const i32x4v b = *reinterpret_cast<const i32x4v *>(tk + r * D + swizzled_chunk<CPR>(r, c0 + 1) * 16);
+            return i32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+        };
+        score_step<true, KQ == 1>(read_k(0, 0), read_k(0, 1), qf[0], start, k_exp8, q_exp8, s);
+        if (KQ == 2) score_step<false, true>(read_k(KQ - 1, 0), read_k(KQ - 1, 1), qf[KQ - 1], start, k_exp8, q_exp8, s);
         int32_t k0, kend;
         bool causal;
         if (t < n_full) {
@@ -352,7 +399,7 @@ __global__ __launch_bounds__(256, 3) void attn_fp8_kernel(Fp8Params p)
         }
         if ((k0 + KT > kend) || (causal && (k0 + KT - 1 > wr_lo))) mask_tile(s, k0, kend, causal, my_row, g32);
         // ---- reference maximum: raised to the running maximum once that is more than kWeightLag above it
-        const float mx = row_max(s) - shift;
+        const float mx = row_max_grouped(s) - shift;
         const bool raise = mx > m_ref + kWeightLag;
         if (__any(raise)) {
             const float m_new = raise ? mx : m_ref;
@@ -374,6 +421,16 @@ __global__ __launch_bounds__(256, 3) void attn_fp8_kernel(Fp8Params p)
 #pragma unroll
             for (int i = 0; i < 16; ++i) start[i] = shift;
         }
+        // the V fragments of the first value MFMA are requested before the weights are formed
+        auto read_v = [&](int b) {
+            const int32_t d = b * 32 + l32;
+            const i32x4v a = *reinterpret_cast<const i32x4v *>(tv + d * KT + swizzled_chunk<4>(d, g32 * 2) * 16);
+            const i32x4v c = *reinterpret_cast<const i32x4v *>(tv + d * KT + swizzled_chunk<4>(d, g32 * 2 + 1) * 16);
+            return i32x8{a[0], a[1], a[2], a[3], c[0], c[1], c[2], c[3]};
+        };
+        i32x8 vf[2];
+        vf[0] = read_v(0);
+        __builtin_amdgcn_sched_barrier(0);
         // ---- weights: E4M3 codes in the order the value MFMA wants them (byte 16 kc + i of the lane)
         float psum = 0.f;
         i32x8 pf;
@@ -386,17 +443,14 @@ __global__ __launch_bounds__(256, 3) void attn_fp8_kernel(Fp8Params p)
                 const float w2 = __builtin_amdgcn_exp2f(s[kc][4 * w + 2]);
                 const float w3 = __builtin_amdgcn_exp2f(s[kc][4 * w + 3]);
                 psum += (w0 + w1) + (w2 + w3);
-                pf[kc * 4 + w] = pack2<true>(w2, w3, pack2<false>(w0, w1, 0));
+                pf[kc * 4 + w] = pack4(w0, w1, w2, w3);
             }
         l_run += psum;
         // ---- O^T += V^T P^T
 #pragma unroll
         for (int b = 0; b < DBLK; ++b) {
-            const int32_t d = b * 32 + l32;
-            const i32x4v a = *reinterpret_cast<const i32x4v *>(tv + d * KT + swizzled_chunk<4>(d, g32 * 2) * 16);
-            const i32x4v c = *reinterpret_cast<const i32x4v *>(tv + d * KT + swizzled_chunk<4>(d, g32 * 2 + 1) * 16);
-            const i32x8 vf = {a[0], a[1], a[2], a[3], c[0], c[1], c[2], c[3]};
-            o[b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vf, pf, o[b], 0, 0, 0, 0, 0, 0);
+            if (b + 1 < DBLK) vf[(b + 1) & 1] = read_v(b + 1);
+            o[b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vf[b & 1], pf, o[b], 0, 0, 0, 0, 0, 0);
         }
     }
 #undef PEVLM_FP8_LOAD_TILE
