@@ -757,42 +757,41 @@ pevlm_status pevlm_block_prefill_attn_fp8(const void *q, const void *k, const vo
     Fp8Item *items = (Fp8Item *)(ws + plan.items);
     pevlm_work_item *key_tiles = (pevlm_work_item *)(ws + plan.key_tiles);
     const int64_t T = layout->cu_seqlens[layout->num_seqs];
+    const float q_factor = scale_of(heads) * 1.4426950408889634f;
     if (stages & PEVLM_FP8_QUANTISE) {
-        // both lists (they depend on the layout only), then the codes
+        // both lists (they depend on the layout only) and the zeroed maxima, then the codes; Q's are left to the
+        // attention kernel if it follows
         int32_t item_offset = 0, tile_offset = 0;
         for (int32_t s0 = 0; s0 < layout->num_seqs; s0 += kMaxSeqsPerLaunch) {
             SeqTable tab;
             Fp8TileBases bases;
+            Fp8ItemBases items_of;
             const int32_t n = std::min(kMaxSeqsPerLaunch, layout->num_seqs - s0);
             fill_table(layout, s0, n, nullptr, &tab);
             bases.base[0] = tile_offset;
+            items_of.base[0] = 0;
             for (int32_t i = 0; i < n; ++i) {
                 tab.item_base[i + 1] = tab.item_base[i] + prefill_items_of_seq(tab.sink[i], tab.block[i], tab.ctx[i], kKeyTile);
                 bases.base[i + 1] = tile_offset + tab.item_base[i + 1];
+                items_of.base[i + 1] = items_of.base[i] + prefill_items_of_seq(tab.sink[i], tab.block[i], tab.ctx[i], kFp8TileRows);
             }
-            if (tab.item_base[n] > 0) {
-                hipError_t e = launch_build_prefill_items(tab, kKeyTile, key_tiles, tile_offset, hs);
-                if (e != hipSuccess) return hip_fail(e, "key-tile list launch");
-            }
+            hipError_t e = launch_fp8_setup(tab, bases, items_of, key_tiles, tile_offset, items, item_offset, (uint32_t *)(ws + plan.kv_amax),
+                                            s0 == 0 ? 2 * heads->n_kv_heads : 0, hs);
+            if (e != hipSuccess) return hip_fail(e, "fp8 work-list launch");
             tile_offset += tab.item_base[n];
-            for (int32_t i = 0; i < n; ++i)
-                tab.item_base[i + 1] = tab.item_base[i] + prefill_items_of_seq(tab.sink[i], tab.block[i], tab.ctx[i], kFp8TileRows);
-            if (tab.item_base[n] > 0) {
-                hipError_t e = launch_build_fp8_items(tab, bases, items, item_offset, hs);
-                if (e != hipSuccess) return hip_fail(e, "fp8 work-list launch");
-            }
-            item_offset += tab.item_base[n];
+            item_offset += items_of.base[n];
         }
-        hipError_t e = launch_fp8_quantise(q, k, v, T, heads->n_q_heads, heads->n_kv_heads, heads->head_dim,
-                                           scale_of(heads) * 1.4426950408889634f, key_tiles,
+        hipError_t e = launch_fp8_quantise(q, k, v, T, heads->n_q_heads, heads->n_kv_heads, heads->head_dim, q_factor, key_tiles,
                                            (int32_t)plan.n_key_tiles, (uint32_t *)(ws + plan.kv_amax), (float *)(ws + plan.q_scales),
                                            (uint8_t *)(ws + plan.q_codes), (uint8_t *)(ws + plan.k_tiles),
-                                           (uint8_t *)(ws + plan.v_tiles), compute_units(), hs);
+                                           (uint8_t *)(ws + plan.v_tiles), compute_units(), !(stages & PEVLM_FP8_ATTEND), hs);
         if (e != hipSuccess) return hip_fail(e, "fp8 quantise launch");
     }
     if (stages & PEVLM_FP8_ATTEND) {
-        p.q_codes = (const uint8_t *)(ws + plan.q_codes);
-        p.q_scales = (const float *)(ws + plan.q_scales);
+        p.q = stages & PEVLM_FP8_QUANTISE ? q : nullptr;
+        p.q_factor = q_factor;
+        p.q_codes = (uint8_t *)(ws + plan.q_codes);
+        p.q_scales = (float *)(ws + plan.q_scales);
         p.k_tiles = (const uint8_t *)(ws + plan.k_tiles);
         p.v_tiles = (const uint8_t *)(ws + plan.v_tiles);
         p.kv_amax = (const uint32_t *)(ws + plan.kv_amax);

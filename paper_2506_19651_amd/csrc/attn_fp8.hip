@@ -23,6 +23,7 @@
 // largest weight of a row lies in [2^7, 2^8] (E4M3 reaches 448) and weights down to 2^-16 of the
 // largest keep at least one significant bit.  The row sum is taken over the unrounded weights.
 #include <algorithm>
+#include <type_traits>
 
 #include "attn_bf16_tile.h"
 
@@ -82,6 +83,17 @@ __device__ __forceinline__ void bf16x8_to_f32(const uint4 &raw, float *dst)
     }
 }
 
+// largest magnitude of eight pairs of bf16 values, as the bit pattern of an fp32 value: magnitudes order like the
+// 15-bit integers that encode them, so the two halves of a word are compared by one packed maximum
+__device__ __forceinline__ uint32_t largest_magnitude(const uint32_t (&w)[8])
+{
+    typedef __attribute__((ext_vector_type(2))) uint16_t u16x2;
+    u16x2 m = {0, 0};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w[i] & 0x7fff7fffu));
+    return (uint32_t)(m[0] > m[1] ? m[0] : m[1]) << 16;
+}
+
 // position of the 16-byte chunk c of row r inside a staged tile whose rows hold CPR chunks: rows that
 // 16 consecutive lanes read together are spread over all LDS banks
 template <int CPR>
@@ -90,28 +102,28 @@ __host__ __device__ __forceinline__ int32_t swizzled_chunk(int32_t r, int32_t c)
     return c ^ ((r / (16 / CPR)) % CPR);
 }
 
-// One k-step of the scores of 64 keys x 32 rows: s[kc] = c + K Q^T with the block exponents of K and Q, c the
-// start values (FIRST) or s[kc].  Written as instructions because both chunks start from the same 16 registers:
+// One k-step of the scores of 64 keys x 32 rows: s[kc] = c + K Q^T with the block exponents of K and Q, c = 0, the
+// start values or s[kc].  Written as instructions because both chunks start from the same 16 registers:
 // left to the compiler the start values are copied for one of the chunks on every tile.  The wait states after the
 // LAST step cover the 16-pass results for whatever reads them next; between two steps a chunk's MFMAs are one
 // MFMA (64 cycles) apart, which the chained accumulator needs no wait for.
-template <bool FIRST, bool LAST>
+enum { kFromZero, kFromStart, kContinue };
+template <int FROM, bool LAST>
 __device__ __forceinline__ void score_step(const i32x8 &k0, const i32x8 &k1, const i32x8 &q, const f32x16 &start, int32_t k_exp8,
                                            int32_t q_exp8, f32x16 (&s)[2])
 {
-#define PEVLM_SCORE(dst, kreg, creg) "v_mfma_scale_f32_32x32x64_f8f6f4 " dst ", " kreg ", %4, " creg ", %6, %7 op_sel_hi:[0,0,0]\n\t"
-#define PEVLM_RESULT_WAIT "s_nop 15\n\ts_nop 3"
-    if (FIRST && LAST)
-        asm volatile(PEVLM_SCORE("%0", "%2", "%5") PEVLM_SCORE("%1", "%3", "%5") PEVLM_RESULT_WAIT
-                     : "=&v"(s[0]), "=&v"(s[1]) : "v"(k0), "v"(k1), "v"(q), "v"(start), "v"(k_exp8), "v"(q_exp8));
-    else if (FIRST)
-        asm volatile(PEVLM_SCORE("%0", "%2", "%5") PEVLM_SCORE("%1", "%3", "%5")
-                     : "=&v"(s[0]), "=&v"(s[1]) : "v"(k0), "v"(k1), "v"(q), "v"(start), "v"(k_exp8), "v"(q_exp8));
+#define PEVLM_SCORE(dst, kreg, creg) "v_mfma_scale_f32_32x32x64_f8f6f4 " dst ", " kreg ", %4, " creg ", %5, %6 op_sel_hi:[0,0,0]\n\t"
+    if (FROM == kFromZero)
+        asm volatile(PEVLM_SCORE("%0", "%2", "0") PEVLM_SCORE("%1", "%3", "0")
+                     : "=&v"(s[0]), "=&v"(s[1]) : "v"(k0), "v"(k1), "v"(q), "v"(k_exp8), "v"(q_exp8));
+    else if (FROM == kFromStart)
+        asm volatile(PEVLM_SCORE("%0", "%2", "%7") PEVLM_SCORE("%1", "%3", "%7")
+                     : "=&v"(s[0]), "=&v"(s[1]) : "v"(k0), "v"(k1), "v"(q), "v"(k_exp8), "v"(q_exp8), "v"(start));
     else
-        asm volatile(PEVLM_SCORE("%0", "%2", "%0") PEVLM_SCORE("%1", "%3", "%1") PEVLM_RESULT_WAIT
-                     : "+v"(s[0]), "+v"(s[1]) : "v"(k0), "v"(k1), "v"(q), "i"(0), "v"(k_exp8), "v"(q_exp8));
+        asm volatile(PEVLM_SCORE("%0", "%2", "%0") PEVLM_SCORE("%1", "%3", "%1")
+                     : "+v"(s[0]), "+v"(s[1]) : "v"(k0), "v"(k1), "v"(q), "v"(k_exp8), "v"(q_exp8));
 #undef PEVLM_SCORE
-#undef PEVLM_RESULT_WAIT
+    if (LAST) asm volatile("s_nop 15\n\ts_nop 3" : "+v"(s[0]), "+v"(s[1]));
 }
 
 // maximum of 8 values without the quieting moves that plain fmaxf puts in front of values it cannot prove canonical
@@ -136,75 +148,87 @@ __device__ __forceinline__ float row_max_grouped(const f32x16 (&s)[2])
 
 }  // namespace
 
-// ---------------------------------------------------------------- work list
-__global__ __launch_bounds__(256) void build_fp8_items_kernel(SeqTable tab, Fp8TileBases bases, Fp8Item *items, int32_t item_offset)
+// ---------------------------------------------------------------- work lists
+// Both lists of a chunk of sequences (tiles.item_base counts 64-row key tiles, items.item_base 128-row items) and,
+// with the first chunk, the zeros that the maxima start from: one launch instead of three of 4-5 us each.
+__global__ __launch_bounds__(256) void fp8_setup_kernel(SeqTable tab, Fp8TileBases bases, Fp8ItemBases items_of, pevlm_work_item *key_tiles,
+                                                        int32_t tile_offset, Fp8Item *items, int32_t item_offset, uint32_t *zero, int32_t n_zero)
 {
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= tab.item_base[tab.num_seqs]) return;
-    int32_t s = 0;
-    while (s + 1 < tab.num_seqs && i >= tab.item_base[s + 1]) ++s;
-    const int32_t S = tab.sink[s], B = tab.block[s];
-    const pevlm_work_item w = prefill_item(tab.start[s], S, B, tab.ctx[s], kFp8TileRows, i - tab.item_base[s], tab.seq_index0 + s);
-    Fp8Item it;
-    it.q_start = w.q_start;
-    it.q_rows = w.q_rows;
-    it.full_start = w.full_start;
-    it.full_len = w.full_len;
-    it.full_tile0 = bases.base[s];  // the sink is the first region of the sequence
-    it.diag_start = w.diag_start;
-    it.diag_len = w.diag_len;
-    const int32_t local = w.diag_start - tab.start[s];  // first position of the item's own region
-    it.diag_tile0 = bases.base[s] + (local < S ? 0 : ceil_div(S, kKeyTile) + ((local - S) / B) * ceil_div(B, kKeyTile));
-    items[item_offset + i] = it;
-}
-
-__global__ void zero_words_kernel(uint32_t *p, int32_t n)
-{
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
+    if (i < n_zero) zero[i] = 0u;
+    if (i < tab.item_base[tab.num_seqs]) {
+        int32_t s = 0;
+        while (s + 1 < tab.num_seqs && i >= tab.item_base[s + 1]) ++s;
+        key_tiles[tile_offset + i] = prefill_item(tab.start[s], tab.sink[s], tab.block[s], tab.ctx[s], kKeyTile, i - tab.item_base[s], tab.seq_index0 + s);
+    }
+    if (i < items_of.base[tab.num_seqs]) {
+        int32_t s = 0;
+        while (s + 1 < tab.num_seqs && i >= items_of.base[s + 1]) ++s;
+        const int32_t S = tab.sink[s], B = tab.block[s];
+        const pevlm_work_item w = prefill_item(tab.start[s], S, B, tab.ctx[s], kFp8TileRows, i - items_of.base[s], tab.seq_index0 + s);
+        Fp8Item it;
+        it.q_start = w.q_start;
+        it.q_rows = w.q_rows;
+        it.full_start = w.full_start;
+        it.full_len = w.full_len;
+        it.full_tile0 = bases.base[s];  // the sink is the first region of the sequence
+        it.diag_start = w.diag_start;
+        it.diag_len = w.diag_len;
+        const int32_t local = w.diag_start - tab.start[s];  // first position of the item's own region
+        it.diag_tile0 = bases.base[s] + (local < S ? 0 : ceil_div(S, kKeyTile) + ((local - S) / B) * ceil_div(B, kKeyTile));
+        items[item_offset + i] = it;
+    }
 }
 
 // ---------------------------------------------------------------- quantise
-// Largest magnitude per KV head of K (amax[g]) and V (amax[Hkv + g]): blockIdx.y = head, blockIdx.z = tensor.
-// Bit patterns of non-negative floats order like the floats, so the reduction is an integer maximum.
+// Largest magnitude per KV head of K (amax[g]) and V (amax[Hkv + g]): blockIdx.y = tensor.  The tensor is read
+// front to back, 16 bytes a lane, in steps that are a multiple of a token's row, so that a lane stays in one
+// head (reading one head's 256 bytes out of every row: 40 us for the 135 MB of 66K tokens x 4 heads; whole rows:
+// 33 us, of which 5 us are the launch).  Bit patterns of non-negative floats order like the floats, so the reduction is an integer
+// maximum, and a bf16 pair's magnitudes compare as its two halves.
 template <int D>
 __global__ __launch_bounds__(256) void amax_kv_kernel(const uint16_t *k, const uint16_t *v, int64_t T, int32_t Hkv, uint32_t *amax)
 {
-    constexpr int CPR = D / 8;          // 16-byte chunks of bf16 per row of one head
-    constexpr int RPS = 256 / CPR;      // rows per step of the workgroup
-    const int32_t g = blockIdx.y;
-    const uint16_t *src = blockIdx.z ? v : k;
-    const int32_t c = threadIdx.x % CPR, r0 = threadIdx.x / CPR;
-    float m = 0.f;
-    const int64_t step = (int64_t)gridDim.x * RPS;
-    int64_t r = (int64_t)blockIdx.x * RPS + r0;
-    for (; r + 3 * step < T; r += 4 * step) {  // four rows in flight per lane
-        uint4 raw[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) raw[u] = *reinterpret_cast<const uint4 *>(src + ((r + u * step) * Hkv + g) * D + c * 8);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            float x[8];
-            bf16x8_to_f32(raw[u], x);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(x[i]));
-        }
-    }
-    for (; r < T; r += step) {
-        const uint4 raw = *reinterpret_cast<const uint4 *>(src + (r * Hkv + g) * D + c * 8);
-        float x[8];
-        bf16x8_to_f32(raw, x);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(x[i]));
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    // one atomic per workgroup: atomics on the same word are served one after the other
-    __shared__ float wave_max[4];
-    if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = m;
+    const int32_t chunks = Hkv * (D / 8);  // 16-byte chunks of a token's row
+    const int64_t total = T * chunks;
+    const int64_t lanes = (int64_t)gridDim.x * 256, step = lanes / chunks * chunks;  // the launch has at least one row of lanes
+    const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint4 *src = reinterpret_cast<const uint4 *>(blockIdx.y ? v : k);
+    __shared__ uint32_t head_max[kMaxHeads];
+    for (int32_t i = threadIdx.x; i < Hkv; i += 256) head_max[i] = 0u;
     __syncthreads();
-    if (threadIdx.x == 0)
-        atomicMax(amax + blockIdx.z * Hkv + g, __float_as_uint(fmaxf(fmaxf(wave_max[0], wave_max[1]), fmaxf(wave_max[2], wave_max[3]))));
+    uint32_t lo = 0u, hi = 0u;  // maxima of the magnitudes in the low and high halves, both as (value << 16)
+    auto take = [&](uint32_t w) {
+        const uint32_t l = (w << 16) & 0x7fff0000u, h = w & 0x7fff0000u;
+        lo = l > lo ? l : lo;
+        hi = h > hi ? h : hi;
+    };
+    if (first < step) {
+        int64_t i = first;
+        constexpr int U = 8;  // loads in flight per lane
+        for (; i + (U - 1) * step < total; i += U * step) {
+            uint4 raw[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) raw[u] = src[i + u * step];
+#pragma unroll
+            for (int u = 0; u < U; ++u) { take(raw[u].x); take(raw[u].y); take(raw[u].z); take(raw[u].w); }
+        }
+        for (; i < total; i += step) {
+            const uint4 raw = src[i];
+            take(raw.x); take(raw.y); take(raw.z); take(raw.w);
+        }
+        // lanes of a head first (D/8 neighbours share one), then the workgroup, then one atomic per workgroup and head
+        uint32_t m = lo > hi ? lo : hi;
+#pragma unroll
+        for (int off = D / 16; off >= 1; off >>= 1) {
+            const uint32_t x = (uint32_t)__shfl_xor((int32_t)m, off);
+            m = x > m ? x : m;
+        }
+        if (threadIdx.x % (D / 8) == 0) atomicMax(&head_max[(int32_t)((first % chunks) / (D / 8))], m);
+    }
+    __syncthreads();
+    for (int32_t i = threadIdx.x; i < Hkv; i += 256)
+        if (head_max[i]) atomicMax(amax + blockIdx.y * Hkv + i, head_max[i]);
 }
 
 // Q: one scale per (token, head); D/16 consecutive lanes share a row of one head.  What is quantised is
@@ -300,7 +324,12 @@ __global__ __launch_bounds__(256) void quantise_kv_tiles_kernel(const uint16_t *
 // them ordinary vector registers -- given more, the compiler parks the MFMA results in accumulation
 // registers and copies them back and forth around every softmax step (measured 24 % slower) -- and
 // lets the vector work of one wavefront run under the MFMAs of the others.
-template <int D>
+//
+// QUANTISE_Q (a call of both stages): every row of Q is used by exactly one wavefront, which quantises it on the
+// way in and leaves codes and scales in the workspace for later ATTEND calls.  The separate kernel reads 472 MB
+// and writes 236 MB of codes that are then read back (64K tokens x 28 heads: 115 us); here the same rows cost
+// 55 us of vector arithmetic inside a kernel that leaves HBM three quarters idle (attention 464 -> 520 us).
+template <int D, bool QUANTISE_Q>
 __global__ __launch_bounds__(256, 3) void attn_fp8_kernel(Fp8Params p)
 {
     constexpr int KT = kKeyTile, CPR = D / 16, TILEB = KT * D;
@@ -347,39 +376,87 @@ __global__ __launch_bounds__(256, 3) void attn_fp8_kernel(Fp8Params p)
 
     // query fragments: lane (row l32, half g32) holds head_dim [64 kk + 32 g32, +32) of its row
     i32x8 qf[KQ];
-    {
-        const uint8_t *qrow = p.q_codes + ((int64_t)my_row * Hq + head) * D;
+    int32_t q_exp8;
+    const int64_t q_unit = (int64_t)my_row * Hq + head;
+    if (QUANTISE_Q) {
+        // D/16 lanes share a row, so that rows are read and codes written as whole lines; the codes reach the lanes
+        // that need them through a wavefront-private quarter of tile stage 1, which is free until every wavefront
+        // has passed the top of tile 0.
+        constexpr int LPR = D / 16, RPS = 64 / LPR, NS = 32 / RPS;  // lanes per row, rows per step, steps
+        uint8_t *const slice = lds + ((wave >> 1) * 2 + 1) * TILEB + (wave & 1) * (32 * D);
+        const int32_t c = lane % LPR;
+        uint4 raw[NS][2];
+#pragma unroll
+        for (int st = 0; st < NS; ++st) {
+            const int32_t r = st * RPS + lane / LPR, row = w_rows > 0 ? wr_lo + (r < w_rows ? r : w_rows - 1) : it.q_start;
+            const uint4 *src = reinterpret_cast<const uint4 *>((const uint16_t *)p.q + ((int64_t)row * Hq + head) * D + c * 16);
+            raw[st][0] = src[0];
+            raw[st][1] = src[1];
+        }
+        q_exp8 = 0;
+#pragma unroll
+        for (int st = 0; st < NS; ++st) {
+            const uint32_t w[8] = {raw[st][0].x, raw[st][0].y, raw[st][0].z, raw[st][0].w, raw[st][1].x, raw[st][1].y, raw[st][1].z, raw[st][1].w};
+            uint32_t m = largest_magnitude(w);
+#pragma unroll
+            for (int off = LPR / 2; off >= 1; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int32_t)m, off));
+            // rounding is monotonic: the largest |q * factor| is the largest |q| times factor.  Multiplying by factor
+            // and then by the power of two rounds like multiplying by their product, but where the product of the
+            // first multiplication is subnormal, and there the code is 0 either way.
+            const int32_t e = scale_exponent(__fmul_rn(__uint_as_float(m), p.q_factor));
+            const float mul = p.q_factor * pow2(-e);
+            float x[16];
+            bf16x8_to_f32(raw[st][0], x);
+            bf16x8_to_f32(raw[st][1], x + 8);
+            const i32x4v codes = quantise16(x, mul);
+            const int32_t r = st * RPS + lane / LPR;
+            *reinterpret_cast<i32x4v *>(slice + r * D + swizzled_chunk<CPR>(r, c) * 16) = codes;
+            const int32_t mine = __shfl(127 + e, (l32 % RPS) * LPR);
+            if (l32 / RPS == st) q_exp8 = mine;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int kk = 0; kk < KQ; ++kk) {
+            const int32_t c0 = kk * 4 + g32 * 2;
+            const i32x4v a = *reinterpret_cast<const i32x4v *>(slice + l32 * D + swizzled_chunk<CPR>(l32, c0) * 16);
+            const i32x4v b = *reinterpret_cast<const i32x4v *>(slice + l32 * D + swizzled_chunk<CPR>(l32, c0 + 1) * 16);
+            qf[kk] = i32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slice has been read before this wavefront passes a barrier
+    } else {
+        const uint8_t *qrow = p.q_codes + q_unit * D;
 #pragma unroll
         for (int kk = 0; kk < KQ; ++kk) {
             const i32x4v a = *reinterpret_cast<const i32x4v *>(qrow + kk * 64 + g32 * 32);
             const i32x4v b = *reinterpret_cast<const i32x4v *>(qrow + kk * 64 + g32 * 32 + 16);
             qf[kk] = i32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
         }
+        q_exp8 = (__float_as_int(p.q_scales[q_unit]) >> 23) & 0xff;
     }
     // The scales of K (per head) and of the query row (per lane: both halves of the wavefront hold the same
     // rows) go into the score MFMAs as 8-bit exponents; the accumulators start from kWeightShift minus the
     // row's reference maximum, so the MFMAs deliver the exponents of the weights directly.
     const int32_t k_exp8 = 127 + scale_exponent(__uint_as_float(p.kv_amax[g]));
-    const int32_t q_exp8 = (__float_as_int(p.q_scales[(int64_t)my_row * Hq + head]) >> 23) & 0xff;
     const float v_scale = pow2(scale_exponent(__uint_as_float(p.kv_amax[Hkv + g])));
 
     f32x16 o[DBLK], s[2];
-#pragma unroll
-    for (int b = 0; b < DBLK; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o[b][i] = 0.f;
     float m_ref = -INFINITY, l_run = 0.f;
-    float shift = kWeightShift;  // kWeightShift - (reference maximum, 0 while the row has none)
-    f32x16 start;                // the same in all 16 accumulator registers of the lane
-#pragma unroll
-    for (int i = 0; i < 16; ++i) start[i] = shift;
+    float shift = 0.f;  // kWeightShift - reference maximum, once there is one
+    f32x16 start;       // the same in all 16 accumulator registers of the lane
 
-    for (int32_t t = 0; t < n_tiles; ++t) {
+    // Tile t for this wavefront.  The first one has no reference yet: its scores start from the inline constant 0
+    // and are moved to their own maximum, its value MFMAs start the accumulators -- no clearing and rescaling of
+    // 64 + 16 registers that hold nothing (150 of the 2700 vector instructions of an item of 12 tiles).
+    auto tile_top = [&](int32_t t) {
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's share of tile t has landed
         __builtin_amdgcn_s_barrier();        // ... everybody's has, and everybody has left tile t - 1
         asm volatile("" ::: "memory");
         if (t + 1 < n_tiles) PEVLM_FP8_LOAD_TILE(t + 1, (t + 1) & 1);
-        if (t >= n_w) continue;
+    };
+    auto tile_step = [&](auto first_tag, int32_t t) {
+        constexpr bool FIRST = decltype(first_tag)::value;
         const uint8_t *tk = lds + (t & 1) * TILEB, *tv = lds + (2 + (t & 1)) * TILEB;
         // ---- S^T = K Q^T: rows = keys of the chunk, columns = this wavefront's query rows
         auto read_k = [&](int kk, int kc) {
@@ -388,8 +465,8 @@ __global__ __launch_bounds__(256, 3) void attn_fp8_kernel(Fp8Params p)
             const i32x4v b = *reinterpret_cast<const i32x4v *>(tk + r * D + swizzled_chunk<CPR>(r, c0 + 1) * 16);
             return i32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
         };
-        score_step<true, KQ == 1>(read_k(0, 0), read_k(0, 1), qf[0], start, k_exp8, q_exp8, s);
-        if (KQ == 2) score_step<false, true>(read_k(KQ - 1, 0), read_k(KQ - 1, 1), qf[KQ - 1], start, k_exp8, q_exp8, s);
+        score_step<FIRST ? kFromZero : kFromStart, KQ == 1>(read_k(0, 0), read_k(0, 1), qf[0], start, k_exp8, q_exp8, s);
+        if (KQ == 2) score_step<kContinue, true>(read_k(KQ - 1, 0), read_k(KQ - 1, 1), qf[KQ - 1], start, k_exp8, q_exp8, s);
         int32_t k0, kend;
         bool causal;
         if (t < n_full) {
@@ -401,17 +478,19 @@ __global__ __launch_bounds__(256, 3) void attn_fp8_kernel(Fp8Params p)
         // ---- reference maximum: raised to the running maximum once that is more than kWeightLag above it
         const float mx = row_max_grouped(s) - shift;
         const bool raise = mx > m_ref + kWeightLag;
-        if (__any(raise)) {
+        if (FIRST || __any(raise)) {
             const float m_new = raise ? mx : m_ref;
-            const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);  // 1 where nothing changes, 0 for the first tile
+            if (!FIRST) {
+                const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);  // 1 where nothing changes
+                l_run *= alpha;
+#pragma unroll
+                for (int b = 0; b < DBLK; ++b)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) o[b][i] *= alpha;
+            }
             m_ref = m_new;
-            l_run *= alpha;
-#pragma unroll
-            for (int b = 0; b < DBLK; ++b)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) o[b][i] *= alpha;
             // the scores of this tile move to the new reference; later tiles start from it
-            const float new_shift = kWeightShift - ((m_ref == -INFINITY) ? 0.f : m_ref);
+            const float new_shift = kWeightShift - m_ref;
             const float delta = new_shift - shift;
             shift = new_shift;
 #pragma unroll
@@ -447,14 +526,32 @@ __global__ __launch_bounds__(256, 3) void attn_fp8_kernel(Fp8Params p)
             }
         l_run += psum;
         // ---- O^T += V^T P^T
+        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int b = 0; b < DBLK; ++b) {
             if (b + 1 < DBLK) vf[(b + 1) & 1] = read_v(b + 1);
-            o[b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vf[b & 1], pf, o[b], 0, 0, 0, 0, 0, 0);
+            o[b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vf[b & 1], pf, FIRST ? zero : o[b], 0, 0, 0, 0, 0, 0);
         }
+    };
+    tile_top(0);
+    if (n_w > 0) tile_step(std::true_type(), 0);
+    for (int32_t t = 1; t < n_tiles; ++t) {
+        tile_top(t);
+        if (t < n_w) tile_step(std::false_type(), t);
     }
 #undef PEVLM_FP8_LOAD_TILE
 
+    // The codes and scales of Q leave with the output: stored in front of the loop they would be waited for at the top
+    // of the first tile (stores and the tile loads share a counter).
+    if (QUANTISE_Q && l32 < w_rows) {
+        uint8_t *dst = p.q_codes + q_unit * D + g32 * 32;
+#pragma unroll
+        for (int kk = 0; kk < KQ; ++kk) {
+            *reinterpret_cast<i32x4v *>(dst + kk * 64) = i32x4v{qf[kk][0], qf[kk][1], qf[kk][2], qf[kk][3]};
+            *reinterpret_cast<i32x4v *>(dst + kk * 64 + 16) = i32x4v{qf[kk][4], qf[kk][5], qf[kk][6], qf[kk][7]};
+        }
+        if (g32 == 0) p.q_scales[q_unit] = pow2(q_exp8 - 127);
+    }
     // ---- output: normalise, undo the V scale, rows out through LDS as whole 2 D-byte rows
     __syncthreads();  // every wavefront has left the tile stages
     uint8_t *slice = lds + wave * 32 * ROWB;
@@ -474,46 +571,56 @@ __global__ __launch_bounds__(256, 3) void attn_fp8_kernel(Fp8Params p)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    uint16_t *const obase = (uint16_t *)p.out;
+    uint8_t *const obase = (uint8_t *)p.out + ((int64_t)wr_lo * Hq + head) * ROWB;  // wavefront-uniform
     const int32_t cp = lane % CH;
+    uint32_t off = (uint32_t)(lane / CH * Hq * ROWB + cp * 16);
 #pragma unroll
-    for (int j = 0; j < NOL; ++j) {
+    for (int j = 0; j < NOL; ++j, off += (uint32_t)(RPI * Hq * ROWB)) {
         const int32_t rl = j * RPI + lane / CH;
         const uint4 val = *reinterpret_cast<const uint4 *>(slice + rl * ROWB + ((cp ^ (rl & (CH - 1))) << 4));
-        if (rl < w_rows) *reinterpret_cast<uint4 *>(obase + ((int64_t)(wr_lo + rl) * Hq + head) * D + cp * 8) = val;
+        if (rl < w_rows) *reinterpret_cast<uint4 *>(obase + off) = val;
     }
     if (p.lse && g32 == 0 && l32 < w_rows)
         p.lse[(int64_t)(wr_lo + l32) * Hq + head] = (m_ref - kWeightShift + __log2f(l_tot)) * 0.69314718056f;
 }
 
 // ---------------------------------------------------------------- launchers
-hipError_t launch_build_fp8_items(const SeqTable &tab, const Fp8TileBases &bases, Fp8Item *items, int32_t item_offset, hipStream_t stream)
+hipError_t launch_fp8_setup(const SeqTable &tab, const Fp8TileBases &bases, const Fp8ItemBases &items_of, pevlm_work_item *key_tiles,
+                            int32_t tile_offset, Fp8Item *items, int32_t item_offset, uint32_t *zero, int32_t n_zero, hipStream_t stream)
 {
-    const int32_t total = tab.item_base[tab.num_seqs];
-    hipLaunchKernelGGL(build_fp8_items_kernel, dim3((total + 255) / 256), dim3(256), 0, stream, tab, bases, items, item_offset);
+    const int32_t n = std::max(std::max(tab.item_base[tab.num_seqs], items_of.base[tab.num_seqs]), n_zero);
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(fp8_setup_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, tab, bases, items_of, key_tiles, tile_offset, items,
+                       item_offset, zero, n_zero);
     return hipGetLastError();
+}
+
+template <int D>
+static void quantise_launches(const uint16_t *q, const uint16_t *k, const uint16_t *v, int64_t T, int32_t Hq, int32_t Hkv, float q_factor,
+                              const pevlm_work_item *key_tiles, int32_t n_key_tiles, uint32_t *kv_amax, float *q_scales, uint8_t *q_codes,
+                              uint8_t *k_tiles, uint8_t *v_tiles, int32_t compute_units, bool with_q, hipStream_t stream)
+{
+    // K and V twice in a row, so that the second reading finds what the last-level cache kept of the first (64K
+    // tokens: tiles 31 us, 43 us with Q's kernel in between).  One workgroup per compute unit and tensor for the maxima:
+    // with four, 4096 atomics on 8 words cost 5 us of 38.
+    const int64_t chunks = T * Hkv * (D / 8);
+    const int32_t row_blocks = (Hkv * (D / 8) + 255) / 256;  // at least one row of lanes
+    const int32_t bx = (int32_t)std::max<int64_t>(row_blocks, std::min<int64_t>((chunks + 2047) / 2048, compute_units));
+    hipLaunchKernelGGL((amax_kv_kernel<D>), dim3(bx, 2), dim3(256), 0, stream, k, v, T, Hkv, kv_amax);
+    hipLaunchKernelGGL((quantise_kv_tiles_kernel<D>), dim3(n_key_tiles, Hkv), dim3(256), 0, stream, k, v, key_tiles, Hkv, kv_amax, k_tiles, v_tiles);
+    if (with_q) {
+        const int64_t q_threads = T * Hq * (D / 16);
+        hipLaunchKernelGGL((quantise_q_kernel<D>), dim3((uint32_t)((q_threads + 255) / 256)), dim3(256), 0, stream, q, T * Hq, q_factor, q_codes, q_scales);
+    }
 }
 
 hipError_t launch_fp8_quantise(const void *q, const void *k, const void *v, int64_t T, int32_t Hq, int32_t Hkv, int32_t D,
                                float q_factor, const pevlm_work_item *key_tiles, int32_t n_key_tiles, uint32_t *kv_amax, float *q_scales,
-                               uint8_t *q_codes, uint8_t *k_tiles, uint8_t *v_tiles, int32_t compute_units, hipStream_t stream)
+                               uint8_t *q_codes, uint8_t *k_tiles, uint8_t *v_tiles, int32_t compute_units, bool with_q, hipStream_t stream)
 {
-    hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(256), 0, stream, kv_amax, 2 * Hkv);
-    const int32_t rows_per_step = 256 / (D / 8);
-    int32_t bx = (int32_t)std::min<int64_t>((T + rows_per_step - 1) / rows_per_step, std::max(1, 8 * compute_units / std::max(1, 2 * Hkv)));
-    const int64_t q_threads = T * Hq * (D / 16);
-    const dim3 q_grid((uint32_t)((q_threads + 255) / 256));
-    if (D == 128) {
-        hipLaunchKernelGGL((amax_kv_kernel<128>), dim3(bx, Hkv, 2), dim3(256), 0, stream, (const uint16_t *)k, (const uint16_t *)v, T, Hkv, kv_amax);
-        hipLaunchKernelGGL((quantise_q_kernel<128>), q_grid, dim3(256), 0, stream, (const uint16_t *)q, T * Hq, q_factor, q_codes, q_scales);
-        hipLaunchKernelGGL((quantise_kv_tiles_kernel<128>), dim3(n_key_tiles, Hkv), dim3(256), 0, stream, (const uint16_t *)k,
-                           (const uint16_t *)v, key_tiles, Hkv, kv_amax, k_tiles, v_tiles);
-    } else {
-        hipLaunchKernelGGL((amax_kv_kernel<64>), dim3(bx, Hkv, 2), dim3(256), 0, stream, (const uint16_t *)k, (const uint16_t *)v, T, Hkv, kv_amax);
-        hipLaunchKernelGGL((quantise_q_kernel<64>), q_grid, dim3(256), 0, stream, (const uint16_t *)q, T * Hq, q_factor, q_codes, q_scales);
-        hipLaunchKernelGGL((quantise_kv_tiles_kernel<64>), dim3(n_key_tiles, Hkv), dim3(256), 0, stream, (const uint16_t *)k,
-                           (const uint16_t *)v, key_tiles, Hkv, kv_amax, k_tiles, v_tiles);
-    }
+    const auto launches = D == 128 ? quantise_launches<128> : quantise_launches<64>;
+    launches((const uint16_t *)q, (const uint16_t *)k, (const uint16_t *)v, T, Hq, Hkv, q_factor, key_tiles, n_key_tiles, kv_amax, q_scales, q_codes,
+             k_tiles, v_tiles, compute_units, with_q, stream);
     return hipGetLastError();
 }
 
@@ -521,8 +628,14 @@ hipError_t launch_attn_fp8(const Fp8Params &p, int32_t D, hipStream_t stream)
 {
     const int32_t n_work = p.n_items * p.n_q_heads;
     const dim3 grid(8 * ((n_work + 7) / 8)), block(256);
-    if (D == 128) hipLaunchKernelGGL((attn_fp8_kernel<128>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((attn_fp8_kernel<64>), grid, block, 0, stream, p);
+    const bool quantise_q = p.q != nullptr;
+    if (D == 128) {
+        if (quantise_q) hipLaunchKernelGGL((attn_fp8_kernel<128, true>), grid, block, 0, stream, p);
+        else hipLaunchKernelGGL((attn_fp8_kernel<128, false>), grid, block, 0, stream, p);
+    } else {
+        if (quantise_q) hipLaunchKernelGGL((attn_fp8_kernel<64, true>), grid, block, 0, stream, p);
+        else hipLaunchKernelGGL((attn_fp8_kernel<64, false>), grid, block, 0, stream, p);
+    }
     return hipGetLastError();
 }
 

@@ -420,9 +420,14 @@ struct Fp8Item {
 struct Fp8TileBases {
     int32_t base[kMaxSeqsPerLaunch + 1];  // first key tile of each sequence of the chunk (batch-absolute)
 };
+struct Fp8ItemBases {
+    int32_t base[kMaxSeqsPerLaunch + 1];  // first work item of each sequence of the chunk (chunk-relative)
+};
 struct Fp8Params {
-    const uint8_t *q_codes;   // [T][Hq][D]
-    const float *q_scales;    // [T][Hq]
+    const void *q;            // bf16 [T][Hq][D], quantised by the kernel itself into codes and scales; NULL: they are read
+    float q_factor;
+    uint8_t *q_codes;         // [T][Hq][D]
+    float *q_scales;          // [T][Hq]
     const uint8_t *k_tiles, *v_tiles;  // [key tile][Hkv][64 * D]
     const uint32_t *kv_amax;  // [2][Hkv] bit patterns of the largest magnitudes of K and V per head
     void *out;                // [T][Hq][D] bf16
@@ -467,11 +472,12 @@ hipError_t launch_build_stream_items(const SeqTable &tab, int32_t G, int32_t Hkv
                                      pevlm_stream_item *items, int32_t item_offset, hipStream_t stream);
 // block-prefill rows of bf16 tensors from a stream-item list; workgroups = compute units (8 wavefronts each)
 hipError_t launch_attn_bf16_stream(const StreamParams &p, int32_t D, int32_t compute_units, hipStream_t stream);
-hipError_t launch_build_fp8_items(const SeqTable &tab, const Fp8TileBases &bases, Fp8Item *items, int32_t item_offset, hipStream_t stream);
-// bf16 Q, K, V -> E4M3 codes and scales (key_tiles: the prefill items of 64 rows, one per K/V tile)
+hipError_t launch_fp8_setup(const SeqTable &tab, const Fp8TileBases &bases, const Fp8ItemBases &items_of, pevlm_work_item *key_tiles,
+                            int32_t tile_offset, Fp8Item *items, int32_t item_offset, uint32_t *zero, int32_t n_zero, hipStream_t stream);
+// bf16 K, V and (with_q) Q -> E4M3 codes and scales (key_tiles: the prefill items of 64 rows, one per K/V tile)
 hipError_t launch_fp8_quantise(const void *q, const void *k, const void *v, int64_t T, int32_t Hq, int32_t Hkv, int32_t D,
                                float q_factor, const pevlm_work_item *key_tiles, int32_t n_key_tiles, uint32_t *kv_amax, float *q_scales,
-                               uint8_t *q_codes, uint8_t *k_tiles, uint8_t *v_tiles, int32_t compute_units, hipStream_t stream);
+                               uint8_t *q_codes, uint8_t *k_tiles, uint8_t *v_tiles, int32_t compute_units, bool with_q, hipStream_t stream);
 hipError_t launch_attn_fp8(const Fp8Params &p, int32_t D, hipStream_t stream);
 hipError_t launch_attn_f32(const AttnParams &p, int32_t D, bool partial, int32_t compute_units, hipStream_t stream);
 hipError_t launch_attn_bf16(const AttnParams &p, int32_t D, bool partial, hipStream_t stream);  // p.rope_tab selects the fused variant

@@ -128,3 +128,36 @@ def test_rope_heads_shared_between_workgroups(oracle, dtype, Hq, Hkv, D, tokens)
             want = oracle.rope(data[name], pos, w.rope_base)
             # one rounding to the storage type (2^-8 relative in bf16, 2^-23 in fp32) on top of fp32 arithmetic
             assert np.all(np.abs(got - want) <= (2.0 ** -8 if dtype == "bf16" else 2.0 ** -22) * np.abs(want) + 1e-6)
+
+
+@pytest.mark.parametrize("D,Hq,Hkv", [(128, 28, 4), (64, 6, 3), (128, 5, 1), (64, 14, 7)])
+@pytest.mark.parametrize("tokens", [1, 63, 129, 3000])
+def test_fp8_both_stages_leave_what_the_stages_leave(D, Hq, Hkv, tokens):
+    """Q quantised by the attention kernel (both stages in one call) against the stages called one after the other:
+    the same codes, scales and output bits; the maxima are those of the tensors."""
+    seqs = [(tokens // 3, max(1, tokens // 4), tokens - tokens // 3, 0)]
+    w = W.Workload(f"fp8both{tokens}", 36, "bf16", Hq, Hkv, D, 1.0e6, seqs, 0.5)
+    data = W.generate(w)
+    rng = np.random.default_rng(7)  # rows of very different magnitude, an all-zero row, zeros of both signs
+    x = W.bf16_bits_to_f32(data["q"]) * (2.0 ** rng.integers(-40, 40, (tokens, Hq, 1))).astype(np.float32)
+    x[tokens // 2] = 0.0
+    x[:, :, 3] = -0.0
+    data["q"] = W.f32_to_bf16_bits(x)
+    lay, heads = layout_heads(w)
+    q, k, v = to_device(data["q"]), to_device(data["k"]), to_device(data["v"])
+    plan = P.pevlm_block_prefill_fp8_plan(lay, heads)
+    outs, spaces = [], []
+    for stages in ((0,), (P.FP8_QUANTISE, P.FP8_ATTEND)):
+        ws = torch.full((plan.total,), 0xEE, dtype=torch.uint8, device=DEV)
+        out = torch.zeros_like(q)
+        for st in stages:
+            P.pevlm_block_prefill_attn_fp8(q, k, v, out, lay, heads, workspace=ws, stages=st)
+        torch.cuda.synchronize()
+        outs.append(out.view(torch.int16).cpu())
+        spaces.append(ws.cpu().numpy())
+    assert torch.equal(outs[0], outs[1])
+    for lo, n in ((plan.q_codes, tokens * Hq * D), (plan.q_scales, tokens * Hq * 4), (plan.kv_amax, 2 * Hkv * 4)):
+        assert np.array_equal(spaces[0][lo:lo + n], spaces[1][lo:lo + n])
+    amax = spaces[0][plan.kv_amax:plan.kv_amax + 2 * Hkv * 4].view(np.float32).reshape(2, Hkv)
+    for i, name in enumerate(("k", "v")):
+        assert np.array_equal(amax[i], np.abs(W.bf16_bits_to_f32(data[name])).max(axis=(0, 2)))
