@@ -305,13 +305,9 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[b][i] = 0.f;
 
-    // scores of tile t -> s (masked where the tile touches the diagonal or the end of its range)
-#define PEVLM_SCORES(t, LOADS)                                                            \
+    // entries of tile t that a row must not see (tiles that touch the diagonal or the end of their range)
+#define PEVLM_MASK(k0, kend, causal)                                                      \
     do {                                                                                  \
-        int32_t k0, kend;                                                                 \
-        bool causal;                                                                      \
-        PEVLM_TILE_RANGE(t, k0, kend, causal);                                            \
-        qk_tile<D, LOADS>(lds_k + ((t) & 1) * TILEB, L, qf, s, ldk);                     \
         if ((k0 + KT > kend) || (causal && (k0 + KT - 1 > wr_lo)))                        \
             mask_tile(s, k0, kend, causal, my_row, g32);                                  \
     } while (0)
@@ -329,7 +325,7 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
             const float alpha = has ? __builtin_amdgcn_exp2f(m_ref - m_new) : 1.f;                    \
             m_ref = m_new;                                                                            \
             psum = 0.f;                                                                               \
-            weights(s, c_log2, PEVLM_MREF, psum, pf_new);                                             \
+            weights(s, c_log2, PEVLM_MREF, psum, pf);                                                 \
             if (__any(has)) { /* rows without a reference have o = l = 0 */                          \
                 l_run *= alpha;                                                                       \
                 _Pragma("unroll") for (int b = 0; b < DBLK; ++b)                                      \
@@ -339,38 +335,46 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
     } while (0)
 
     f32x16 s[2];
-    u32x4 pf_prev[4], pf_new[4];
+    u32x4 pf[4];  // weights of the last tile whose scores are known, bf16 pairs
     float psum;
     TileLoads<NLD> ldk, ldv;
     bool k_mod = false, v_mod = false;
+    int32_t k0, kend;
+    bool causal;
     if (n_tiles > 0) {  // top of tile 0 for every wavefront
         __syncthreads();  // K(0), V(0) of every wavefront have landed; the query slices in stage 1 have been read
         if (1 < n_tiles) PEVLM_ISSUE_K(1);
     }
     if (n_w > 0) {
-        PEVLM_SCORES(0, false);
+        qk_tile<D, false, NLD>(lds_k, L, qf, s, ldk, [] {}, [] {});
+        PEVLM_TILE_RANGE(0, k0, kend, causal);
+        PEVLM_MASK(k0, kend, causal);
         psum = 0.f;  // no row has a reference yet: the first tile always takes the exact path
         PEVLM_FIX_REFERENCE();
         l_run += psum;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) pf_prev[j] = pf_new[j];
         for (int32_t t = 1; t < n_w; ++t) {
             // top of tile t as in PEVLM_TOP, but K(t+1) and V(t) are fetched piecewise between the
             // MFMAs below; after the last tile the K loads repeat that tile into the stage nobody
             // reads any more, which keeps the loop body free of branches
             __builtin_amdgcn_s_waitcnt(0x0F70);
             __syncthreads();
-            const int32_t tk = t + 1 < n_tiles ? t + 1 : n_tiles - 1;
-            PEVLM_SET_LOADS(ldk, K, koff, k_mod, (row & (CH - 1)), lds_k_addr, tk, (t + 1) & 1);
-            PEVLM_SET_LOADS(ldv, V, voff, v_mod, ((row & VSW) << 2), lds_v_addr, t, t & 1);
-            PEVLM_SCORES(t, true);
+            const uint8_t *const tv = lds_v + ((t - 1) & 1) * TILEB;
+            bf16x8 vfirst[kValuesAhead];
+            qk_tile<D, true, NLD>(
+                lds_k + (t & 1) * TILEB, L, qf, s, ldk,
+                [&] {
+                    const int32_t tk = t + 1 < n_tiles ? t + 1 : n_tiles - 1;
+                    PEVLM_SET_LOADS(ldk, K, koff, k_mod, (row & (CH - 1)), lds_k_addr, tk, (t + 1) & 1);
+                    PEVLM_SET_LOADS(ldv, V, voff, v_mod, ((row & VSW) << 2), lds_v_addr, t, t & 1);
+                    PEVLM_TILE_RANGE(t, k0, kend, causal);
+                },
+                [&] { first_v<D>(tv, L, vfirst); });
+            PEVLM_MASK(k0, kend, causal);
             // values of tile t-1 (matrix cores) under the weights of tile t (vector ALU)
             psum = 0.f;
-            pv_prev_weights_cur<D>(lds_v + ((t - 1) & 1) * TILEB, L, pf_prev, o, s, c_log2, PEVLM_MREF, psum, pf_new, ldv);
+            pv_prev_weights_cur<D, NLD>(tv, L, pf, o, s, c_log2, PEVLM_MREF, psum, ldv, vfirst);
             PEVLM_FIX_REFERENCE();
             l_run += psum;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) pf_prev[j] = pf_new[j];
         }
     }
     // the burst loads below use the plain per-lane offsets
@@ -400,7 +404,7 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
         __syncthreads();
         synced = true;
     }
-    if (n_w > 0) pv_tile<D>(lds_v + ((n_w - 1) & 1) * TILEB, L, pf_prev, o);
+    if (n_w > 0) pv_tile<D>(lds_v + ((n_w - 1) & 1) * TILEB, L, pf, o);
     for (int32_t t = t_rest; t < n_tiles; ++t) PEVLM_TOP(t);
     if (!synced) {
         __builtin_amdgcn_s_waitcnt(0x0F70);

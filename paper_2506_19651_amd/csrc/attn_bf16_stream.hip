@@ -236,7 +236,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
     // ---- per-wavefront compute state
     bf16x8 qf[KSTEPS];
     f32x16 o[DBLK], s[2];
-    u32x4 pf_prev[4], pf_new[4];
+    u32x4 pf[4];
     float m_ref = -INFINITY, l_run = 0.f, psum = 0.f;
     const float c_log2 = p.scale * 1.4426950408889634f;
 #define PEVLM_MREF ((m_ref == -INFINITY) ? 0.f : m_ref)
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
             const float alpha = has ? __builtin_amdgcn_exp2f(m_ref - m_new) : 1.f;                    \
             m_ref = m_new;                                                                            \
             psum = 0.f;                                                                               \
-            weights(s, c_log2, PEVLM_MREF, psum, pf_new);                                             \
+            weights(s, c_log2, PEVLM_MREF, psum, pf);                                             \
             if (__any(has)) {                                                                         \
                 l_run *= alpha;                                                                       \
                 _Pragma("unroll") for (int b = 0; b < DBLK; ++b)                                      \
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
     // last value tile of a finished slot (V stage pend_vs), normalisation, rows out through the slice
 #define PEVLM_FINISH_PENDING()                                                                        \
     do {                                                                                              \
-        pv_tile<D>(lds_v + pend_vs * TILEB, L, pf_prev, o);                                           \
+        pv_tile<D>(lds_v + pend_vs * TILEB, L, pf, o);                                           \
         const float l_tot = l_run + __shfl_xor(l_run, 32);                                            \
         const float inv = 1.f / l_tot;                                                                \
         const int32_t ln_ = opaque(lane), r32_ = ln_ & 31, h32_ = ln_ >> 5, cp_ = ln_ % CH;           \
@@ -343,8 +343,8 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
         if (q_age <= 2) wait_vm<TL + NQL>(); else wait_vm<TL>();                                      \
         __builtin_amdgcn_s_barrier();                                                                 \
         asm volatile("" ::: "memory");                                                                \
-        PEVLM_TILE_LOADS_SETUP((ks >= 1 ? ks - 1 : 2), (ks + 1 < NST ? ks + 1 : 0));                  \
     } while (0)
+#define PEVLM_NEXT_LOADS() PEVLM_TILE_LOADS_SETUP((ks >= 1 ? ks - 1 : 2), (ks + 1 < NST ? ks + 1 : 0))
 #define PEVLM_NEXT_TILE()                  \
     do {                                   \
         ks = ks + 1 < NST ? ks + 1 : 0;    \
@@ -408,6 +408,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
         // ---- tile 0: loads in one burst, the pending end of the previous item's slot, then the first
         // tile's exact softmax (no row has a reference maximum yet)
         PEVLM_TOP();
+        PEVLM_NEXT_LOADS();
         PEVLM_TILE_LOADS_BURST();
         if (pend) {
             PEVLM_FINISH_PENDING();
@@ -421,13 +422,11 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
 #pragma unroll
                 for (int i = 0; i < 16; ++i) o[b][i] = 0.f;
             PEVLM_TILE_RANGE(0, k0, kend, causal);
-            qk_tile_ring<D, false, NL>(lds_k + ks * TILEB, L, qf, s, ldk);
+            qk_tile<D, false, NL>(lds_k + ks * TILEB, L, qf, s, ldk, [] {}, [] {});
             if ((k0 + KT > kend) || (causal && (k0 + KT - 1 > wr_lo))) mask_tile(s, k0, kend, causal, my_row, g32);
             psum = 0.f;
             PEVLM_FIX_REFERENCE();
             l_run += psum;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) pf_prev[j] = pf_new[j];
         }
         if (n_w <= 1) PEVLM_END_OF_COMPUTE(ord);
         PEVLM_NEXT_TILE();
@@ -436,15 +435,20 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
         // under the weights of tile t with V(t+1) requested piecewise
         for (int32_t t = 1; t < n_w; ++t) {
             PEVLM_TOP();
-            PEVLM_TILE_RANGE(t, k0, kend, causal);
-            qk_tile_ring<D, true, NL>(lds_k + ks * TILEB, L, qf, s, ldk);
+            bf16x8 vfirst[kValuesAhead];
+            const uint8_t *const tv = lds_v + (ks >= 1 ? ks - 1 : 2) * TILEB;
+            qk_tile<D, true, NL>(
+                lds_k + ks * TILEB, L, qf, s, ldk,
+                [&] {
+                    PEVLM_NEXT_LOADS();
+                    PEVLM_TILE_RANGE(t, k0, kend, causal);
+                },
+                [&] { first_v<D>(tv, L, vfirst); });
             if ((k0 + KT > kend) || (causal && (k0 + KT - 1 > wr_lo))) mask_tile(s, k0, kend, causal, my_row, g32);
             psum = 0.f;
-            pv_prev_weights_cur_ring<D, NL>(lds_v + (ks >= 1 ? ks - 1 : 2) * TILEB, L, pf_prev, o, s, c_log2, PEVLM_MREF, psum, pf_new, ldv);
+            pv_prev_weights_cur<D, NL>(tv, L, pf, o, s, c_log2, PEVLM_MREF, psum, ldv, vfirst);
             PEVLM_FIX_REFERENCE();
             l_run += psum;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) pf_prev[j] = pf_new[j];
             if (t == n_w - 1) PEVLM_END_OF_COMPUTE(ord);
             PEVLM_NEXT_TILE();
         }
@@ -453,6 +457,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
         // loads; in the first of them the slot's last value tile and output
         for (int32_t t = n_w > 1 ? n_w : 1; t < n_tiles; ++t) {
             PEVLM_TOP();
+            PEVLM_NEXT_LOADS();
             PEVLM_TILE_LOADS_BURST();
             if (pend) {
                 PEVLM_FINISH_PENDING();

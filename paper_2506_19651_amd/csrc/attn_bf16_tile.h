@@ -24,68 +24,28 @@ struct LaneOff {
     int32_t k_row_off, k_swz, v_row_off, v_ch_lo, v_swz, g32;
 };
 
-// Global->LDS loads a wavefront slips between the MFMAs of a tile (its share of the next K tile
-// during the score MFMAs, of the current V tile during the value MFMAs): a wavefront-uniform base
-// address, per-lane byte offsets and the LDS address of the wave's first 1 KB piece.
+// Global->LDS loads a wavefront slips between the MFMAs of a tile (its share of a later K tile
+// during the score MFMAs, of a V tile during the value MFMAs): a wavefront-uniform base
+// address, per-lane byte offsets and the LDS address of the wave's first 1 KB piece; four wavefronts share a
+// tile, so its j-th piece lies 4 KB after its (j-1)-th.
 template <int NLD>
 struct TileLoads {
     const void *base;
-    uint32_t off[NLD > 0 ? NLD : 1];
+    uint32_t off[NLD];
     uint32_t lds;
+    __device__ __forceinline__ void issue(int j) const { load_lds_16_base(base, off[j], lds + j * 4096); }
 };
-// The wave's j-th 1 KB piece of a tile lies PSTEP bytes after its (j-1)-th: 4 wavefronts share a tile
-// in the one-item kernel (4 KB), 8 in the streaming kernel (8 KB).
 
 constexpr float kRescaleStep = 8.f;  // log2 units the row maximum may outgrow the reference maximum
 
 // S^T = K Q^T for the 64 keys of a staged tile: two independent accumulation chains (one per
-// 32-key chunk) issued alternately; A fragments (16 bytes per lane) are fetched half a tile ahead.
-template <int D, bool LOADS, int NL = D / 32, int PSTEP = 4096>
+// 32-key chunk) issued alternately; A fragments (16 bytes per lane) are fetched PF k-steps ahead of their MFMAs.
+// `ld.issue(j)` requests the wavefront's j-th piece (of NL) of a later K tile.  `pre` runs while the first fragments
+// are under way (scalar set-up of the tile: in front of them it delays both wavefronts of the SIMD, which
+// leave the barrier together), `post` before the last pair of MFMAs (first reads of what follows them).
+template <int D, bool LOADS, int NL, int PF = 2, class LD, class Pre, class Post>
 __device__ __forceinline__ void qk_tile(const uint8_t *tk, const LaneOff &L, const bf16x8 (&qf)[D / 16], f32x16 (&s)[2],
-                                        const TileLoads<NL> &ld)
-{
-    using C = TileCfg<D>;
-    constexpr int HK = C::KSTEPS / 2;
-    const f32x16 init = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    bf16x8 a0[C::KSTEPS], a1[C::KSTEPS];
-#define PEVLM_KFRAG(kc, kk) \
-    (*reinterpret_cast<const bf16x8 *>(tk + (kc) * 32 * C::ROWB + L.k_row_off + ((((kk) * 2 + L.g32) ^ L.k_swz) << 4)))
-#pragma unroll
-    for (int kk = 0; kk < HK; ++kk) {
-        a0[kk] = PEVLM_KFRAG(0, kk);
-        a1[kk] = PEVLM_KFRAG(1, kk);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int kk = 0; kk < HK; ++kk) {
-        s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[kk], qf[kk], kk == 0 ? init : s[0], 0, 0, 0);
-        a0[kk + HK] = PEVLM_KFRAG(0, kk + HK);
-        s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[kk], qf[kk], kk == 0 ? init : s[1], 0, 0, 0);
-        a1[kk + HK] = PEVLM_KFRAG(1, kk + HK);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int kk = HK; kk < C::KSTEPS; ++kk) {
-        s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[kk], qf[kk], s[0], 0, 0, 0);
-        s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[kk], qf[kk], s[1], 0, 0, 0);
-        if (LOADS && kk - HK < NL) {  // one 1 KB piece of a later K tile per pair of MFMAs
-            load_lds_16_base(ld.base, ld.off[kk - HK < NL ? kk - HK : 0], ld.lds + (kk - HK) * PSTEP);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-#undef PEVLM_KFRAG
-}
-
-// Same scores with the A fragments fetched only PF k-steps ahead of their MFMAs (a ring of PF
-// fragments per 32-key chunk instead of half a tile): fewer live registers, for the kernel that has
-// none to spare.  `ld.issue(j)` requests the wavefront's j-th piece (of NL) of a later K tile.
-template <int D, bool LOADS, int NL, class LD, int PF = 2>
-__device__ __forceinline__ void qk_tile_ring(const uint8_t *tk, const LaneOff &L, const bf16x8 (&qf)[D / 16], f32x16 (&s)[2],
-                                             const LD &ld)
+                                        const LD &ld, Pre pre, Post post)
 {
     using C = TileCfg<D>;
     constexpr int KS = C::KSTEPS, HK = KS / 2;
@@ -99,8 +59,10 @@ __device__ __forceinline__ void qk_tile_ring(const uint8_t *tk, const LaneOff &L
         a1[kk] = PEVLM_KFRAG(1, kk);
     }
     __builtin_amdgcn_sched_barrier(0);
+    pre();
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
+        if (kk == KS - 1) post();
         s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[kk], qf[kk], kk == 0 ? init : s[0], 0, 0, 0);
         if (kk + PF < KS) a0[kk + PF] = PEVLM_KFRAG(0, kk + PF);
         s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[kk], qf[kk], kk == 0 ? init : s[1], 0, 0, 0);
@@ -157,28 +119,48 @@ __device__ __forceinline__ float row_max(const f32x16 (&s)[2])
 }
 
 // weights p = exp2(c s - m) of the tile (c = scale*log2(e), m = the row's reference maximum in
-// base-2 units): bf16 pairs (B fragments of the value MFMAs) and their sum over this lane's 32 keys
-// (dot product of each pair with (1, 1)).  Weights are non-negative, so a sum below 2^kRescaleStep
-// bounds every one of them; an overflowed or invalid weight makes the sum inf or nan.
+// base-2 units): bf16 pairs (B fragments of the value MFMAs) and their sum over this lane's 32 keys.  Weights
+// are non-negative, so a sum below 2^kRescaleStep bounds every one of them; an overflowed or invalid weight makes
+// the sum inf or nan.
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-__device__ __forceinline__ uint32_t weight_pair(float s0, float s1, float c_log2, float mref, float &psum)
+__device__ __forceinline__ uint32_t weight_pair(float p0, float p1)
 {
     bf16x2 pr;
-    pr[0] = (__bf16)__builtin_amdgcn_exp2f(s0 * c_log2 - mref);
-    pr[1] = (__bf16)__builtin_amdgcn_exp2f(s1 * c_log2 - mref);
-    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-    psum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, psum, false);
+    pr[0] = (__bf16)p0;
+    pr[1] = (__bf16)p1;
     return __builtin_bit_cast(uint32_t, pr);
+}
+
+// Adds four pairs of rounded weights to the lane's fp32 sum.  v_mfma_f32_4x4x4 with a block of ones adds the four
+// values that a lane supplies to the lane's own accumulators (all four end up alike): 8 cycles for two words.
+// v_dot2_f32_bf16 with (1, 1) is as exact and one instruction a word, but does not run beside an MFMA of
+// either wavefront of the SIMD (four of them between two MFMAs: 28.4 ns a round where four multiply-adds,
+// exponentials or conversions leave it at the 17.8 ns of the bare MFMAs); unpacking to fp32 costs 4 vector
+// instructions a word (5 % of the 64K prefill).
+__device__ __forceinline__ void add_weights(const u32x4 &pairs, f32x4 &sum)
+{
+    const s16x4 ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
+    const u32x2 a = {pairs[0], pairs[1]}, b = {pairs[2], pairs[3]};
+    sum = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(s16x4, a), sum, 0, 0, 0);
+    sum = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(s16x4, b), sum, 0, 0, 0);
 }
 
 __device__ __forceinline__ void weights(const f32x16 (&s)[2], float c_log2, float mref, float &psum, u32x4 (&pf)[4])
 {
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kc = 0; kc < 2; ++kc)
+    for (int j = 0; j < 4; ++j) {
 #pragma unroll
-        for (int i = 0; i < 16; i += 2) pf[kc * 2 + (i >> 3)][(i & 7) >> 1] = weight_pair(s[kc][i], s[kc][i + 1], c_log2, mref, psum);
+        for (int w = 0; w < 4; ++w) {
+            const int kc = j >> 1, i = (j & 1) * 8 + w * 2;
+            pf[j][w] = weight_pair(__builtin_amdgcn_exp2f(s[kc][i] * c_log2 - mref), __builtin_amdgcn_exp2f(s[kc][i + 1] * c_log2 - mref));
+        }
+        add_weights(pf[j], sum);
+    }
+    psum = sum[0];
 }
 
 // true unless this lane's sum of weights proves that all of them stayed below 2^kRescaleStep
@@ -220,69 +202,58 @@ __device__ __forceinline__ bf16x8 read_v_one(const uint8_t *tv, const LaneOff &L
     return dst;
 }
 
-// The pipelined step: O^T += V^T P^T of the previous tile (matrix cores) issued one MFMA at a time,
-// each followed by the vector-ALU work for a pair (or two) of weights of the current tile, so that
-// both pipes of the SIMD run from one instruction stream.  V^T fragments are read one k-step ahead.
-template <int D, int NL = D / 32, int PSTEP = 4096>
-__device__ __forceinline__ void pv_prev_weights_cur(const uint8_t *tv_prev, const LaneOff &L, const u32x4 (&pf_prev)[4],
-                                                    f32x16 (&o)[D / 32], const f32x16 (&s)[2], float c_log2,
-                                                    float mref, float &psum, u32x4 (&pf_new)[4], const TileLoads<NL> &ld)
+// V^T fragments of the first value MFMAs of a tile
+constexpr int kValuesAhead = 3;
+template <int D>
+__device__ __forceinline__ void first_v(const uint8_t *tv, const LaneOff &L, bf16x8 (&vf)[kValuesAhead])
 {
-    using C = TileCfg<D>;
-    constexpr int NM = 4 * C::DBLK;  // MFMAs of the tile
-    constexpr int PPM = 16 / NM;     // weight pairs formed per MFMA
-    bf16x8 vf[2][C::DBLK];
 #pragma unroll
-    for (int b = 0; b < C::DBLK; ++b) vf[0][b] = read_v_one<D>(tv_prev, L, 0, b);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int n = 0; n < NM; ++n) {
-        const int ks = n / C::DBLK, b = n % C::DBLK;
-        if (ks + 1 < 4) vf[(ks + 1) & 1][b] = read_v_one<D>(tv_prev, L, ks + 1, b);
-        o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks & 1][b], __builtin_bit_cast(bf16x8, pf_prev[ks]), o[b], 0, 0, 0);
-        if (n % 4 == 0 && n / 4 < NL) load_lds_16_base(ld.base, ld.off[n / 4 < NL ? n / 4 : 0], ld.lds + (n / 4) * PSTEP);  // a piece of a V tile
-#pragma unroll
-        for (int e = 0; e < PPM; ++e) {
-            const int pi = n * PPM + e, kc = pi >> 3, i = (pi & 7) * 2;
-            pf_new[kc * 2 + (i >> 3)][(i & 7) >> 1] = weight_pair(s[kc][i], s[kc][i + 1], c_log2, mref, psum);
-        }
-        // keep the running values here (plain arithmetic would otherwise be emitted after the last MFMA)
-        asm volatile("" : "+v"(psum));
-        if (((n + 1) * PPM) % 4 == 0) asm volatile("" : "+v"(pf_new[((n + 1) * PPM) / 4 - 1]));
-        __builtin_amdgcn_sched_barrier(0);
-    }
+    for (int n = 0; n < kValuesAhead; ++n) vf[n] = read_v_one<D>(tv, L, n / TileCfg<D>::DBLK, n % TileCfg<D>::DBLK);
 }
 
-// The same pipelined step with the V^T fragments fetched only PF MFMAs ahead (a ring of PF fragments
-// instead of two k-steps of them): fewer live registers.  `ld.issue(j)` requests the wavefront's j-th
-// piece (of NL) of a later V tile.
-template <int D, int NL, class LD, int PF = 3>
-__device__ __forceinline__ void pv_prev_weights_cur_ring(const uint8_t *tv_prev, const LaneOff &L, const u32x4 (&pf_prev)[4],
-                                                         f32x16 (&o)[D / 32], const f32x16 (&s)[2], float c_log2,
-                                                         float mref, float &psum, u32x4 (&pf_new)[4], const LD &ld)
+// The pipelined step: O^T += V^T P^T of the previous tile (matrix cores) issued one MFMA at a time,
+// each followed by the vector-ALU work for a pair (or two) of weights of the current tile, so that
+// both pipes of the SIMD run from one instruction stream.  V^T fragments are read kValuesAhead MFMAs ahead, the first
+// ones by the caller.  The four words of weights that a k-step of value MFMAs has used are rewritten with those of the
+// current tile right after it (formed in other registers, all 16 words are copied on every tile).
+// `ld.issue(j)` requests the wavefront's j-th piece (of NL) of a later V tile.
+template <int D, int NL, class LD>
+__device__ __forceinline__ void pv_prev_weights_cur(const uint8_t *tv_prev, const LaneOff &L, u32x4 (&pf)[4], f32x16 (&o)[D / 32],
+                                                    const f32x16 (&s)[2], float c_log2, float mref, float &psum, const LD &ld,
+                                                    const bf16x8 (&vfirst)[kValuesAhead])
 {
     using C = TileCfg<D>;
+    constexpr int PF = kValuesAhead;
     constexpr int NM = 4 * C::DBLK;  // MFMAs of the tile
     constexpr int PPM = 16 / NM;     // weight pairs formed per MFMA
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
     bf16x8 vf[NM];
+    float e[8];
 #pragma unroll
-    for (int n = 0; n < PF; ++n) vf[n] = read_v_one<D>(tv_prev, L, n / C::DBLK, n % C::DBLK);
-    __builtin_amdgcn_sched_barrier(0);
+    for (int n = 0; n < PF; ++n) vf[n] = vfirst[n];
 #pragma unroll
     for (int n = 0; n < NM; ++n) {
         const int ks = n / C::DBLK, b = n % C::DBLK;
         if (n + PF < NM) vf[n + PF] = read_v_one<D>(tv_prev, L, (n + PF) / C::DBLK, (n + PF) % C::DBLK);
-        o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[n], __builtin_bit_cast(bf16x8, pf_prev[ks]), o[b], 0, 0, 0);
+        o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[n], __builtin_bit_cast(bf16x8, pf[ks]), o[b], 0, 0, 0);
         if (n % 4 == 0 && n / 4 < NL) ld.issue(n / 4);
 #pragma unroll
-        for (int e = 0; e < PPM; ++e) {
-            const int pi = n * PPM + e, kc = pi >> 3, i = (pi & 7) * 2;
-            pf_new[kc * 2 + (i >> 3)][(i & 7) >> 1] = weight_pair(s[kc][i], s[kc][i + 1], c_log2, mref, psum);
+        for (int x = 0; x < PPM; ++x) {
+            const int pi = n * PPM + x, kc = pi >> 3, i = (pi & 7) * 2;
+            float &e0 = e[(pi & 3) * 2], &e1 = e[(pi & 3) * 2 + 1];
+            e0 = __builtin_amdgcn_exp2f(s[kc][i] * c_log2 - mref);
+            e1 = __builtin_amdgcn_exp2f(s[kc][i + 1] * c_log2 - mref);
+            asm volatile("" : "+v"(e0), "+v"(e1));  // here, not after the last MFMA
         }
-        asm volatile("" : "+v"(psum));
-        if (((n + 1) * PPM) % 4 == 0) asm volatile("" : "+v"(pf_new[((n + 1) * PPM) / 4 - 1]));
+        if (b == C::DBLK - 1) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) pf[ks][w] = weight_pair(e[w * 2], e[w * 2 + 1]);
+            add_weights(pf[ks], sum);
+            asm volatile("" : "+v"(pf[ks]));
+        }
         __builtin_amdgcn_sched_barrier(0);
     }
+    psum = sum[0];
 }
 
 }  // namespace pevlm

@@ -84,7 +84,7 @@ __global__ __launch_bounds__(256, 2) void probe_tile_loop_kernel(float *sink, co
     for (int kk = 0; kk < C::KSTEPS; ++kk)
         qf[kk] = *reinterpret_cast<const bf16x8 *>(kv + (size_t)((blockIdx.x * 4 + wave) % 2) * TILEB + l32 * ROWB + (kk * 2 + g32) * 16);
     f32x16 o[C::DBLK], s[2];
-    u32x4 pf_prev[4], pf_new[4];
+    u32x4 pf[4];
 #pragma unroll
     for (int b = 0; b < C::DBLK; ++b)
 #pragma unroll
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(256, 2) void probe_tile_loop_kernel(float *sink, co
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) pf_prev[j][e] = 0x3c003c00u, pf_new[j][e] = 0x3c003c00u;
+        for (int e = 0; e < 4; ++e) pf[j][e] = 0x3c003c00u;
     float l_run = 0.f;
     const float c_log2 = 0.0883883f * 1.4426950408889634f, m_ref = 4.f;
     const int32_t half = n_tiles / 2;  // K tiles in the first half of the buffer, V tiles in the second
@@ -109,25 +109,29 @@ __global__ __launch_bounds__(256, 2) void probe_tile_loop_kernel(float *sink, co
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        const int32_t nt = (t + 1 + blockIdx.x) % half;
-        ldk.base = uniform_ptr(kv + (size_t)nt * TILEB);
-        ldv.base = uniform_ptr(kv + (size_t)(half + nt) * TILEB);
-        ldk.lds = lds_addr + ((t + 1) & 1) * TILEB + wave * 1024;
-        ldv.lds = lds_addr + (2 + ((t + 1) & 1)) * TILEB + wave * 1024;
-        qk_tile<D, true>(lds + (t & 1) * TILEB, L, qf, s, ldk);
+        const uint8_t *const tv = lds + (2 + (t & 1)) * TILEB;
+        bf16x8 vfirst[kValuesAhead];
+        qk_tile<D, true, NLD>(
+            lds + (t & 1) * TILEB, L, qf, s, ldk,
+            [&] {
+                const int32_t nt = (t + 1 + blockIdx.x) % half;
+                ldk.base = uniform_ptr(kv + (size_t)nt * TILEB);
+                ldv.base = uniform_ptr(kv + (size_t)(half + nt) * TILEB);
+                ldk.lds = lds_addr + ((t + 1) & 1) * TILEB + wave * 1024;
+                ldv.lds = lds_addr + (2 + ((t + 1) & 1)) * TILEB + wave * 1024;
+            },
+            [&] { if (WEIGHTS) first_v<D>(tv, L, vfirst); });
         float psum = 0.f;
         if (WEIGHTS) {
-            pv_prev_weights_cur<D>(lds + (2 + (t & 1)) * TILEB, L, pf_prev, o, s, c_log2, m_ref, psum, pf_new, ldv);
+            pv_prev_weights_cur<D, NLD>(tv, L, pf, o, s, c_log2, m_ref, psum, ldv, vfirst);
         } else {
             // value MFMAs and V loads only; the scores stay live through one cheap use
-            pv_tile<D>(lds + (2 + (t & 1)) * TILEB, L, pf_prev, o);
+            pv_tile<D>(tv, L, pf, o);
 #pragma unroll
-            for (int j = 0; j < NLD; ++j) load_lds_16_base(ldv.base, ldv.off[j], ldv.lds + j * 4096);
+            for (int j = 0; j < NLD; ++j) ldv.issue(j);
             psum = s[0][0] + s[1][15];
         }
         l_run += psum;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) pf_prev[j] = pf_new[j];
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
     float r = l_run;
