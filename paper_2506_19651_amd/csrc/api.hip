@@ -274,7 +274,9 @@ static bool stream_kernel_applies(const pevlm_layout *lay, const pevlm_heads *h)
 // workgroup the shares come out too uneven, and the one-item-per-workgroup kernel (two small workgroups
 // per compute unit, dispatched as slots free up) finishes sooner.  So it does on regions far longer
 // than any block the method uses (a dense causal attention written as one block: measured 8 % faster at
-// 64K rows), where the key stream of an item no longer stays in the L2 of its XCD.
+// 64K rows), where the key stream of an item no longer stays in the L2 of its XCD.  64-wide heads always
+// go to the one-item kernel: it fits three wavefronts on a SIMD there, resident workgroups with three stages per
+// tensor two (98K tokens x 14 heads in blocks of 1024: 341 us against 362, of 3136: 695 against 758, of 128: 185 against 207).
 constexpr int32_t kMinStreamItemsPerWorkgroup = 12;
 constexpr int32_t kMaxStreamRegionRows = 16384;
 
@@ -305,7 +307,7 @@ static int64_t stream_items_if_chosen(const pevlm_layout *lay, const pevlm_heads
     const int32_t mode = prefill_kernel_mode().load(std::memory_order_relaxed);
     if (fuse_rope || mode == 1 || !stream_kernel_applies(lay, h)) return 0;
     const int64_t n = count_stream_items(lay, h, r);
-    return (mode == 2 || (n >= (int64_t)kMinStreamItemsPerWorkgroup * compute_units() && regions_fit_stream_kernel(lay))) ? n : 0;
+    return (mode == 2 || (h->head_dim == 128 && n >= (int64_t)kMinStreamItemsPerWorkgroup * compute_units() && regions_fit_stream_kernel(lay))) ? n : 0;
 }
 
 // Compute units of the current device (256 when it cannot be queried, e.g. no GPU present).
@@ -367,7 +369,7 @@ static int32_t auto_splits(const pevlm_layout *lay, const pevlm_heads *h, const 
     const double cus = compute_units(), slots = 2 * cus;
     const double tile_one = h->head_dim == 128 ? 1.0 : 0.75;   // us per key tile, up to one workgroup per compute unit
     const double tile_some = h->head_dim == 128 ? 1.25 : 0.95;  // ... some compute units with two
-    const double tile_full = h->head_dim == 128 ? 1.68 : 1.2;   // ... all with two
+    const double tile_full = h->head_dim == 128 ? 1.62 : 1.2;   // ... all with two
     const double partial_us = (double)total_query_rows(lay) * h->n_q_heads * (h->head_dim + 2) * 4 / 2.5e6;  // one split's partials, written and read
     int32_t best = 1, asking = 0;
     double best_us = 0;
