@@ -450,6 +450,8 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         uint16_t *const obase = (uint16_t *)p.out;
+        // Rows leave as non-temporal stores: nothing here reads them again, and the lines stay free for keys and values
+        // (16 K tokens, rotation and question included: 279 -> 272 us; dense 16 K 2139 -> 2122 us).
         if (hg.identity) {
             uint8_t *const ob = (uint8_t *)(obase + item_off);
             PEVLM_PAIR_WALK_BEGIN();
@@ -457,7 +459,7 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
             for (int j = 0; j < WSLICE / 1024; ++j) {
                 const int32_t rl = j * RPI + lane / CH, cpos = lane % CH;
                 const uint4 val = *reinterpret_cast<const uint4 *>(oslice + rl * ROWB + ((cpos ^ (rl & (CH - 1))) << 4));
-                if (walk_v < n_pairs) *reinterpret_cast<uint4 *>(ob + (walk_off + (uint32_t)(cpos << 4))) = val;
+                if (walk_v < n_pairs) __builtin_nontemporal_store(__builtin_bit_cast(u32x4, val), reinterpret_cast<u32x4 *>(ob + (walk_off + (uint32_t)(cpos << 4))));
                 PEVLM_PAIR_WALK_NEXT();
             }
         } else {

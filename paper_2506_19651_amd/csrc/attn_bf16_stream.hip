@@ -78,6 +78,15 @@ __device__ __forceinline__ void load_lds_16_buf(const i32x4 &rsrc, uint32_t voff
                  : "memory");
 }
 
+// ... for query rows, which are read once: the lines stay free for the key stream (64K layer 1083 -> 1067 us, 1096
+// with ordinary output stores too; in the one-item kernel, whose short prompts find their rotated queries
+// in the last-level cache, it costs 2 % of a 16K layer)
+__device__ __forceinline__ void load_lds_16_buf_once(const i32x4 &rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds\n" ::"s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory");
+}
+
 // the loads of one tensor for one tile step: piece j of the wavefront lies `sstep` bytes further in
 // memory (32 or 64 rows) and PSTEP bytes further in LDS
 template <int PSTEP>
@@ -223,7 +232,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
         const int32_t ln_ = opaque(lane);                                                               \
         _Pragma("unroll") for (int j = 0; j < NQL; ++j) {                                               \
             const int32_t rl = j * RPI + ln_ / CH;                                                      \
-            load_lds_16_buf(rq_, (uint32_t)rl * qrb_ + (uint32_t)(((ln_ % CH) ^ (rl & (CH - 1))) << 4), 0u, slice_addr + j * 1024); \
+            load_lds_16_buf_once(rq_, (uint32_t)rl * qrb_ + (uint32_t)(((ln_ % CH) ^ (rl & (CH - 1))) << 4), 0u, slice_addr + j * 1024); \
         }                                                                                               \
     } while (0)
 #define PEVLM_READ_QF()                                                                                 \
@@ -288,7 +297,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
             const int32_t rl = j * RPI + ln_ / CH;                                                    \
             const uint4 val = *reinterpret_cast<const uint4 *>(slice + rl * ROWB + ((cp_ ^ (rl & (CH - 1))) << 4)); \
             if (rl < pend_q_rows)                                                                     \
-                *reinterpret_cast<uint4 *>(obase + ((int64_t)(pend_q_start + rl) * Hq + pend_head) * D + cp_ * 8) = val; \
+                __builtin_nontemporal_store(__builtin_bit_cast(u32x4, val), reinterpret_cast<u32x4 *>(obase + ((int64_t)(pend_q_start + rl) * Hq + pend_head) * D + cp_ * 8)); \
         }                                                                                             \
         if (p.lse && h32_ == 0 && r32_ < pend_q_rows)                                                 \
             p.lse[(int64_t)(pend_q_start + r32_) * Hq + pend_head] = (m_ref + __log2f(l_tot)) * 0.69314718056f; \

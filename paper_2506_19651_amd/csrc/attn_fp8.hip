@@ -552,7 +552,8 @@ __global__ __launch_bounds__(256, 3) void attn_fp8_kernel(Fp8Params p)
         }
         if (g32 == 0) p.q_scales[q_unit] = pow2(q_exp8 - 127);
     }
-    // ---- output: normalise, undo the V scale, rows out through LDS as whole 2 D-byte rows
+    // ---- output: normalise, undo the V scale, rows out through LDS as whole 2 D-byte rows (non-temporal: nothing here
+    // reads them again; 64K call 604 -> 595 us)
     __syncthreads();  // every wavefront has left the tile stages
     uint8_t *slice = lds + wave * 32 * ROWB;
     const float l_tot = l_run + __shfl_xor(l_run, 32);
@@ -578,7 +579,7 @@ __global__ __launch_bounds__(256, 3) void attn_fp8_kernel(Fp8Params p)
     for (int j = 0; j < NOL; ++j, off += (uint32_t)(RPI * Hq * ROWB)) {
         const int32_t rl = j * RPI + lane / CH;
         const uint4 val = *reinterpret_cast<const uint4 *>(slice + rl * ROWB + ((cp ^ (rl & (CH - 1))) << 4));
-        if (rl < w_rows) *reinterpret_cast<uint4 *>(obase + off) = val;
+        if (rl < w_rows) __builtin_nontemporal_store(__builtin_bit_cast(u32x4, val), reinterpret_cast<u32x4 *>(obase + off));
     }
     if (p.lse && g32 == 0 && l32 < w_rows)
         p.lse[(int64_t)(wr_lo + l32) * Hq + head] = (m_ref - kWeightShift + __log2f(l_tot)) * 0.69314718056f;
