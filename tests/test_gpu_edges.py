@@ -161,3 +161,28 @@ def test_fp8_both_stages_leave_what_the_stages_leave(D, Hq, Hkv, tokens):
     amax = spaces[0][plan.kv_amax:plan.kv_amax + 2 * Hkv * 4].view(np.float32).reshape(2, Hkv)
     for i, name in enumerate(("k", "v")):
         assert np.array_equal(amax[i], np.abs(W.bf16_bits_to_f32(data[name])).max(axis=(0, 2)))
+
+
+@pytest.mark.parametrize("kernel", ["classic", "stream"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("keys", [1, 4, 63, 64, 65, 128, 191, 257])
+def test_row_sums_of_equal_weights(D, kernel, keys):
+    """Keys of one value: every visible key has the weight 1 and lse - score is the logarithm of their number, for each
+    of the lanes and accumulators that the sums are spread over (n weights of 1 add up exactly in fp32: what is
+    left is a logarithm and one rounding of the score, 1e-4)."""
+    lay, heads = P.Layout.from_seqs([(0, keys, keys, 0)]), P.Heads(4, 2, D, "bf16")
+    q = torch.ones(keys, 4, D, device=DEV, dtype=torch.bfloat16)
+    k = torch.full((keys, 2, D), 0.25, device=DEV, dtype=torch.bfloat16)
+    v = torch.arange(keys, device=DEV, dtype=torch.float32).view(-1, 1, 1).expand(keys, 2, D).to(torch.bfloat16).contiguous()
+    out, lse = torch.empty_like(q), torch.empty(keys, 4, device=DEV, dtype=torch.float32)
+    prev = P.pevlm_set_prefill_kernel(kernel)
+    try:
+        P.pevlm_block_prefill_attn(q, k, v, out, lay, heads, lse=lse)
+    finally:
+        P.pevlm_set_prefill_kernel(prev)
+    n = torch.arange(1, keys + 1, dtype=torch.float64)
+    want = 0.25 * D / D ** 0.5 + n.log()
+    assert (lse.cpu().double() - want.view(-1, 1)).abs().max() <= 1e-4
+    mean = torch.cumsum(v[:, 0, 0].cpu().double(), 0) / n
+    err = (out.cpu().double() - mean.view(-1, 1, 1)).abs()
+    assert (err <= 2.0 ** -8 * mean.view(-1, 1, 1) + 1e-3).all()  # one bf16 rounding of the result

@@ -153,6 +153,25 @@ def test_stream_items_of_a_block_selection_and_unequal_groups():
         P.pevlm_set_prefill_kernel(prev)
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(14, 2), (28, 4), (8, 8), (4, 1)])
+@pytest.mark.parametrize("seqs", [[(256, 1024, 98304, 64)], [(0, 16384, 16384, 0)] * 3, [(77, 333, 90001, 1)] * 2])
+def test_64_wide_heads_go_to_the_one_item_kernel(Hq, Hkv, seqs):
+    """The rule looks at head_dim before the length of the list; either kernel can be forced and takes the same workspace."""
+    lay = P.Layout.from_seqs(seqs)
+    narrow, wide = P.Heads(Hq, Hkv, 64, "bf16"), P.Heads(Hq, Hkv, 128, "bf16")
+    prev = P.pevlm_set_prefill_kernel("auto")
+    try:
+        enough = len(P.pevlm_prefill_stream_items_host(lay, wide)) >= 12 * 256
+        assert bool(P.pevlm_prefill_uses_stream_kernel(lay, wide)) == enough
+        assert not P.pevlm_prefill_uses_stream_kernel(lay, narrow)
+        need = P.pevlm_block_prefill_workspace_bytes(lay, narrow)
+        P.pevlm_set_prefill_kernel("stream")
+        assert P.pevlm_prefill_uses_stream_kernel(lay, narrow)
+        assert P.pevlm_block_prefill_workspace_bytes(lay, narrow) == need
+    finally:
+        P.pevlm_set_prefill_kernel(prev)
+
+
 @pytest.mark.parametrize("seqs", LAYOUTS)
 @pytest.mark.parametrize("tile_rows,num_splits", [(16, 1), (16, 3), (128, 4), (128, 64), (1, 2)])
 def test_query_worklist_expands_to_oracle_mask(oracle, seqs, tile_rows, num_splits):
