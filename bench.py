@@ -26,7 +26,7 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 matrix peak
 MFMA_FP8_PEAK_TFLOPS = 5000.0   # ... dense fp8
 # HBM bytes per block-prefill launch from the FETCH_SIZE / WRITE_SIZE passes recorded in
 # profiles/attn_bf16_prefill_c3_counters.md (scaled by the same counters on a 1 GiB device copy)
-MEASURED_PREFILL_TRAFFIC_BYTES = {("c3", "attn_bf16_stream_kernel<128>"): 1.280e9}
+MEASURED_PREFILL_TRAFFIC_BYTES = {("c3", "attn_bf16_stream_kernel<128>"): 1.090e9}
 HBM_PEAK_GBS = 8000.0
 
 
