@@ -20,6 +20,10 @@
 // 86 TFLOP/s useful, of which the matrix instructions alone would take 0.166 ms; what is left is the uneven
 // number of tiles per wavefront, the chain before an item's first tile and its join.  (One row per
 // wavefront with plain multiply-adds, keys over lanes: 4.59 ms.)
+//
+// A key that a row must not see enters its value MFMAs with the weight 0, which hides every finite value but not an
+// infinite or invalid one.  Such a value leaves a NaN in the row, so rows that do not come out finite are done again
+// over the keys that they see and no others (attn_f32_rows).
 #include <algorithm>
 
 #include "common.h"
@@ -39,16 +43,33 @@ template <int D>
 struct F32Shared {
     float ml[NW][2][kRows][2];        // per wavefront, head and row: maximum of the raw scores, sum of the weights
     float o[NW][kRows][D + 4];        // one head at a time: values of every wavefront, scaled to the common maximum
-    f32x4 q[D / 8][64];               // two heads: the B fragments of Q K^T, the same for every wavefront
+    union {
+        f32x4 q[D / 8][64];           // two heads: the B fragments of Q K^T, the same for every wavefront
+        struct { float q[D], w[64]; } row[NW];  // attn_f32_rows: a wavefront's query row and weights of 64 keys
+    };
 };
 
 // Rows of one head (number n of the workgroup's heads): the wavefronts' values in sh.o, already scaled to
-// the row's common maximum, are added and stored.
+// the row's common maximum, are added and stored, four rows by a wavefront.  Returns false, with none of the
+// wavefront's rows stored, if one of them is not finite.
+constexpr int kRowsPerWave = kRows / NW;
 template <int D, bool PARTIAL>
-__device__ __forceinline__ void store_rows(const AttnParams &p, const pevlm_work_item &it, int32_t head, int32_t n, const F32Shared<D> &sh)
+__device__ __forceinline__ bool store_rows(const AttnParams &p, const pevlm_work_item &it, int32_t head, int32_t n, const F32Shared<D> &sh)
 {
     const int32_t orow = threadIdx.x / 16, c = threadIdx.x % 16, Hq = p.n_q_heads;
-    if (orow >= it.q_rows) return;
+    const bool live = orow < it.q_rows;
+    f32x4 x[D / 64];
+    float zero = 0.f;  // stays 0 while every value is finite
+#pragma unroll
+    for (int i = 0; i < D / 64; ++i) {
+        x[i] = *reinterpret_cast<const f32x4 *>(&sh.o[0][orow][64 * i + 4 * c]);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) x[i] += *reinterpret_cast<const f32x4 *>(&sh.o[w][orow][64 * i + 4 * c]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) zero = fmaf(x[i][j], 0.f, zero);
+    }
+    if (__any(live && zero != 0.f)) return false;
+    if (!live) return true;
     float M = -INFINITY, L = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) M = fmaxf(M, sh.ml[w][n][orow][0]);
@@ -61,12 +82,7 @@ __device__ __forceinline__ void store_rows(const AttnParams &p, const pevlm_work
     const int64_t slot = PARTIAL ? it.reserved + orow : it.q_start + orow;
     float *dst = (PARTIAL ? p.part_acc : (float *)p.out) + (slot * Hq + head) * D;
 #pragma unroll
-    for (int d = 4 * c; d < D; d += 64) {
-        f32x4 x = *reinterpret_cast<const f32x4 *>(&sh.o[0][orow][d]);
-#pragma unroll
-        for (int w = 1; w < NW; ++w) x += *reinterpret_cast<const f32x4 *>(&sh.o[w][orow][d]);
-        *reinterpret_cast<f32x4 *>(dst + d) = x * inv;
-    }
+    for (int i = 0; i < D / 64; ++i) *reinterpret_cast<f32x4 *>(dst + 64 * i + 4 * c) = x[i] * inv;
     if (c == 0) {
         if (PARTIAL) {
             p.part_ml[(slot * Hq + head) * 2] = M;
@@ -75,13 +91,83 @@ __device__ __forceinline__ void store_rows(const AttnParams &p, const pevlm_work
             p.lse[slot * Hq + head] = M * p.scale + logf(L);
         }
     }
+    return true;
 }
 
-// Two heads h[0], h[1] of KV head g.  Column c = lane % 32: row c % 16 of head c / 16; the lane's half (lane / 32)
+// The same four rows with plain multiply-adds, over the keys that a row sees and no others: one row after the other, lanes
+// over the keys for the scores and over head_dim for the values.  Taken where infinite or invalid numbers are about.
+template <int D, bool PARTIAL>
+__device__ __forceinline__ void attn_f32_rows(const AttnParams &p, const pevlm_work_item &it, int32_t h, int32_t g, F32Shared<D> &sh)
+{
+    constexpr int DV = D / 64;
+    const int32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t Hq = p.n_q_heads, Hkv = p.n_kv_heads;
+    const float *Q = (const float *)p.q, *K = (const float *)p.k, *V = (const float *)p.v;
+    float *const q_s = sh.row[wave].q, *const w_s = sh.row[wave].w;
+    auto exchanged = [] {  // what a lane has written to the wavefront's own LDS is read by its other lanes
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    for (int32_t rr = wave * kRowsPerWave; rr < it.q_rows && rr < (wave + 1) * kRowsPerWave; ++rr) {
+        const int32_t row = it.q_start + rr;
+        exchanged();
+        for (int c = 0; c < DV; ++c) q_s[lane + 64 * c] = Q[((int64_t)row * Hq + h) * D + lane + 64 * c];
+        exchanged();
+        float m = -INFINITY, l = 0.f, acc[DV];
+        for (int c = 0; c < DV; ++c) acc[c] = 0.f;
+        for (int seg = 0; seg < 2; ++seg) {
+            const int32_t start = seg == 0 ? it.full_start : it.diag_start;
+            const int32_t n = seg == 0 ? it.full_len : (row - start + 1 < it.diag_len ? row - start + 1 : it.diag_len);
+            for (int32_t k0 = 0; k0 < n; k0 += 64) {
+                const int32_t j = k0 + lane, cnt = n - k0 < 64 ? n - k0 : 64;
+                float s = -INFINITY;
+                if (j < n) {
+                    const f32x4 *kp = reinterpret_cast<const f32x4 *>(K + ((int64_t)(start + j) * Hkv + g) * D);
+                    s = 0.f;
+                    for (int d = 0; d < D / 4; ++d) {
+                        const f32x4 x = kp[d];
+                        s += q_s[4 * d] * x[0] + q_s[4 * d + 1] * x[1] + q_s[4 * d + 2] * x[2] + q_s[4 * d + 3] * x[3];
+                    }
+                }
+                float mx = s;
+                for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+                const float m_new = fmaxf(m, mx);
+                const float w = j < n ? expf((s - m_new) * p.scale) : 0.f;
+                const float alpha = expf((m - m_new) * p.scale);  // m = -inf gives 0
+                float sum = w;
+                for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+                l = l * alpha + sum;
+                for (int c = 0; c < DV; ++c) acc[c] *= alpha;
+                m = m_new;
+                exchanged();
+                w_s[lane] = w;
+                exchanged();
+                for (int32_t jj = 0; jj < cnt; ++jj) {
+                    const float *vp = V + ((int64_t)(start + k0 + jj) * Hkv + g) * D;
+                    for (int c = 0; c < DV; ++c) acc[c] += w_s[jj] * vp[lane + 64 * c];
+                }
+            }
+        }
+        const int64_t slot = ((int64_t)(PARTIAL ? it.reserved + rr : row)) * Hq + h;
+        float *const dst = (PARTIAL ? p.part_acc : (float *)p.out) + slot * D;
+        for (int c = 0; c < DV; ++c) dst[lane + 64 * c] = PARTIAL ? acc[c] : acc[c] * (1.f / l);
+        if (lane == 0) {
+            if (PARTIAL) {
+                p.part_ml[slot * 2] = m;
+                p.part_ml[slot * 2 + 1] = l;
+            } else if (p.lse) {
+                p.lse[slot] = m * p.scale + logf(l);
+            }
+        }
+    }
+}
+
+// Two heads h[0], h[1] of KV head g; returns the heads (bit 0, bit 1) whose rows of this wavefront are still to be done.  Column c = lane % 32: row c % 16 of head c / 16; the lane's half (lane / 32)
 // is the k index.  Step j of group i of Q K^T contracts head_dim 8 i + 4 half + j; the lane's score v belongs
 // to key (v & 3) + 8 (v >> 2) + 4 half of the tile; row r of block b of O^T is head_dim DB r + b.
 template <int D, bool PARTIAL>
-__device__ __forceinline__ void attn_f32_pair(const AttnParams &p, const pevlm_work_item &it, const int32_t (&h)[2], int32_t g, F32Shared<D> &sh)
+__device__ __forceinline__ int32_t attn_f32_pair(const AttnParams &p, const pevlm_work_item &it, const int32_t (&h)[2], int32_t g, F32Shared<D> &sh)
 {
     constexpr int KT = 32, KI = D / 8, DB = D / 32;
     typedef __attribute__((ext_vector_type(DB))) float f32xdb;
@@ -210,6 +296,7 @@ __device__ __forceinline__ void attn_f32_pair(const AttnParams &p, const pevlm_w
 #pragma unroll
     for (int w = 0; w < NW; ++w) M = fmaxf(M, sh.ml[w][mine][r16][0]);
     const float f = m == -INFINITY ? 0.f : expf((m - M) * p.scale);
+    int32_t left = 0;
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
         if (mine == n) {
@@ -222,16 +309,17 @@ __device__ __forceinline__ void attn_f32_pair(const AttnParams &p, const pevlm_w
             }
         }
         __syncthreads();
-        store_rows<D, PARTIAL>(p, it, h[n], n, sh);
+        if (!store_rows<D, PARTIAL>(p, it, h[n], n, sh)) left |= 1 << n;
         if (n == 0) __syncthreads();
     }
+    return left;
 }
 
 // One head on 16 columns: lane % 16 is the row, lane / 16 the k index; step j of group i of Q K^T contracts
 // head_dim 16 i + 4 kq + j, the lane's score v of a block of 16 keys is that of key 4 kq + v, row r of
 // block 4 hh + b of O^T is head_dim 64 hh + 4 r + b.
 template <int D, bool PARTIAL>
-__device__ __forceinline__ void attn_f32_single(const AttnParams &p, const pevlm_work_item &it, int32_t h, int32_t g, F32Shared<D> &sh)
+__device__ __forceinline__ int32_t attn_f32_single(const AttnParams &p, const pevlm_work_item &it, int32_t h, int32_t g, F32Shared<D> &sh)
 {
     constexpr int KI = D / 16;  // 16-wide groups of head_dim in Q K^T
     constexpr int VH = D / 64;  // 64-wide halves of head_dim in O^T
@@ -347,7 +435,7 @@ __device__ __forceinline__ void attn_f32_single(const AttnParams &p, const pevlm
             *reinterpret_cast<f32x4 *>(&sh.o[wave][r16][64 * hh + 16 * kq + 4 * v]) =
                 f32x4{o[4 * hh][v] * f, o[4 * hh + 1][v] * f, o[4 * hh + 2][v] * f, o[4 * hh + 3][v] * f};
     __syncthreads();
-    store_rows<D, PARTIAL>(p, it, h, 0, sh);
+    return store_rows<D, PARTIAL>(p, it, h, 0, sh) ? 0 : 1;
 }
 
 }  // namespace
@@ -376,15 +464,21 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(AttnParams p, int32_t 
     } else {
         it = p.items[idx];
     }
+    // Each kind of workgroup has a call of its own (104 tokens x 2 heads, RoPE included: 18.5 us, 19.2 with the two single ones joined).
+    int32_t left, g = group, h[2];
     if (pairs) {
         const int32_t G = p.n_q_heads / p.n_kv_heads;
-        const int32_t h[2] = {p.heads.head_order[group * G + 2 * u], p.heads.head_order[group * G + (2 * u + 1 < G ? 2 * u + 1 : 2 * u)]};
-        if (2 * u + 1 < G) attn_f32_pair<D, PARTIAL>(p, it, h, group, sh);
-        else attn_f32_single<D, PARTIAL>(p, it, h[0], group, sh);
+        h[0] = p.heads.head_order[group * G + 2 * u];
+        h[1] = p.heads.head_order[group * G + (2 * u + 1 < G ? 2 * u + 1 : 2 * u)];
+        if (2 * u + 1 < G) left = attn_f32_pair<D, PARTIAL>(p, it, h, group, sh);
+        else left = attn_f32_single<D, PARTIAL>(p, it, h[0], group, sh);
     } else {
-        const int32_t h = p.heads.head_order[group * units + u];
-        attn_f32_single<D, PARTIAL>(p, it, h, p.heads.kv_of_q[h], sh);
+        h[0] = h[1] = p.heads.head_order[group * units + u];
+        g = p.heads.kv_of_q[h[0]];
+        left = attn_f32_single<D, PARTIAL>(p, it, h[0], g, sh);
     }
+    for (int32_t n = 0; left >> n; ++n)
+        if (left >> n & 1) attn_f32_rows<D, PARTIAL>(p, it, n ? h[1] : h[0], g, sh);
 }
 
 hipError_t launch_attn_f32(const AttnParams &p, int32_t D, bool partial, int32_t compute_units, hipStream_t stream)

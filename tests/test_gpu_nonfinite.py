@@ -1,0 +1,34 @@
+"""Infinite and invalid values in keys and values: they reach the rows that see them and no others."""
+import numpy as np
+import pytest
+
+import workloads as W
+from gpu_util import oracle_layout, run_path, to_host_f32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,splits", [(2, 1, 64, 0), (7, 1, 128, 3), (8, 8, 64, 1), (8, 2, 128, 5)])
+@pytest.mark.parametrize("where", ["value", "key"])
+def test_fp32_rows_that_do_not_see_a_bad_key_stay_finite(oracle, Hq, Hkv, D, splits, where):
+    """fp32 kernel, one and two heads per workgroup: bad keys at both ends of a key tile, of an item of 16 rows, of a block
+    and of the sequence, in the sink, the block and the question."""
+    seqs = [(21, 100, 330, 37), (5, 40, 0, 0), (0, 64, 1600, 3)]
+    w = W.Workload("bad_f32", 41, "f32", Hq, Hkv, D, 1.0e4, seqs, 1.0)
+    data = W.generate(w)
+    starts = np.concatenate([[0], np.cumsum([s + c + q for s, _b, c, q in seqs])])
+    # sequence 0: last sink key, a block's first and middle keys, question keys; 1: a sink key; 2: a block's last key
+    bad = [20, 121, 160, 351, 357, 387, starts[1] + 3, starts[2] + 64 * 7 + 63]
+    numbers = [np.nan, np.inf, -np.inf]
+    for i, t in enumerate(bad):
+        x = data["v" if where == "value" else "k"]
+        x[t, i % Hkv, (5 * i) % D] = numbers[i % 3] if where == "value" else np.nan
+    r = run_path(w, data, num_splits=splits, want_lse=True)
+    got, lse = to_host_f32(r["out"]), to_host_f32(r["lse"])
+    want, want_lse = oracle.forward(data["q"], data["k"], data["v"], oracle_layout(oracle, w), w.rope_base)
+    fine = np.isfinite(want)
+    assert 0.2 < fine.mean() < 1.0  # the inputs do what they are meant to
+    assert np.array_equal(np.isfinite(got), fine)
+    assert np.abs(got[fine] - want[fine]).max() <= 1e-5  # the bound of every fp32 test
+    both = np.isfinite(want_lse)
+    assert np.array_equal(np.isfinite(lse), both) and np.abs(lse[both] - want_lse[both]).max() <= 1e-4
