@@ -119,7 +119,8 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeParams p)
     float M = m;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
-    const float w = m == -INFINITY ? 0.f : expf((m - M) * p.scale);  // 0: this split saw no key of the row
+    const uint64_t seen = __ballot(m != -INFINITY);  // splits that saw a key of the row
+    const float w = m == -INFINITY ? 0.f : expf((m - M) * p.scale);
     float denom = w * l;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) denom += __shfl_xor(denom, o);
@@ -132,11 +133,11 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeParams p)
         float ws[UNROLL];
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
-            const int32_t s = s0 + u * NSUB + sub;
-            ws[u] = __shfl(w, s & 63);
-            if (s >= p.num_splits) ws[u] = 0.f;
+            const int32_t s = s0 + u * NSUB + sub;  // below 64: the last step of 64 splits ends there
+            ws[u] = __shfl(w, s);
             a[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (ws[u] != 0.f) a[u] = *reinterpret_cast<const float4 *>(acc_row + s * n_units * D);
+            // a weight too small for fp32 is no reason to leave a split out: its values may be infinite
+            if (seen >> s & 1) a[u] = *reinterpret_cast<const float4 *>(acc_row + s * n_units * D);
         }
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeParams p)
 
 hipError_t launch_merge(const MergeParams &p, hipStream_t stream)
 {
-    static_assert(PEVLM_MAX_SPLITS <= 64, "one lane per split");
+    static_assert(PEVLM_MAX_SPLITS == 64, "one lane per split, steps of 8 or 16 splits");
     const int64_t units = (int64_t)p.total_q_rows * p.n_q_heads;
     const dim3 grid((uint32_t)((units + 3) / 4)), block(256);
     if (p.head_dim == 128) hipLaunchKernelGGL(merge_kernel<128>, grid, block, 0, stream, p);

@@ -1,9 +1,11 @@
 """Infinite and invalid values in keys and values: they reach the rows that see them and no others."""
 import numpy as np
 import pytest
+import torch
 
+import paper_2506_19651_amd as P
 import workloads as W
-from gpu_util import oracle_layout, run_path, to_host_f32
+from gpu_util import DEV, oracle_layout, run_path, to_host_f32
 
 pytestmark = pytest.mark.gpu
 
@@ -32,3 +34,25 @@ def test_fp32_rows_that_do_not_see_a_bad_key_stay_finite(oracle, Hq, Hkv, D, spl
     assert np.abs(got[fine] - want[fine]).max() <= 1e-5  # the bound of every fp32 test
     both = np.isfinite(want_lse)
     assert np.array_equal(np.isfinite(lse), both) and np.abs(lse[both] - want_lse[both]).max() <= 1e-4
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("splits", [1, 2, 9, 64])
+def test_infinite_value_behind_a_vanishing_weight(dtype, D, splits):
+    """One question row: its weight of every early key underflows (scores 512 and more below the largest), the value of one
+    of them is infinite.  0 x inf stays visible however the keys are split: in that element and in no other."""
+    n = 700
+    lay, heads = P.Layout.from_seqs([(0, n - 1, n - 1, 1)]), P.Heads(2, 1, D, dtype)
+    kind = torch.float32 if dtype == "f32" else torch.bfloat16
+    q = torch.full((n, 2, D), 8.0, device=DEV, dtype=kind)
+    k = torch.zeros((n, 1, D), device=DEV, dtype=kind)
+    k[650:] = 8.0
+    v = torch.ones((n, 1, D), device=DEV, dtype=kind)
+    v[100, 0, 7] = float("inf")
+    out = torch.zeros_like(q)
+    P.pevlm_query_attn(q, k, v, out, lay, heads, num_splits=splits)
+    row = out[n - 1].float().cpu()
+    assert not torch.isfinite(row[:, 7]).any()
+    row[:, 7] = 1.0
+    assert torch.equal(row, torch.ones_like(row))  # equal weights of values 1
