@@ -274,7 +274,7 @@ int64_t pevlm_prefill_stream_items_host(const pevlm_layout *layout, const pevlm_
  * (0 = both): PEVLM_FP8_QUANTISE writes the work lists and the codes into the workspace,
  * PEVLM_FP8_ATTEND computes `out` (and `lse`) from a workspace a QUANTISE stage has filled for the
  * same layout, heads and tensors (q, k, v are not read by it).  A call of both stages leaves the workspace
- * filled for later ATTEND calls too; Q's codes and scales are then those of the rows it computed.
+ * filled as a QUANTISE stage does.
  *
  * A tensor is stored as codes times a power-of-two scale 2^e, e the smallest integer with
  * amax * 2^-e <= 448 (amax: the largest magnitude the scale covers; e = 0 if that is 0; e within

@@ -761,8 +761,8 @@ pevlm_status pevlm_block_prefill_attn_fp8(const void *q, const void *k, const vo
     const int64_t T = layout->cu_seqlens[layout->num_seqs];
     const float q_factor = scale_of(heads) * 1.4426950408889634f;
     if (stages & PEVLM_FP8_QUANTISE) {
-        // both lists (they depend on the layout only) and the zeroed maxima, then the codes; Q's are left to the
-        // attention kernel if it follows
+        // both lists (they depend on the layout only) and the zeroed maxima, then the codes; if the attention kernel follows,
+        // Q's are left to it but for the question rows, which the set-up launch takes
         int32_t item_offset = 0, tile_offset = 0;
         for (int32_t s0 = 0; s0 < layout->num_seqs; s0 += kMaxSeqsPerLaunch) {
             SeqTable tab;
@@ -770,15 +770,18 @@ pevlm_status pevlm_block_prefill_attn_fp8(const void *q, const void *k, const vo
             Fp8ItemBases items_of;
             const int32_t n = std::min(kMaxSeqsPerLaunch, layout->num_seqs - s0);
             fill_table(layout, s0, n, nullptr, &tab);
+            Fp8Question qu = {q, q_factor, (uint8_t *)(ws + plan.q_codes), (float *)(ws + plan.q_scales), 0, heads->n_q_heads};
             bases.base[0] = tile_offset;
             items_of.base[0] = 0;
             for (int32_t i = 0; i < n; ++i) {
+                tab.qrow_base[i] = qu.n_rows;
+                if (stages & PEVLM_FP8_ATTEND) qu.n_rows += tab.query[i];
                 tab.item_base[i + 1] = tab.item_base[i] + prefill_items_of_seq(tab.sink[i], tab.block[i], tab.ctx[i], kKeyTile);
                 bases.base[i + 1] = tile_offset + tab.item_base[i + 1];
                 items_of.base[i + 1] = items_of.base[i] + prefill_items_of_seq(tab.sink[i], tab.block[i], tab.ctx[i], kFp8TileRows);
             }
             hipError_t e = launch_fp8_setup(tab, bases, items_of, key_tiles, tile_offset, items, item_offset, (uint32_t *)(ws + plan.kv_amax),
-                                            s0 == 0 ? 2 * heads->n_kv_heads : 0, hs);
+                                            s0 == 0 ? 2 * heads->n_kv_heads : 0, qu, heads->head_dim, hs);
             if (e != hipSuccess) return hip_fail(e, "fp8 work-list launch");
             tile_offset += tab.item_base[n];
             item_offset += items_of.base[n];

@@ -146,14 +146,56 @@ __device__ __forceinline__ float row_max_grouped(const f32x16 (&s)[2])
     return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
 }
 
+// Q: one scale per (token, head); D/16 consecutive lanes share a row of one head (rh: token x heads + head, c: the lane's
+// 16 values).  What is quantised is q * factor (factor = softmax factor * log2(e), one fp32 multiplication per element),
+// so that the score MFMAs deliver base-2 exponents.
+template <int D>
+__device__ __forceinline__ void quantise_q_part(const uint16_t *q, int64_t rh, bool live, int32_t c, float factor, uint8_t *codes, float *scales)
+{
+    float x[16];
+    if (live) {
+        const uint4 *src = reinterpret_cast<const uint4 *>(q + rh * D + c * 16);
+        bf16x8_to_f32(src[0], x);
+        bf16x8_to_f32(src[1], x + 8);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = __fmul_rn(x[i], factor);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = 0.f;
+    }
+    float m = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(x[i]));
+#pragma unroll
+    for (int off = D / 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+    const int32_t e = scale_exponent(m);
+    if (live) {
+        *reinterpret_cast<i32x4v *>(codes + rh * D + c * 16) = quantise16(x, pow2(-e));
+        if (c == 0) scales[rh] = pow2(e);
+    }
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------- work lists
 // Both lists of a chunk of sequences (tiles.item_base counts 64-row key tiles, items.item_base 128-row items) and,
-// with the first chunk, the zeros that the maxima start from: one launch instead of three of 4-5 us each.
+// with the first chunk, the zeros that the maxima start from: one launch instead of three of 4-5 us each.  Workgroups
+// from list_blocks on quantise the chunk's question rows (n_question of them, tab.qrow_base counts them) in a call
+// whose attention kernel quantises the other rows.
+template <int D>
 __global__ __launch_bounds__(256) void fp8_setup_kernel(SeqTable tab, Fp8TileBases bases, Fp8ItemBases items_of, pevlm_work_item *key_tiles,
-                                                        int32_t tile_offset, Fp8Item *items, int32_t item_offset, uint32_t *zero, int32_t n_zero)
+                                                        int32_t tile_offset, Fp8Item *items, int32_t item_offset, uint32_t *zero, int32_t n_zero,
+                                                        int32_t list_blocks, Fp8Question qu)
 {
+    if ((int32_t)blockIdx.x >= list_blocks) {
+        const int64_t t = (int64_t)((int32_t)blockIdx.x - list_blocks) * 256 + threadIdx.x, unit = t / (D / 16);
+        const int32_t r = (int32_t)(unit / qu.n_q_heads), head = (int32_t)(unit % qu.n_q_heads);
+        int32_t s = 0;
+        while (s + 1 < tab.num_seqs && r >= tab.qrow_base[s + 1]) ++s;
+        const int64_t row = tab.start[s] + tab.sink[s] + tab.ctx[s] + r - tab.qrow_base[s];
+        quantise_q_part<D>((const uint16_t *)qu.q, row * qu.n_q_heads + head, r < qu.n_rows, (int32_t)(t % (D / 16)), qu.factor, qu.codes, qu.scales);
+        return;
+    }
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n_zero) zero[i] = 0u;
     if (i < tab.item_base[tab.num_seqs]) {
@@ -231,38 +273,11 @@ __global__ __launch_bounds__(256) void amax_kv_kernel(const uint16_t *k, const u
         if (head_max[i]) atomicMax(amax + blockIdx.y * Hkv + i, head_max[i]);
 }
 
-// Q: one scale per (token, head); D/16 consecutive lanes share a row of one head.  What is quantised is
-// q * factor (factor = softmax factor * log2(e), one fp32 multiplication per element), so that the score
-// MFMAs deliver base-2 exponents.
 template <int D>
 __global__ __launch_bounds__(256) void quantise_q_kernel(const uint16_t *q, int64_t n_rows_heads, float factor, uint8_t *codes, float *scales)
 {
-    constexpr int LPR = D / 16;  // lanes per row of one head
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t rh = t / LPR;
-    const int32_t c = (int32_t)(t % LPR);
-    const bool live = rh < n_rows_heads;
-    float x[16];
-    if (live) {
-        const uint4 *src = reinterpret_cast<const uint4 *>(q + rh * D + c * 16);
-        bf16x8_to_f32(src[0], x);
-        bf16x8_to_f32(src[1], x + 8);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = __fmul_rn(x[i], factor);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = 0.f;
-    }
-    float m = 0.f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(x[i]));
-#pragma unroll
-    for (int off = LPR / 2; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    const int32_t e = scale_exponent(m);
-    if (live) {
-        *reinterpret_cast<i32x4v *>(codes + rh * D + c * 16) = quantise16(x, pow2(-e));
-        if (c == 0) scales[rh] = pow2(e);
-    }
+    quantise_q_part<D>(q, t / (D / 16), t / (D / 16) < n_rows_heads, (int32_t)(t % (D / 16)), factor, codes, scales);
 }
 
 // K and V tiles: blockIdx.x = key tile (64 rows of one region), blockIdx.y = KV head.
@@ -587,12 +602,16 @@ __global__ __launch_bounds__(256, 3) void attn_fp8_kernel(Fp8Params p)
 
 // ---------------------------------------------------------------- launchers
 hipError_t launch_fp8_setup(const SeqTable &tab, const Fp8TileBases &bases, const Fp8ItemBases &items_of, pevlm_work_item *key_tiles,
-                            int32_t tile_offset, Fp8Item *items, int32_t item_offset, uint32_t *zero, int32_t n_zero, hipStream_t stream)
+                            int32_t tile_offset, Fp8Item *items, int32_t item_offset, uint32_t *zero, int32_t n_zero, const Fp8Question &qu,
+                            int32_t D, hipStream_t stream)
 {
     const int32_t n = std::max(std::max(tab.item_base[tab.num_seqs], items_of.base[tab.num_seqs]), n_zero);
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(fp8_setup_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, tab, bases, items_of, key_tiles, tile_offset, items,
-                       item_offset, zero, n_zero);
+    const int32_t list_blocks = ceil_div(n, 256);
+    const int64_t threads = (int64_t)qu.n_rows * qu.n_q_heads * (D / 16), blocks = list_blocks + (threads + 255) / 256;
+    if (blocks == 0) return hipSuccess;
+    const auto kernel = D == 128 ? fp8_setup_kernel<128> : fp8_setup_kernel<64>;
+    hipLaunchKernelGGL(kernel, dim3((uint32_t)blocks), dim3(256), 0, stream, tab, bases, items_of, key_tiles, tile_offset, items,
+                       item_offset, zero, n_zero, list_blocks, qu);
     return hipGetLastError();
 }
 

@@ -423,6 +423,13 @@ struct Fp8TileBases {
 struct Fp8ItemBases {
     int32_t base[kMaxSeqsPerLaunch + 1];  // first work item of each sequence of the chunk (chunk-relative)
 };
+struct Fp8Question {  // question rows of a chunk of sequences that the set-up launch quantises (n_rows 0: none)
+    const void *q;
+    float factor;
+    uint8_t *codes;
+    float *scales;
+    int32_t n_rows, n_q_heads;
+};
 struct Fp8Params {
     const void *q;            // bf16 [T][Hq][D], quantised by the kernel itself into codes and scales; NULL: they are read
     float q_factor;
@@ -473,7 +480,8 @@ hipError_t launch_build_stream_items(const SeqTable &tab, int32_t G, int32_t Hkv
 // block-prefill rows of bf16 tensors from a stream-item list; workgroups = compute units (8 wavefronts each)
 hipError_t launch_attn_bf16_stream(const StreamParams &p, int32_t D, int32_t compute_units, hipStream_t stream);
 hipError_t launch_fp8_setup(const SeqTable &tab, const Fp8TileBases &bases, const Fp8ItemBases &items_of, pevlm_work_item *key_tiles,
-                            int32_t tile_offset, Fp8Item *items, int32_t item_offset, uint32_t *zero, int32_t n_zero, hipStream_t stream);
+                            int32_t tile_offset, Fp8Item *items, int32_t item_offset, uint32_t *zero, int32_t n_zero, const Fp8Question &qu,
+                            int32_t D, hipStream_t stream);
 // bf16 K, V and (with_q) Q -> E4M3 codes and scales (key_tiles: the prefill items of 64 rows, one per K/V tile)
 hipError_t launch_fp8_quantise(const void *q, const void *k, const void *v, int64_t T, int32_t Hq, int32_t Hkv, int32_t D,
                                float q_factor, const pevlm_work_item *key_tiles, int32_t n_key_tiles, uint32_t *kv_amax, float *q_scales,

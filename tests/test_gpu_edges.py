@@ -186,3 +186,21 @@ def test_row_sums_of_equal_weights(D, kernel, keys):
     mean = torch.cumsum(v[:, 0, 0].cpu().double(), 0) / n
     err = (out.cpu().double() - mean.view(-1, 1, 1)).abs()
     assert (err <= 2.0 ** -8 * mean.view(-1, 1, 1) + 1e-3).all()  # one bf16 rounding of the result
+
+
+@pytest.mark.parametrize("D,Hq,Hkv", [(128, 7, 1), (64, 6, 3)])
+@pytest.mark.parametrize("seqs", [[(3, 50, 70, 129)], [(0, 1, 0, 5), (9, 30, 61, 0), (2, 40, 100, 33), (0, 16, 16, 1)] * 13])
+def test_fp8_both_stages_quantise_question_rows(D, Hq, Hkv, seqs):
+    """Codes and scales of every row of Q, the question's included, sequences without one and more sequences than a
+    table holds: one call of both stages against a QUANTISE stage."""
+    w = W.Workload("fp8question", 37, "bf16", Hq, Hkv, D, 1.0e6, seqs, 0.5)
+    data = W.generate(w)
+    lay, heads = layout_heads(w)
+    q, k, v = to_device(data["q"]), to_device(data["k"]), to_device(data["v"])
+    plan, out, spaces = P.pevlm_block_prefill_fp8_plan(lay, heads), torch.zeros_like(q), []
+    for stages in (0, P.FP8_QUANTISE):
+        ws = torch.full((plan.total,), 0xEE, dtype=torch.uint8, device=DEV)
+        P.pevlm_block_prefill_attn_fp8(q, k, v, out, lay, heads, workspace=ws, stages=stages)
+        spaces.append(ws.cpu().numpy())
+    for lo, n in ((plan.q_codes, w.total_tokens * Hq * D), (plan.q_scales, w.total_tokens * Hq * 4)):
+        assert np.array_equal(spaces[0][lo:lo + n], spaces[1][lo:lo + n])
