@@ -388,11 +388,13 @@ def pevlm_query_attn_static(q, k, v, out, layout: Layout, heads: Heads, num_spli
 
 def _i32_array(values):
     """(owner, what the C call takes) of a host array of int32.  A list of integers becomes a ctypes array at
-    once, a third of the time of the way through numpy."""
+    once (0.6 us; through numpy 3.1); anything else, integers that int32 does not hold and ctypes has wrapped
+    among it, is left to numpy."""
     if isinstance(values, (list, tuple)):
         try:
             a = (ctypes.c_int32 * len(values))(*values)
-            return a, a
+            if a[:] == list(values):
+                return a, a
         except TypeError:
             pass
     a = np.ascontiguousarray(values, dtype=np.int32)

@@ -417,3 +417,24 @@ def test_fp8_plan_offsets_and_counts():
         P.pevlm_block_prefill_fp8_plan(P.Layout.from_seqs([(8, 8, 16, 0)]), P.Heads(2, 1, 64, "f32"))
     assert P.pevlm_block_prefill_fp8_workspace_bytes(P.Layout.from_seqs([(8, 8, 16, 0)]), P.Heads(2, 1, 64, "f32")) == 0
 
+
+
+@pytest.mark.parametrize("value", [2**31, 2**32 + 5, -2**31 - 1])
+@pytest.mark.parametrize("kind", [list, tuple])
+def test_host_arrays_refuse_what_int32_does_not_hold(value, kind):
+    """Offsets and block numbers out of range are an error, not the number modulo 2^32."""
+    lay, heads = P.Layout.from_seqs([(4, 8, 16, 2), (0, 8, 16, 2)]), P.Heads(2, 1, 64, "bf16")
+    with pytest.raises(OverflowError):
+        P.pevlm_rope_seq(None, None, lay, heads, 1.0e4, kind([0, value]), stream=0)
+    with pytest.raises(OverflowError):
+        P.pevlm_prefill_worklist_blocks_host(lay, 128, kind([value, 0]), [1, 1], False)
+    with pytest.raises(OverflowError):
+        P.pevlm_query_worklist_window_host(lay, 128, 2, kind([value, 0]))
+
+
+@pytest.mark.parametrize("values", [[-2**31, 2**31 - 1], (3, -1), [True, 0], [np.int64(7), 2], [2.0, 3.0], np.array([1, 2])], ids=str)
+def test_host_arrays_take_what_numpy_takes(values):
+    from paper_2506_19651_amd.binding import _i32_array
+
+    owner, array = _i32_array(values)
+    assert [array[i] for i in range(2)] == [int(v) for v in values]
