@@ -315,19 +315,22 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
     // Only if a lane's weights may have reached 2^kRescaleStep (or a row has no reference yet) is the
     // row maximum of the tile computed, the reference raised, o and l scaled down and the tile's weights formed
     // again: weights stay below 2^kRescaleStep, which fp32 sums and bf16 weights carry without loss,
-    // and on almost every tile the vector ALU only does exp2, convert and sum.
+    // and on almost every tile the vector ALU only does exp2, convert and sum.  A row is raised for its own weights
+    // only: its result does not depend on which rows share its wavefront, which the two prefill kernels, the calls with
+    // RoPE folded in and a prefill in pieces choose differently.
 #define PEVLM_FIX_REFERENCE()                                                                         \
     do {                                                                                              \
-        if (__any(sum_reached_step(psum) || m_ref == -INFINITY)) {                                    \
+        const uint64_t up_ = __ballot(sum_reached_step(psum) || m_ref == -INFINITY);                  \
+        if (up_) {                                                                                    \
             const float mx = row_max(s) * c_log2;                                                     \
             const bool has = m_ref != -INFINITY;                                                      \
-            const float m_new = fmaxf(m_ref, mx);                                                     \
+            const float m_new = row_flag(up_, lane) ? fmaxf(m_ref, mx) : m_ref;                       \
             const float alpha = has ? __builtin_amdgcn_exp2f(m_ref - m_new) : 1.f;                    \
             m_ref = m_new;                                                                            \
             psum = 0.f;                                                                               \
             weights(s, c_log2, PEVLM_MREF, psum, pf);                                                 \
             if (__any(has)) { /* rows without a reference have o = l = 0 */                          \
-                l_run *= alpha;                                                                       \
+                l_run = rounded_product(l_run, alpha);                                                \
                 _Pragma("unroll") for (int b = 0; b < DBLK; ++b)                                      \
                     _Pragma("unroll") for (int i = 0; i < 16; ++i) o[b][i] *= alpha;                  \
             }                                                                                         \

@@ -257,16 +257,17 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
     // same check-after-the-fact reference maximum as the one-item kernel
 #define PEVLM_FIX_REFERENCE()                                                                         \
     do {                                                                                              \
-        if (__any(sum_reached_step(psum) || m_ref == -INFINITY)) {                                    \
+        const uint64_t up_ = __ballot(sum_reached_step(psum) || m_ref == -INFINITY);                  \
+        if (up_) {                                                                                    \
             const float mx = row_max(s) * c_log2;                                                     \
             const bool has = m_ref != -INFINITY;                                                      \
-            const float m_new = fmaxf(m_ref, mx);                                                     \
+            const float m_new = row_flag(up_, lane) ? fmaxf(m_ref, mx) : m_ref;                       \
             const float alpha = has ? __builtin_amdgcn_exp2f(m_ref - m_new) : 1.f;                    \
             m_ref = m_new;                                                                            \
             psum = 0.f;                                                                               \
             weights(s, c_log2, PEVLM_MREF, psum, pf);                                             \
             if (__any(has)) {                                                                         \
-                l_run *= alpha;                                                                       \
+                l_run = rounded_product(l_run, alpha);                                                \
                 _Pragma("unroll") for (int b = 0; b < DBLK; ++b)                                      \
                     _Pragma("unroll") for (int i = 0; i < 16; ++i) o[b][i] *= alpha;                  \
             }                                                                                         \

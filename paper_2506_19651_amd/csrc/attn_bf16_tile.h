@@ -126,6 +126,10 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
+// fused in every place (left to the compiler it is in some): a row's weights are formed in one or the other as the rows beside
+// it need it, and come out the same
+__device__ __forceinline__ float weight(float s, float c_log2, float mref) { return __builtin_amdgcn_exp2f(__builtin_fmaf(s, c_log2, -mref)); }
+
 __device__ __forceinline__ uint32_t weight_pair(float p0, float p1)
 {
     bf16x2 pr;
@@ -156,7 +160,7 @@ __device__ __forceinline__ void weights(const f32x16 (&s)[2], float c_log2, floa
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
             const int kc = j >> 1, i = (j & 1) * 8 + w * 2;
-            pf[j][w] = weight_pair(__builtin_amdgcn_exp2f(s[kc][i] * c_log2 - mref), __builtin_amdgcn_exp2f(s[kc][i + 1] * c_log2 - mref));
+            pf[j][w] = weight_pair(weight(s[kc][i], c_log2, mref), weight(s[kc][i + 1], c_log2, mref));
         }
         add_weights(pf[j], sum);
     }
@@ -166,6 +170,14 @@ __device__ __forceinline__ void weights(const f32x16 (&s)[2], float c_log2, floa
 // true unless this lane's sum of weights proves that all of them stayed below 2^kRescaleStep
 __device__ __forceinline__ bool sum_reached_step(float psum) { return !(psum < 256.f); }
 static_assert(kRescaleStep == 8.f, "sum_reached_step compares with 2^kRescaleStep");
+// a ballot's flag of this lane's row, whose keys are spread over the lanes l and l + 32
+__device__ __forceinline__ bool row_flag(uint64_t flags, int32_t lane) { return ((uint32_t)flags | (uint32_t)(flags >> 32)) >> (lane & 31) & 1; }
+// the row sum moved to a new reference: a product that is not fused with the addition after it in one kernel and not in another
+__device__ __forceinline__ float rounded_product(float a, float b)
+{
+#pragma clang fp contract(off)
+    return a * b;
+}
 
 // O^T += V^T P^T for a staged V tile (16 MFMAs per 32 values of head_dim ... 4 k-steps x DBLK blocks)
 template <int D>
@@ -241,8 +253,8 @@ __device__ __forceinline__ void pv_prev_weights_cur(const uint8_t *tv_prev, cons
         for (int x = 0; x < PPM; ++x) {
             const int pi = n * PPM + x, kc = pi >> 3, i = (pi & 7) * 2;
             float &e0 = e[(pi & 3) * 2], &e1 = e[(pi & 3) * 2 + 1];
-            e0 = __builtin_amdgcn_exp2f(s[kc][i] * c_log2 - mref);
-            e1 = __builtin_amdgcn_exp2f(s[kc][i + 1] * c_log2 - mref);
+            e0 = weight(s[kc][i], c_log2, mref);
+            e1 = weight(s[kc][i + 1], c_log2, mref);
             asm volatile("" : "+v"(e0), "+v"(e1));  // here, not after the last MFMA
         }
         if (b == C::DBLK - 1) {

@@ -204,3 +204,41 @@ def test_fp8_both_stages_quantise_question_rows(D, Hq, Hkv, seqs):
         spaces.append(ws.cpu().numpy())
     for lo, n in ((plan.q_codes, w.total_tokens * Hq * D), (plan.q_scales, w.total_tokens * Hq * 4)):
         assert np.array_equal(spaces[0][lo:lo + n], spaces[1][lo:lo + n])
+
+
+@pytest.mark.parametrize("extra", [dict(qk_scale=2.5), dict(qk_scale=1.5, key_ramp=6.0), dict(qk_scale=6.0, key_ramp=3.0)],
+                         ids=["peaky", "rising_max", "huge_scores"])
+@pytest.mark.parametrize("Hq,Hkv,D", [(8, 2, 128), (7, 1, 128), (6, 2, 64), (4, 4, 64)])
+def test_a_row_does_not_depend_on_the_rows_beside_it(Hq, Hkv, D, extra):
+    """Reference maxima that have to be raised on the way: the same bits from the one-item kernel (32 (row, head) pairs in a
+    wavefront), the streaming kernel (32 rows of one head), the call with RoPE folded in and a prefill block by block."""
+    seqs = [(200, 300, 1000, 0), (0, 130, 700, 0), (33, 64, 200, 0)]
+    w = W.Workload("beside", 38, "bf16", Hq, Hkv, D, 1.0e6, seqs, 0.5, **extra)
+    data = W.generate(w)
+    lay, heads = layout_heads(w)
+    q, k, v = to_device(data["q"]), to_device(data["k"]), to_device(data["v"])
+    raw = q.clone()
+    P.pevlm_rope_seq(q, k, lay, heads, w.rope_base)
+
+    def result(call):
+        out, lse = torch.zeros_like(q), torch.zeros(w.total_tokens, Hq, device=DEV)
+        call(out, lse)
+        return out.view(torch.int16).cpu(), lse.view(torch.int32).cpu()
+
+    def in_pieces(out, lse):
+        blocks = [-(-c // b) for _s, b, c, _q in seqs]
+        for i in range(max(blocks)):
+            P.pevlm_block_prefill_attn_blocks(q, k, v, out, lay, heads, [min(i, n - 1) for n in blocks], [int(i < n) for n in blocks], i == 0,
+                                              lse=lse)
+
+    results, prev = {}, P.pevlm_set_prefill_kernel("classic")
+    try:
+        for kernel in ("classic", "stream"):
+            P.pevlm_set_prefill_kernel(kernel)
+            results[kernel] = result(lambda out, lse: P.pevlm_block_prefill_attn(q, k, v, out, lay, heads, lse=lse))
+            results[kernel + " in pieces"] = result(in_pieces)
+    finally:
+        P.pevlm_set_prefill_kernel(prev)
+    results["folded"] = result(lambda out, lse: P.pevlm_block_prefill_attn_rope(raw, k, v, out, lay, heads, w.rope_base, k_is_rotated=True, lse=lse))
+    for name, (out, lse) in results.items():
+        assert torch.equal(out, results["classic"][0]) and torch.equal(lse, results["classic"][1]), name
