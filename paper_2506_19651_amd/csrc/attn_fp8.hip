@@ -104,26 +104,34 @@ __host__ __device__ __forceinline__ int32_t swizzled_chunk(int32_t r, int32_t c)
 
 // One k-step of the scores of 64 keys x 32 rows: s[kc] = c + K Q^T with the block exponents of K and Q, c = 0, the
 // start values or s[kc].  Written as instructions because both chunks start from the same 16 registers:
-// left to the compiler the start values are copied for one of the chunks on every tile.  The wait states after the
-// LAST step cover the 16-pass results for whatever reads them next; between two steps a chunk's MFMAs are one
-// MFMA (64 cycles) apart, which the chained accumulator needs no wait for.
+// left to the compiler the start values are copied for one of the chunks on every tile.  The compiler sees no matrix
+// instruction here, so the waits are part of the block: two states in front, for operands that a vector instruction has
+// just written, and after the LAST step the 16 passes and 4 states that a reader of the results needs (row_max_grouped
+// reads them in instructions of its own, so that a builtin as the last step would not do).  Between two steps a
+// chunk's MFMAs are one MFMA (64 cycles) apart, which the chained accumulator needs no wait for.
 enum { kFromZero, kFromStart, kContinue };
 template <int FROM, bool LAST>
 __device__ __forceinline__ void score_step(const i32x8 &k0, const i32x8 &k1, const i32x8 &q, const f32x16 &start, int32_t k_exp8,
                                            int32_t q_exp8, f32x16 (&s)[2])
 {
 #define PEVLM_SCORE(dst, kreg, creg) "v_mfma_scale_f32_32x32x64_f8f6f4 " dst ", " kreg ", %4, " creg ", %5, %6 op_sel_hi:[0,0,0]\n\t"
-    if (FROM == kFromZero)
-        asm volatile(PEVLM_SCORE("%0", "%2", "0") PEVLM_SCORE("%1", "%3", "0")
-                     : "=&v"(s[0]), "=&v"(s[1]) : "v"(k0), "v"(k1), "v"(q), "v"(k_exp8), "v"(q_exp8));
-    else if (FROM == kFromStart)
-        asm volatile(PEVLM_SCORE("%0", "%2", "%7") PEVLM_SCORE("%1", "%3", "%7")
-                     : "=&v"(s[0]), "=&v"(s[1]) : "v"(k0), "v"(k1), "v"(q), "v"(k_exp8), "v"(q_exp8), "v"(start));
-    else
-        asm volatile(PEVLM_SCORE("%0", "%2", "%0") PEVLM_SCORE("%1", "%3", "%1")
-                     : "+v"(s[0]), "+v"(s[1]) : "v"(k0), "v"(k1), "v"(q), "v"(k_exp8), "v"(q_exp8));
+#define PEVLM_SCORES(bind, c0, c1, tail, ...)                                                                   \
+    asm volatile("s_nop 1\n\t" PEVLM_SCORE("%0", "%2", c0) PEVLM_SCORE("%1", "%3", c1) tail                     \
+                 : bind(s[0]), bind(s[1]) : "v"(k0), "v"(k1), "v"(q), "v"(k_exp8), "v"(q_exp8), ##__VA_ARGS__)
+#define PEVLM_WAIT "s_nop 15\n\ts_nop 3"
+    if (FROM == kFromZero) {
+        if (LAST) PEVLM_SCORES("=&v", "0", "0", PEVLM_WAIT);
+        else PEVLM_SCORES("=&v", "0", "0", "");
+    } else if (FROM == kFromStart) {
+        if (LAST) PEVLM_SCORES("=&v", "%7", "%7", PEVLM_WAIT, "v"(start));
+        else PEVLM_SCORES("=&v", "%7", "%7", "", "v"(start));
+    } else {
+        if (LAST) PEVLM_SCORES("+v", "%0", "%1", PEVLM_WAIT);
+        else PEVLM_SCORES("+v", "%0", "%1", "");
+    }
+#undef PEVLM_WAIT
+#undef PEVLM_SCORES
 #undef PEVLM_SCORE
-    if (LAST) asm volatile("s_nop 15\n\ts_nop 3" : "+v"(s[0]), "+v"(s[1]));
 }
 
 // maximum of 8 values without the quieting moves that plain fmaxf puts in front of values it cannot prove canonical
