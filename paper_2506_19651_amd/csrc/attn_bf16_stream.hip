@@ -257,11 +257,11 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
     // same check-after-the-fact reference maximum as the one-item kernel
 #define PEVLM_FIX_REFERENCE()                                                                         \
     do {                                                                                              \
-        const uint64_t up_ = __ballot(sum_reached_step(psum) || m_ref == -INFINITY);                  \
-        if (up_) {                                                                                    \
+        const int32_t up_ = sum_reached_step(psum) || m_ref == -INFINITY;                             \
+        if (__any(up_)) {                                                                             \
             const float mx = row_max(s) * c_log2;                                                     \
             const bool has = m_ref != -INFINITY;                                                      \
-            const float m_new = row_flag(up_, lane) ? fmaxf(m_ref, mx) : m_ref;                       \
+            const float m_new = up_ | __shfl_xor(up_, 32) ? fmaxf(m_ref, mx) : m_ref;                   \
             const float alpha = has ? __builtin_amdgcn_exp2f(m_ref - m_new) : 1.f;                    \
             m_ref = m_new;                                                                            \
             psum = 0.f;                                                                               \

@@ -170,8 +170,6 @@ __device__ __forceinline__ void weights(const f32x16 (&s)[2], float c_log2, floa
 // true unless this lane's sum of weights proves that all of them stayed below 2^kRescaleStep
 __device__ __forceinline__ bool sum_reached_step(float psum) { return !(psum < 256.f); }
 static_assert(kRescaleStep == 8.f, "sum_reached_step compares with 2^kRescaleStep");
-// a ballot's flag of this lane's row, whose keys are spread over the lanes l and l + 32
-__device__ __forceinline__ bool row_flag(uint64_t flags, int32_t lane) { return ((uint32_t)flags | (uint32_t)(flags >> 32)) >> (lane & 31) & 1; }
 // the row sum moved to a new reference: a product that is not fused with the addition after it in one kernel and not in another
 __device__ __forceinline__ float rounded_product(float a, float b)
 {
