@@ -110,10 +110,11 @@ __device__ __forceinline__ void mask_tile(f32x16 (&s)[2], int32_t k0, int32_t ke
 // maximum over the 64 keys of the tile for this lane's row (both lanes of a row end up with it)
 __device__ __forceinline__ float row_max(const f32x16 (&s)[2])
 {
-    float mx = max3f(s[0][0], s[0][1], s[0][2]);
+    // max3f is an instruction that the compiler does not know (it quiets the operands of its own): no wait for matrix results
+    // is added in front of it.  The first maximum is one that it knows, and the others come after it.
+    float mx = fmaxf(s[0][0], s[0][1]);
 #pragma unroll
-    for (int i = 3; i < 31; i += 2) mx = max3f(mx, s[i >> 4][i & 15], s[(i + 1) >> 4][(i + 1) & 15]);
-    mx = fmaxf(mx, s[1][15]);
+    for (int i = 2; i < 32; i += 2) mx = max3f(mx, s[i >> 4][i & 15], s[(i + 1) >> 4][(i + 1) & 15]);
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
     return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
 }
