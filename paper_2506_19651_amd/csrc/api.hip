@@ -329,6 +329,38 @@ static int32_t compute_units()
     return have;
 }
 
+// bytes of the (cos, sin) table of the fused query rotation: head_dim/2 pairs of floats per entry
+static size_t rope_table_bytes(int64_t entries, const pevlm_heads *h) { return align256((size_t)entries * h->head_dim * sizeof(float)); }
+
+struct QueryPlan {
+    int32_t num_splits, tile_rows;
+    int64_t n_items, total_q;
+    size_t off_items, off_qrow, off_ml, off_acc, off_rope, bytes;
+};
+
+// The workspace of a question call with this number of splits.
+static QueryPlan carve_query(int64_t tiles, int64_t total_q, const pevlm_heads *h, int32_t num_splits, bool fuse_rope = false)
+{
+    QueryPlan p;
+    p.num_splits = num_splits;
+    p.tile_rows = tile_rows_of(h, true);
+    p.total_q = total_q;
+    p.n_items = tiles * num_splits;
+    size_t off = 0;
+    p.off_items = off;
+    off += align256((size_t)p.n_items * sizeof(pevlm_work_item));
+    p.off_qrow = off;
+    off += align256((size_t)p.total_q * sizeof(int32_t));
+    p.off_ml = off;
+    off += align256((size_t)num_splits * p.total_q * h->n_q_heads * 2 * sizeof(float));
+    p.off_acc = off;
+    off += align256((size_t)num_splits * p.total_q * h->n_q_heads * h->head_dim * sizeof(float));
+    p.off_rope = off;
+    if (fuse_rope) off += rope_table_bytes(p.total_q, h);  // one entry per compact question row
+    p.bytes = off;
+    return p;
+}
+
 // Split count when the caller leaves it to the library.
 //
 // fp32: workgroups (16 rows x two heads x split) are brought as close as possible to one or two full rounds of 2
@@ -341,16 +373,31 @@ static int32_t compute_units()
 // layout, question) points x 15 counts from 1 to 64, 1 K to 100 K keys, 1 to 256 rows: the picked count is within
 // 1 % of the best one's time on average, 4 % at worst; "one or two full rounds, at least 768 keys" was up
 // to twice as slow on short contexts (1124 keys: 13 us at 18 splits, 26 us at 1).
-static int32_t auto_splits_f32(const pevlm_layout *lay, const pevlm_heads *h)
+//
+// Batches: pieces of nearly one length (the shortest at least 3/4 of the longest) run in rounds too; otherwise an even load
+// plus half of the longest piece at the end.  Over 260 batches (2-48 sequences, 256 to 150 K keys, 1-256 rows, 9 head
+// shapes) x 25 counts the least prediction takes 0.92 of the time of the full rounds on average; it is taken where it
+// promises 5 % (6 of the 260 then lose more than 5 %, 19 % at worst; 13 without that margin).
+//
+// Neither takes more partials than the full rounds would, unless they fit the array of pevlm_query_attn_static: what
+// fitted that array fits it, and other callers' workspaces do not grow past its size for a few per cent.
+constexpr size_t kFreeQueryBytes = PEVLM_STATIC_SCRATCH_BYTES;
+
+// Workgroups of `heads_together(rows of the tile)` heads, brought close to one or two full rounds of 2 x CUs from below
+template <class HeadsTogether>
+static int32_t splits_of_full_rounds(const pevlm_layout *lay, const pevlm_heads *h, int32_t min_keys, HeadsTogether heads_together)
 {
-    const int32_t G = h->n_q_heads / h->n_kv_heads, hpw = G > 1 && !h->kv_head_of_q ? 2 : 1;
+    const int32_t G = h->n_q_heads / h->n_kv_heads, tile = tile_rows_of(h, true);
+    const bool together = G > 1 && !h->kv_head_of_q;
+    const int32_t per_full_tile = ceil_div(G, together ? heads_together(tile) : 1);
     int64_t units = 0, max_len = 0, min_len = INT64_MAX;
     for (int32_t s = 0; s < lay->num_seqs; ++s) {
-        if (lay->query_len[s] == 0) continue;
+        const int32_t Q = lay->query_len[s], rest = Q % tile;
+        if (Q == 0) continue;
         const int64_t len = (int64_t)lay->cu_seqlens[s + 1] - lay->cu_seqlens[s];
         max_len = std::max(max_len, len);
         min_len = std::min(min_len, len);
-        units += (int64_t)ceil_div(lay->query_len[s], kTileRowsF32) * h->n_kv_heads * ceil_div(G, hpw);
+        units += (int64_t)h->n_kv_heads * ((int64_t)(Q / tile) * per_full_tile + (rest ? ceil_div(G, together ? heads_together(rest) : 1) : 0));
     }
     if (units == 0) return 1;
     const int64_t slots = 2 * (int64_t)compute_units();
@@ -358,12 +405,11 @@ static int32_t auto_splits_f32(const pevlm_layout *lay, const pevlm_heads *h)
     // a badly filled round, or sequences of very different length (every sequence gets the same
     // number of splits, so the long ones set the pace): take two rounds of finer pieces
     if (want * units * 4 < slots * 3 || 2 * min_len < max_len) want = (2 * slots) / units;
-    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, max_len / 256), PEVLM_MAX_SPLITS));
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, max_len / min_keys), PEVLM_MAX_SPLITS));
 }
 
-static int32_t auto_splits(const pevlm_layout *lay, const pevlm_heads *h, const Restrict &sel = Restrict())
+static int32_t predicted_splits(const pevlm_layout *lay, const pevlm_heads *h, const Restrict &sel, int32_t full_rounds)
 {
-    if (h->dtype == PEVLM_F32) return auto_splits_f32(lay, h);
     const int32_t G = equal_head_groups(h) ? h->n_q_heads / h->n_kv_heads : 1, groups = h->n_q_heads / G;
     const bool windowed = sel.window_blocks != nullptr;
     const double cus = compute_units(), slots = 2 * cus;
@@ -371,12 +417,13 @@ static int32_t auto_splits(const pevlm_layout *lay, const pevlm_heads *h, const 
     const double tile_some = h->head_dim == 128 ? 1.25 : 0.95;  // ... some compute units with two
     const double tile_full = h->head_dim == 128 ? 1.62 : 1.2;   // ... all with two
     const double partial_us = (double)total_query_rows(lay) * h->n_q_heads * (h->head_dim + 2) * 4 / 2.5e6;  // one split's partials, written and read
-    int32_t best = 1, asking = 0;
-    double best_us = 0;
+    int32_t asking = 0;
     for (int32_t s = 0; s < lay->num_seqs; ++s) asking += lay->query_len[s] > 0;
     if (asking == 0) return 1;
-    for (int32_t n = windowed ? 2 : 1; n <= PEVLM_MAX_SPLITS; n += n < 20 ? 1 : (n < 32 ? 2 : 4)) {
-        double wgs = 0, sum_us = 0, longest_tiles = 0;
+    double least_load = 0;  // what the pieces take on all compute units, however they are cut
+    auto predict = [&](int32_t n) {
+        double wgs = 0, sum_us = 0, longest_tiles = 0, shortest_tiles = 1e30;
+        least_load = 0;
         for (int32_t s = 0; s < lay->num_seqs; ++s) {
             const int32_t Q = lay->query_len[s];
             if (Q == 0) continue;
@@ -391,59 +438,54 @@ static int32_t auto_splits(const pevlm_layout *lay, const pevlm_heads *h, const 
             const double units = (double)groups * ((Q / 128) * G + ceil_div(Q % 128 * G, 128));
             wgs += units * used;
             sum_us += units * used * (6 + tile_full * tiles);
+            least_load += units * (6 + tile_full * keys / kKeyTile) / slots;
             longest_tiles = std::max(longest_tiles, tiles);
+            shortest_tiles = std::min(shortest_tiles, tiles);
         }
         double us;
-        const double longest = 6 + tile_full * longest_tiles;
-        if (asking == 1) {
+        if (asking == 1 || shortest_tiles >= 0.75 * longest_tiles) {
             const double full = floor(wgs / slots), rest = wgs - full * slots;
-            us = full * longest;
+            us = full * (sum_us / wgs);
             if (rest > 0) us += 6 + longest_tiles * (rest <= cus ? tile_one : tile_some + (tile_full - tile_some) * (rest - cus) / cus);
-        } else {  // lengths differ: an even load plus half of the longest piece at the end
+        } else {
+            const double longest = 6 + tile_full * longest_tiles;
             us = std::max(longest, sum_us / slots + 0.5 * longest);
         }
-        if (n > 1) us += 4 + n * (partial_us + 0.04);
-        if (best_us == 0 || us < best_us) { best_us = us; best = n; }
+        return n > 1 ? us + 4 + n * (partial_us + 0.04) : us;
+    };
+    int32_t best = windowed ? 2 : 1;
+    double best_us = predict(best);
+    for (int32_t n = best + 1; n <= PEVLM_MAX_SPLITS; n += n < 20 ? 1 : (n < 32 ? 2 : 4)) {
+        if (least_load + 4 + n * (partial_us + 0.04) >= best_us) break;  // no larger count can be predicted shorter
+        const double us = predict(n);
+        if (us < best_us) { best_us = us; best = n; }
     }
+    if (asking > 1 && best != full_rounds && best_us > 0.95 * predict(full_rounds)) best = full_rounds;
     return best;
 }
 
-// bytes of the (cos, sin) table of the fused query rotation: head_dim/2 pairs of floats per entry
-static size_t rope_table_bytes(int64_t entries, const pevlm_heads *h) { return align256((size_t)entries * h->head_dim * sizeof(float)); }
-
-struct QueryPlan {
-    int32_t num_splits, tile_rows;
-    int64_t n_items, total_q;
-    size_t off_items, off_qrow, off_ml, off_acc, off_rope, bytes;
-};
+static int32_t auto_splits(const pevlm_layout *lay, const pevlm_heads *h, const Restrict &sel = Restrict())
+{
+    const bool f32 = h->dtype == PEVLM_F32, windowed = sel.window_blocks != nullptr;
+    const int32_t rounds = splits_of_full_rounds(lay, h, 768, [&](int32_t rows) { return f32 ? 1 : (rows <= 32 ? 4 : (rows <= 64 ? 2 : 1)); });
+    int32_t n = f32 ? splits_of_full_rounds(lay, h, 256, [](int32_t) { return 2; })
+                    : predicted_splits(lay, h, sel, std::min(PEVLM_MAX_SPLITS, rounds + (windowed ? 1 : 0)));
+    const int64_t tiles = count_query_tiles(lay, tile_rows_of(h, true)), total_q = total_query_rows(lay);
+    while (n > rounds && carve_query(tiles, total_q, h, n).bytes > kFreeQueryBytes) --n;
+    return n;
+}
 
 // sel: the call's window if it is known; the workspace is sized without it, for any window
 static QueryPlan plan_query(const pevlm_layout *lay, const pevlm_heads *h, int32_t num_splits, bool fuse_rope = false,
                             bool windowed = false, const Restrict &sel = Restrict())
 {
-    QueryPlan p;
-    p.tile_rows = tile_rows_of(h, true);
-    p.num_splits = num_splits > 0 ? num_splits : auto_splits(lay, h);
+    int32_t n = num_splits > 0 ? num_splits : auto_splits(lay, h);
     // with a window the sink is a split of its own, the rest of the keys takes at least one more
     if (windowed) {
-        p.num_splits = std::min(PEVLM_MAX_SPLITS, std::max(2, p.num_splits + (num_splits > 0 ? 0 : 1)));
-        if (num_splits == 0 && sel.window_blocks) p.num_splits = std::min(p.num_splits, std::max(2, auto_splits(lay, h, sel)));
+        n = std::min(PEVLM_MAX_SPLITS, std::max(2, n + (num_splits > 0 ? 0 : 1)));
+        if (num_splits == 0 && sel.window_blocks) n = std::min(n, std::max(2, auto_splits(lay, h, sel)));
     }
-    p.total_q = total_query_rows(lay);
-    p.n_items = count_query_tiles(lay, p.tile_rows) * p.num_splits;
-    size_t off = 0;
-    p.off_items = off;
-    off += align256((size_t)p.n_items * sizeof(pevlm_work_item));
-    p.off_qrow = off;
-    off += align256((size_t)p.total_q * sizeof(int32_t));
-    p.off_ml = off;
-    off += align256((size_t)p.num_splits * p.total_q * h->n_q_heads * 2 * sizeof(float));
-    p.off_acc = off;
-    off += align256((size_t)p.num_splits * p.total_q * h->n_q_heads * h->head_dim * sizeof(float));
-    p.off_rope = off;
-    if (fuse_rope) off += rope_table_bytes(p.total_q, h);  // one entry per compact question row
-    p.bytes = off;
-    return p;
+    return carve_query(count_query_tiles(lay, tile_rows_of(h, true)), total_query_rows(lay), h, n, fuse_rope);
 }
 
 // ------------------------------------------------------------------------------------------

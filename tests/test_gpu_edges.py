@@ -242,3 +242,15 @@ def test_a_row_does_not_depend_on_the_rows_beside_it(Hq, Hkv, D, extra):
     results["folded"] = result(lambda out, lse: P.pevlm_block_prefill_attn_rope(raw, k, v, out, lay, heads, w.rope_base, k_is_rotated=True, lse=lse))
     for name, (out, lse) in results.items():
         assert torch.equal(out, results["classic"][0]) and torch.equal(lse, results["classic"][1]), name
+
+
+@pytest.mark.parametrize("seqs", [[(256, 1024, 256 * f, 64) for f in (33, 97, 161, 255)], [(256, 1024, 65536, 128)] * 2])
+def test_static_call_takes_batches_with_the_librarys_split_count(seqs):
+    """Batches whose partials nearly fill the built-in array: accepted, and the bits of the call with a workspace."""
+    lay, heads = P.Layout.from_seqs(seqs), P.Heads(28, 4, 128, "bf16")
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    q, k, v = (torch.randn(lay.total_tokens, h, 128, device=DEV, dtype=torch.bfloat16, generator=gen) for h in (28, 4, 4))
+    outs = [torch.zeros_like(q), torch.zeros_like(q)]
+    P.pevlm_query_attn(q, k, v, outs[0], lay, heads)
+    P.pevlm_query_attn_static(q, k, v, outs[1], lay, heads)
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16)) and outs[0].any()

@@ -438,3 +438,56 @@ def test_host_arrays_take_what_numpy_takes(values):
 
     owner, array = _i32_array(values)
     assert [array[i] for i in range(2)] == [int(v) for v in values]
+
+
+def _splits_of_full_rounds(seqs, Hq, Hkv, dtype, cus=256):
+    """Full rounds of two workgroups per compute unit with at least 768 keys a split: the most partials that the library's own
+    choice may take, unless they fit the built-in scratch array."""
+    tile, G = (128 if dtype == "bf16" else 16), Hq // Hkv
+    asking = [s for s in seqs if s[3]]
+    units = 0
+    for _s, _b, _c, q in asking:
+        for r0 in range(0, q, tile):
+            rows = min(tile, q - r0)
+            together = 1 if dtype == "f32" or G == 1 else 4 if rows <= 32 else 2 if rows <= 64 else 1
+            units += Hkv * -(-G // together)
+    lens = [s + c + q for s, _b, c, q in asking]
+    want = max(1, 2 * cus // units)
+    if want * units * 4 < 2 * cus * 3 or 2 * min(lens) < max(lens):
+        want = 4 * cus // units
+    return max(1, min(want, max(lens) // 768, 64))
+
+
+STATIC_SCRATCH = 64 << 20
+
+
+@pytest.mark.parametrize("Hq,Hkv,seqs", [
+    (28, 4, [(256, 1024, 256 * f, 64) for f in (33, 97, 161, 255)]),
+    (28, 4, [(256, 1024, 65536, 128)] * 2),
+    (28, 4, [(256, 1024, 65536, 64)] * 4),
+    (64, 8, [(256, 1024, 100000, 300)]),
+    (40, 8, [(256, 1024, 8192, 100)] * 32),
+])
+def test_the_librarys_split_count_fits_the_static_array_where_full_rounds_do(Hq, Hkv, seqs):
+    lay, heads = P.Layout.from_seqs(seqs), P.Heads(Hq, Hkv, 128, "bf16")
+    rounds = P.pevlm_query_workspace_bytes(lay, heads, _splits_of_full_rounds(seqs, Hq, Hkv, "bf16")) - 256
+    assert P.pevlm_query_workspace_bytes(lay, heads) - 256 <= max(STATIC_SCRATCH, rounds)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_workspace_of_the_librarys_split_count_over_many_layouts(dtype):
+    rng = np.random.default_rng(5)
+    grown = 0
+    for _ in range(1500):
+        Hkv = int(rng.choice([1, 2, 4, 8]))
+        Hq = Hkv * int(rng.choice([1, 2, 3, 7, 8]))
+        seqs = [(int(rng.integers(0, 600)), 1024, int(2 ** rng.uniform(7, 17)), int(rng.choice([0, 1, rng.integers(2, 400)])))
+                for _ in range(int(rng.choice([1, 2, 3, 5, 17, 60])))]
+        if not any(q for *_, q in seqs):
+            continue
+        lay, heads = P.Layout.from_seqs(seqs), P.Heads(Hq, Hkv, int(rng.choice([64, 128])), dtype)
+        rounds = P.pevlm_query_workspace_bytes(lay, heads, _splits_of_full_rounds(seqs, Hq, Hkv, dtype))
+        chosen = P.pevlm_query_workspace_bytes(lay, heads)
+        assert chosen - 256 <= max(STATIC_SCRATCH, rounds - 256), (seqs, Hq, Hkv)
+        grown += chosen > rounds
+    assert grown > 50  # the bound is not all that decides
