@@ -94,7 +94,13 @@ hipError_t launch_build_query_items(const SeqTable &tab, int32_t tile_rows, int3
 // groups of them take the splits in turn, four in flight per lane.  Bound by reading the partials once
 // (33 MB for 128 rows x 28 heads x 18 splits: 6.5 us at the copy rate); a thread that walks all splits of its
 // four outputs takes one round trip per split: 47 us for 20 rows x 28 heads x 64 splits.
+//
+// FEW splits leave most of such a wavefront idle: up to 8 of them D/4 lanes take a row, and a wavefront two or four rows.
+// us, wavefront per row against D/4 lanes: 1600 rows x 28 heads x 128, 2 splits 18.4 / 12.2, 8 splits 24.9 / 21.6;
+// 1600 x 14 x 64, 2 splits 10.8 / 5.0; 8 rows x 28 heads, 8 splits 3.7 / 4.1, 16 splits 4.0 / 4.7.
 // ------------------------------------------------------------------------------------------
+constexpr int32_t kFewSplits = 8;
+
 __device__ inline uint16_t f32_to_bf16_rne(float f)
 {
     uint32_t u = __float_as_uint(f);
@@ -102,30 +108,31 @@ __device__ inline uint16_t f32_to_bf16_rne(float f)
     return (uint16_t)(u >> 16);
 }
 
-template <int D>
+template <int D, bool FEW>
 __global__ __launch_bounds__(256) void merge_kernel(MergeParams p)
 {
-    constexpr int LPR = D / 4, NSUB = 64 / LPR, UNROLL = 4;
-    const int32_t lane = threadIdx.x & 63;
-    const int64_t unit = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // (compact row, head)
+    constexpr int LPR = D / 4, UNIT = FEW ? LPR : 64, NSUB = UNIT / LPR, UNROLL = 4;
+    const int32_t lane = threadIdx.x & 63, split = lane % UNIT, first_lane = lane - split;
     const int64_t n_units = (int64_t)p.total_q_rows * p.n_q_heads;
+    int64_t unit = ((int64_t)blockIdx.x * 256 + threadIdx.x) / UNIT;  // (compact row, head)
+    if (!FEW) unit = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (unit >= n_units) return;
     float m = -INFINITY, l = 0.f;
-    if (lane < p.num_splits) {
-        const float2 ml = *reinterpret_cast<const float2 *>(p.part_ml + ((int64_t)lane * n_units + unit) * 2);
+    if (split < p.num_splits) {
+        const float2 ml = *reinterpret_cast<const float2 *>(p.part_ml + ((int64_t)split * n_units + unit) * 2);
         m = ml.x;
         l = ml.y;
     }
     float M = m;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
-    const uint64_t seen = __ballot(m != -INFINITY);  // splits that saw a key of the row
+    for (int o = UNIT / 2; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
+    const uint64_t seen = __ballot(m != -INFINITY) >> first_lane;  // splits that saw a key of the row
     const float w = m == -INFINITY ? 0.f : expf((m - M) * p.scale);
     float denom = w * l;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) denom += __shfl_xor(denom, o);
+    for (int o = UNIT / 2; o > 0; o >>= 1) denom += __shfl_xor(denom, o);
 
-    const int32_t sub = lane / LPR, d4 = (lane % LPR) * 4;
+    const int32_t sub = split / LPR, d4 = (lane % LPR) * 4;
     const float *acc_row = p.part_acc + unit * D + d4;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int32_t s0 = 0; s0 < p.num_splits; s0 += NSUB * UNROLL) {
@@ -133,8 +140,8 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeParams p)
         float ws[UNROLL];
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
-            const int32_t s = s0 + u * NSUB + sub;  // below 64: the last step of 64 splits ends there
-            ws[u] = __shfl(w, s);
+            const int32_t s = s0 + u * NSUB + sub;  // below UNIT: the last step of UNIT splits ends there
+            ws[u] = __shfl(w, first_lane + s);
             a[u] = make_float4(0.f, 0.f, 0.f, 0.f);
             // a weight too small for fp32 is no reason to leave a split out: its values may be infinite
             if (seen >> s & 1) a[u] = *reinterpret_cast<const float4 *>(acc_row + s * n_units * D);
@@ -145,7 +152,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeParams p)
         }
     }
 #pragma unroll
-    for (int o = LPR; o < 64; o <<= 1) {
+    for (int o = LPR; o < UNIT; o <<= 1) {
         acc.x += __shfl_xor(acc.x, o); acc.y += __shfl_xor(acc.y, o);
         acc.z += __shfl_xor(acc.z, o); acc.w += __shfl_xor(acc.w, o);
     }
@@ -170,9 +177,12 @@ hipError_t launch_merge(const MergeParams &p, hipStream_t stream)
 {
     static_assert(PEVLM_MAX_SPLITS == 64, "one lane per split, steps of 8 or 16 splits");
     const int64_t units = (int64_t)p.total_q_rows * p.n_q_heads;
-    const dim3 grid((uint32_t)((units + 3) / 4)), block(256);
-    if (p.head_dim == 128) hipLaunchKernelGGL(merge_kernel<128>, grid, block, 0, stream, p);
-    else hipLaunchKernelGGL(merge_kernel<64>, grid, block, 0, stream, p);
+    const bool few = p.num_splits <= kFewSplits;
+    const int64_t lanes = units * (few ? p.head_dim / 4 : 64);
+    const dim3 grid((uint32_t)((lanes + 255) / 256)), block(256);
+    const auto kernel = p.head_dim == 128 ? (few ? merge_kernel<128, true> : merge_kernel<128, false>)
+                                          : (few ? merge_kernel<64, true> : merge_kernel<64, false>);
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, p);
     return hipGetLastError();
 }
 
