@@ -25,7 +25,9 @@
 //
 // Variants: PARTIAL writes un-normalised fp32 partials (question attention, merged afterwards);
 // ROPEQ rotates the query rows in registers from a (cos, sin) table instead of expecting rotated
-// queries.
+// queries; MAPPED takes a head map other than the default one.
+#include <type_traits>
+
 #include "attn_bf16_tile.h"
 #include "rope_math.h"
 
@@ -39,22 +41,33 @@ namespace pevlm {
 // the number of rows (1 question row x 7 heads: one wavefront instead of seven with one column each; K and V are
 // then read once per KV head), and the pairs of a workgroup lie within 128/G + 1 rows of each other: it stages
 // the tiles up to its own last row, not up to the item's.  `logical` indexes (KV head group, item,
-// workgroup of the item); where heads are not in equal groups every head is a group of its own.  Against one head
+// workgroup of the item).  Where heads are not in equal groups every head is a group of its own, and the groups run
+// inside the item, so that heads on one KV head find its keys in L2 (64/8 heads on a map, 12 K tokens in blocks of
+// 152: 242 us, 320 with the items inside the head).  Against one head
 // per wavefront group (two or four heads together for items of <= 64 or <= 32 rows): question of 20 rows x 28/4
 // heads over 65 K keys 60 -> 45 us at the same 64 splits, block prefill of 16 K tokens 210 -> 208 us, 100 K
 // tokens in blocks of 3136 with the rotation folded in 3.40 -> 3.28 ms.
-template <int D, bool PARTIAL, bool ROPEQ>
+template <int D, bool PARTIAL, bool ROPEQ, bool MAPPED>
 __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, const HeadGroups &hg, uint8_t *lds_k, uint8_t *lds_v)
 {
     using C = TileCfg<D>;
     constexpr int KT = C::KT, ROWB = C::ROWB, CH = C::CH, NLD = C::NLD, KSTEPS = C::KSTEPS, DBLK = C::DBLK;
     constexpr int VSW = C::VSW, TILEB = C::TILEB, RPI = C::RPI;
-    const int32_t inner = logical % hg.wgs_per_item;
-    const int32_t rest = logical / hg.wgs_per_item;
+    int32_t inner, rest, group;
+    if (!MAPPED || hg.groups_inside == 1) {
+        inner = logical % hg.wgs_per_item;
+        rest = logical / hg.wgs_per_item;
+        group = rest / p.n_items;
+    } else {
+        inner = logical % (hg.wgs_per_item * hg.groups_inside);
+        rest = logical / (hg.wgs_per_item * hg.groups_inside);
+        group = inner / hg.wgs_per_item;
+        inner %= hg.wgs_per_item;
+    }
     // last item first: within a context block the later tiles are the longer ones, and a launch that
     // ends on short items has a shorter tail
     const int32_t item_idx = p.n_items - 1 - rest % p.n_items;
-    const int32_t group = rest / p.n_items, G = hg.heads_per_group;
+    const int32_t G = hg.heads_per_group;
     pevlm_work_item it;
     if (p.inline_items.mode) {
         it = inline_item(p.inline_items, item_idx);
@@ -66,18 +79,21 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
     if (pair0 >= n_pairs) return;  // an item with fewer rows than the launch's longest
     // With the default head map (query head h on KV head h / G) the indices are plain arithmetic; the tables
     // live in kernel-argument memory and looking them up costs two dependent memory round trips before the
-    // first query row can be requested.
-    const int32_t g = hg.identity ? group : __builtin_amdgcn_readfirstlane((int32_t)p.heads.kv_of_q[p.heads.head_order[group * G]]);
+    // first query row can be requested.  Under another map of equal groups lane j holds the group's j-th head.
+    const int32_t head0 = !MAPPED ? group * G : __builtin_amdgcn_readfirstlane((int32_t)p.heads.head_order[group * G]);
+    const int32_t g = !MAPPED ? group : __builtin_amdgcn_readfirstlane((int32_t)p.heads.kv_of_q[head0]);
     const int32_t Hq = p.n_q_heads, Hkv = p.n_kv_heads;
 
     const int32_t tid = threadIdx.x, lane = tid & 63;
     const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t l32 = lane & 31, g32 = lane >> 5;
     const uint16_t *Q = (const uint16_t *)p.q, *K = (const uint16_t *)p.k, *V = (const uint16_t *)p.v;
-    // pair -> (row of the item, query head)
-#define PEVLM_PAIR(v, row, head)                                                                  \
-    const int32_t row = div_by(v, hg.group_rcp);                                                  \
-    const int32_t head = hg.identity ? group * G + ((v) - row * G) : (int32_t)p.heads.head_order[group * G + ((v) - row * G)]
+    const bool listed = MAPPED && G > 1;  // otherwise the group's heads are head0, head0 + 1, ...
+    const int32_t head_base = listed ? 0 : head0;
+    // the j-th head of the group, relative to head_base; the list is fetched again for the output rows
+    const auto head_list = [&](int32_t ln) { return listed ? (int32_t)p.heads.head_order[group * G + (ln < G ? ln : 0)] : 0; };
+    const auto head_of = [&](int32_t list, int32_t j) { return listed ? __shfl(list, j) : j; };
+    const int32_t heads = head_list(lane);
 
     LaneOff L;
     L.g32 = g32;
@@ -90,9 +106,8 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
     // ---- this lane's query row and head, and the rows of the wavefront and of the workgroup
     const int32_t wave_pair0 = pair0 + wave * 32;
     const bool wave_active = wave_pair0 < n_pairs;
-    const bool pair_valid = wave_pair0 + l32 < n_pairs;
-    const int32_t my_pair = pair_valid ? wave_pair0 + l32 : n_pairs - 1;
-    PEVLM_PAIR(my_pair, row_in_item, my_head);
+    const int32_t my_pair = wave_pair0 + l32 < n_pairs ? wave_pair0 + l32 : n_pairs - 1;
+    const int32_t row_in_item = div_by(my_pair, hg.group_rcp);
     const int32_t my_row = it.q_start + row_in_item;
     const int32_t wr_lo = it.q_start + div_by(wave_active ? wave_pair0 : n_pairs - 1, hg.group_rcp);
     const int32_t wr_hi = it.q_start + div_by(wave_pair0 + 31 < n_pairs ? wave_pair0 + 31 : n_pairs - 1, hg.group_rcp);
@@ -224,47 +239,45 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
     }
     // Walk of a lane over the wavefront's pairs, RPI at a time: byte offset of the pair's row from the item's first
     // one, advanced without a division (an integer product costs as much as four additions).
-    const uint32_t row_bytes = (uint32_t)(Hq * ROWB), step_bytes = (uint32_t)hg.step_rows * row_bytes + (uint32_t)(hg.step_heads * ROWB);
-    const int64_t item_off = ((int64_t)it.q_start * Hq + group * G) * D;  // elements; with the default head map
+    const uint32_t row_bytes = (uint32_t)(Hq * ROWB), step_bytes = (uint32_t)hg.step_rows * row_bytes;
+    const int64_t item_off = ((int64_t)it.q_start * Hq + head_base) * D;  // elements
 #define PEVLM_PAIR_WALK_BEGIN()                                              \
     int32_t walk_v = wave_pair0 + lane / CH, walk_h;                          \
-    uint32_t walk_off;                                                        \
+    uint32_t walk_row;                                                        \
     {                                                                         \
         const int32_t r_ = div_by(walk_v, hg.group_rcp);                      \
         walk_h = walk_v - r_ * G;                                             \
-        walk_off = (uint32_t)r_ * row_bytes + (uint32_t)(walk_h * ROWB);      \
+        walk_row = (uint32_t)r_ * row_bytes;                                  \
     }
+    // LISTED is settled outside the loops over rows: a branch in each step keeps their reads and stores from running together
+#define PEVLM_PAIR_WALK_OFF(LISTED, list) (walk_row + (uint32_t)((LISTED ? __shfl(list, walk_h) : walk_h) * ROWB))
 #define PEVLM_PAIR_WALK_NEXT()                                               \
     do {                                                                      \
         walk_v += RPI;                                                        \
         walk_h += hg.step_heads;                                              \
-        walk_off += step_bytes;                                               \
+        walk_row += step_bytes;                                               \
         if (walk_h >= G) {                                                    \
             walk_h -= G;                                                      \
-            walk_off += row_bytes - (uint32_t)(G * ROWB);                     \
+            walk_row += row_bytes;                                            \
         }                                                                     \
     } while (0)
-    if (hg.identity) {
+    {
         const int32_t last_row = div_by(n_pairs - 1, hg.group_rcp);
-        const uint32_t last_off = (uint32_t)last_row * row_bytes + (uint32_t)((n_pairs - 1 - last_row * G) * ROWB);
+        const uint32_t last_off = (uint32_t)last_row * row_bytes + (uint32_t)(head_of(heads, n_pairs - 1 - last_row * G) * ROWB);
         const uint16_t *qbase = uniform_ptr(Q + item_off);
-        PEVLM_PAIR_WALK_BEGIN();
+        const auto rows_in = [&](auto listed_tag) {
+            PEVLM_PAIR_WALK_BEGIN();
 #pragma unroll
-        for (int j = 0; j < WSLICE / 1024; ++j) {
-            const int32_t rl = j * RPI + lane / CH;
-            const uint32_t off = walk_off < last_off ? walk_off : last_off;  // pairs past the item repeat its last one
-            load_lds_16_base(qbase, off + (uint32_t)(((lane % CH) ^ (rl & (CH - 1))) << 4), wave_slice_addr + j * 1024);
-            PEVLM_PAIR_WALK_NEXT();
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < WSLICE / 1024; ++j) {
-            const int32_t rl = j * RPI + lane / CH, cpos = lane % CH;
-            const int32_t v = wave_pair0 + rl < n_pairs ? wave_pair0 + rl : n_pairs - 1;
-            PEVLM_PAIR(v, r, h);
-            load_lds_16(Q + ((int64_t)(it.q_start + r) * Hq + h) * D + ((cpos ^ (rl & (CH - 1))) << 3),
-                        wave_slice_addr + j * 1024);
-        }
+            for (int j = 0; j < WSLICE / 1024; ++j) {
+                const int32_t rl = j * RPI + lane / CH;
+                const uint32_t walk_off = PEVLM_PAIR_WALK_OFF(decltype(listed_tag)::value, heads);
+                const uint32_t off = walk_v < n_pairs ? walk_off : last_off;  // pairs past the item repeat its last one
+                load_lds_16_base(qbase, off + (uint32_t)(((lane % CH) ^ (rl & (CH - 1))) << 4), wave_slice_addr + j * 1024);
+                PEVLM_PAIR_WALK_NEXT();
+            }
+        };
+        if (MAPPED && listed) rows_in(std::true_type());
+        else rows_in(std::false_type());
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
     asm volatile("" ::: "memory");
@@ -414,11 +427,19 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
         __syncthreads();
     }
 
-    // ---- epilogue ----
+    // ---- epilogue: the lane's pair once more, from a lane number that the compiler takes for another (a register held
+    // through the tile loop costs 64-wide heads the third wavefront on a SIMD)
+    int32_t out_lane = lane;
+    asm volatile("" : "+v"(out_lane));
+    const int32_t heads_again = head_list(out_lane);
+    const int32_t out_pair = wave_pair0 + (out_lane & 31);
+    const bool pair_valid = out_pair < n_pairs;
+    const int32_t out_row = div_by(pair_valid ? out_pair : n_pairs - 1, hg.group_rcp);
+    const int32_t out_head = head_base + head_of(heads_again, (pair_valid ? out_pair : n_pairs - 1) - out_row * G);
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     if (PARTIAL) {
         if (!pair_valid) return;
-        const int64_t slot = ((int64_t)it.reserved + row_in_item) * Hq + my_head;
+        const int64_t slot = ((int64_t)it.reserved + out_row) * Hq + out_head;
         float *acc = p.part_acc + slot * D;
 #pragma unroll
         for (int b = 0; b < DBLK; ++b)
@@ -455,33 +476,28 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
         uint16_t *const obase = (uint16_t *)p.out;
         // Rows leave as non-temporal stores: nothing here reads them again, and the lines stay free for keys and values
         // (16 K tokens, rotation and question included: 279 -> 272 us; dense 16 K 2139 -> 2122 us).
-        if (hg.identity) {
-            uint8_t *const ob = (uint8_t *)(obase + item_off);
+        uint8_t *const ob = (uint8_t *)(obase + item_off);
+        const auto rows_out = [&](auto listed_tag) {
             PEVLM_PAIR_WALK_BEGIN();
 #pragma unroll
             for (int j = 0; j < WSLICE / 1024; ++j) {
                 const int32_t rl = j * RPI + lane / CH, cpos = lane % CH;
                 const uint4 val = *reinterpret_cast<const uint4 *>(oslice + rl * ROWB + ((cpos ^ (rl & (CH - 1))) << 4));
+                const uint32_t walk_off = PEVLM_PAIR_WALK_OFF(decltype(listed_tag)::value, heads_again);
                 if (walk_v < n_pairs) __builtin_nontemporal_store(__builtin_bit_cast(u32x4, val), reinterpret_cast<u32x4 *>(ob + (walk_off + (uint32_t)(cpos << 4))));
                 PEVLM_PAIR_WALK_NEXT();
             }
-        } else {
-#pragma unroll
-            for (int j = 0; j < WSLICE / 1024; ++j) {
-                const int32_t rl = j * RPI + lane / CH, cpos = lane % CH, v = wave_pair0 + rl;
-                const uint4 val = *reinterpret_cast<const uint4 *>(oslice + rl * ROWB + ((cpos ^ (rl & (CH - 1))) << 4));
-                PEVLM_PAIR(v, r, h);
-                if (v < n_pairs) *reinterpret_cast<uint4 *>(obase + ((int64_t)(it.q_start + r) * Hq + h) * D + cpos * 8) = val;
-            }
-        }
-        if (p.lse && g32 == 0 && pair_valid) p.lse[(int64_t)my_row * Hq + my_head] = (m_ref + __log2f(l_tot)) * 0.69314718056f;
+        };
+        if (MAPPED && listed) rows_out(std::true_type());
+        else rows_out(std::false_type());
+        if (p.lse && g32 == 0 && pair_valid) p.lse[(int64_t)(it.q_start + out_row) * Hq + out_head] = (m_ref + __log2f(l_tot)) * 0.69314718056f;
     }
 }
 
 // One workgroup per logical id.  Consecutive workgroup ids land on different XCDs (8 of them, each
 // with its own L2); every XCD gets one contiguous run of logical ids so that the heads of a GQA
 // group working on the same context block share that XCD's L2.
-template <int D, bool PARTIAL, bool ROPEQ>
+template <int D, bool PARTIAL, bool ROPEQ, bool MAPPED>
 __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnParams p, int32_t n_logical, HeadGroups hg)
 {
     __shared__ __attribute__((aligned(1024))) uint8_t lds_k[2 * TileCfg<D>::TILEB];
@@ -489,29 +505,34 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnParams p, int32_t
     const int32_t per_xcd = gridDim.x >> 3;
     const int32_t logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (logical >= n_logical) return;
-    attn_item<D, PARTIAL, ROPEQ>(p, logical, hg, lds_k, lds_v);
+    attn_item<D, PARTIAL, ROPEQ, MAPPED>(p, logical, hg, lds_k, lds_v);
 }
 
 hipError_t launch_attn_bf16(const AttnParams &p, int32_t D, bool partial, hipStream_t stream)
 {
-    // heads that share a KV head are taken together when the groups are equal
+    // heads that share a KV head are taken together when the groups are equal (and a wavefront's lanes can hold the group)
     const int32_t G = p.n_q_heads / p.n_kv_heads;
     bool uniform = true, identity = true;
     for (int32_t i = 0; i < p.n_q_heads; ++i) {
         if (p.heads.kv_of_q[p.heads.head_order[i]] != i / G) uniform = false;
         if (p.heads.head_order[i] != i || p.heads.kv_of_q[i] != i / G) identity = false;
     }
+    const bool together = uniform && (identity || G <= 64);
     HeadGroups hg;
-    hg.heads_per_group = uniform ? G : 1;
+    hg.heads_per_group = together ? G : 1;
     hg.group_rcp = reciprocal_of(hg.heads_per_group);
-    hg.identity = uniform && identity;
+    hg.groups_inside = together ? 1 : p.n_q_heads;
     const int32_t rows_per_load = 512 / D;  // rows one wavefront-wide 16-byte-per-lane load covers
     hg.step_rows = rows_per_load / hg.heads_per_group;
     hg.step_heads = rows_per_load % hg.heads_per_group;
     hg.wgs_per_item = ceil_div(p.max_item_rows * hg.heads_per_group, 128);
-    const int32_t n_logical = p.n_items * hg.wgs_per_item * (uniform ? p.n_kv_heads : p.n_q_heads);
+    const int32_t n_logical = p.n_items * hg.wgs_per_item * (together ? p.n_kv_heads : p.n_q_heads);
     const dim3 grid((n_logical + 7) / 8 * 8), block(256);
-#define PEVLM_ATTN_LAUNCH(DD, PP, RR) hipLaunchKernelGGL((attn_bf16_kernel<DD, PP, RR>), grid, block, 0, stream, p, n_logical, hg)
+#define PEVLM_ATTN_LAUNCH(DD, PP, RR)                                                                             \
+    do {                                                                                                          \
+        if (identity) hipLaunchKernelGGL((attn_bf16_kernel<DD, PP, RR, false>), grid, block, 0, stream, p, n_logical, hg); \
+        else hipLaunchKernelGGL((attn_bf16_kernel<DD, PP, RR, true>), grid, block, 0, stream, p, n_logical, hg);           \
+    } while (0)
     const bool rope = p.rope_tab != nullptr;
     if (D == 128) {
         if (partial) { if (rope) PEVLM_ATTN_LAUNCH(128, true, true); else PEVLM_ATTN_LAUNCH(128, true, false); }

@@ -394,8 +394,8 @@ struct AttnParams {
 struct HeadGroups {
     int32_t heads_per_group;  // query heads taken together (those of a KV head, or 1 where the groups differ)
     uint32_t group_rcp;       // for / heads_per_group
-    int32_t identity;         // query head h is on KV head h / heads_per_group
     int32_t wgs_per_item;     // workgroups of 128 (row, head) pairs per item and group
+    int32_t groups_inside;    // groups that an item's workgroups run over before the next item (1: the next item comes first)
     int32_t step_rows, step_heads;  // the pairs that one wavefront-wide load covers, as rows and heads
 };
 

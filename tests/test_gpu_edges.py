@@ -254,3 +254,28 @@ def test_static_call_takes_batches_with_the_librarys_split_count(seqs):
     P.pevlm_query_attn(q, k, v, outs[0], lay, heads)
     P.pevlm_query_attn_static(q, k, v, outs[1], lay, heads)
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16)) and outs[0].any()
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(128, 2), (132, 2), (9, 3), (12, 4)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_head_maps_against_the_default_map(Hq, Hkv, D):
+    """Query heads dealt out over the KV heads in turn: groups that a wavefront's lanes can hold (up to 64 heads) and a larger
+    one; the same bits as the default map on reordered heads, every call."""
+    lay = P.Layout.from_seqs([(9, 70, 150, 21), (0, 64, 40, 3)])
+    T = lay.total_tokens
+    gen = torch.Generator(device=DEV).manual_seed(4)
+    q, k, v = (torch.randn(T, h, D, device=DEV, dtype=torch.bfloat16, generator=gen) for h in (Hq, Hkv, Hkv))
+    mapped = P.Heads(Hq, Hkv, D, "bf16", [i % Hkv for i in range(Hq)])
+    order = sorted(range(Hq), key=lambda i: (i % Hkv, i))  # query heads by KV head
+    plain, q2 = P.Heads(Hq, Hkv, D, "bf16"), q[:, order].contiguous()
+    prev = P.pevlm_set_prefill_kernel("classic")
+    try:
+        res = []
+        for heads, x in ((mapped, q), (plain, q2)):
+            out, lse = torch.zeros_like(x), torch.zeros(T, Hq, device=DEV)
+            P.pevlm_block_prefill_attn(x, k, v, out, lay, heads, lse=lse)
+            P.pevlm_query_attn(x, k, v, out, lay, heads, num_splits=3, lse=lse)
+            res.append((out.view(torch.int16), lse.view(torch.int32)))
+    finally:
+        P.pevlm_set_prefill_kernel(prev)
+    assert torch.equal(res[0][0][:, order], res[1][0]) and torch.equal(res[0][1][:, order], res[1][1])
