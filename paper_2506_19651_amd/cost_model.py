@@ -27,21 +27,29 @@ def useful_flops(layout: Layout, heads: Heads):
 # workgroups of 4 wavefronts per compute unit, dispatched as slots free up):
 #     time * (2 * CUs) = US_PER_WORKGROUP * workgroups + US_PER_WORKGROUP_TILE * sum of key tiles.
 # The constants are fitted to measured runs on one MI355X (profiles/block_prefill_sweep.md); the
-# predictions stay within +-12 % of them (head_dim 128).
-STREAM_US_PER_ITEM = 3.48
-STREAM_US_PER_TILE = 1.778
-US_PER_WORKGROUP = 6.1
-US_PER_WORKGROUP_TILE = 1.865
+# predictions stay within 7 % of them.  The one-item kernel's at head_dim 128 come from 68 prompts of 4 K to
+# 40 K tokens that fill the chip at least twice (ratio to the measured time 1.02 +- 0.09).  64-wide heads run on the
+# one-item kernel only, unless the streaming kernel is forced, which the model does not cover.
+STREAM_US_PER_ITEM = 3.9
+STREAM_US_PER_TILE = 1.665
+US_PER_WORKGROUP = {128: 6.1, 64: 2.7}
+US_PER_WORKGROUP_TILE = {128: 1.865, 64: 1.065}
 _TILE_ROWS, _KEY_TILE, _PAIRS = 128, 64, 128
 
 
 def prefill_work(layout: Layout, heads: Heads):
     """(workgroups, workgroup key tiles) of the one-item-per-workgroup kernel, from the same host
     enumeration the library offers: 128 (row, query head) pairs of an item and KV head per workgroup (one
-    head at a time under a head map), which stages the tiles up to its own last row."""
+    head at a time where a head map's groups are unequal, or hold more than 64 heads), which stages the tiles up to
+    its own last row."""
     from .binding import pevlm_prefill_worklist_host
 
-    G = heads.n_q_heads // heads.n_kv_heads if heads.map is None else 1
+    G = heads.n_q_heads // heads.n_kv_heads
+    if heads.map is not None:
+        kv = [int(g) for g in heads.map]
+        equal = all(kv.count(g) == G for g in range(heads.n_kv_heads))
+        if not equal or (G > 64 and kv != sorted(kv)):
+            G = 1
     groups = heads.n_q_heads // G
     n_wg = n_tiles = 0
     for it in pevlm_prefill_worklist_host(layout, _TILE_ROWS):
@@ -89,7 +97,8 @@ def predict_block_prefill_ms(layout: Layout, heads: Heads, compute_units: int = 
         cnt, til = stream_work(layout, heads, compute_units)
         return float((STREAM_US_PER_ITEM * cnt + STREAM_US_PER_TILE * til).max()) * 1e-3
     n_wg, n_tiles = prefill_work(layout, heads)
-    return (US_PER_WORKGROUP * n_wg + US_PER_WORKGROUP_TILE * n_tiles) / (2 * compute_units) * 1e-3
+    d = heads.head_dim
+    return (US_PER_WORKGROUP[d] * n_wg + US_PER_WORKGROUP_TILE[d] * n_tiles) / (2 * compute_units) * 1e-3
 
 
 def choose_block_len(sink_len: int, ctx_len: int, query_len: int, heads: Heads, candidates, max_ms: float,

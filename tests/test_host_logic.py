@@ -491,3 +491,26 @@ def test_workspace_of_the_librarys_split_count_over_many_layouts(dtype):
         assert chosen - 256 <= max(STATIC_SCRATCH, rounds - 256), (seqs, Hq, Hkv)
         grown += chosen > rounds
     assert grown > 50  # the bound is not all that decides
+
+
+def test_time_model_of_64_wide_heads_and_of_head_maps():
+    """64-wide heads against the measured grid, on the constants of the kernel that runs them; under a map of equal
+    groups the kernel packs heads as under the default map, under one of unequal groups it takes them one by one."""
+    from paper_2506_19651_amd.cost_model import predict_block_prefill_ms, prefill_work
+    n = 0
+    for line in open(os.path.join(ROOT, "profiles", "block_prefill_sweep.md")):
+        f = line.split()
+        if len(f) != 7 or f[0] != "d64":
+            continue
+        S, B, C, Q = (int(x) for x in f[1:5])
+        pred = predict_block_prefill_ms(P.Layout.from_seqs([(S, B, C, Q)]), P.Heads(14, 2, 64, "bf16"))
+        assert f[6] == "0" and abs(pred / float(f[5]) - 1.0) <= 0.12, (line, pred)
+        n += 1
+    assert n >= 10
+    lay = P.Layout.from_seqs([(100, 333, 5000, 10)])
+    work = lambda *a: prefill_work(lay, P.Heads(*a))
+    assert work(9, 3, 128, "bf16", [0, 1, 2] * 3) == work(9, 3, 128, "bf16")
+    one_by_one = work(9, 9, 128, "bf16")
+    assert work(9, 3, 128, "bf16", [0, 0, 0, 0, 1, 1, 1, 2, 2]) == one_by_one != work(9, 3, 128, "bf16")
+    assert work(132, 2, 64, "bf16", [0, 1] * 66) == work(132, 132, 64, "bf16")
+    assert work(132, 2, 64, "bf16", [0] * 66 + [1] * 66) == work(132, 2, 64, "bf16")
