@@ -464,21 +464,20 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(AttnParams p, int32_t 
     } else {
         it = p.items[idx];
     }
-    // Each kind of workgroup has a call of its own (104 tokens x 2 heads, RoPE included: 18.5 us, 19.2 with the two single ones joined).
-    int32_t left, g = group, h[2];
+    // Each kind of workgroup keeps its own branch to the end: with the rows that are left joined behind both, the compiler
+    // makes the one-head kernel slower (842 tokens x 4/1 heads x 128: 24 us, 13 as here).
     if (pairs) {
         const int32_t G = p.n_q_heads / p.n_kv_heads;
-        h[0] = p.heads.head_order[group * G + 2 * u];
-        h[1] = p.heads.head_order[group * G + (2 * u + 1 < G ? 2 * u + 1 : 2 * u)];
+        const int32_t h[2] = {p.heads.head_order[group * G + 2 * u], p.heads.head_order[group * G + (2 * u + 1 < G ? 2 * u + 1 : 2 * u)]};
+        int32_t left;
         if (2 * u + 1 < G) left = attn_f32_pair<D, PARTIAL>(p, it, h, group, sh);
         else left = attn_f32_single<D, PARTIAL>(p, it, h[0], group, sh);
+        for (int32_t n = 0; left >> n; ++n)
+            if (left >> n & 1) attn_f32_rows<D, PARTIAL>(p, it, n ? h[1] : h[0], group, sh);
     } else {
-        h[0] = h[1] = p.heads.head_order[group * units + u];
-        g = p.heads.kv_of_q[h[0]];
-        left = attn_f32_single<D, PARTIAL>(p, it, h[0], g, sh);
+        const int32_t h = p.heads.head_order[group * units + u], g = p.heads.kv_of_q[h];
+        if (attn_f32_single<D, PARTIAL>(p, it, h, g, sh)) attn_f32_rows<D, PARTIAL>(p, it, h, g, sh);
     }
-    for (int32_t n = 0; left >> n; ++n)
-        if (left >> n & 1) attn_f32_rows<D, PARTIAL>(p, it, n ? h[1] : h[0], g, sh);
 }
 
 hipError_t launch_attn_f32(const AttnParams &p, int32_t D, bool partial, int32_t compute_units, hipStream_t stream)
