@@ -196,12 +196,13 @@ __global__ __launch_bounds__(256) void fp8_setup_kernel(SeqTable tab, Fp8TileBas
                                                         int32_t list_blocks, Fp8Question qu)
 {
     if ((int32_t)blockIdx.x >= list_blocks) {
-        const int64_t t = (int64_t)((int32_t)blockIdx.x - list_blocks) * 256 + threadIdx.x, unit = t / (D / 16);
-        const int32_t r = (int32_t)(unit / qu.n_q_heads), head = (int32_t)(unit % qu.n_q_heads);
+        // 32 bits hold a (row, head) number: 2^32 rows of one head would be a tensor of 512 GB and more
+        const uint32_t block = (uint32_t)((int32_t)blockIdx.x - list_blocks), unit = block * (256 / (D / 16)) + threadIdx.x / (D / 16);
+        const int32_t r = (int32_t)(unit / (uint32_t)qu.n_q_heads), head = (int32_t)(unit - (uint32_t)r * (uint32_t)qu.n_q_heads);
         int32_t s = 0;
         while (s + 1 < tab.num_seqs && r >= tab.qrow_base[s + 1]) ++s;
         const int64_t row = tab.start[s] + tab.sink[s] + tab.ctx[s] + r - tab.qrow_base[s];
-        quantise_q_part<D>((const uint16_t *)qu.q, row * qu.n_q_heads + head, r < qu.n_rows, (int32_t)(t % (D / 16)), qu.factor, qu.codes, qu.scales);
+        quantise_q_part<D>((const uint16_t *)qu.q, row * qu.n_q_heads + head, r < qu.n_rows, (int32_t)(threadIdx.x % (D / 16)), qu.factor, qu.codes, qu.scales);
         return;
     }
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
