@@ -49,7 +49,7 @@ typedef enum {
 } pevlm_status;
 
 typedef enum {
-    PEVLM_F32 = 0,  /* fp32 storage and arithmetic (plain FMA kernels; the numerical anchor)       */
+    PEVLM_F32 = 0,  /* fp32 storage and arithmetic (fp32 matrix cores; the numerical anchor)       */
     PEVLM_BF16 = 1  /* bf16 storage, bf16 MFMA with fp32 accumulation and fp32 softmax             */
 } pevlm_dtype;
 
@@ -120,7 +120,8 @@ pevlm_status pevlm_block_prefill_attn(const void *q, const void *k, const void *
  * (sink, all context blocks, earlier question tokens).  The key range is cut into num_splits
  * parts (0 = chosen from the layout; 1..PEVLM_MAX_SPLITS otherwise) that are processed by
  * different workgroups into fp32 partials (max, sum, weighted values) in the workspace and then
- * merged with the log-sum-exp identity.  Writes question rows of `out` (and `lse`) only.
+ * merged with the log-sum-exp identity (one part is written directly).  Writes question rows of
+ * `out` (and `lse`) only.
  */
 #define PEVLM_MAX_SPLITS 64
 size_t pevlm_query_workspace_bytes(const pevlm_layout *layout, const pevlm_heads *heads, int32_t num_splits);
@@ -250,8 +251,8 @@ typedef struct {
 /* 1 if pevlm_block_prefill_attn runs the streaming kernel for this layout and head descriptor on the
  * current device, else 0: then the one-item-per-workgroup kernel and the pevlm_work_item list are
  * used.  The streaming kernel needs bf16 tensors, every KV head serving the same number of query
- * heads, and fewer than 2 GiB per K (or V) tensor; left to itself the library takes it when the list
- * holds at least 12 stream items per compute unit and no sink or block is longer than 16384 rows. */
+ * heads, and fewer than 2 GiB per K (or V) tensor; left to itself the library takes it for 128-wide heads
+ * when the list holds at least 12 stream items per compute unit and no sink or block is longer than 16384 rows. */
 int32_t pevlm_prefill_uses_stream_kernel(const pevlm_layout *layout, const pevlm_heads *heads);
 /* Process-wide choice of that kernel, for timing comparisons and tests: 0 = per call as described
  * above (the default; the environment variable PEVLM_PREFILL_KERNEL=classic|stream sets the start

@@ -344,10 +344,10 @@ __global__ __launch_bounds__(256) void quantise_kv_tiles_kernel(const uint16_t *
 }
 
 // ---------------------------------------------------------------- attend
-// Three wavefronts per SIMD (the second launch bound): it keeps the kernel within 168 registers, all of
-// them ordinary vector registers -- given more, the compiler parks the MFMA results in accumulation
-// registers and copies them back and forth around every softmax step (measured 24 % slower) -- and
-// lets the vector work of one wavefront run under the MFMAs of the others.
+// Three wavefronts per SIMD (the second launch bound): it keeps the kernel within 168 registers (head_dim 128 uses
+// them all and, where it quantises Q, spills two), all of them ordinary vector registers -- given more, the
+// compiler parks the MFMA results in accumulation registers and copies them back and forth around every softmax
+// step (measured 24 % slower) -- and lets the vector work of one wavefront run under the MFMAs of the others.
 //
 // QUANTISE_Q (a call of both stages): every row of Q is used by exactly one wavefront, which quantises it on the
 // way in and leaves codes and scales in the workspace for later ATTEND calls.  The separate kernel reads 472 MB
