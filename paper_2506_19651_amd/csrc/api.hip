@@ -208,15 +208,15 @@ static int64_t count_prefill_items(const pevlm_layout *lay, int32_t tile_rows, c
     return n;
 }
 
-// rows of the longest work item: of the block-prefill call, of the question call
-static int32_t max_prefill_rows(const pevlm_layout *lay, int32_t tile_rows, const Restrict &r)
+// rows of the longest region of the block-prefill call, rows of the question call's longest work item
+static int32_t max_region_rows(const pevlm_layout *lay, const Restrict &r)
 {
     int32_t n = 0;
     for (int32_t s = 0; s < lay->num_seqs; ++s) {
         if (r.with_sink) n = std::max(n, lay->sink_len[s]);
         if (lay->ctx_len[s] > 0 && (!r.num_blocks || r.num_blocks[s] > 0)) n = std::max(n, std::min(lay->block_len[s], lay->ctx_len[s]));
     }
-    return std::min(n, tile_rows);
+    return n;
 }
 static int32_t max_query_rows(const pevlm_layout *lay, int32_t tile_rows)
 {
@@ -699,7 +699,9 @@ static pevlm_status prefill_impl(const void *q, const void *k, const void *v, vo
     p.rope_compact_rows = 0;
     p.items = items;
     p.n_items = (int32_t)n_items;
-    p.max_item_rows = max_prefill_rows(layout, tile_rows, sel);
+    const int32_t region_rows = max_region_rows(layout, sel);
+    p.max_item_rows = std::min(region_rows, tile_rows);
+    p.max_region_items = ceil_div(region_rows, tile_rows);
     p.n_q_heads = heads->n_q_heads;
     p.n_kv_heads = heads->n_kv_heads;
     p.scale = scale_of(heads);

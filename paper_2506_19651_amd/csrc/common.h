@@ -382,6 +382,7 @@ struct AttnParams {
     float *part_ml;                 // partial mode: [slots][Hq][2] (running max of raw scores, sum)
     pevlm_work_item *items;         // read, or (inline_items.mode != 0) written by the workgroups of the first head
     int32_t n_items, max_item_rows; // items, rows of the longest of them
+    int32_t max_region_items;       // block prefill: items of the longest sink or block
     int32_t n_q_heads, n_kv_heads;
     float scale;                    // softmax scale
     InlineItems inline_items;
@@ -400,6 +401,7 @@ struct HeadGroups {
     int32_t wgs_per_item;     // workgroups of 128 (row, head) pairs per item and group
     int32_t groups_inside;    // groups that an item's workgroups run over before the next item (1: the next item comes first)
     int32_t step_rows, step_heads;  // the pairs that one wavefront-wide load covers, as rows and heads
+    int32_t deal_runs, deal_len;    // items dealt in turn over deal_runs runs of deal_len, the few others last (1: in order)
 };
 
 struct StreamParams {

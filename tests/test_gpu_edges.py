@@ -279,3 +279,31 @@ def test_head_maps_against_the_default_map(Hq, Hkv, D):
     finally:
         P.pevlm_set_prefill_kernel(prev)
     assert torch.equal(res[0][0][:, order], res[1][0]) and torch.equal(res[0][1][:, order], res[1][1])
+
+
+@pytest.mark.parametrize("Hkv", [1, 2, 4])
+@pytest.mark.parametrize("seqs", [[(0, 900, 900, 0)], [(0, 1024, 1024, 3)], [(0, 1100, 1100, 0)], [(130, 1500, 1700, 5)], [(40, 700, 1400, 0)],
+                                  [(0, 60, 60, 0), (0, 2000, 2000, 7)], [(0, 200, 5000, 0)]])
+def test_items_dealt_over_xcds(Hkv, seqs):
+    """One region that fills the runs of the XCDs on a KV head (7 to 18 items over 2, 4 or 8 runs, remainders among them), and
+    layouts on the other side of the rule: every row once, with the bits of the streaming kernel, folded calls too."""
+    lay, heads = P.Layout.from_seqs(seqs), P.Heads(3 * Hkv, Hkv, 128, "bf16")
+    gen = torch.Generator(device=DEV).manual_seed(9)
+    q, k, v = (torch.randn(lay.total_tokens, h, 128, device=DEV, dtype=torch.bfloat16, generator=gen) for h in (3 * Hkv, Hkv, Hkv))
+    rot = q.clone()
+    P.pevlm_rope_seq(rot, k, lay, heads, 1.0e6)
+    outs, prev = {}, P.pevlm_set_prefill_kernel("auto")
+    try:
+        for kernel in ("classic", "stream", "folded"):
+            outs[kernel] = torch.full_like(q, float("nan"))
+            if kernel == "folded":
+                P.pevlm_block_prefill_attn_rope(q, k, v, outs[kernel], lay, heads, 1.0e6, k_is_rotated=True)
+                continue
+            P.pevlm_set_prefill_kernel(kernel)
+            P.pevlm_block_prefill_attn(rot, k, v, outs[kernel], lay, heads)
+    finally:
+        P.pevlm_set_prefill_kernel(prev)
+    question = sum(s[3] for s in seqs)
+    assert int(torch.isnan(outs["classic"].float()).any(dim=-1).any(dim=-1).sum()) == question  # rows that the call does not compute
+    for kernel in ("stream", "folded"):
+        assert torch.equal(outs[kernel].view(torch.int16), outs["classic"].view(torch.int16)), kernel
