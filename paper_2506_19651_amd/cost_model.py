@@ -20,14 +20,14 @@ def useful_flops(layout: Layout, heads: Heads):
 # The paper observes that both sizes trade accuracy against attention time and leaves their choice to
 # tuning (Sec. on sink and block size; cost side: Eq. 7, Eq. 8 and Eq. 10, quadratic in both).
 #
-# Streaming kernel (one resident workgroup of 8 wavefronts per compute unit, items dealt round robin
-# inside each XCD's eighth of the list): a workgroup needs
+# Streaming kernel (one resident workgroup of 8 wavefronts per compute unit, items dealt by length inside each XCD's
+# run of the list): a workgroup needs
 #     STREAM_US_PER_ITEM * items + STREAM_US_PER_TILE * key tiles of its items,
 # and the launch takes as long as its slowest workgroup.  One-item-per-workgroup kernel (two
 # workgroups of 4 wavefronts per compute unit, dispatched as slots free up):
 #     time * (2 * CUs) = US_PER_WORKGROUP * workgroups + US_PER_WORKGROUP_TILE * sum of key tiles.
 # The constants are fitted to measured runs on one MI355X (profiles/block_prefill_sweep.md); the
-# predictions stay within 7 % of them.  The one-item kernel's at head_dim 128 come from 68 prompts of 4 K to
+# predictions stay within 10 % of them.  The one-item kernel's at head_dim 128 come from 68 prompts of 4 K to
 # 40 K tokens that fill the chip at least twice (ratio to the measured time 1.02 +- 0.09).  64-wide heads run on the
 # one-item kernel only, unless the streaming kernel is forced, which the model does not cover.
 STREAM_US_PER_ITEM = 3.9
@@ -61,10 +61,50 @@ def prefill_work(layout: Layout, heads: Heads):
     return n_wg, n_tiles
 
 
+_XCDS, _DEALT_ROUNDS, _DEALT_ITEMS, _DEALT_WGS, _DEALT_SEQS, _EVEN_SHARE = 8, 4, 4096, 32, 48, 28
+
+
+def stream_shares(tiles, num_seqs: int, compute_units: int = 256):
+    """The library's own assignment of a stream-item list (key tiles of each item) to workgroups: one array of item
+    numbers per workgroup, in its order.  Runs of the list per XCD are cut by cost, 7 an item and 3 a tile; inside a run
+    the items go round by round to the workgroups, as listed where that is even enough, else ranked by cost there and
+    back, the last rounds' sorted and to the least loads."""
+    import numpy as np
+
+    n, wgs = len(tiles), min(max(compute_units // _XCDS, 1), _DEALT_WGS)
+    cost = 7 + 3 * np.asarray(tiles, dtype=np.int64)
+    before, total = np.cumsum(cost) - cost, int(cost.sum())
+    # a run ends with the last item of which it would take the larger part
+    first = [0] + [int((2 * (total * x // _XCDS - before) >= cost).sum()) for x in range(1, _XCDS)] + [n]
+    dealt = num_seqs <= _DEALT_SEQS and wgs == _DEALT_WGS and max(np.diff(first)) <= _DEALT_ITEMS
+    if not dealt:
+        first = [n * x // _XCDS for x in range(_XCDS + 1)]
+    shares = []
+    for lo, hi in zip(first[:-1], first[1:]):
+        c, m = cost[lo:hi], hi - lo
+        listed = [np.arange(lo + w, hi, wgs) for w in range(wgs)]
+        most = max((int(cost[i].sum()) for i in listed), default=0)
+        if not dealt or most * wgs * _EVEN_SHARE <= int(c.sum()) * (_EVEN_SHARE + 1):
+            shares += listed
+            continue
+        plain = max(0, -(-m // wgs) - _DEALT_ROUNDS) * wgs
+        mine, load = [[] for _ in range(wgs)], np.zeros(wgs, np.int64)
+        for r0 in range(0, plain, wgs):
+            ranked = r0 + np.argsort(-c[r0:r0 + wgs], kind="stable")
+            for w, i in enumerate(ranked if r0 // wgs % 2 == 0 else ranked[::-1]):
+                mine[w].append(lo + int(i))
+                load[w] += c[i]
+        rest = plain + np.argsort(-c[plain:], kind="stable")
+        for r0 in range(0, m - plain, wgs):
+            for w, i in zip(np.argsort(load, kind="stable"), rest[r0:r0 + wgs]):
+                mine[w].append(lo + int(i))
+                load[w] += c[i]
+        shares += [np.asarray(i, dtype=np.int64) for i in mine]
+    return shares
+
+
 def stream_work(layout: Layout, heads: Heads, compute_units: int = 256):
-    """Per workgroup of the streaming kernel: (items, key tiles), as two arrays, following the
-    kernel's own assignment (XCD x takes items [x * ceil(n/8), ...), its workgroups take them round
-    robin)."""
+    """Per workgroup of the streaming kernel: (items, key tiles), as two arrays."""
     import ctypes
 
     import numpy as np
@@ -79,15 +119,8 @@ def stream_work(layout: Layout, heads: Heads, compute_units: int = 256):
     lib.pevlm_prefill_stream_items_host(layout.ref(), heads.ref(), None, None, 1, items, n)
     words = ctypes.sizeof(StreamItem) // 4
     tiles = np.frombuffer(items, dtype=np.int32).reshape(n, words)[:, 6].astype(np.int64)  # n_tiles
-    per_xcd = (n + 7) // 8
-    wgs = min(max(compute_units // 8, 1), per_xcd)
-    cnt, til = [], []
-    for x in range(8):
-        t = tiles[x * per_xcd:min(n, (x + 1) * per_xcd)]
-        for j in range(wgs):
-            cnt.append(len(t[j::wgs]))
-            til.append(int(t[j::wgs].sum()))
-    return np.asarray(cnt), np.asarray(til)
+    shares = stream_shares(tiles, len(layout.cu) - 1, compute_units)
+    return np.asarray([len(i) for i in shares]), np.asarray([int(tiles[i].sum()) for i in shares])
 
 
 def predict_block_prefill_ms(layout: Layout, heads: Heads, compute_units: int = 256) -> float:

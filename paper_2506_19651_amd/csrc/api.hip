@@ -299,6 +299,54 @@ static int64_t count_stream_items(const pevlm_layout *lay, const pevlm_heads *h,
     return n;
 }
 
+// First item of every XCD: the list cut into kXcds runs that take the same time, to within an item.
+static void cut_by_cost(const SeqTable &tab, int32_t G, int32_t Hkv, StreamShares *sh)
+{
+    struct Regions {  // `count` regions of R rows, each Hkv times the same items
+        int32_t R, full_len, count, items;
+        int64_t cost;
+    };
+    const auto cost_of = [&](int32_t R, int32_t full_len) {
+        int64_t c = 0;
+        for (int32_t j = 0, n = stream_items_of_region(R, G); j < n; ++j) c += stream_item_cost(R, full_len, G, j);
+        return c;
+    };
+    Regions list[3 * kMaxSeqsPerLaunch];
+    int32_t n = 0;
+    int64_t total = 0;
+    const auto add = [&](int32_t R, int32_t full_len, int32_t count) {
+        if (R <= 0 || count <= 0) return;
+        list[n] = {R, full_len, count * Hkv, stream_items_of_region(R, G), cost_of(R, full_len)};
+        total += list[n].count * list[n].cost;
+        n += 1;
+    };
+    for (int32_t s = 0; s < tab.num_seqs; ++s) {
+        const int32_t S = tab.sink[s], B = tab.block[s], C = tab.ctx[s];
+        if (tab.sel_sink) add(S, 0, 1);
+        const int32_t nb = C > 0 ? ceil_div(C, B) : 0, count = C > 0 ? tab.sel_count[s] : 0;
+        const bool last = count > 0 && tab.sel_first[s] + count == nb && C % B != 0;  // a short last block among them
+        add(B, S, count - (last ? 1 : 0));
+        if (last) add(C % B, S, 1);
+    }
+    sh->first[0] = 0;
+    int32_t at = 0, x = 1;  // items before list[r]
+    int64_t before = 0;     // their cost
+    for (int32_t r = 0; r < n; ++r) {
+        const int64_t all = list[r].count * list[r].cost;
+        for (; x < kXcds && total * x / kXcds < before + all; ++x) {
+            int64_t rest = total * x / kXcds - before;
+            const int32_t whole = (int32_t)(rest / list[r].cost);
+            rest -= whole * list[r].cost;
+            int32_t j = 0;
+            for (int32_t c; j < list[r].items && 2 * rest >= (c = stream_item_cost(list[r].R, list[r].full_len, G, j)); ++j) rest -= c;
+            sh->first[x] = at + whole * list[r].items + j;
+        }
+        at += list[r].count * list[r].items;
+        before += all;
+    }
+    for (; x <= kXcds; ++x) sh->first[x] = at;
+}
+
 static int32_t compute_units();
 
 // Stream items of the call if the streaming kernel is to run it, else 0.
@@ -567,6 +615,9 @@ pevlm_status pevlm_rope_mrope(void *q, void *k, int64_t num_tokens, const pevlm_
     return e == hipSuccess ? PEVLM_OK : hip_fail(e, "mrope launch");
 }
 
+// the streaming kernel's list and the order of its items
+static size_t stream_list_bytes(int64_t n) { return align256((size_t)n * sizeof(pevlm_stream_item)) + align256((size_t)share_entries(n) * sizeof(int32_t)); }
+
 static size_t prefill_workspace(const pevlm_layout *layout, const pevlm_heads *heads, bool fuse_rope)
 {
     if (check_layout(layout) != PEVLM_OK || check_heads(heads, nullptr) != PEVLM_OK) return 0;
@@ -574,7 +625,7 @@ static size_t prefill_workspace(const pevlm_layout *layout, const pevlm_heads *h
     if (fuse_rope) n += rope_table_bytes(layout->cu_seqlens[layout->num_seqs], heads);
     // the streaming kernel's list (plain calls on bf16 tensors) lives in the same workspace
     if (!fuse_rope && heads->dtype == PEVLM_BF16 && equal_head_groups(heads))
-        n = std::max(n, align256((size_t)count_stream_items(layout, heads) * sizeof(pevlm_stream_item)));
+        n = std::max(n, stream_list_bytes(count_stream_items(layout, heads)));
     return n + 256;
 }
 
@@ -631,7 +682,11 @@ static pevlm_status prefill_impl(const void *q, const void *k, const void *v, vo
                         workspace ? workspace_bytes : (size_t)0);
         hipStream_t hs = (hipStream_t)stream;
         pevlm_stream_item *sitems = (pevlm_stream_item *)workspace;
+        int32_t *order = (int32_t *)((char *)workspace + align256((size_t)n_stream * sizeof(pevlm_stream_item)));
         const int32_t G = heads->n_q_heads / heads->n_kv_heads;
+        StreamParams sp;
+        sp.shares.wgs = std::min(std::max(compute_units() / kXcds, 1), kMaxWgsPerXcd);
+        bool whole = layout->num_seqs <= kMaxSeqsPerLaunch && sp.shares.wgs == kMaxWgsPerXcd;  // one chunk: its builder sees the whole list
         int32_t offset = 0;
         for (int32_t s0 = 0; s0 < layout->num_seqs; s0 += kMaxSeqsPerLaunch) {
             SeqTable tab;
@@ -640,20 +695,24 @@ static pevlm_status prefill_impl(const void *q, const void *k, const void *v, vo
             for (int32_t i = 0; i < n; ++i)
                 tab.item_base[i + 1] = tab.item_base[i] + stream_items_of_seq(tab.sink[i], tab.block[i], tab.ctx[i], G, heads->n_kv_heads,
                                                                               tab.sel_first[i], tab.sel_count[i], tab.sel_sink);
+            if (s0 == 0) {
+                if (whole) cut_by_cost(tab, G, heads->n_kv_heads, &sp.shares);
+                for (int32_t x = 0; x < kXcds; ++x) whole = whole && sp.shares.first[x + 1] - sp.shares.first[x] <= kDealtItems;
+                if (!whole) for (int32_t x = 0; x <= kXcds; ++x) sp.shares.first[x] = (int32_t)(n_stream * x / kXcds);
+            }
             if (tab.item_base[n] > 0) {
-                hipError_t e = launch_build_stream_items(tab, G, heads->n_kv_heads, p.heads, sitems, offset, hs);
+                hipError_t e = launch_build_stream_items(tab, G, heads->n_kv_heads, p.heads, sitems, offset, sp.shares, order, whole, hs);
                 if (e != hipSuccess) return hip_fail(e, "stream-item builder launch");
             }
             offset += tab.item_base[n];
         }
-        StreamParams sp;
         sp.q = q; sp.k = k; sp.v = v; sp.out = out; sp.lse = lse;
         sp.items = sitems;
-        sp.n_items = (int32_t)n_stream;
+        sp.order = order;
         sp.n_q_heads = heads->n_q_heads;
         sp.n_kv_heads = heads->n_kv_heads;
         sp.scale = scale_of(heads);
-        hipError_t e = launch_attn_bf16_stream(sp, heads->head_dim, compute_units(), hs);
+        hipError_t e = launch_attn_bf16_stream(sp, heads->head_dim, hs);
         if (e != hipSuccess) return hip_fail(e, "block-prefill launch");
         return PEVLM_OK;
     }

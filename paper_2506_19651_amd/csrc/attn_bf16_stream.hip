@@ -100,6 +100,7 @@ struct BufTileLoads {
 // that item as (byte address of the first K row of the KV head, bytes up to the end of the range)
 struct TileCursor {
     int32_t ord, t;
+    int32_t item_next;  // list index of item number ord + 1
     int32_t n_full, n_tiles;
     uint64_t base_full, base_diag;
     uint32_t bytes_full, bytes_diag;
@@ -123,16 +124,17 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
     static_assert(NL >= 1 && NL <= 2 && (NW * RPI) % 16 == 0, "tile loads per wavefront");
     __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * NST * TILEB + NW * WSLICE];
 
-    // ---- the items of this workgroup: every XCD takes one contiguous eighth of the list (its L2 then
-    // holds the K/V of the few regions its workgroups are in), its workgroups take items round robin
-    const int32_t xcd = blockIdx.x & 7, wg_in_xcd = blockIdx.x >> 3, wgs_per_xcd = gridDim.x >> 3;
-    const int32_t per_xcd = (p.n_items + 7) >> 3;
-    const int32_t lo = xcd * per_xcd;
-    const int32_t hi = lo + per_xcd < p.n_items ? lo + per_xcd : p.n_items;
-    const int32_t first = lo + wg_in_xcd;
-    if (first >= hi) return;
-    const int32_t n_mine = (hi - first + wgs_per_xcd - 1) / wgs_per_xcd;
-#define PEVLM_ITEM(ord) (p.items + (first + (ord) * wgs_per_xcd))
+    // ---- the items of this workgroup, in the order of StreamShares.  An entry of the order is read well before the item it
+    // names: behind the item's own words it would double their latency.
+    const int32_t xcd = blockIdx.x & 7, wg_in_xcd = blockIdx.x >> 3, wgs = p.shares.wgs;
+    const int32_t n_xcd = p.shares.first[xcd + 1] - p.shares.first[xcd];
+    if (n_xcd <= 0) return;
+    const int32_t rounds = (n_xcd + wgs - 1) / wgs;
+    const const_i32_ptr order = (const_i32_ptr)(uintptr_t)(p.order + share_segment(p.shares, xcd) + wg_in_xcd * rounds);
+    const int32_t n_mine = sgpr(order[rounds - 1]) < 0 ? rounds - 1 : rounds;
+    if (n_mine == 0) return;
+#define PEVLM_ORDER(ord) sgpr(order[(ord) < n_mine ? (ord) : n_mine - 1])
+    int32_t item_now = PEVLM_ORDER(0), item_next = PEVLM_ORDER(1), item_after = PEVLM_ORDER(2);
 
     const int32_t tid = threadIdx.x, lane = tid & 63;
     const int32_t wave = sgpr(tid >> 6);
@@ -171,15 +173,17 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
     // ---- load stream state.  kc is the tile whose K is loaded next; the V loads of a tile follow one
     // tile later and use the descriptor remembered in (v_base, v_bytes, v_soff).
     TileCursor kc;
+    kc.item_next = item_now;
 #define PEVLM_CURSOR_SET(ord_)                                                                          \
     do {                                                                                                \
-        const pevlm_stream_item *ci_ = PEVLM_ITEM(ord_);                                                \
+        const pevlm_stream_item *ci_ = p.items + kc.item_next;                                          \
         const int32_t g_ = item_word(ci_, F_KV_HEAD);                                                   \
         const int32_t fs_ = item_word(ci_, F_FULL_START), fl_ = item_word(ci_, F_FULL_LEN);             \
         const int32_t ds_ = item_word(ci_, F_DIAG_START), dl_ = item_word(ci_, F_DIAG_LEN);             \
         kc.n_full = item_word(ci_, F_N_FULL);                                                           \
         kc.n_tiles = item_word(ci_, F_N_TILES);                                                         \
         kc.ord = (ord_);                                                                                \
+        kc.item_next = PEVLM_ORDER((ord_) + 1);                                                         \
         kc.t = 0;                                                                                       \
         kc.base_full = (uint64_t)p.k + ((uint64_t)((int64_t)fs_ * Hkv + g_) * D) * 2;                   \
         kc.base_diag = (uint64_t)p.k + ((uint64_t)((int64_t)ds_ * Hkv + g_) * D) * 2;                   \
@@ -308,11 +312,11 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
 
     // query rows of the item after next (the next item's are already in registers or in the slice); past
     // the last item, or for an unused slot, a descriptor of zero rows: zeros arrive, no memory is touched
-#define PEVLM_PREFETCH_Q(ord_target)                                                                  \
+#define PEVLM_PREFETCH_Q(ord_target, item_target)                                                     \
     do {                                                                                              \
         int32_t ps_ = 0, pr_ = 0, ph_ = 0;                                                            \
         if ((ord_target) < n_mine) {                                                                  \
-            const pevlm_stream_item *nx_ = PEVLM_ITEM(ord_target);                                    \
+            const pevlm_stream_item *nx_ = p.items + (item_target);                                   \
             ps_ = item_word(nx_, F_SLOT0 + wave * S_WORDS + S_Q_START);                               \
             pr_ = item_word(nx_, F_SLOT0 + wave * S_WORDS + S_Q_ROWS);                                \
             ph_ = item_word(nx_, F_SLOT0 + wave * S_WORDS + S_HEAD);                                  \
@@ -331,7 +335,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
         PEVLM_TILE_LOADS_BURST();
     }
     {
-        const pevlm_stream_item *it0 = PEVLM_ITEM(0);
+        const pevlm_stream_item *it0 = p.items + item_now;
         q_start = item_word(it0, F_SLOT0 + wave * S_WORDS + S_Q_START);
         q_rows = item_word(it0, F_SLOT0 + wave * S_WORDS + S_Q_ROWS);
         head = item_word(it0, F_SLOT0 + wave * S_WORDS + S_HEAD);
@@ -339,7 +343,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
         PEVLM_WAIT_VM(0);
         PEVLM_READ_QF();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        PEVLM_PREFETCH_Q(1);
+        PEVLM_PREFETCH_Q(1, item_next);
         q_age = 1;  // issued before the loads of tile 0: as if in the tile before it
     }
 
@@ -390,13 +394,14 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
             pend_head = head;                                                                         \
         } else {                                                                                      \
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                                        \
-            PEVLM_PREFETCH_Q((ord) + 2);                                                              \
+            PEVLM_PREFETCH_Q((ord) + 2, item_after);                                                              \
         }                                                                                             \
     } while (0)
 
     // ================= the item loop =================
     for (int32_t ord = 0; ord < n_mine; ++ord) {
-        const pevlm_stream_item *it = PEVLM_ITEM(ord);
+        const pevlm_stream_item *it = p.items + item_now;
+        const int32_t item_then = PEVLM_ORDER(ord + 3);
         const int32_t full_start = item_word(it, F_FULL_START), full_len = item_word(it, F_FULL_LEN);
         const int32_t diag_start = item_word(it, F_DIAG_START), diag_len = item_word(it, F_DIAG_LEN);
         const int32_t n_full_tiles = item_word(it, F_N_FULL), n_tiles = item_word(it, F_N_TILES);
@@ -422,7 +427,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
         PEVLM_TILE_LOADS_BURST();
         if (pend) {
             PEVLM_FINISH_PENDING();
-            PEVLM_PREFETCH_Q(ord + 1);
+            PEVLM_PREFETCH_Q(ord + 1, item_next);
         }
         if (n_w > 0) {
             m_ref = -INFINITY;
@@ -471,26 +476,25 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
             PEVLM_TILE_LOADS_BURST();
             if (pend) {
                 PEVLM_FINISH_PENDING();
-                PEVLM_PREFETCH_Q(ord + 2);
+                PEVLM_PREFETCH_Q(ord + 2, item_after);
             }
             PEVLM_NEXT_TILE();
         }
+        item_now = item_next;
+        item_next = item_after;
+        item_after = item_then;
     }
     // ================= flush: the last item's last value tile and output =================
     PEVLM_WAIT_VM(0);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if (pend) PEVLM_FINISH_PENDING();
-#undef PEVLM_ITEM
+#undef PEVLM_ORDER
 }
 
-hipError_t launch_attn_bf16_stream(const StreamParams &p, int32_t D, int32_t compute_units, hipStream_t stream)
+hipError_t launch_attn_bf16_stream(const StreamParams &p, int32_t D, hipStream_t stream)
 {
-    // one resident workgroup per compute unit, a multiple of 8 so that every XCD gets the same number
-    int32_t per_xcd_items = (p.n_items + 7) / 8;
-    int32_t wgs_per_xcd = compute_units / 8 > 0 ? compute_units / 8 : 1;
-    if (wgs_per_xcd > per_xcd_items) wgs_per_xcd = per_xcd_items;
-    dim3 grid(8 * wgs_per_xcd), block(512);
+    dim3 grid(kXcds * p.shares.wgs), block(512);
     if (D == 128) hipLaunchKernelGGL((attn_bf16_stream_kernel<128>), grid, block, 0, stream, p);
     else hipLaunchKernelGGL((attn_bf16_stream_kernel<64>), grid, block, 0, stream, p);
     return hipGetLastError();

@@ -141,21 +141,21 @@ __host__ __device__ inline int32_t stream_items_of_seq(int32_t S, int32_t B, int
     return n * Hkv;
 }
 
-// idx-th stream item of a sequence that starts at packed row `start`.  head_order (may be NULL =
-// identity) lists the query heads grouped by KV head: heads of KV head g are entries g*G .. g*G+G-1.
-__host__ __device__ inline pevlm_stream_item stream_item(int32_t start, int32_t S, int32_t B, int32_t C, int32_t G, int32_t Hkv,
-                                                         int32_t first, int32_t with_sink, int32_t idx, int32_t seq,
-                                                         const uint8_t *head_order)
+// Where the idx-th stream item of a sequence lies: `in_head`-th item of a KV head of a region of R rows that starts at local
+// position r_start and sees full_len sink keys besides its own.
+struct StreamPlace {
+    int32_t R, r_start, full_len, kv_head, in_head;
+};
+__host__ __device__ inline StreamPlace stream_place(int32_t S, int32_t B, int32_t C, int32_t G, int32_t Hkv, int32_t first,
+                                                    int32_t with_sink, int32_t idx)
 {
-    pevlm_stream_item it;
-    int32_t sink_items = with_sink ? stream_items_of_region(S, G) * Hkv : 0;
-    int32_t R, r_start, in_region;  // rows of the region, its first local position, item index inside it
+    StreamPlace pl;
+    const int32_t sink_items = with_sink ? stream_items_of_region(S, G) * Hkv : 0;
+    int32_t in_region = idx;
     if (idx < sink_items) {  // Eq. 3
-        R = S;
-        r_start = 0;
-        in_region = idx;
-        it.full_start = start;
-        it.full_len = 0;
+        pl.R = S;
+        pl.r_start = 0;
+        pl.full_len = 0;
     } else {  // Eq. 4: the whole sink plus the block itself up to the diagonal
         int32_t j = idx - sink_items;
         int32_t per_block = stream_items_of_region(B, G) * Hkv;
@@ -163,40 +163,86 @@ __host__ __device__ inline pevlm_stream_item stream_item(int32_t start, int32_t 
         int32_t b = first + j / per_block;
         if (b >= nb) b = nb - 1;  // items of a short last block: fewer than per_block, all beyond the full blocks
         in_region = j - (b - first) * per_block;
-        R = (C - b * B < B) ? C - b * B : B;
-        r_start = S + b * B;
-        it.full_start = start;
-        it.full_len = S;
+        pl.R = (C - b * B < B) ? C - b * B : B;
+        pl.r_start = S + b * B;
+        pl.full_len = S;
     }
-    int32_t per_head = stream_items_of_region(R, G);
-    int32_t g = in_region / per_head, jj = in_region % per_head;
-    int32_t n_slots = G * ceil_div(R, kSlotRows);
-    it.diag_start = start + r_start;
-    it.kv_head = g;
+    const int32_t per_head = stream_items_of_region(pl.R, G);
+    pl.kv_head = in_region / per_head;
+    pl.in_head = in_region % per_head;
+    return pl;
+}
+
+// Rows of a region of R rows up to the last one of its in_head-th item: what the item's own key range holds
+__host__ __device__ inline int32_t stream_item_row_end(int32_t R, int32_t G, int32_t in_head)
+{
+    int32_t last = (in_head + 1) * kSlotsPerItem - 1, n_slots = G * ceil_div(R, kSlotRows);
+    if (last >= n_slots) last = n_slots - 1;
+    const int32_t end = (last / G + 1) * kSlotRows;
+    return end < R ? end : R;
+}
+
+// What an item takes, in thirds of a key tile's time: 7 and 3 a tile (3.9 and 1.665 us, the time model's fit)
+__host__ __device__ inline int32_t stream_item_cost(int32_t R, int32_t full_len, int32_t G, int32_t in_head)
+{
+    return 7 + 3 * (ceil_div(full_len, 64) + ceil_div(stream_item_row_end(R, G, in_head), 64));
+}
+
+// idx-th stream item of a sequence that starts at packed row `start`.  head_order (may be NULL =
+// identity) lists the query heads grouped by KV head: heads of KV head g are entries g*G .. g*G+G-1.
+__host__ __device__ inline pevlm_stream_item stream_item(int32_t start, int32_t S, int32_t B, int32_t C, int32_t G, int32_t Hkv,
+                                                         int32_t first, int32_t with_sink, int32_t idx, int32_t seq,
+                                                         const uint8_t *head_order)
+{
+    pevlm_stream_item it;
+    const StreamPlace pl = stream_place(S, B, C, G, Hkv, first, with_sink, idx);
+    const int32_t n_slots = G * ceil_div(pl.R, kSlotRows);
+    it.full_start = start;
+    it.full_len = pl.full_len;
+    it.diag_start = start + pl.r_start;
+    it.kv_head = pl.kv_head;
     it.seq = seq;
-    int32_t row_end = 0;
     for (int32_t w = 0; w < kSlotsPerItem; ++w) {
-        int32_t k = jj * kSlotsPerItem + w;
+        int32_t k = pl.in_head * kSlotsPerItem + w;
         if (k < n_slots) {
             int32_t r0 = (k / G) * kSlotRows;
-            int32_t rows = (R - r0 < kSlotRows) ? R - r0 : kSlotRows;
-            int32_t hs = g * G + k % G;
-            it.slot[w].q_start = start + r_start + r0;
-            it.slot[w].q_rows = rows;
+            int32_t hs = pl.kv_head * G + k % G;
+            it.slot[w].q_start = start + pl.r_start + r0;
+            it.slot[w].q_rows = (pl.R - r0 < kSlotRows) ? pl.R - r0 : kSlotRows;
             it.slot[w].head = head_order ? (int32_t)head_order[hs] : hs;
-            row_end = r0 + rows;
         } else {
-            it.slot[w].q_start = start + r_start;
+            it.slot[w].q_start = start + pl.r_start;
             it.slot[w].q_rows = 0;
             it.slot[w].head = 0;
         }
         it.slot[w].reserved = 0;
     }
-    it.diag_len = row_end;
+    it.diag_len = stream_item_row_end(pl.R, G, pl.in_head);
     it.n_full_tiles = ceil_div(it.full_len, 64);
     it.n_tiles = it.n_full_tiles + ceil_div(it.diag_len, 64);
     return it;
 }
+
+// ------------------------------------------------------------------------------------------
+// How the streaming kernel's workgroups share the list.  XCD x takes items [first[x], first[x + 1]) of it, cut by what the
+// items take (one L2 then holds the keys of a few regions), and its wgs workgroups get them in rounds of one item each:
+// workgroup w the item order[segment(x) + w * rounds + round] (-1: none, in the last round).  Dealt out in list order a workgroup
+// meets the same lengths again and again, since a region's items rise in length and come at a fixed stride: most and mean
+// load of 64 K tokens in blocks of 1024 x 28/4 heads 779 and 703 us, of four ragged videos 1.09 of the mean.  So the items
+// of a round are ranked by length and dealt there and back, and those of the last kDealtRounds rounds, sorted, go
+// round by round to the workgroups with the least load: 1.015 and 1.01 of the mean, 1.02 over other layouts.
+// ------------------------------------------------------------------------------------------
+constexpr int32_t kXcds = 8;
+constexpr int32_t kMaxWgsPerXcd = 32;
+constexpr int32_t kDealtRounds = 4;
+constexpr int32_t kDealtItems = 4096;  // an XCD's share of a longer list is not dealt: 128 items a workgroup even out by themselves
+struct StreamShares {
+    int32_t wgs;               // workgroups of an XCD
+    int32_t first[kXcds + 1];  // first item of each XCD
+};
+__host__ __device__ inline int32_t share_segment(const StreamShares &sh, int32_t xcd) { return sh.first[xcd] + xcd * sh.wgs; }
+// entries of the order for a list of n items: every XCD's last round is filled up
+__host__ __device__ inline int64_t share_entries(int64_t n) { return n + kXcds * kMaxWgsPerXcd; }
 
 // Question items (Eq. 5): tiles of question rows x key splits.  The keys of a sequence
 // [start, start + L) are cut into num_splits runs of split_len keys; everything before the
@@ -409,7 +455,8 @@ struct StreamParams {
     void *out;     // [T][Hq][D] bf16
     float *lse;    // [T][Hq] or nullptr
     const pevlm_stream_item *items;
-    int32_t n_items;
+    const int32_t *order;
+    StreamShares shares;
     int32_t n_q_heads, n_kv_heads;
     float scale;
 };
@@ -480,10 +527,11 @@ hipError_t launch_rope_table(float *table, bool question, const SeqTable &tab, i
                              hipStream_t stream);
 hipError_t launch_rope_mrope(void *q, void *k, int64_t T, int32_t Hq, int32_t Hkv, int32_t D, bool bf16, double rope_base,
                              const int32_t *pos3, int32_t sec0, int32_t sec01, float *table, hipStream_t stream);
-hipError_t launch_build_stream_items(const SeqTable &tab, int32_t G, int32_t Hkv, const HeadTable &heads,
-                                     pevlm_stream_item *items, int32_t item_offset, hipStream_t stream);
-// block-prefill rows of bf16 tensors from a stream-item list; workgroups = compute units (8 wavefronts each)
-hipError_t launch_attn_bf16_stream(const StreamParams &p, int32_t D, int32_t compute_units, hipStream_t stream);
+// the list's items of one chunk of sequences, and their order: dealt by length if the chunk is the whole list, else as listed
+hipError_t launch_build_stream_items(const SeqTable &tab, int32_t G, int32_t Hkv, const HeadTable &heads, pevlm_stream_item *items,
+                                     int32_t item_offset, const StreamShares &shares, int32_t *order, bool whole, hipStream_t stream);
+// block-prefill rows of bf16 tensors from a stream-item list, 8 * shares.wgs workgroups of 8 wavefronts
+hipError_t launch_attn_bf16_stream(const StreamParams &p, int32_t D, hipStream_t stream);
 hipError_t launch_fp8_setup(const SeqTable &tab, const Fp8TileBases &bases, const Fp8ItemBases &items_of, pevlm_work_item *key_tiles,
                             int32_t tile_offset, Fp8Item *items, int32_t item_offset, uint32_t *zero, int32_t n_zero, const Fp8Question &qu,
                             int32_t D, hipStream_t stream);

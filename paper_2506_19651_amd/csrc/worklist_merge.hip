@@ -41,25 +41,145 @@ __global__ __launch_bounds__(256) void build_query_items_kernel(SeqTable tab, in
             qrow_of_compact[tab.qrow_base[s] + r] = tab.start[s] + tab.sink[s] + tab.ctx[s] + r;
 }
 
-// Same for the stream items of the bf16 streaming block-prefill kernel (item_base counts stream items).
-__global__ __launch_bounds__(256) void build_stream_items_kernel(SeqTable tab, int32_t G, int32_t Hkv, HeadTable heads,
-                                                                 pevlm_stream_item *items, int32_t item_offset)
+// What a dealer keeps of a sequence: the items of a head of its sink, of a block and of a short last block, and where the
+// blocks and the short block start.  An item's cost depends on its number inside its head alone.
+struct DealtRegion {
+    int32_t items, R, full_len;
+};
+struct DealtSeq {
+    int32_t base, blocks, last;
+    DealtRegion region[3];
+};
+
+// The order of one XCD's items (one workgroup): as listed where that leaves no workgroup more than 1/kEvenShare above the mean (a
+// round's workgroups then stay closer together: 100 K tokens in blocks of 392, most load 1.02 of the mean, 1228 us as
+// listed and 1250 dealt), else as StreamShares says.  Keys are all different: equal
+// costs go by their place.
+constexpr int32_t kDealThreads = 512;
+constexpr int32_t kEvenShare = 28;
+// keys v[0 .. N) above mine; a short loop, since what is fetched of a kernel that runs once costs more than its cycles
+template <int N>
+__device__ __forceinline__ int32_t keys_above(const uint32_t *v, uint32_t mine)
 {
-    int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    int32_t rank = 0;
+#pragma unroll 2
+    for (int32_t j = 0; j < N; j += 4) {
+        const uint4 x = *reinterpret_cast<const uint4 *>(v + j);
+        rank += x.x > mine;
+        rank += x.y > mine;
+        rank += x.z > mine;
+        rank += x.w > mine;
+    }
+    return rank;
+}
+__device__ __forceinline__ void deal_stream_items(const SeqTable &tab, int32_t G, int32_t Hkv, const StreamShares &sh, int32_t xcd, int32_t *order)
+{
+    constexpr int32_t W = kMaxWgsPerXcd, TAIL = kDealtRounds * W;
+    __shared__ __attribute__((aligned(16))) uint32_t key[kDealtItems];  // cost * 2^7 + 127 - place % 128
+    __shared__ __attribute__((aligned(16))) uint32_t tail[TAIL], load[W], listed[W];  // load: sum of costs * 2^5 + workgroup
+    __shared__ DealtSeq seqs[kMaxSeqsPerLaunch];
+    __shared__ uint2 sorted[TAIL];  // (item, cost)
+    const int32_t tid = threadIdx.x, lo = sh.first[xcd], n = sh.first[xcd + 1] - lo;
+    const int32_t rounds = ceil_div(n, W), plain = rounds > kDealtRounds ? rounds - kDealtRounds : 0;  // rounds dealt there and back
+    int32_t *const seg = order + share_segment(sh, xcd);
+    const int32_t num_seqs = tab.num_seqs;
+    if (tid < num_seqs) {
+        const int32_t S = tab.sink[tid], B = tab.block[tid], C = tab.ctx[tid], first = tab.sel_first[tid], count = C > 0 ? tab.sel_count[tid] : 0;
+        const int32_t nb = C > 0 ? ceil_div(C, B) : 0, rest = C > 0 && first + count == nb ? C - (nb - 1) * B : B;
+        DealtSeq d;
+        d.base = tab.item_base[tid];
+        d.region[0] = {stream_items_of_region(S, G), S, 0};
+        d.region[1] = {stream_items_of_region(B, G), B, S};
+        d.region[2] = {stream_items_of_region(rest, G), rest, S};
+        d.blocks = d.base + (tab.sel_sink ? d.region[0].items * Hkv : 0);
+        d.last = d.blocks + (count > 0 ? (count - 1) * d.region[1].items * Hkv : 0);
+        seqs[tid] = d;
+    }
+    if (tid < W) {
+        load[tid] = (uint32_t)tid;
+        listed[tid] = 0u;
+    }
+    __syncthreads();
+    for (int32_t i = tid; i < n; i += kDealThreads) {
+        const int32_t idx = lo + i;
+        int32_t s = 0;
+        while (s + 1 < num_seqs && idx >= seqs[s + 1].base) ++s;
+        const DealtSeq &d = seqs[s];
+        const bool in_sink = idx < d.blocks, in_last = idx >= d.last;
+        const DealtRegion r = d.region[in_sink ? 0 : (in_last ? 2 : 1)];
+        const uint32_t c = stream_item_cost(r.R, r.full_len, G, (idx - (in_sink ? d.base : (in_last ? d.last : d.blocks))) % r.items);
+        key[i] = (c << 7) + (uint32_t)(127 - i % 128);
+        atomicAdd(&listed[i % W], c);
+    }
+    __syncthreads();
+    uint32_t sum = 0u, most = 0u;
+#pragma unroll 4
+    for (int32_t w = 0; w < W; ++w) {
+        sum += listed[w];
+        most = listed[w] > most ? listed[w] : most;
+    }
+    if ((uint64_t)most * W * kEvenShare <= (uint64_t)sum * (kEvenShare + 1)) {
+        for (int32_t i = tid; i < rounds * W; i += kDealThreads) seg[i % W * rounds + i / W] = i < n ? lo + i : -1;
+        return;
+    }
+    const int32_t t0 = plain * W, m = n - t0;  // at most TAIL items are left
+    if (tid < TAIL) tail[tid] = tid < m ? key[t0 + tid] : (uint32_t)tid;
+    for (int32_t i = tid; i < t0; i += kDealThreads) {
+        const int32_t round = i / W, rank = keys_above<W>(key + round * W, key[i]), w = round & 1 ? W - 1 - rank : rank;
+        seg[w * rounds + round] = lo + i;
+        atomicAdd(&load[w], key[i] >> 7 << 5);
+    }
+    __syncthreads();
+    if (tid < TAIL) sorted[keys_above<TAIL>(tail, tail[tid])] = make_uint2(tid < m ? lo + t0 + tid : -1, tail[tid] >> 7 << 5);
+    __syncthreads();
+    if (tid >= W) return;
+    // lane w for workgroup w: the round's longest item to the least load, and so on
+    for (int32_t round = plain; round < rounds; ++round) {
+        const uint32_t mine = load[tid];
+        const uint2 item = sorted[(round - plain) * W + W - 1 - keys_above<W>(load, mine)];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        seg[tid * rounds + round] = (int32_t)item.x;
+        load[tid] = mine + item.y;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// Same for the stream items of the bf16 streaming block-prefill kernel (item_base counts stream items) and their order: the
+// first kXcds workgroups deal it out if the chunk is the whole list, otherwise every thread lists its own item.
+__global__ __launch_bounds__(kDealThreads) void build_stream_items_kernel(SeqTable tab, int32_t G, int32_t Hkv, HeadTable heads,
+                                                                          pevlm_stream_item *items, int32_t item_offset, StreamShares shares,
+                                                                          int32_t *order, int32_t dealers)
+{
+    if ((int32_t)blockIdx.x < dealers) {
+        deal_stream_items(tab, G, Hkv, shares, blockIdx.x, order);
+        return;
+    }
+    int32_t i = ((int32_t)blockIdx.x - dealers) * kDealThreads + threadIdx.x;
     int32_t total = tab.item_base[tab.num_seqs];
     if (i >= total) return;
     int32_t s = 0;
     while (s + 1 < tab.num_seqs && i >= tab.item_base[s + 1]) ++s;
     items[item_offset + i] = stream_item(tab.start[s], tab.sink[s], tab.block[s], tab.ctx[s], G, Hkv, tab.sel_first[s], tab.sel_sink,
                                          i - tab.item_base[s], tab.seq_index0 + s, heads.head_order);
+    if (dealers) return;
+    i += item_offset;
+    int32_t x = 0;
+    while (i >= shares.first[x + 1]) ++x;
+    const int32_t n = shares.first[x + 1] - shares.first[x], W = shares.wgs, rounds = ceil_div(n, W), at = i - shares.first[x];
+    int32_t *const seg = order + share_segment(shares, x);
+    seg[at % W * rounds + at / W] = i;
+    if (at == n - 1)  // no items in the rest of the last round
+        for (int32_t left = n; left < rounds * W; ++left) seg[left % W * rounds + rounds - 1] = -1;
 }
 
-hipError_t launch_build_stream_items(const SeqTable &tab, int32_t G, int32_t Hkv, const HeadTable &heads,
-                                     pevlm_stream_item *items, int32_t item_offset, hipStream_t stream)
+hipError_t launch_build_stream_items(const SeqTable &tab, int32_t G, int32_t Hkv, const HeadTable &heads, pevlm_stream_item *items,
+                                     int32_t item_offset, const StreamShares &shares, int32_t *order, bool whole, hipStream_t stream)
 {
-    int32_t total = tab.item_base[tab.num_seqs];
-    hipLaunchKernelGGL(build_stream_items_kernel, dim3((total + 255) / 256), dim3(256), 0, stream, tab, G, Hkv, heads, items,
-                       item_offset);
+    const int32_t total = tab.item_base[tab.num_seqs], dealers = whole ? kXcds : 0;
+    hipLaunchKernelGGL(build_stream_items_kernel, dim3(dealers + (total + kDealThreads - 1) / kDealThreads), dim3(kDealThreads), 0, stream, tab, G, Hkv,
+                       heads, items, item_offset, shares, order, dealers);
     return hipGetLastError();
 }
 

@@ -307,3 +307,43 @@ def test_items_dealt_over_xcds(Hkv, seqs):
     assert int(torch.isnan(outs["classic"].float()).any(dim=-1).any(dim=-1).sum()) == question  # rows that the call does not compute
     for kernel in ("stream", "folded"):
         assert torch.equal(outs[kernel].view(torch.int16), outs["classic"].view(torch.int16)), kernel
+
+
+@pytest.mark.parametrize("Hq,Hkv,seqs", [
+    (2, 1, [(0, 40, 40, 3)]),                                            # fewer items than XCDs
+    (7, 1, [(100, 1024, 20480, 0)]),                                     # fewer rounds than are sorted together
+    (14, 2, [(256, 1024, 30000, 1), (0, 64, 0, 9), (33, 700, 5000, 0)]),  # dealt there and back first; an empty context, short last blocks
+    (16, 8, [(392, 392, 39592, 0)]),                                     # even as listed, a short last block
+    (4, 2, [(16, 500, 900, 2)] * 50),                                    # more sequences than a table holds: as listed
+])
+def test_shares_of_the_streaming_kernel(Hq, Hkv, seqs):
+    """The order that the builder leaves behind the list: every item once, gaps in the last round only, each XCD's share of the
+    work within an item of the others', no workgroup far above the mean; and the bits of the one-item kernel."""
+    lay, heads = P.Layout.from_seqs(seqs), P.Heads(Hq, Hkv, 128, "bf16")
+    gen = torch.Generator(device=DEV).manual_seed(12)
+    q, k, v = (torch.randn(lay.total_tokens, h, 128, device=DEV, dtype=torch.bfloat16, generator=gen) for h in (Hq, Hkv, Hkv))
+    ws = torch.zeros(P.pevlm_block_prefill_workspace_bytes(lay, heads), dtype=torch.uint8, device=DEV)
+    outs, prev = [], P.pevlm_set_prefill_kernel("classic")
+    try:
+        for kernel in ("classic", "stream"):
+            P.pevlm_set_prefill_kernel(kernel)
+            outs.append(torch.full_like(q, float("nan")))
+            P.pevlm_block_prefill_attn(q, k, v, outs[-1], lay, heads, workspace=ws)
+        items = P.pevlm_prefill_stream_items_host(lay, heads)
+    finally:
+        P.pevlm_set_prefill_kernel(prev)
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+    n, W = len(items), torch.cuda.get_device_properties(0).multi_processor_count // 8
+    cost = np.array([7 + 3 * it.n_tiles for it in items])
+    before, dealt = np.cumsum(cost) - cost, len(seqs) <= 48
+    # an XCD's run ends with the last item of which it would take the larger part
+    first = [int((2 * (cost.sum() * x // 8 - before) >= cost).sum()) if dealt and 0 < x < 8 else n * x // 8 for x in range(9)]
+    order = ws.cpu().numpy()[(n * 160 + 255) // 256 * 256:].view(np.int32)
+    for x in range(8):
+        mine = first[x + 1] - first[x]
+        rounds = -(-mine // W)
+        seg = order[first[x] + x * W:][:rounds * W].reshape(W, rounds)
+        assert np.array_equal(np.sort(seg[seg >= 0]), np.arange(first[x], first[x + 1])) and (seg[:, :-1] >= 0).all()
+        if mine and dealt:
+            load = np.where(seg >= 0, cost[seg], 0).sum(axis=1)
+            assert load.max() <= max(1.04 * load.mean(), load.mean() + cost[first[x]:first[x + 1]].max())
