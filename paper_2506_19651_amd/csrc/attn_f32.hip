@@ -49,6 +49,23 @@ struct F32Shared {
     };
 };
 
+// exp(d * scale) for c = scale * log2(e): two instructions where expf takes twelve, which is what the vector ALU had to do
+// between the matrix instructions (fp32 ones leave it no cycles of their own).  The product is rounded once, as the argument of
+// expf was.
+__device__ __forceinline__ float weight_of(float d, float c) { return __builtin_amdgcn_exp2f(d * c); }
+__device__ __forceinline__ float other_half(float x)  // the value of lane ^ 32
+{
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float((threadIdx.x & 32) ? sw[0] : sw[1]);
+}
+// A row's weights are formed against the reference maximum it has; it is raised (and the row scaled) on its first tile and when
+// a lane's sum of weights reaches this bound: they are not negative, so each stays below it, and an overflow is seen.
+constexpr float kSumBound = 256.f;
+// The wavefronts of a workgroup take its tiles in turn, wavefront 0 not always first: it sits on the same SIMD in every
+// workgroup, and where the tiles do not divide by four that one had the most to do.  The row decides, so that a row's
+// result does not depend on the launch.
+__device__ __forceinline__ int32_t first_tile(const pevlm_work_item &it, int32_t u, int32_t wave) { return (wave + u + (it.q_start >> 4) + (it.q_start >> 7)) % NW; }
+
 // Rows of one head (number n of the workgroup's heads): the wavefronts' values in sh.o, already scaled to
 // the row's common maximum, are added and stored, four rows by a wavefront.  Returns false, with none of the
 // wavefront's rows stored, if one of them is not finite.
@@ -167,7 +184,7 @@ __device__ __forceinline__ void attn_f32_rows(const AttnParams &p, const pevlm_w
 // is the k index.  Step j of group i of Q K^T contracts head_dim 8 i + 4 half + j; the lane's score v belongs
 // to key (v & 3) + 8 (v >> 2) + 4 half of the tile; row r of block b of O^T is head_dim DB r + b.
 template <int D, bool PARTIAL>
-__device__ __forceinline__ int32_t attn_f32_pair(const AttnParams &p, const pevlm_work_item &it, const int32_t (&h)[2], int32_t g, F32Shared<D> &sh)
+__device__ __forceinline__ int32_t attn_f32_pair(const AttnParams &p, const pevlm_work_item &it, const int32_t (&h)[2], int32_t g, int32_t u, F32Shared<D> &sh)
 {
     constexpr int KT = 32, KI = D / 8, DB = D / 32;
     typedef __attribute__((ext_vector_type(DB))) float f32xdb;
@@ -217,12 +234,14 @@ __device__ __forceinline__ int32_t attn_f32_pair(const AttnParams &p, const pevl
             vbuf[hf][u] = *reinterpret_cast<const f32xdb *>(vt + ((uint32_t)(kl < last ? kl : last) * kv_row + 4 * DB * (lane & 31)));
         }
     };
-    if (wave < n_tiles) {
-        tile_range(wave);
+    const int32_t t_first = first_tile(it, u, wave);
+    const float c_log2 = p.scale * 1.4426950408889634f;
+    if (t_first < n_tiles) {
+        tile_range(t_first);
         load_k(0);
     }
     __syncthreads();  // the queries are in LDS
-    for (int32_t t = wave; t < n_tiles; t += NW) {
+    for (int32_t t = t_first; t < n_tiles; t += NW) {
         const bool causal = t >= n_full;
         f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, s2 = s;
         auto scores = [&](int hf) {
@@ -244,36 +263,49 @@ __device__ __forceinline__ int32_t attn_f32_pair(const AttnParams &p, const pevl
         load_v(1);
         __builtin_amdgcn_sched_barrier(0);
         s += s2;
-        const int32_t lim = (causal && row - k0 < last ? row - k0 : last) - 4 * half;
-        float mx = -INFINITY;
+        if (last < KT - 1 || (causal && k0 + KT - 1 > it.q_start)) {  // the range ends in the tile, or the diagonal runs through it
+            const int32_t lim = (causal && row - k0 < last ? row - k0 : last) - 4 * half;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            s[v] = (v & 3) + 8 * (v >> 2) <= lim ? s[v] : -INFINITY;
-            mx = fmaxf(mx, s[v]);
+            for (int v = 0; v < 16; ++v) s[v] = (v & 3) + 8 * (v >> 2) <= lim ? s[v] : -INFINITY;
         }
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float m_new = fmaxf(m, mx);
-        const float m_use = m_new == -INFINITY ? 0.f : m_new;  // no visible key yet: all weights come out 0
         float psum = 0.f;
+        f32x16 w;
+        if (t != t_first) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            s[v] = expf((s[v] - m_use) * p.scale);
-            psum += s[v];
+            for (int v = 0; v < 16; ++v) {
+                w[v] = weight_of(s[v] - m, c_log2);  // no key seen yet: m = -inf makes the sum inf or invalid
+                psum += w[v];
+            }
         }
-        if (__any(m_new > m)) {
-            const float alpha = expf((m - m_use) * p.scale);  // m = -inf gives 0
-            l *= alpha;
+        const int32_t up = t == t_first || !(psum < kSumBound) || m == -INFINITY;
+        if (__any(up)) {
+            float mx = s[0];
 #pragma unroll
-            for (int b = 0; b < DB; ++b)
+            for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+            mx = fmaxf(mx, other_half(mx));
+            const float m_new = up | __shfl_xor(up, 32) ? fmaxf(m, mx) : m;
+            const float m_use = m_new == -INFINITY ? 0.f : m_new;  // no visible key yet: all weights come out 0
+            psum = 0.f;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) o[b][i] *= alpha;
+            for (int v = 0; v < 16; ++v) {
+                w[v] = weight_of(s[v] - m_use, c_log2);
+                psum += w[v];
+            }
+            if (t != t_first) {
+                const float alpha = weight_of(m - m_use, c_log2);  // m = -inf gives 0
+                l *= alpha;
+#pragma unroll
+                for (int b = 0; b < DB; ++b)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) o[b][i] *= alpha;
+            }
             m = m_new;
         }
         l += psum;
 #pragma unroll
         for (int u = 0; u < 8; ++u)
 #pragma unroll
-            for (int b = 0; b < DB; ++b) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(vbuf[0][u][b], s[u], o[b], 0, 0, 0);
+            for (int b = 0; b < DB; ++b) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(vbuf[0][u][b], w[u], o[b], 0, 0, 0);
         if (t + NW < n_tiles) {
             tile_range(t + NW);
             load_k(0);
@@ -282,7 +314,7 @@ __device__ __forceinline__ int32_t attn_f32_pair(const AttnParams &p, const pevl
 #pragma unroll
         for (int u = 0; u < 8; ++u)
 #pragma unroll
-            for (int b = 0; b < DB; ++b) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(vbuf[1][u][b], s[8 + u], o[b], 0, 0, 0);
+            for (int b = 0; b < DB; ++b) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(vbuf[1][u][b], w[8 + u], o[b], 0, 0, 0);
     }
 
     // ---- join the wavefronts: common maximum per row, values scaled to it and added through LDS
@@ -319,7 +351,7 @@ __device__ __forceinline__ int32_t attn_f32_pair(const AttnParams &p, const pevl
 // head_dim 16 i + 4 kq + j, the lane's score v of a block of 16 keys is that of key 4 kq + v, row r of
 // block 4 hh + b of O^T is head_dim 64 hh + 4 r + b.
 template <int D, bool PARTIAL>
-__device__ __forceinline__ int32_t attn_f32_single(const AttnParams &p, const pevlm_work_item &it, int32_t h, int32_t g, F32Shared<D> &sh)
+__device__ __forceinline__ int32_t attn_f32_single(const AttnParams &p, const pevlm_work_item &it, int32_t h, int32_t g, int32_t u, F32Shared<D> &sh)
 {
     constexpr int KI = D / 16;  // 16-wide groups of head_dim in Q K^T
     constexpr int VH = D / 64;  // 64-wide halves of head_dim in O^T
@@ -342,7 +374,8 @@ __device__ __forceinline__ int32_t attn_f32_single(const AttnParams &p, const pe
     f32x4 o[4 * VH];
 #pragma unroll
     for (int b = 0; b < 4 * VH; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int32_t t = wave; t < n_tiles; t += NW) {
+    const float c_log2 = p.scale * 1.4426950408889634f;
+    for (int32_t t = first_tile(it, u, wave); t < n_tiles; t += NW) {
         const bool causal = t >= n_full;
         const int32_t k0 = causal ? it.diag_start + (t - n_full) * KT : it.full_start + t * KT;
         const int32_t kend = causal ? it.diag_start + it.diag_len : it.full_start + it.full_len;
@@ -385,12 +418,12 @@ __device__ __forceinline__ int32_t attn_f32_single(const AttnParams &p, const pe
             if (b < nblk) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    s[b][v] = expf((s[b][v] - m_use) * p.scale);
+                    s[b][v] = weight_of(s[b][v] - m_use, c_log2);
                     psum += s[b][v];
                 }
             }
         if (__any(m_new > m)) {
-            const float alpha = expf((m - m_use) * p.scale);  // m = -inf gives 0
+            const float alpha = weight_of(m - m_use, c_log2);  // m = -inf gives 0
             l *= alpha;
 #pragma unroll
             for (int b = 0; b < 4 * VH; ++b) o[b] *= alpha;
@@ -470,13 +503,13 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(AttnParams p, int32_t 
         const int32_t G = p.n_q_heads / p.n_kv_heads;
         const int32_t h[2] = {p.heads.head_order[group * G + 2 * u], p.heads.head_order[group * G + (2 * u + 1 < G ? 2 * u + 1 : 2 * u)]};
         int32_t left;
-        if (2 * u + 1 < G) left = attn_f32_pair<D, PARTIAL>(p, it, h, group, sh);
-        else left = attn_f32_single<D, PARTIAL>(p, it, h[0], group, sh);
+        if (2 * u + 1 < G) left = attn_f32_pair<D, PARTIAL>(p, it, h, group, u, sh);
+        else left = attn_f32_single<D, PARTIAL>(p, it, h[0], group, u, sh);
         for (int32_t n = 0; left >> n; ++n)
             if (left >> n & 1) attn_f32_rows<D, PARTIAL>(p, it, n ? h[1] : h[0], group, sh);
     } else {
         const int32_t h = p.heads.head_order[group * units + u], g = p.heads.kv_of_q[h];
-        if (attn_f32_single<D, PARTIAL>(p, it, h, g, sh)) attn_f32_rows<D, PARTIAL>(p, it, h, g, sh);
+        if (attn_f32_single<D, PARTIAL>(p, it, h, g, u, sh)) attn_f32_rows<D, PARTIAL>(p, it, h, g, sh);
     }
 }
 
