@@ -411,9 +411,9 @@ static QueryPlan carve_query(int64_t tiles, int64_t total_q, const pevlm_heads *
 
 // Split count when the caller leaves it to the library.
 //
-// fp32: workgroups (16 rows x two heads x split) are brought as close as possible to one or two full rounds of 2
-// x CUs from below, with at least 256 keys per split (64 question rows over 2.4 K keys: 0.047 ms at 8
-// splits, 0.052 ms at 3).
+// fp32: splits_of_f32 (64 question rows x 28/4 heads over 2.4 K keys: 36 us at 16 splits, 51 at 9); where that does not go,
+// workgroups (16 rows x two heads x split) are brought as close as possible to one or two full rounds of 2 x CUs from below,
+// with at least 256 keys per split.
 //
 // bf16: the count with the least predicted time.  A workgroup (128 (row, head) pairs x split) takes 6 us plus a
 // time per key tile that depends on how full the compute units are, workgroups run in rounds of two per
@@ -454,6 +454,25 @@ static int32_t splits_of_full_rounds(const pevlm_layout *lay, const pevlm_heads 
     // number of splits, so the long ones set the pace): take two rounds of finer pieces
     if (want * units * 4 < slots * 3 || 2 * min_len < max_len) want = (2 * slots) / units;
     return (int32_t)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, max_len / min_keys), PEVLM_MAX_SPLITS));
+}
+
+// fp32: a workgroup for every compute unit from the kernel that takes all heads of a group, two where the splits stay
+// long, if the keys go that far
+static int32_t splits_of_f32(const pevlm_layout *lay, const pevlm_heads *h)
+{
+    const int32_t G = h->n_q_heads / h->n_kv_heads;
+    int64_t units = 0, max_len = 0;
+    for (int32_t s = 0; s < lay->num_seqs; ++s)
+        if (lay->query_len[s] > 0) {
+            units += (int64_t)ceil_div(lay->query_len[s], kTileRowsF32) * ceil_div(kTileRowsF32 * G, 128) * h->n_kv_heads;
+            max_len = std::max(max_len, (int64_t)lay->cu_seqlens[s + 1] - lay->cu_seqlens[s]);
+        }
+    if (units > 0 && G > 4 && equal_head_groups(h)) {
+        const int64_t one = (compute_units() + units - 1) / units, two = (2 * (int64_t)compute_units() + units - 1) / units;
+        const int64_t n = max_len >= 512 * two ? two : one;
+        if (n <= PEVLM_MAX_SPLITS && max_len >= 128 * n) return (int32_t)n;
+    }
+    return splits_of_full_rounds(lay, h, 256, [](int32_t) { return 2; });
 }
 
 static int32_t predicted_splits(const pevlm_layout *lay, const pevlm_heads *h, const Restrict &sel, int32_t full_rounds)
@@ -516,7 +535,7 @@ static int32_t auto_splits(const pevlm_layout *lay, const pevlm_heads *h, const 
 {
     const bool f32 = h->dtype == PEVLM_F32, windowed = sel.window_blocks != nullptr;
     const int32_t rounds = splits_of_full_rounds(lay, h, 768, [&](int32_t rows) { return f32 ? 1 : (rows <= 32 ? 4 : (rows <= 64 ? 2 : 1)); });
-    int32_t n = f32 ? splits_of_full_rounds(lay, h, 256, [](int32_t) { return 2; })
+    int32_t n = f32 ? splits_of_f32(lay, h)
                     : predicted_splits(lay, h, sel, std::min(PEVLM_MAX_SPLITS, rounds + (windowed ? 1 : 0)));
     const int64_t tiles = count_query_tiles(lay, tile_rows_of(h, true)), total_q = total_query_rows(lay);
     while (n > rounds && carve_query(tiles, total_q, h, n).bytes > kFreeQueryBytes) --n;
@@ -761,6 +780,7 @@ static pevlm_status prefill_impl(const void *q, const void *k, const void *v, vo
     const int32_t region_rows = max_region_rows(layout, sel);
     p.max_item_rows = std::min(region_rows, tile_rows);
     p.max_region_items = ceil_div(region_rows, tile_rows);
+    p.num_splits = 1;
     p.n_q_heads = heads->n_q_heads;
     p.n_kv_heads = heads->n_kv_heads;
     p.scale = scale_of(heads);
@@ -996,6 +1016,7 @@ static pevlm_status query_impl(const void *q, const void *k, const void *v, void
     p.items = items;
     p.n_items = (int32_t)plan.n_items;
     p.max_item_rows = max_query_rows(layout, plan.tile_rows);
+    p.num_splits = plan.num_splits;
     p.n_q_heads = heads->n_q_heads;
     p.n_kv_heads = heads->n_kv_heads;
     p.scale = scale_of(heads);

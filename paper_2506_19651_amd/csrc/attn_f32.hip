@@ -1,38 +1,30 @@
-// fp32 attention kernel on the fp32 matrix cores (fp32 products and sums): the numerical anchor of the
-// library and the path taken for fp32 tensors.
+// fp32 attention: the numerical anchor of the library and the path taken for fp32 tensors.  Two kernels over the same work
+// items (<= 16 query rows), both with scores formed transposed, S^T = K Q^T (A: keys, B: query rows): what a lane then holds of
+// a query row is the B operand of O^T += V^T P^T as it stands.
 //
-// A workgroup takes one work item (<= 16 query rows) for one or two heads of a KV group; its 4 wavefronts
-// take the item's key tiles in turn, each with an online softmax of its own, and are joined at the end
-// by the log-sum-exp identity.  So an item of a few hundred keys is a chain of one or two tiles, and a
-// short prompt, which has few items, still spreads over the chip.
+// attn_f32_group, where it gives every compute unit a workgroup: all heads of a KV group together, 128 (row, head) columns to a
+// workgroup of 4 wavefronts, on the bf16 matrix instructions: every fp32 value is split into three bf16 ones that add up to it
+// exactly, and six of their nine products are taken (the others are below 2^-26 of the whole).  Six bf16 instructions take 192
+// cycles where the fp32 ones take 512, and leave the vector ALU its cycles.  K and V are split once per workgroup, on their way
+// into LDS.  Prefill of 2304 rows (sink 256, two blocks of 1024) x 28/4 heads x 128: 272 us on the fp32 instructions (two heads
+// x 16 rows, 56 % of the time matrix instructions, every wavefront loading its own keys), 180 now; 20.7 K rows 2350 -> 1360 us,
+// 1.2 PFLOP/s of bf16 products.  Distance to the same attention in 64 bits 1.8e-7, 2.9e-7 before.  Bound: the bf16 matrix
+// instructions, and with few workgroups their unequal lengths.
 //
-// Two heads: the 32 columns (row, head) fill v_mfma_f32_32x32x2_f32, which sustains 153 TFLOP/s from
-// registers; one head (the odd one of a group, or a grid that would not fill the chip): 16 columns on
-// v_mfma_f32_16x16x4_f32, which sustains 102.
-//
-// Scores are formed transposed, S^T = K Q^T (A: keys, B: query rows): what a lane then holds of a query row is
-// the B operand of O^T += V^T P^T as it stands.  The order of a contraction and of the output rows is free, and
-// is chosen so that a lane feeds 4 MFMA steps from one 16-byte load.  K and V go from global memory to
-// registers: the four SIMDs of a compute unit ask its L1 for 16 bytes a cycle, a quarter of what it
-// delivers, so nothing is staged in LDS and the tile loop has no barrier.
-//
-// Bound: the fp32 matrix rate.  Prefill of 2304 rows (sink 256, two blocks of 1024, 28/4 heads x 128): 0.268 ms,
-// 86 TFLOP/s useful, of which the matrix instructions alone would take 0.166 ms; what is left is the uneven
-// number of tiles per wavefront, the chain before an item's first tile and its join.  (One row per
-// wavefront with plain multiply-adds, keys over lanes: 4.59 ms.)
+// attn_f32_single elsewhere: one head on 16 columns of v_mfma_f32_16x16x4_f32; the 4 wavefronts take the item's key tiles in turn,
+// each with an online softmax of its own, and are joined at the end by the log-sum-exp identity, so that an item of a few
+// hundred keys is a chain of one or two tiles, and a short prompt still spreads over the chip.  The order of a
+// contraction and of the output rows is free, and is chosen so that a lane feeds 4 MFMA steps from one 16-byte load.
 //
 // A key that a row must not see enters its value MFMAs with the weight 0, which hides every finite value but not an
-// infinite or invalid one.  Such a value leaves a NaN in the row, so rows that do not come out finite are done again
-// over the keys that they see and no others (attn_f32_rows).
+// infinite or invalid one (nor one that overflows its first bf16 part).  Such a value leaves a NaN in the row, so rows that do
+// not come out finite are done again over the keys that they see and no others (attn_f32_rows).
 #include <algorithm>
+#include <type_traits>
 
-#include "common.h"
+#include "attn_bf16_tile.h"
 
 namespace pevlm {
-
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 namespace {
 
@@ -40,18 +32,18 @@ constexpr int kRows = 16;  // query rows of an item
 constexpr int NW = 4;      // wavefronts of a workgroup
 
 template <int D>
+struct F32Row {  // a wavefront's query row and weights of 64 keys
+    float q[D], w[64];
+};
+template <int D>
 struct F32Shared {
-    float ml[NW][2][kRows][2];        // per wavefront, head and row: maximum of the raw scores, sum of the weights
-    float o[NW][kRows][D + 4];        // one head at a time: values of every wavefront, scaled to the common maximum
-    union {
-        f32x4 q[D / 8][64];           // two heads: the B fragments of Q K^T, the same for every wavefront
-        struct { float q[D], w[64]; } row[NW];  // attn_f32_rows: a wavefront's query row and weights of 64 keys
-    };
+    float ml[NW][kRows][2];           // per wavefront and row: maximum of the raw scores, sum of the weights
+    float o[NW][kRows][D + 4];        // values of every wavefront, scaled to the common maximum
+    F32Row<D> row[NW];                // attn_f32_rows
 };
 
-// exp(d * scale) for c = scale * log2(e): two instructions where expf takes twelve, which is what the vector ALU had to do
-// between the matrix instructions (fp32 ones leave it no cycles of their own).  The product is rounded once, as the argument of
-// expf was.
+// exp(d * scale) for c = scale * log2(e): two instructions where expf takes twelve.  The product is rounded once, as the argument
+// of expf was.
 __device__ __forceinline__ float weight_of(float d, float c) { return __builtin_amdgcn_exp2f(d * c); }
 __device__ __forceinline__ float other_half(float x)  // the value of lane ^ 32
 {
@@ -66,12 +58,12 @@ constexpr float kSumBound = 256.f;
 // result does not depend on the launch.
 __device__ __forceinline__ int32_t first_tile(const pevlm_work_item &it, int32_t u, int32_t wave) { return (wave + u + (it.q_start >> 4) + (it.q_start >> 7)) % NW; }
 
-// Rows of one head (number n of the workgroup's heads): the wavefronts' values in sh.o, already scaled to
+// Rows of one head: the wavefronts' values in sh.o, already scaled to
 // the row's common maximum, are added and stored, four rows by a wavefront.  Returns false, with none of the
 // wavefront's rows stored, if one of them is not finite.
 constexpr int kRowsPerWave = kRows / NW;
 template <int D, bool PARTIAL>
-__device__ __forceinline__ bool store_rows(const AttnParams &p, const pevlm_work_item &it, int32_t head, int32_t n, const F32Shared<D> &sh)
+__device__ __forceinline__ bool store_rows(const AttnParams &p, const pevlm_work_item &it, int32_t head, const F32Shared<D> &sh)
 {
     const int32_t orow = threadIdx.x / 16, c = threadIdx.x % 16, Hq = p.n_q_heads;
     const bool live = orow < it.q_rows;
@@ -89,11 +81,11 @@ __device__ __forceinline__ bool store_rows(const AttnParams &p, const pevlm_work
     if (!live) return true;
     float M = -INFINITY, L = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) M = fmaxf(M, sh.ml[w][n][orow][0]);
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, sh.ml[w][orow][0]);
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-        const float mw = sh.ml[w][n][orow][0];
-        L += mw == -INFINITY ? 0.f : sh.ml[w][n][orow][1] * expf((mw - M) * p.scale);
+        const float mw = sh.ml[w][orow][0];
+        L += mw == -INFINITY ? 0.f : sh.ml[w][orow][1] * expf((mw - M) * p.scale);
     }
     const float inv = PARTIAL ? 1.f : 1.f / L;
     const int64_t slot = PARTIAL ? it.reserved + orow : it.q_start + orow;
@@ -114,13 +106,13 @@ __device__ __forceinline__ bool store_rows(const AttnParams &p, const pevlm_work
 // The same four rows with plain multiply-adds, over the keys that a row sees and no others: one row after the other, lanes
 // over the keys for the scores and over head_dim for the values.  Taken where infinite or invalid numbers are about.
 template <int D, bool PARTIAL>
-__device__ __forceinline__ void attn_f32_rows(const AttnParams &p, const pevlm_work_item &it, int32_t h, int32_t g, F32Shared<D> &sh)
+__device__ __forceinline__ void attn_f32_rows(const AttnParams &p, const pevlm_work_item &it, int32_t h, int32_t g, F32Row<D> *rows)
 {
     constexpr int DV = D / 64;
     const int32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int32_t Hq = p.n_q_heads, Hkv = p.n_kv_heads;
     const float *Q = (const float *)p.q, *K = (const float *)p.k, *V = (const float *)p.v;
-    float *const q_s = sh.row[wave].q, *const w_s = sh.row[wave].w;
+    float *const q_s = rows[wave].q, *const w_s = rows[wave].w;
     auto exchanged = [] {  // what a lane has written to the wavefront's own LDS is read by its other lanes
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -178,173 +170,6 @@ __device__ __forceinline__ void attn_f32_rows(const AttnParams &p, const pevlm_w
             }
         }
     }
-}
-
-// Two heads h[0], h[1] of KV head g; returns the heads (bit 0, bit 1) whose rows of this wavefront are still to be done.  Column c = lane % 32: row c % 16 of head c / 16; the lane's half (lane / 32)
-// is the k index.  Step j of group i of Q K^T contracts head_dim 8 i + 4 half + j; the lane's score v belongs
-// to key (v & 3) + 8 (v >> 2) + 4 half of the tile; row r of block b of O^T is head_dim DB r + b.
-template <int D, bool PARTIAL>
-__device__ __forceinline__ int32_t attn_f32_pair(const AttnParams &p, const pevlm_work_item &it, const int32_t (&h)[2], int32_t g, int32_t u, F32Shared<D> &sh)
-{
-    constexpr int KT = 32, KI = D / 8, DB = D / 32;
-    typedef __attribute__((ext_vector_type(DB))) float f32xdb;
-    const int32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int32_t r16 = lane & 15, mine = (lane >> 4) & 1, half = lane >> 5;
-    const int32_t Hq = p.n_q_heads, Hkv = p.n_kv_heads;
-    const int32_t row = it.q_start + (r16 < it.q_rows ? r16 : it.q_rows - 1);
-    const float *const q = (const float *)p.q + ((int64_t)row * Hq + (mine ? h[1] : h[0])) * D + 4 * half;
-    // a lane's address inside a tile is a 32-bit byte offset from the tile's first row (at most 32 rows further)
-    const uint32_t kv_row = (uint32_t)(Hkv * D * 4);
-
-#pragma unroll
-    for (int i = 0; i < KI / NW; ++i) sh.q[wave * (KI / NW) + i][lane] = *reinterpret_cast<const f32x4 *>(q + 8 * (wave * (KI / NW) + i));
-    float m = -INFINITY, l = 0.f;
-    f32x16 o[DB];
-#pragma unroll
-    for (int b = 0; b < DB; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o[b][i] = 0.f;
-
-    // A tile is four stages of 32 MFMAs: the two halves of K's head_dim, the two halves of the keys of V.  The loads
-    // of a stage are issued before the MFMAs of the stage ahead of it (the first one's during the last stage
-    // of the tile before), into the buffer that the stage before that has left.
-    constexpr int KH = KI / 2;
-    f32x4 kbuf[2][KH];
-    f32xdb vbuf[2][8];
-    const int32_t n_full = ceil_div(it.full_len, KT), n_tiles = n_full + ceil_div(it.diag_len, KT);
-    int32_t k0 = 0, last = 0;  // first key of the tile, its last key relative to that
-    const char *kt = nullptr, *vt = nullptr;  // row k0 of the KV head
-    auto tile_range = [&](int32_t t) {
-        const bool own = t >= n_full;
-        k0 = own ? it.diag_start + (t - n_full) * KT : it.full_start + t * KT;
-        const int32_t kend = own ? it.diag_start + it.diag_len : it.full_start + it.full_len;
-        last = (kend - k0 < KT ? kend - k0 : KT) - 1;
-        kt = (const char *)p.k + ((int64_t)k0 * Hkv + g) * D * 4;
-        vt = (const char *)p.v + ((int64_t)k0 * Hkv + g) * D * 4;
-    };
-    auto load_k = [&](int hf) {
-        const uint32_t off = (uint32_t)((lane & 31) < last ? lane & 31 : last) * kv_row + 16 * half;
-#pragma unroll
-        for (int i = 0; i < KH; ++i) kbuf[hf][i] = *reinterpret_cast<const f32x4 *>(kt + (off + (hf * KH + i) * 32));
-    };
-    auto load_v = [&](int hf) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int32_t kl = (u & 3) + 8 * (2 * hf + (u >> 2)) + 4 * half;
-            vbuf[hf][u] = *reinterpret_cast<const f32xdb *>(vt + ((uint32_t)(kl < last ? kl : last) * kv_row + 4 * DB * (lane & 31)));
-        }
-    };
-    const int32_t t_first = first_tile(it, u, wave);
-    const float c_log2 = p.scale * 1.4426950408889634f;
-    if (t_first < n_tiles) {
-        tile_range(t_first);
-        load_k(0);
-    }
-    __syncthreads();  // the queries are in LDS
-    for (int32_t t = t_first; t < n_tiles; t += NW) {
-        const bool causal = t >= n_full;
-        f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, s2 = s;
-        auto scores = [&](int hf) {
-#pragma unroll
-            for (int i = 0; i < KH; ++i) {
-                const f32x4 qf = sh.q[hf * KH + i][lane];
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kbuf[hf][i][0], qf[0], s, 0, 0, 0);
-                s2 = __builtin_amdgcn_mfma_f32_32x32x2f32(kbuf[hf][i][1], qf[1], s2, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kbuf[hf][i][2], qf[2], s, 0, 0, 0);
-                s2 = __builtin_amdgcn_mfma_f32_32x32x2f32(kbuf[hf][i][3], qf[3], s2, 0, 0, 0);
-            }
-        };
-        load_k(1);
-        __builtin_amdgcn_sched_barrier(0);
-        scores(0);
-        load_v(0);
-        __builtin_amdgcn_sched_barrier(0);
-        scores(1);
-        load_v(1);
-        __builtin_amdgcn_sched_barrier(0);
-        s += s2;
-        if (last < KT - 1 || (causal && k0 + KT - 1 > it.q_start)) {  // the range ends in the tile, or the diagonal runs through it
-            const int32_t lim = (causal && row - k0 < last ? row - k0 : last) - 4 * half;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) s[v] = (v & 3) + 8 * (v >> 2) <= lim ? s[v] : -INFINITY;
-        }
-        float psum = 0.f;
-        f32x16 w;
-        if (t != t_first) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                w[v] = weight_of(s[v] - m, c_log2);  // no key seen yet: m = -inf makes the sum inf or invalid
-                psum += w[v];
-            }
-        }
-        const int32_t up = t == t_first || !(psum < kSumBound) || m == -INFINITY;
-        if (__any(up)) {
-            float mx = s[0];
-#pragma unroll
-            for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
-            mx = fmaxf(mx, other_half(mx));
-            const float m_new = up | __shfl_xor(up, 32) ? fmaxf(m, mx) : m;
-            const float m_use = m_new == -INFINITY ? 0.f : m_new;  // no visible key yet: all weights come out 0
-            psum = 0.f;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                w[v] = weight_of(s[v] - m_use, c_log2);
-                psum += w[v];
-            }
-            if (t != t_first) {
-                const float alpha = weight_of(m - m_use, c_log2);  // m = -inf gives 0
-                l *= alpha;
-#pragma unroll
-                for (int b = 0; b < DB; ++b)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) o[b][i] *= alpha;
-            }
-            m = m_new;
-        }
-        l += psum;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-#pragma unroll
-            for (int b = 0; b < DB; ++b) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(vbuf[0][u][b], w[u], o[b], 0, 0, 0);
-        if (t + NW < n_tiles) {
-            tile_range(t + NW);
-            load_k(0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-#pragma unroll
-            for (int b = 0; b < DB; ++b) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(vbuf[1][u][b], w[8 + u], o[b], 0, 0, 0);
-    }
-
-    // ---- join the wavefronts: common maximum per row, values scaled to it and added through LDS
-    l += __shfl_xor(l, 32);
-    if (half == 0) {
-        sh.ml[wave][mine][r16][0] = m;
-        sh.ml[wave][mine][r16][1] = l;
-    }
-    __syncthreads();
-    float M = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) M = fmaxf(M, sh.ml[w][mine][r16][0]);
-    const float f = m == -INFINITY ? 0.f : expf((m - M) * p.scale);
-    int32_t left = 0;
-#pragma unroll
-    for (int n = 0; n < 2; ++n) {
-        if (mine == n) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                f32xdb x;
-#pragma unroll
-                for (int b = 0; b < DB; ++b) x[b] = o[b][v] * f;
-                *reinterpret_cast<f32xdb *>(&sh.o[wave][r16][DB * ((v & 3) + 8 * (v >> 2) + 4 * half)]) = x;
-            }
-        }
-        __syncthreads();
-        if (!store_rows<D, PARTIAL>(p, it, h[n], n, sh)) left |= 1 << n;
-        if (n == 0) __syncthreads();
-    }
-    return left;
 }
 
 // One head on 16 columns: lane % 16 is the row, lane / 16 the k index; step j of group i of Q K^T contracts
@@ -453,13 +278,13 @@ __device__ __forceinline__ int32_t attn_f32_single(const AttnParams &p, const pe
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
     if (kq == 0) {
-        sh.ml[wave][0][r16][0] = m;
-        sh.ml[wave][0][r16][1] = l;
+        sh.ml[wave][r16][0] = m;
+        sh.ml[wave][r16][1] = l;
     }
     __syncthreads();
     float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) M = fmaxf(M, sh.ml[w][0][r16][0]);
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, sh.ml[w][r16][0]);
     const float f = m == -INFINITY ? 0.f : expf((m - M) * p.scale);
 #pragma unroll
     for (int hh = 0; hh < VH; ++hh)
@@ -468,66 +293,371 @@ __device__ __forceinline__ int32_t attn_f32_single(const AttnParams &p, const pe
             *reinterpret_cast<f32x4 *>(&sh.o[wave][r16][64 * hh + 16 * kq + 4 * v]) =
                 f32x4{o[4 * hh][v] * f, o[4 * hh + 1][v] * f, o[4 * hh + 2][v] * f, o[4 * hh + 3][v] * f};
     __syncthreads();
-    return store_rows<D, PARTIAL>(p, it, h, 0, sh) ? 0 : 1;
+    return store_rows<D, PARTIAL>(p, it, h, sh) ? 0 : 1;
+}
+
+// ---------------------------------------------------------------- all heads of a KV group, on bf16 matrix instructions
+// Every fp32 value is the sum of three bf16 ones, to the last bit: x = x1 + x2 + x3, each the rounding of what the ones before
+// leave, each at most 2^-9 of the one before.  A product is then x1 y1 + (x1 y2 + x2 y1) + (x1 y3 + x2 y2 + x3 y1), bf16
+// products that are exact in fp32, but for 2^-26 of it.
+struct Planes {
+    u32x4 x[3];  // eight values each
+};
+__device__ __forceinline__ Planes split8(const f32x4 &a, const f32x4 &b)
+{
+    Planes r;
+    float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+#pragma unroll
+    for (int n = 0; n < 3; ++n)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const uint32_t u = weight_pair(x[2 * w], x[2 * w + 1]);
+            r.x[n][w] = u;
+            if (n < 2) {
+                x[2 * w] -= __uint_as_float(u << 16);
+                x[2 * w + 1] -= __uint_as_float(u & 0xffff0000u);
+            }
+        }
+    return r;
+}
+__device__ __forceinline__ f32x16 mfma_bf16(const u32x4 &a, const u32x4 &b, const f32x16 &c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+constexpr int kGroupColumns = 128;  // (row, head) pairs of a workgroup, 32 to a wavefront
+constexpr int kGroupKeys = 32;      // keys of a tile
+template <int D>
+union F32GroupShared {
+    struct {
+        uint8_t k[3][kGroupKeys * D * 2], v[3][kGroupKeys * D * 2];  // the planes of a tile, laid out as a bf16 tile
+        u32x4 q3[NW][D / 16][64];                                    // third planes of the queries
+    };
+    struct {
+        float o[kGroupColumns][D + 4];  // rows on their way out
+        F32Row<D> row[NW];
+        uint32_t left[kMaxHeads / 32];  // heads whose rows are to be done again
+    };
+};
+static_assert(2 * sizeof(F32GroupShared<128>) <= 160 * 1024, "two workgroups on a compute unit");
+
+// One work item for 128 of its (row, head) pairs, head fastest (16 rows of up to 8 heads: all of them).  A tile's K is split
+// behind the values of the tile before, its V behind its scores; the two workgroups of a compute unit take matrix
+// instructions and splitting in an order of their own.
+template <int D, bool PARTIAL>
+__device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_work_item &it, int32_t g, int32_t inner, int32_t turn, F32GroupShared<D> &sh)
+{
+    using C = TileCfg<D>;
+    constexpr int KT = kGroupKeys, ROWB = C::ROWB, CH = C::CH, KS = C::KSTEPS, DBLK = C::DBLK, VSW = C::VSW;
+    constexpr int THREADS = NW * 64, NCH = KT * CH / THREADS;  // chunks of 8 values that a lane stages of a tile
+    const int32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int32_t l32 = lane & 31, g32 = lane >> 5;
+    const int32_t Hq = p.n_q_heads, Hkv = p.n_kv_heads, G = Hq / Hkv;
+    const int32_t n_pairs = it.q_rows * G, pair0 = inner * kGroupColumns, col0 = pair0 + (wave + turn) % NW * 32;
+    if (pair0 >= n_pairs) return;  // an item with fewer rows than the launch's longest
+    const bool active = col0 < n_pairs;
+    const int32_t my_pair = min(col0 + l32, n_pairs - 1);
+    const int32_t my_row = it.q_start + my_pair / G;
+    const int32_t my_head = p.heads.head_order[g * G + my_pair % G];
+    const int32_t w_lo = it.q_start + min(col0, n_pairs - 1) / G, w_hi = it.q_start + min(col0 + 31, n_pairs - 1) / G;
+
+    LaneOff L;
+    L.g32 = g32;
+    L.k_row_off = l32 * ROWB;
+    L.k_swz = l32 & (CH - 1);
+    L.v_row_off = (g32 * 4 + ((lane & 15) >> 2)) * ROWB + (lane & 1) * 8;
+    L.v_ch_lo = ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
+    L.v_swz = (lane >> 2) & VSW;
+
+    const int32_t n_full = ceil_div(it.full_len, KT);
+    const int32_t wg_hi = it.q_start + min(pair0 + kGroupColumns - 1, n_pairs - 1) / G;
+    const int32_t n_diag = wg_hi >= it.diag_start ? min(ceil_div(it.diag_len, KT), (wg_hi - it.diag_start) / KT + 1) : 0;
+    const int32_t n_tiles = n_full + n_diag;
+    auto tile_range = [&](int32_t t, int32_t &k0, int32_t &kend) {
+        const bool own = t >= n_full;
+        k0 = own ? it.diag_start + (t - n_full) * KT : it.full_start + t * KT;
+        kend = own ? it.diag_start + it.diag_len : it.full_start + it.full_len;
+    };
+
+    // ---- staging: a lane reads 8 values of a row (keys past the range repeat its last one) and writes 16 bytes of each plane
+    const int32_t ch = tid % CH, srow = tid / CH;
+    f32x4 raw[NCH][2];
+    auto load_raw = [&](const void *base, int32_t t) {
+        int32_t k0, kend;
+        tile_range(t, k0, kend);
+        const char *const first = (const char *)base + ((int64_t)k0 * Hkv + g) * D * 4;
+        const int32_t last = min(KT, kend - k0) - 1;
+#pragma unroll
+        for (int j = 0; j < NCH; ++j) {
+            const f32x4 *src = reinterpret_cast<const f32x4 *>(first + ((uint32_t)min(srow + j * (THREADS / CH), last) * (uint32_t)(Hkv * D * 4) + ch * 32));
+            raw[j][0] = src[0];
+            raw[j][1] = src[1];
+        }
+    };
+    auto stage = [&](uint8_t (&planes)[3][KT * ROWB], bool is_v) {
+#pragma unroll
+        for (int j = 0; j < NCH; ++j) {
+            const int32_t r = srow + j * (THREADS / CH);
+            const int32_t at = r * ROWB + ((ch ^ (is_v ? (r & VSW) << 2 : r & (CH - 1))) << 4);
+            const Planes x = split8(raw[j][0], raw[j][1]);
+#pragma unroll
+            for (int n = 0; n < 3; ++n) *reinterpret_cast<u32x4 *>(planes[n] + at) = x.x[n];
+        }
+    };
+    // everybody's LDS writes have landed and everybody has read what comes next to be overwritten
+    auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+    // ---- queries: planes 1 and 2 in registers, plane 3 in LDS
+    u32x4 q1[KS], q2[KS];
+    if (n_tiles > 0) load_raw(p.k, 0);
+    {
+        const f32x4 *q = reinterpret_cast<const f32x4 *>((const float *)p.q + ((int64_t)my_row * Hq + my_head) * D + 8 * g32);
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+            const Planes x = split8(q[kk * 4], q[kk * 4 + 1]);
+            q1[kk] = x.x[0];
+            q2[kk] = x.x[1];
+            sh.q3[wave][kk][lane] = x.x[2];
+        }
+    }
+    if (n_tiles > 0) {
+        stage(sh.k, false);
+        load_raw(p.v, 0);
+    }
+    barrier();
+
+    float m = -INFINITY, l = 0.f;
+    const float c_log2 = p.scale * 1.4426950408889634f;
+    f32x16 o[DBLK];
+#pragma unroll
+    for (int b = 0; b < DBLK; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[b][i] = 0.f;
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int32_t t = 0; t < n_tiles; ++t) {
+        int32_t k0, kend;
+        tile_range(t, k0, kend);
+        const bool causal = t >= n_full, work = active && !(causal && k0 > w_hi);
+        // ---- scores; V of this tile goes to LDS.  The products of second and third planes are summed by themselves.
+        f32x16 s = zero;
+        if (work) {
+            f32x16 lo = zero;
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) {
+                const int32_t at = L.k_row_off + (((kk * 2 + g32) ^ L.k_swz) << 4);
+                const u32x4 k1 = *reinterpret_cast<const u32x4 *>(sh.k[0] + at), k2 = *reinterpret_cast<const u32x4 *>(sh.k[1] + at);
+                const u32x4 k3 = *reinterpret_cast<const u32x4 *>(sh.k[2] + at), q3 = sh.q3[wave][kk][lane];
+                s = mfma_bf16(k1, q1[kk], s);
+                lo = mfma_bf16(k1, q2[kk], lo);
+                lo = mfma_bf16(k2, q1[kk], lo);
+                lo = mfma_bf16(k2, q2[kk], lo);
+                lo = mfma_bf16(k1, q3, lo);
+                lo = mfma_bf16(k3, q1[kk], lo);
+            }
+            s += lo;
+        }
+        stage(sh.v, true);
+        if (t + 1 < n_tiles) load_raw(p.k, t + 1);
+        barrier();
+        // ---- weights and values; K of the next tile goes to LDS
+        if (work) {
+            if (k0 + KT > kend || (causal && k0 + KT - 1 > w_lo)) {  // the range ends in the tile, or the diagonal runs through it
+                const int32_t lim = (causal && my_row < kend - 1 ? my_row : kend - 1) - k0 - 4 * g32;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) s[v] = (v & 3) + 8 * (v >> 2) <= lim ? s[v] : -INFINITY;
+            }
+            float psum = 0.f;
+            f32x16 w;
+            if (t > 0) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    w[v] = weight_of(s[v] - m, c_log2);  // no key seen yet: m = -inf makes the sum inf or invalid
+                    psum += w[v];
+                }
+            }
+            const int32_t up = t == 0 || !(psum < kSumBound) || m == -INFINITY;
+            if (__any(up)) {
+                float mx = s[0];
+#pragma unroll
+                for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+                mx = fmaxf(mx, other_half(mx));
+                const float m_new = up | __shfl_xor(up, 32) ? fmaxf(m, mx) : m;
+                const float m_use = m_new == -INFINITY ? 0.f : m_new;  // no visible key yet: all weights come out 0
+                psum = 0.f;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    w[v] = weight_of(s[v] - m_use, c_log2);
+                    psum += w[v];
+                }
+                if (t > 0) {
+                    const float alpha = weight_of(m - m_use, c_log2);  // m = -inf gives 0
+                    l *= alpha;
+#pragma unroll
+                    for (int b = 0; b < DBLK; ++b)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) o[b][i] *= alpha;
+                }
+                m = m_new;
+            }
+            l += psum;
+            // A tile's values are summed from zero and added to those before: one rounding at their size a tile instead of twelve.
+            Planes w8[2];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+                w8[ks] = split8(f32x4{w[8 * ks], w[8 * ks + 1], w[8 * ks + 2], w[8 * ks + 3]},
+                                f32x4{w[8 * ks + 4], w[8 * ks + 5], w[8 * ks + 6], w[8 * ks + 7]});
+#pragma unroll
+            for (int b = 0; b < DBLK; ++b) {
+                f32x16 sum = zero;
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    u32x4 v[3];
+#pragma unroll
+                    for (int n = 0; n < 3; ++n) v[n] = __builtin_bit_cast(u32x4, read_v_one<D>(sh.v[n], L, ks, b));
+                    sum = mfma_bf16(v[0], w8[ks].x[0], sum);
+                    sum = mfma_bf16(v[0], w8[ks].x[1], sum);
+                    sum = mfma_bf16(v[1], w8[ks].x[0], sum);
+                    sum = mfma_bf16(v[1], w8[ks].x[1], sum);
+                    sum = mfma_bf16(v[0], w8[ks].x[2], sum);
+                    sum = mfma_bf16(v[2], w8[ks].x[0], sum);
+                }
+                o[b] += sum;
+            }
+        }
+        if (t + 1 < n_tiles) {
+            stage(sh.k, false);
+            load_raw(p.v, t + 1);
+        }
+        barrier();
+    }
+
+    // ---- rows out through LDS, D/4 lanes a row
+    l += other_half(l);
+    if (tid < kMaxHeads / 32) sh.left[tid] = 0u;
+    barrier();
+    const bool live = col0 + l32 < n_pairs;
+    const float inv = PARTIAL ? 1.f : 1.f / l;
+    float wrong = 0.f;  // stays 0 while every value is finite
+#pragma unroll
+    for (int b = 0; b < DBLK; ++b)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+            f32x4 x = {o[b][i4 * 4], o[b][i4 * 4 + 1], o[b][i4 * 4 + 2], o[b][i4 * 4 + 3]};
+            x *= inv;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) wrong = fmaf(x[j], 0.f, wrong);
+            *reinterpret_cast<f32x4 *>(&sh.o[wave * 32 + l32][b * 32 + i4 * 8 + g32 * 4]) = x;
+        }
+    if (live && wrong != 0.f) atomicOr(&sh.left[my_pair % G / 32], 1u << (my_pair % G % 32));
+    const int64_t slot = (int64_t)(PARTIAL ? it.reserved + my_pair / G : my_row) * Hq + my_head;
+    if (live && g32 == 0) {
+        if (PARTIAL) {
+            p.part_ml[slot * 2] = m;
+            p.part_ml[slot * 2 + 1] = l;
+        } else if (p.lse) {
+            p.lse[slot] = m * p.scale + logf(l);
+        }
+    }
+    barrier();
+    constexpr int LPR = D / 4;
+#pragma unroll
+    for (int j = 0; j < 32; j += 64 / LPR) {
+        const int32_t c = j + lane / LPR, c_slot_lo = __shfl((int32_t)(uint32_t)slot, c), c_slot_hi = __shfl((int32_t)(slot >> 32), c);
+        const int64_t row = ((int64_t)c_slot_hi << 32) | (uint32_t)c_slot_lo;
+        if (col0 + c < n_pairs)
+            *reinterpret_cast<f32x4 *>((PARTIAL ? p.part_acc : (float *)p.out) + row * D + lane % LPR * 4) = *reinterpret_cast<const f32x4 *>(&sh.o[wave * 32 + c][lane % LPR * 4]);
+    }
+    for (int32_t j = 0; j < G; ++j)
+        if (sh.left[j / 32] >> (j % 32) & 1) attn_f32_rows<D, PARTIAL>(p, it, p.heads.head_order[g * G + j], g, sh.row);
 }
 
 }  // namespace
 
-// Logical workgroup ids run over (KV head, item, unit of the KV head's query heads), and every XCD (workgroup b
+// how a launch's items are shared out
+struct F32Shares {
+    int32_t items;      // items of a workgroup (a batch): more than one where a group has few heads
+    int32_t step;       // list distance of items that may continue each other: a question's splits lie between its row tiles
+    int32_t n_batches, units, stride, cus_per_xcd;
+};
+
+// Logical workgroup ids run over (KV head, batch of items, unit of the KV head's query heads), and every XCD (workgroup b
 // runs on XCD b % 8) gets one contiguous run of them, so that its L2 holds the keys it works on.  Items
 // are taken last first (the later tiles of a block are the longer ones), and where several XCDs share a KV
-// head, every `stride`-th item in turn, so that each gets as many long ones.  With pairs != 0 unit u takes query
-// heads 2u and 2u + 1 (the last one alone if their number is odd), which share every K and V load; otherwise
-// one head each.
-template <int D, bool PARTIAL>
-__global__ __launch_bounds__(256, 2) void attn_f32_kernel(AttnParams p, int32_t n_logical, int32_t units, int32_t pairs,
-                                                          int32_t stride)
+// head, every `stride`-th item in turn, so that each gets as many long ones.  Units: one head each, or (GROUP) 128 (row, head) pairs.
+template <int D, bool PARTIAL, bool GROUP>
+__global__ __launch_bounds__(256, 2) void attn_f32_kernel(AttnParams p, int32_t n_logical, F32Shares gs)
 {
-    __shared__ F32Shared<D> sh;
-    const int32_t logical = (int32_t)(blockIdx.x & 7) * (int32_t)(gridDim.x >> 3) + (int32_t)(blockIdx.x >> 3);
+    __shared__ __attribute__((aligned(1024))) std::conditional_t<GROUP, F32GroupShared<D>, F32Shared<D>> sh;
+    const int32_t per_xcd = gridDim.x >> 3;
+    int32_t place = blockIdx.x >> 3;
+    const int32_t layer = place / gs.cus_per_xcd;  // the compute units get their first workgroups in layers: a long and a short one
+    if (GROUP && layer == 1) place = gs.cus_per_xcd + min(2 * gs.cus_per_xcd, per_xcd) - 1 - place;
+    const int32_t logical = (int32_t)(blockIdx.x & 7) * per_xcd + place;
     if (logical >= n_logical) return;
-    const int32_t u = logical % units, outer = logical / units;  // outer: (group of units, item)
-    const int32_t group = outer / p.n_items, j = outer % p.n_items;
-    const int32_t full = p.n_items / stride * stride;  // items dealt out in `stride` runs; the few others come last
-    const int32_t idx = p.n_items - 1 - (j < full ? j % (full / stride) * stride + j / (full / stride) : j);
-    pevlm_work_item it;
-    if (p.inline_items.mode) {
-        it = inline_item(p.inline_items, idx);
+    const int32_t u = logical % gs.units, outer = logical / gs.units;  // outer: (group of units, item or items)
+    const int32_t group = outer / gs.n_batches, j = outer % gs.n_batches;
+    const int32_t full = gs.n_batches / gs.stride * gs.stride;  // dealt out in `stride` runs; the few others come last
+    const int32_t batch = gs.n_batches - 1 - (j < full ? j % (full / gs.stride) * gs.stride + j / (full / gs.stride) : j);
+    auto item = [&](int32_t idx) {
+        if (!p.inline_items.mode) return p.items[idx];
+        const pevlm_work_item it = inline_item(p.inline_items, idx);
         if (group == 0 && u == 0 && threadIdx.x == 0) p.items[idx] = it;
+        return it;
+    };
+    if constexpr (GROUP) {
+        // the items of the batch, those that continue each other in one go: a region's rows, or a question's for the same keys
+        int32_t idx = batch % gs.step + batch / gs.step * gs.step * gs.items;
+        pevlm_work_item next = item(idx);
+        for (int32_t left = gs.items; left > 0;) {
+            pevlm_work_item it = next;
+            while (--left > 0 && (idx += gs.step) < p.n_items) {
+                next = item(idx);
+                if (next.q_start != it.q_start + it.q_rows || next.diag_start != it.diag_start || next.full_start != it.full_start || next.full_len != it.full_len) break;
+                it.q_rows += next.q_rows;
+                it.diag_len = next.diag_len;
+            }
+            attn_f32_group<D, PARTIAL>(p, it, group, u, 2 * layer, sh);
+            if (idx >= p.n_items) break;
+            if (left > 0) __syncthreads();
+        }
     } else {
-        it = p.items[idx];
-    }
-    // Each kind of workgroup keeps its own branch to the end: with the rows that are left joined behind both, the compiler
-    // makes the one-head kernel slower (842 tokens x 4/1 heads x 128: 24 us, 13 as here).
-    if (pairs) {
-        const int32_t G = p.n_q_heads / p.n_kv_heads;
-        const int32_t h[2] = {p.heads.head_order[group * G + 2 * u], p.heads.head_order[group * G + (2 * u + 1 < G ? 2 * u + 1 : 2 * u)]};
-        int32_t left;
-        if (2 * u + 1 < G) left = attn_f32_pair<D, PARTIAL>(p, it, h, group, u, sh);
-        else left = attn_f32_single<D, PARTIAL>(p, it, h[0], group, u, sh);
-        for (int32_t n = 0; left >> n; ++n)
-            if (left >> n & 1) attn_f32_rows<D, PARTIAL>(p, it, n ? h[1] : h[0], group, sh);
-    } else {
-        const int32_t h = p.heads.head_order[group * units + u], g = p.heads.kv_of_q[h];
-        if (attn_f32_single<D, PARTIAL>(p, it, h, g, u, sh)) attn_f32_rows<D, PARTIAL>(p, it, h, g, sh);
+        const pevlm_work_item it = item(batch);
+        const int32_t h = p.heads.head_order[group * gs.units + u], g = p.heads.kv_of_q[h];
+        if (attn_f32_single<D, PARTIAL>(p, it, h, g, u, sh)) attn_f32_rows<D, PARTIAL>(p, it, h, g, sh.row);
     }
 }
 
 hipError_t launch_attn_f32(const AttnParams &p, int32_t D, bool partial, int32_t compute_units, hipStream_t stream)
 {
-    // Two heads per workgroup halve the K and V traffic and use the faster instruction; one head per workgroup
-    // has the shorter chain (104 tokens, 2 heads: 5.4 us against 6.7), and is taken where that alone leaves
-    // the chip unfilled.
     const int32_t G = p.n_q_heads / p.n_kv_heads;
     bool uniform = true;
     for (int32_t i = 0; i < p.n_q_heads; ++i)
         if (p.heads.kv_of_q[p.heads.head_order[i]] != i / G) uniform = false;
-    const int32_t pairs = uniform && G > 1 && (int64_t)p.n_items * p.n_q_heads > 2 * (int64_t)compute_units;
-    const int32_t units = pairs ? (G + 1) / 2 : (uniform ? G : p.n_q_heads);  // per KV head, or per item if their groups differ
-    const int32_t n_logical = p.n_items * units * (pairs || uniform ? p.n_kv_heads : 1);
-    const int32_t stride = uniform && p.n_kv_heads <= 4 ? std::min(8 / p.n_kv_heads, p.n_items) : 1;
-    const dim3 grid((n_logical + 7) / 8 * 8), block(256);
-#define PEVLM_F32_LAUNCH(DD, PP) hipLaunchKernelGGL((attn_f32_kernel<DD, PP>), grid, block, 0, stream, p, n_logical, units, pairs, stride)
+    F32Shares gs;
+    gs.cus_per_xcd = std::max(1, compute_units / 8);
+    gs.step = p.num_splits;
+    gs.items = 1;
+    // All heads of a group together, and for small groups as many items as columns go, while that leaves every compute unit
+    // a workgroup and half of them a second one (111 items x 32/8 heads: two together 107 us, one by one 136).  With fewer
+    // workgroups than compute units one head at a time has the shorter chain (us, all heads against one: 28/4 heads, 84
+    // workgroups 24.5 / 18.4, 168 40.1 / 36.1, 284 58.7 / 70.0; 14/2 x 64, 142 31.3 / 24.2, 222 60.0 / 60.4, 346 82 / 99),
+    // and with less than half of the columns filled it does more per instruction.
+    const int64_t cus = compute_units;
+    const auto batches = [&](int32_t items) { return ceil_div(p.n_items / gs.step, items) * gs.step; };
+    while (kRows * G * gs.items * 2 <= kGroupColumns && 2 * (int64_t)batches(gs.items * 2) * p.n_kv_heads >= 3 * cus) gs.items *= 2;
+    const int32_t group_units = ceil_div(kRows * G * gs.items, kGroupColumns);
+    const bool groups = uniform && G > 1 && kRows * G * gs.items >= kGroupColumns / 2 && (int64_t)batches(gs.items) * group_units * p.n_kv_heads >= cus;
+    if (!groups) gs.items = 1;
+    gs.n_batches = batches(gs.items);
+    gs.units = groups ? group_units : (uniform ? G : p.n_q_heads);  // per KV head, or per item if their groups differ
+    const int32_t n_logical = gs.n_batches * gs.units * (uniform ? p.n_kv_heads : 1);
+    gs.stride = uniform && p.n_kv_heads <= 4 ? std::min(8 / p.n_kv_heads, gs.n_batches) : 1;
+    const dim3 grid((n_logical + 7) / 8 * 8);
+#define PEVLM_F32_LAUNCH(DD, PP)                                                                                                  \
+    do {                                                                                                                          \
+        if (groups) hipLaunchKernelGGL((attn_f32_kernel<DD, PP, true>), grid, dim3(256), 0, stream, p, n_logical, gs);            \
+        else hipLaunchKernelGGL((attn_f32_kernel<DD, PP, false>), grid, dim3(256), 0, stream, p, n_logical, gs);                  \
+    } while (0)
     if (D == 128) { if (partial) PEVLM_F32_LAUNCH(128, true); else PEVLM_F32_LAUNCH(128, false); }
     else { if (partial) PEVLM_F32_LAUNCH(64, true); else PEVLM_F32_LAUNCH(64, false); }
 #undef PEVLM_F32_LAUNCH

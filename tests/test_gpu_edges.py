@@ -347,3 +347,40 @@ def test_shares_of_the_streaming_kernel(Hq, Hkv, seqs):
         if mine and dealt:
             load = np.where(seg >= 0, cost[seg], 0).sum(axis=1)
             assert load.max() <= max(1.04 * load.mean(), load.mean() + cost[first[x]:first[x + 1]].max())
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,seqs,splits", [
+    (56, 8, 128, [(37, 150, 480, 70)], 13),            # 7 heads: 112 of 128 columns, the last item of 5 rows
+    (64, 8, 64, [(0, 533, 533, 16), (5, 64, 30, 1)], 9),  # 8 heads: every column; a block that ends inside a tile of 32 keys
+    (72, 8, 64, [(16, 90, 300, 33)], 12),              # 9 heads: two workgroups of an item
+    (64, 4, 128, [(20, 130, 300, 40)], 16),            # 16 heads: two full ones
+    (64, 16, 64, [(33, 100, 470, 35)], 8),             # 4 heads, items one by one: half of the columns
+    (64, 16, 64, [(33, 135, 860, 50)], 13),            # 4 heads, two items together, regions of an odd number of items
+    (48, 16, 64, [(33, 100, 870, 50)], 12),            # 3 heads, two items together
+    (32, 16, 128, [(0, 70, 1200, 40)], 40),            # 2 heads, two or four items together, short blocks
+    (56, 8, 64, [(7, 60, 100, 17)] * 6, 7),            # a list that is read
+])
+def test_fp32_groups_of_heads(oracle, Hq, Hkv, D, seqs, splits):
+    """The fp32 kernel that takes all heads of a group: column and key remainders, items joined inside a region and not across
+    its end, questions; against the oracle, and windowed questions against the kernel that takes one head (a KV head at
+    a time does not fill the chip)."""
+    w = W.Workload("f32g", 34, "f32", Hq, Hkv, D, 1.0e4, seqs, 1.0)
+    data = W.generate(w)
+    r = run_path(w, data, num_splits=splits, want_lse=True)
+    want, want_lse = oracle.forward(data["q"], data["k"], data["v"], oracle_layout(oracle, w), w.rope_base)
+    got = to_host_f32(r["out"])
+    assert np.isfinite(got).all()
+    print(error_stats(got, want))
+    assert np.max(np.abs(got - want)) <= F32_TOL
+    assert np.max(np.abs(to_host_f32(r["lse"]) - want_lse)) <= 1e-4
+    G, q, k, v = Hq // Hkv, r["q_rot"], r["k_rot"], r["v"]
+    outs = [torch.zeros_like(q), torch.zeros_like(q)]
+    window = [2 - i % 2 for i in range(len(seqs))]
+    P.pevlm_query_attn_window(q, k, v, outs[0], r["lay"], r["heads"], window, num_splits=splits)
+    one = P.Heads(G, 1, D, "f32")
+    for g in range(Hkv):
+        part = torch.zeros_like(q[:, g * G:(g + 1) * G])
+        P.pevlm_query_attn_window(q[:, g * G:(g + 1) * G].contiguous(), k[:, g:g + 1].contiguous(), v[:, g:g + 1].contiguous(), part, r["lay"], one, window,
+                                  num_splits=splits)
+        outs[1][:, g * G:(g + 1) * G] = part
+    assert outs[0].any() and (outs[0] - outs[1]).abs().max() <= F32_TOL

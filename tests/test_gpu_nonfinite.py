@@ -36,6 +36,28 @@ def test_fp32_rows_that_do_not_see_a_bad_key_stay_finite(oracle, Hq, Hkv, D, spl
     assert np.array_equal(np.isfinite(lse), both) and np.abs(lse[both] - want_lse[both]).max() <= 1e-4
 
 
+@pytest.mark.parametrize("Hq,Hkv,D", [(56, 8, 64), (32, 8, 128)])
+@pytest.mark.parametrize("where", ["value", "key"])
+def test_fp32_groups_of_heads_with_bad_keys(oracle, Hq, Hkv, D, where):
+    """The same for the kernel that takes all heads of a group, where a bad key meets the other rows and heads in matrix
+    instructions; the largest finite numbers too, which overflow their first bf16 plane."""
+    seqs = [(21, 100, 430, 37)]
+    w = W.Workload("bad_f32g", 42, "f32", Hq, Hkv, D, 1.0e4, seqs, 1.0)
+    data = W.generate(w)
+    x = data["v" if where == "value" else "k"]
+    for i, t in enumerate([20, 121, 160, 351, 457, 487]):
+        x[t, i % Hkv, (5 * i) % D] = [np.nan, np.inf, -np.inf][i % 3] if where == "value" else np.nan
+    if where == "value":
+        x[300, 7, 3] = 3.4e38
+    r = run_path(w, data, num_splits=11)
+    got = to_host_f32(r["out"])
+    want, _ = oracle.forward(data["q"], data["k"], data["v"], oracle_layout(oracle, w), w.rope_base)
+    fine = np.isfinite(want)
+    assert 0.2 < fine.mean() < 1.0
+    assert np.array_equal(np.isfinite(got), fine)
+    assert (np.abs(got[fine] - want[fine]) <= 1e-5 * np.maximum(1.0, np.abs(want[fine]))).all()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("splits", [1, 2, 9, 64])
