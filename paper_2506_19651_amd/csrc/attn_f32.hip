@@ -356,18 +356,12 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
     const int32_t n_pairs = it.q_rows * G, pair0 = inner * kGroupColumns, col0 = pair0 + (wave + turn) % NW * 32;
     if (pair0 >= n_pairs) return;  // an item with fewer rows than the launch's longest
     const bool active = col0 < n_pairs;
-    const int32_t my_pair = min(col0 + l32, n_pairs - 1);
-    const int32_t my_row = it.q_start + my_pair / G;
-    const int32_t my_head = p.heads.head_order[g * G + my_pair % G];
+    const int32_t my_row = it.q_start + min(col0 + l32, n_pairs - 1) / G;
     const int32_t w_lo = it.q_start + min(col0, n_pairs - 1) / G, w_hi = it.q_start + min(col0 + 31, n_pairs - 1) / G;
 
-    LaneOff L;
-    L.g32 = g32;
-    L.k_row_off = l32 * ROWB;
-    L.k_swz = l32 & (CH - 1);
-    L.v_row_off = (g32 * 4 + ((lane & 15) >> 2)) * ROWB + (lane & 1) * 8;
-    L.v_ch_lo = ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
-    L.v_swz = (lane >> 2) & VSW;
+    // a lane's fragment of k-step kk, or of block b of head_dim: the swizzle's exclusive or goes over bits that the row leaves free
+    const uint32_t k_at = (uint32_t)(l32 * ROWB + ((g32 ^ (l32 & (CH - 1))) << 4));
+    const uint32_t v_at = (uint32_t)((g32 * 4 + ((lane & 15) >> 2)) * ROWB + (lane & 1) * 8 + ((((lane >> 2) & VSW) * 4 + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) << 4));
 
     const int32_t n_full = ceil_div(it.full_len, KT);
     const int32_t wg_hi = it.q_start + min(pair0 + kGroupColumns - 1, n_pairs - 1) / G;
@@ -404,6 +398,16 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
             for (int n = 0; n < 3; ++n) *reinterpret_cast<u32x4 *>(planes[n] + at) = x.x[n];
         }
     };
+    // V^T fragment: 16 keys (k-step ks) x block b of head_dim
+    auto read_v = [&](const uint8_t *plane, int ks, int b) {
+        union {
+            s16x4 part[2];
+            u32x4 all;
+        } r;
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt) r.part[tt] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, plane + (ks * 16 + tt * 8) * ROWB + (v_at ^ (uint32_t)(b << 6))));
+        return r.all;
+    };
     // everybody's LDS writes have landed and everybody has read what comes next to be overwritten
     auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
@@ -411,7 +415,8 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
     u32x4 q1[KS], q2[KS];
     if (n_tiles > 0) load_raw(p.k, 0);
     {
-        const f32x4 *q = reinterpret_cast<const f32x4 *>((const float *)p.q + ((int64_t)my_row * Hq + my_head) * D + 8 * g32);
+        const int32_t head = p.heads.head_order[g * G + min(col0 + l32, n_pairs - 1) % G];
+        const f32x4 *q = reinterpret_cast<const f32x4 *>((const float *)p.q + ((int64_t)my_row * Hq + head) * D + 8 * g32);
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
             const Planes x = split8(q[kk * 4], q[kk * 4 + 1]);
@@ -444,7 +449,7 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
             f32x16 lo = zero;
 #pragma unroll
             for (int kk = 0; kk < KS; ++kk) {
-                const int32_t at = L.k_row_off + (((kk * 2 + g32) ^ L.k_swz) << 4);
+                const uint32_t at = k_at ^ (uint32_t)(kk << 5);
                 const u32x4 k1 = *reinterpret_cast<const u32x4 *>(sh.k[0] + at), k2 = *reinterpret_cast<const u32x4 *>(sh.k[1] + at);
                 const u32x4 k3 = *reinterpret_cast<const u32x4 *>(sh.k[2] + at), q3 = sh.q3[wave][kk][lane];
                 s = mfma_bf16(k1, q1[kk], s);
@@ -513,7 +518,7 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
                 for (int ks = 0; ks < 2; ++ks) {
                     u32x4 v[3];
 #pragma unroll
-                    for (int n = 0; n < 3; ++n) v[n] = __builtin_bit_cast(u32x4, read_v_one<D>(sh.v[n], L, ks, b));
+                    for (int n = 0; n < 3; ++n) v[n] = read_v(sh.v[n], ks, b);
                     sum = mfma_bf16(v[0], w8[ks].x[0], sum);
                     sum = mfma_bf16(v[0], w8[ks].x[1], sum);
                     sum = mfma_bf16(v[1], w8[ks].x[0], sum);
@@ -531,7 +536,11 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
         barrier();
     }
 
-    // ---- rows out through LDS, D/4 lanes a row
+    // ---- rows out through LDS, D/4 lanes a row.  The lane's pair once more, from a lane number that the compiler takes for
+    // another: the registers are full through the loop.
+    int32_t out_lane = lane;
+    asm volatile("" : "+v"(out_lane));
+    const int32_t my_pair = min(col0 + (out_lane & 31), n_pairs - 1), my_head = p.heads.head_order[g * G + my_pair % G];
     l += other_half(l);
     if (tid < kMaxHeads / 32) sh.left[tid] = 0u;
     barrier();
@@ -549,7 +558,7 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
             *reinterpret_cast<f32x4 *>(&sh.o[wave * 32 + l32][b * 32 + i4 * 8 + g32 * 4]) = x;
         }
     if (live && wrong != 0.f) atomicOr(&sh.left[my_pair % G / 32], 1u << (my_pair % G % 32));
-    const int64_t slot = (int64_t)(PARTIAL ? it.reserved + my_pair / G : my_row) * Hq + my_head;
+    const int64_t slot = (int64_t)((PARTIAL ? it.reserved : it.q_start) + my_pair / G) * Hq + my_head;
     if (live && g32 == 0) {
         if (PARTIAL) {
             p.part_ml[slot * 2] = m;
