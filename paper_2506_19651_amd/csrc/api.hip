@@ -475,6 +475,14 @@ static int32_t splits_of_f32(const pevlm_layout *lay, const pevlm_heads *h)
     return splits_of_full_rounds(lay, h, 256, [](int32_t) { return 2; });
 }
 
+// keys of a sequence that its window leaves, the sink apart
+static int32_t window_keys(const pevlm_layout *lay, int32_t s, const Restrict &sel)
+{
+    const int32_t hidden = sel.window_blocks[s] < 0 ? 0 : std::max(0, blocks_of(lay, s) - sel.window_blocks[s]);
+    return lay->cu_seqlens[s + 1] - lay->cu_seqlens[s] - lay->sink_len[s] - (int32_t)std::min<int64_t>((int64_t)hidden * lay->block_len[s], lay->ctx_len[s]);
+}
+
+
 static int32_t predicted_splits(const pevlm_layout *lay, const pevlm_heads *h, const Restrict &sel, int32_t full_rounds)
 {
     const int32_t G = equal_head_groups(h) ? h->n_q_heads / h->n_kv_heads : 1, groups = h->n_q_heads / G;
@@ -496,8 +504,7 @@ static int32_t predicted_splits(const pevlm_layout *lay, const pevlm_heads *h, c
             if (Q == 0) continue;
             int32_t keys = lay->cu_seqlens[s + 1] - lay->cu_seqlens[s], cuts = n;
             if (windowed) {  // the sink is a split of its own
-                const int32_t hidden = sel.window_blocks[s] < 0 ? 0 : std::max(0, blocks_of(lay, s) - sel.window_blocks[s]);
-                keys -= lay->sink_len[s] + (int32_t)std::min<int64_t>((int64_t)hidden * lay->block_len[s], lay->ctx_len[s]);
+                keys = window_keys(lay, s, sel);
                 cuts = n - 1;
             }
             const int32_t len = split_len_of_seq(keys, cuts, kKeyTile), used = ceil_div(keys, len) + (windowed ? 1 : 0);
@@ -531,12 +538,40 @@ static int32_t predicted_splits(const pevlm_layout *lay, const pevlm_heads *h, c
     return best;
 }
 
-static int32_t auto_splits(const pevlm_layout *lay, const pevlm_heads *h, const Restrict &sel = Restrict())
+// Short questions (one tile of rows, 256 (row, head) pairs a KV head) over many keys: a compute unit for every KV head and
+// split, which is what their kernel takes, from 512 keys a split on, and from 768 where the pairs need its upper four wavefronts.
+// us, the time model's count and the one-item kernel / this, 65 K keys: 20 rows x 28/4 heads 46.1 / 41.8, x 32/8 60.9 / 53.3,
+// 64 rows x 32/8 93.1 / 88.3, two of 20 rows over 33 K 71.1 / 54.3; at the lines: 20 rows x 32/8 over 17 K (560 a split)
+// 26.2 / 24.4, 12 K (400) 22.6 / 22.5; 64 rows x 32/8 over 24 K (790) 41.4 / 41.9, 17 K 33.8 / 36.3.
+// With a window the sink is one of the splits.  0: not such a question.
+static int32_t splits_of_short_questions(const pevlm_layout *lay, const pevlm_heads *h, const Restrict &sel)
+{
+    if (h->dtype != PEVLM_BF16 || h->kv_head_of_q || !equal_head_groups(h)) return 0;
+    const int32_t G = h->n_q_heads / h->n_kv_heads;
+    const bool windowed = sel.window_blocks != nullptr;
+    int64_t units = 0;
+    int32_t max_keys = 0, min_keys = INT32_MAX, max_pairs = 0;
+    for (int32_t s = 0; s < lay->num_seqs; ++s) {
+        if (lay->query_len[s] == 0) continue;
+        if (lay->query_len[s] > kTileRowsBf16 || lay->query_len[s] * G > 32 * kQuestionWaves) return 0;
+        max_pairs = std::max(max_pairs, lay->query_len[s] * G);
+        const int32_t keys = windowed ? window_keys(lay, s, sel) : lay->cu_seqlens[s + 1] - lay->cu_seqlens[s];
+        units += h->n_kv_heads;
+        max_keys = std::max(max_keys, keys);
+        min_keys = std::min(min_keys, keys);
+    }
+    if (units == 0 || min_keys < max_keys - max_keys / 4) return 0;
+    const int64_t n = std::min<int64_t>(PEVLM_MAX_SPLITS, compute_units() / units), cuts = windowed ? n - 1 : n;
+    if (cuts < 1 || n < 2 || 4 * n * units < 3 * (int64_t)compute_units()) return 0;
+    return min_keys >= (max_pairs <= 128 ? 512 : 768) * cuts ? (int32_t)n : 0;
+}
+
+static int32_t auto_splits(const pevlm_layout *lay, const pevlm_heads *h, const Restrict &sel = Restrict(), bool short_rule = true)
 {
     const bool f32 = h->dtype == PEVLM_F32, windowed = sel.window_blocks != nullptr;
     const int32_t rounds = splits_of_full_rounds(lay, h, 768, [&](int32_t rows) { return f32 ? 1 : (rows <= 32 ? 4 : (rows <= 64 ? 2 : 1)); });
-    int32_t n = f32 ? splits_of_f32(lay, h)
-                    : predicted_splits(lay, h, sel, std::min(PEVLM_MAX_SPLITS, rounds + (windowed ? 1 : 0)));
+    int32_t n = f32 ? splits_of_f32(lay, h) : (short_rule ? splits_of_short_questions(lay, h, sel) : 0);
+    if (n == 0) n = predicted_splits(lay, h, sel, std::min(PEVLM_MAX_SPLITS, rounds + (windowed ? 1 : 0)));
     const int64_t tiles = count_query_tiles(lay, tile_rows_of(h, true)), total_q = total_query_rows(lay);
     while (n > rounds && carve_query(tiles, total_q, h, n).bytes > kFreeQueryBytes) --n;
     return n;
@@ -549,7 +584,9 @@ static QueryPlan plan_query(const pevlm_layout *lay, const pevlm_heads *h, int32
     int32_t n = num_splits > 0 ? num_splits : auto_splits(lay, h);
     // with a window the sink is a split of its own, the rest of the keys takes at least one more
     if (windowed) {
-        n = std::min(PEVLM_MAX_SPLITS, std::max(2, n + (num_splits > 0 ? 0 : 1)));
+        // (sized for either rule: with its window a call may come under the other one)
+        if (num_splits == 0) n = std::max(n, auto_splits(lay, h, Restrict(), false)) + 1;
+        n = std::min(PEVLM_MAX_SPLITS, std::max(2, n));
         if (num_splits == 0 && sel.window_blocks) n = std::min(n, std::max(2, auto_splits(lay, h, sel)));
     }
     return carve_query(count_query_tiles(lay, tile_rows_of(h, true)), total_query_rows(lay), h, n, fuse_rope);
@@ -784,7 +821,7 @@ static pevlm_status prefill_impl(const void *q, const void *k, const void *v, vo
     p.n_q_heads = heads->n_q_heads;
     p.n_kv_heads = heads->n_kv_heads;
     p.scale = scale_of(heads);
-    hipError_t e = heads->dtype == PEVLM_BF16 ? launch_attn_bf16(p, heads->head_dim, false, hs)
+    hipError_t e = heads->dtype == PEVLM_BF16 ? launch_attn_bf16(p, heads->head_dim, false, compute_units(), hs)
                                                 : launch_attn_f32(p, heads->head_dim, false, compute_units(), hs);
     if (e != hipSuccess) return hip_fail(e, "block-prefill launch");
     return PEVLM_OK;
@@ -1024,7 +1061,7 @@ static pevlm_status query_impl(const void *q, const void *k, const void *v, void
     const bool partial = plan.num_splits > 1;
     p.out = out;
     p.lse = lse;
-    hipError_t e = heads->dtype == PEVLM_BF16 ? launch_attn_bf16(p, heads->head_dim, partial, hs)
+    hipError_t e = heads->dtype == PEVLM_BF16 ? launch_attn_bf16(p, heads->head_dim, partial, compute_units(), hs)
                                               : launch_attn_f32(p, heads->head_dim, partial, compute_units(), hs);
     if (e != hipSuccess) return hip_fail(e, "query split launch");
     if (!partial) return PEVLM_OK;

@@ -1,0 +1,291 @@
+// Split-KV attention of a short question for gfx950 (CDNA4), bf16: the (row, head) pairs of one KV head fit one workgroup, and what
+// bounds the call is how fast the keys and values come from HBM (20 rows x 28/4 heads over 65 K keys: 135 MB, 9 GFLOP).
+//
+// Same work items, tile arithmetic and partials as the one-item kernel (attn_bf16.hip), bit for bit, under another schedule.
+// That one has a tile and a half under way per workgroup of 4 wavefronts, and where every compute unit has one item of its own,
+// or two workgroups that read the same keys, each tile waits for memory (2.0 us of a tile's 2.1 here).  This one has one workgroup of
+// 8 wavefronts to a compute unit, three LDS stages per tensor, K two tiles and V one and a half ahead of the arithmetic: 64 KB
+// under way, and the keys are staged once for up to 256 pairs.
+//
+// Waits.  Loads into LDS complete in issue order per wavefront, and every wavefront issues the same number in every tile
+// (past the last tile the last one again, into a stage that nobody reads): the top of a tile waits until only those of the
+// tile before are outstanding.
+#include "attn_bf16_tile.h"
+#include "rope_math.h"
+
+namespace pevlm {
+
+namespace {
+constexpr int NW = kQuestionWaves;
+constexpr int NST = 3;
+
+template <int NL>
+struct QuestionLoads {
+    const void *base;
+    uint32_t off[NL];
+    uint32_t lds;
+    __device__ __forceinline__ void issue(int j) const { load_lds_16_base(base, off[j], lds + j * NW * 1024); }
+};
+}  // namespace
+
+template <int D, bool ROPEQ>
+__global__ __launch_bounds__(NW * 64, 2) void attn_bf16_question_kernel(AttnParams p, int32_t n_logical, uint32_t group_rcp)
+{
+    using C = TileCfg<D>;
+    constexpr int KT = C::KT, ROWB = C::ROWB, CH = C::CH, KSTEPS = C::KSTEPS, DBLK = C::DBLK;
+    constexpr int VSW = C::VSW, TILEB = C::TILEB, RPI = C::RPI, NL = KT * CH / (64 * NW), WSLICE = 32 * ROWB;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * NST * TILEB + NW * WSLICE];
+    const int32_t per_xcd = gridDim.x >> 3, logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (logical >= n_logical) return;
+    const int32_t g = logical / p.n_items, item_idx = p.n_items - 1 - logical % p.n_items;
+    const int32_t Hq = p.n_q_heads, Hkv = p.n_kv_heads, G = Hq / Hkv;
+    pevlm_work_item it;
+    if (p.inline_items.mode) {
+        it = inline_item(p.inline_items, item_idx);
+        if (g == 0 && threadIdx.x == 0) p.items[item_idx] = it;
+    } else {
+        it = p.items[item_idx];
+    }
+    const int32_t n_pairs = it.q_rows * G;
+
+    const int32_t tid = threadIdx.x, lane = tid & 63;
+    const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int32_t l32 = lane & 31, g32 = lane >> 5;
+    const uint16_t *Q = (const uint16_t *)p.q, *K = (const uint16_t *)p.k, *V = (const uint16_t *)p.v;
+
+    LaneOff L;
+    L.g32 = g32;
+    L.k_row_off = l32 * ROWB;
+    L.k_swz = l32 & (CH - 1);
+    L.v_row_off = (g32 * 4 + ((lane & 15) >> 2)) * ROWB + (lane & 1) * 8;
+    L.v_ch_lo = ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
+    L.v_swz = (lane >> 2) & VSW;
+
+    const int32_t wave_pair0 = wave * 32;
+    const bool wave_active = wave_pair0 < n_pairs;
+    const int32_t my_pair = wave_pair0 + l32 < n_pairs ? wave_pair0 + l32 : n_pairs - 1;
+    const int32_t row_in_item = div_by(my_pair, group_rcp), my_row = it.q_start + row_in_item;
+    const int32_t wr_lo = it.q_start + div_by(wave_active ? wave_pair0 : n_pairs - 1, group_rcp);
+    const int32_t wr_hi = it.q_start + div_by(wave_pair0 + 31 < n_pairs ? wave_pair0 + 31 : n_pairs - 1, group_rcp);
+    const int32_t wg_hi = it.q_start + it.q_rows - 1;
+    const int32_t n_full_tiles = (it.full_len + KT - 1) / KT, n_diag_tiles = (it.diag_len + KT - 1) / KT;
+    const int32_t wg_diag = wg_hi >= it.diag_start ? (wg_hi - it.diag_start) / KT + 1 : 0;
+    const int32_t n_tiles = n_full_tiles + (wg_diag < n_diag_tiles ? wg_diag : n_diag_tiles);
+    int32_t n_w = 0;  // tiles that this wavefront computes
+    if (wave_active) {
+        const int32_t nd = wr_hi >= it.diag_start ? (wr_hi - it.diag_start) / KT + 1 : 0;
+        n_w = n_full_tiles + (nd < n_diag_tiles ? nd : n_diag_tiles);
+    }
+    const uint32_t lds_k_addr = (uint32_t)(size_t)LDS_PTR(void, lds), lds_v_addr = lds_k_addr + NST * TILEB;
+    uint8_t *const lds_k = lds, *const lds_v = lds + NST * TILEB, *const slice = lds + 2 * NST * TILEB + wave * WSLICE;
+    const uint32_t slice_addr = lds_k_addr + 2 * NST * TILEB + wave * WSLICE;
+
+    auto tile_range = [&](int32_t t, int32_t &k0, int32_t &kend) {
+        const bool own = t >= n_full_tiles;
+        k0 = own ? it.diag_start + (t - n_full_tiles) * KT : it.full_start + t * KT;
+        kend = own ? it.diag_start + it.diag_len : it.full_start + it.full_len;
+        return own;
+    };
+    // Loads of a tile: per-lane offsets are fixed but for a tile that runs past its range, whose rows repeat the last key
+    // (their scores are masked, their values stay finite).
+    QuestionLoads<NL> ldk, ldv;
+    auto set_loads = [&](QuestionLoads<NL> &ld, const uint16_t *T, bool is_v, uint32_t lds_addr, int32_t t, int32_t stage) {
+        t = t < n_tiles ? t : n_tiles - 1;
+        int32_t k0, kend;
+        tile_range(t, k0, kend);
+        const int32_t last = kend - k0 < KT ? kend - k0 - 1 : KT - 1;
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+            const int32_t row = (j * NW + wave) * RPI + lane / CH, cpos = lane % CH;
+            const int32_t key = row < last ? row : last;
+            ld.off[j] = (uint32_t)((key * Hkv * D + ((cpos ^ (is_v ? (row & VSW) << 2 : row & (CH - 1))) << 3)) * 2);
+        }
+        ld.base = uniform_ptr(T + ((int64_t)k0 * Hkv + g) * D);
+        ld.lds = lds_addr + stage * TILEB + wave * 1024;
+    };
+    auto burst = [&](const QuestionLoads<NL> &ld) {
+#pragma unroll
+        for (int j = 0; j < NL; ++j) ld.issue(j);
+    };
+
+    f32x4 rope_cs[ROPEQ ? KSTEPS / 2 : 1][4];
+    if (n_tiles > 0) {
+        set_loads(ldk, K, false, lds_k_addr, 0, 0);
+        burst(ldk);
+        set_loads(ldv, V, true, lds_v_addr, 0, 0);
+        burst(ldv);
+        set_loads(ldk, K, false, lds_k_addr, 1, 1);
+        burst(ldk);
+    }
+    {
+        // query rows, whole rows through the wavefront's slice
+        const uint16_t *qbase = uniform_ptr(Q + ((int64_t)it.q_start * Hq + (int64_t)g * G) * D);
+#pragma unroll
+        for (int j = 0; j < WSLICE / 1024; ++j) {
+            const int32_t rl = j * RPI + lane / CH, pair = wave_pair0 + rl < n_pairs ? wave_pair0 + rl : n_pairs - 1;
+            const int32_t r = div_by(pair, group_rcp);
+            load_lds_16_base(qbase, (uint32_t)((r * Hq + pair - r * G) * ROWB + (((lane % CH) ^ (rl & (CH - 1))) << 4)), slice_addr + j * 1024);
+        }
+    }
+    if (ROPEQ) {
+        const int64_t entry = it.reserved % p.rope_compact_rows + row_in_item;
+        const f32x4 *tab = reinterpret_cast<const f32x4 *>(p.rope_tab + entry * D) + g32 * 4;
+#pragma unroll
+        for (int kk = 0; kk < KSTEPS / 2; ++kk)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) rope_cs[kk][j] = tab[kk * 8 + j];
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    asm volatile("" ::: "memory");
+    bf16x8 qf[KSTEPS];
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk) qf[kk] = *reinterpret_cast<const bf16x8 *>(slice + l32 * ROWB + (((kk * 2 + g32) ^ (l32 & (CH - 1))) << 4));
+    if (ROPEQ) {
+#pragma unroll
+        for (int kk = 0; kk < KSTEPS / 2; ++kk) {
+            const f32x4 *cs = rope_cs[kk];
+            const u32x4 lo = __builtin_bit_cast(u32x4, qf[kk]), hi = __builtin_bit_cast(u32x4, qf[kk + KSTEPS / 2]);
+            u32x4 rl, rh;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const float a0 = __uint_as_float(lo[w] << 16), a1 = __uint_as_float(lo[w] & 0xffff0000u);
+                const float b0 = __uint_as_float(hi[w] << 16), b1 = __uint_as_float(hi[w] & 0xffff0000u);
+                float r0, r1, t0, t1;
+                rope_rotate(a0, b0, cs[w][0], cs[w][1], r0, t0);
+                rope_rotate(a1, b1, cs[w][2], cs[w][3], r1, t1);
+                rl[w] = rope_pack_bf16(r0, r1);
+                rh[w] = rope_pack_bf16(t0, t1);
+            }
+            qf[kk] = __builtin_bit_cast(bf16x8, rl);
+            qf[kk + KSTEPS / 2] = __builtin_bit_cast(bf16x8, rh);
+        }
+    }
+
+    const float c_log2 = p.scale * 1.4426950408889634f;
+    float m_ref = -INFINITY, l_run = 0.f, psum = 0.f;
+    f32x16 o[DBLK], s[2];
+#pragma unroll
+    for (int b = 0; b < DBLK; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[b][i] = 0.f;
+    u32x4 pf[4];
+    auto mref = [&] { return m_ref == -INFINITY ? 0.f : m_ref; };
+    auto mask = [&](int32_t t) {
+        int32_t k0, kend;
+        const bool causal = tile_range(t, k0, kend);
+        if ((k0 + KT > kend) || (causal && (k0 + KT - 1 > wr_lo))) mask_tile(s, k0, kend, causal, my_row, g32);
+    };
+    // as in the one-item kernel: a row's reference maximum is raised for its own weights only
+    auto fix_reference = [&] {
+        const int32_t up = sum_reached_step(psum) || m_ref == -INFINITY;
+        if (__any(up)) {
+            const float mx = row_max(s) * c_log2;
+            const bool has = m_ref != -INFINITY;
+            const float m_new = up | __shfl_xor(up, 32) ? fmaxf(m_ref, mx) : m_ref;
+            const float alpha = has ? __builtin_amdgcn_exp2f(m_ref - m_new) : 1.f;
+            m_ref = m_new;
+            psum = 0.f;
+            weights(s, c_log2, mref(), psum, pf);
+            if (__any(has)) {
+                l_run = rounded_product(l_run, alpha);
+#pragma unroll
+                for (int b = 0; b < DBLK; ++b)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) o[b][i] *= alpha;
+            }
+        }
+    };
+    const auto next = [](int32_t st) { return st + 1 < NST ? st + 1 : 0; };
+    const auto before = [](int32_t st) { return st > 0 ? st - 1 : NST - 1; };
+    // loads of tile t's step: K(t + 2) into the stage of K(t - 1), V(t + 1) into that of V(t - 2); st = t % NST
+    auto prepare = [&](int32_t t, int32_t st) {
+        set_loads(ldk, K, false, lds_k_addr, t + 2, before(st));
+        set_loads(ldv, V, true, lds_v_addr, t + 1, next(st));
+    };
+    auto top = [&] {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    int32_t st = 0;  // t % NST of the tile at hand
+    if (n_tiles > 0) {
+        __builtin_amdgcn_s_barrier();  // K(0), V(0) and K(1) of every wavefront have landed
+        asm volatile("" ::: "memory");
+        prepare(0, 0);
+        burst(ldk);
+        burst(ldv);
+    }
+    if (n_w > 0) {
+        qk_tile<D, false, NL>(lds_k, L, qf, s, ldk, [] {}, [] {});
+        mask(0);
+        psum = 0.f;
+        fix_reference();
+        l_run += psum;
+        for (int32_t t = 1; t < n_w; ++t) {
+            st = next(st);
+            top();
+            const uint8_t *const tv = lds_v + before(st) * TILEB;
+            bf16x8 vfirst[kValuesAhead];
+            qk_tile<D, true, NL>(lds_k + st * TILEB, L, qf, s, ldk, [&] { prepare(t, st); }, [&] { first_v<D>(tv, L, vfirst); });
+            mask(t);
+            psum = 0.f;
+            pv_prev_weights_cur<D, NL>(tv, L, pf, o, s, c_log2, mref(), psum, ldv, vfirst);
+            fix_reference();
+            l_run += psum;
+        }
+    }
+    // Every wavefront passes the tops of all tiles and one barrier behind them.  The values of the last tile that a wavefront
+    // computed are added behind the next one, where they have landed.
+    const int32_t last_st = st;
+    bool pending = n_w > 0;
+    for (int32_t t = n_w > 0 ? n_w : 1; t < n_tiles; ++t) {
+        st = next(st);
+        top();
+        prepare(t, st);
+        burst(ldk);
+        burst(ldv);
+        if (pending) {
+            pv_tile<D>(lds_v + last_st * TILEB, L, pf, o);
+            pending = false;
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (pending) pv_tile<D>(lds_v + last_st * TILEB, L, pf, o);
+
+    // ---- partials of the split
+    int32_t out_lane = lane;
+    asm volatile("" : "+v"(out_lane));
+    const int32_t out_pair = wave_pair0 + (out_lane & 31);
+    const float l_tot = l_run + __shfl_xor(l_run, 32);
+    if (out_pair >= n_pairs) return;
+    const int32_t out_row = div_by(out_pair, group_rcp);
+    const int64_t slot = ((int64_t)it.reserved + out_row) * Hq + g * G + out_pair - out_row * G;
+    float *acc = p.part_acc + slot * D;
+#pragma unroll
+    for (int b = 0; b < DBLK; ++b)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+            const f32x4 v4 = {o[b][i4 * 4], o[b][i4 * 4 + 1], o[b][i4 * 4 + 2], o[b][i4 * 4 + 3]};
+            *reinterpret_cast<f32x4 *>(acc + b * 32 + i4 * 8 + g32 * 4) = v4;
+        }
+    if (g32 == 0) {
+        p.part_ml[slot * 2] = m_ref / c_log2;  // back to raw score units (-inf stays)
+        p.part_ml[slot * 2 + 1] = l_tot;
+    }
+}
+
+hipError_t launch_attn_bf16_question(const AttnParams &p, int32_t D, hipStream_t stream)
+{
+    const int32_t n_logical = p.n_items * p.n_kv_heads;
+    const dim3 grid((n_logical + 7) / 8 * 8), block(NW * 64);
+    const uint32_t rcp = reciprocal_of(p.n_q_heads / p.n_kv_heads);
+    const bool rope = p.rope_tab != nullptr;
+    const auto kernel = D == 128 ? (rope ? attn_bf16_question_kernel<128, true> : attn_bf16_question_kernel<128, false>)
+                                 : (rope ? attn_bf16_question_kernel<64, true> : attn_bf16_question_kernel<64, false>);
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, p, n_logical, rcp);
+    return hipGetLastError();
+}
+
+}  // namespace pevlm

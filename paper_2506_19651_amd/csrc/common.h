@@ -542,7 +542,9 @@ hipError_t launch_fp8_quantise(const void *q, const void *k, const void *v, int6
                                uint8_t *q_codes, uint8_t *k_tiles, uint8_t *v_tiles, int32_t compute_units, bool with_q, hipStream_t stream);
 hipError_t launch_attn_fp8(const Fp8Params &p, int32_t D, hipStream_t stream);
 hipError_t launch_attn_f32(const AttnParams &p, int32_t D, bool partial, int32_t compute_units, hipStream_t stream);
-hipError_t launch_attn_bf16(const AttnParams &p, int32_t D, bool partial, hipStream_t stream);  // p.rope_tab selects the fused variant
+hipError_t launch_attn_bf16(const AttnParams &p, int32_t D, bool partial, int32_t compute_units, hipStream_t stream);  // p.rope_tab selects the fused variant
+// partials of a question whose (row, head) pairs of a KV head fit one workgroup, default head map
+hipError_t launch_attn_bf16_question(const AttnParams &p, int32_t D, hipStream_t stream);
 hipError_t launch_merge(const MergeParams &p, hipStream_t stream);
 hipError_t launch_probe_mfma(float *sink, int32_t workgroups, int32_t iters, hipStream_t stream);
 hipError_t launch_probe_copy(void *dst, const void *src, int64_t bytes, hipStream_t stream);
@@ -551,6 +553,7 @@ hipError_t launch_probe_tile_loop(float *sink, const void *kv, int32_t n_tiles, 
 
 constexpr int32_t kTileRowsF32 = 16;   // query rows per work item of the fp32 kernels
 constexpr int32_t kTileRowsBf16 = 128; // query rows per work item of the bf16 MFMA kernels
+constexpr int32_t kQuestionWaves = 8;  // wavefronts (32 (row, head) pairs each) of the kernel for short questions
 constexpr int32_t kKeyTile = 64;       // keys staged per step by the bf16 and fp8 kernels
 constexpr int32_t kFp8TileRows = 128;  // query rows per work item of the fp8 kernel
 

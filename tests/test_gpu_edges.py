@@ -384,3 +384,37 @@ def test_fp32_groups_of_heads(oracle, Hq, Hkv, D, seqs, splits):
                                   num_splits=splits)
         outs[1][:, g * G:(g + 1) * G] = part
     assert outs[0].any() and (outs[0] - outs[1]).abs().max() <= F32_TOL
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,seqs,splits", [
+    (3, 3, 128, [(0, 64, 0, 1)], 64),                                       # one pair, one key, empty splits
+    (7, 1, 128, [(65, 128, 300, 18)], 13),                                  # 126 of 128 pairs; key ranges of part of a tile
+    (8, 2, 64, [(1, 64, 1000, 32), (0, 100, 0, 31), (5, 50, 5000, 1)], 9),  # 128 pairs; sequences of 1 to 80 tiles, in a batch
+    (14, 2, 128, [(256, 1024, 20000, 36)], 64),                             # 252 of 256 pairs, half of the compute units: the other kernel
+    (28, 4, 128, [(256, 1024, 20000, 36)], 64),                             # ... all of them
+    (16, 8, 64, [(30, 700, 9000, 128)], 32),                                # 256 pairs, 128 rows of the diagonal: two tiles of it
+    (64, 1, 128, [(0, 512, 3000, 4)] * 5, 50),                              # 256 pairs of a wide group; more sequences than kernel arguments hold
+])
+@pytest.mark.parametrize("call", ["plain", "rope", "window", "bad"])
+def test_short_questions(Hq, Hkv, D, seqs, splits, call):
+    """The kernel that stages the keys once for all pairs of a KV head, with the bits of the one-item kernel: that one
+    takes the same question under a map to the KV heads in reverse."""
+    lay = P.Layout.from_seqs(seqs)
+    back = [Hkv - 1 - h * Hkv // Hq for h in range(Hq)]
+    gen = torch.Generator(device=DEV).manual_seed(14)
+    q, k, v = (torch.randn(lay.total_tokens, h, D, device=DEV, dtype=torch.bfloat16, generator=gen) for h in (Hq, Hkv, Hkv))
+    if call == "bad":  # a question row's own key and a value, both seen by the rows behind them only
+        k[-1, 0], v[-1, -1, 0] = float("nan"), float("inf")
+    res = []
+    for hmap in (None, back):
+        heads = P.Heads(Hq, Hkv, D, "bf16", kv_head_of_q=hmap)
+        kk, vv = (k, v) if hmap is None else (k.flip(1).contiguous(), v.flip(1).contiguous())
+        out, lse = torch.full_like(q, 7.0), torch.full((lay.total_tokens, Hq), 7.0, device=DEV)
+        if call == "rope":
+            P.pevlm_query_attn_rope(q, kk, vv, out, lay, heads, 1.0e6, num_splits=splits, lse=lse)
+        elif call == "window":
+            P.pevlm_query_attn_window(q, kk, vv, out, lay, heads, [2] * len(seqs), num_splits=splits, lse=lse)
+        else:
+            P.pevlm_query_attn(q, kk, vv, out, lay, heads, num_splits=splits, lse=lse)
+        res.append((out.view(torch.int16), lse.view(torch.int32)))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
