@@ -70,8 +70,11 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
     // take them in turn
     int32_t in_order = rest % p.n_items;
     if (hg.deal_runs > 1) {
-        const int32_t run = in_order / hg.deal_len;
-        if (run < hg.deal_runs) in_order = (in_order - run * hg.deal_len) * hg.deal_runs + run;
+        // run r has the positions from ceil(r n / runs) on; what is left over goes, a shortest item each, where two XCDs
+        // meet inside an item
+        const int32_t run = in_order * hg.deal_runs / p.n_items, start = (run * p.n_items + hg.deal_runs - 1) / hg.deal_runs;
+        const int32_t nth = in_order - start;
+        in_order = nth < hg.deal_len ? nth * hg.deal_runs + run : hg.deal_len * (hg.deal_runs - run) + start;
     }
     const int32_t item_idx = p.n_items - 1 - in_order;
     const int32_t G = hg.heads_per_group;
@@ -503,15 +506,16 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
 
 // One workgroup per logical id.  Consecutive workgroup ids land on different XCDs (8 of them, each
 // with its own L2); every XCD gets one contiguous run of logical ids so that the heads of a GQA
-// group working on the same context block share that XCD's L2.
+// group working on the same context block share that XCD's L2.  The runs differ by one id at most and start at
+// eighths of the ids, so that two, four or eight XCDs end where their KV head does.
 template <int D, bool PARTIAL, bool ROPEQ, bool MAPPED>
 __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnParams p, int32_t n_logical, HeadGroups hg)
 {
     __shared__ __attribute__((aligned(1024))) uint8_t lds_k[2 * TileCfg<D>::TILEB];
     __shared__ __attribute__((aligned(1024))) uint8_t lds_v[2 * TileCfg<D>::TILEB];
-    const int32_t per_xcd = gridDim.x >> 3;
-    const int32_t logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (logical >= n_logical) return;
+    const int32_t xcd = blockIdx.x & 7, eighth = n_logical >> 3, over = n_logical & 7;
+    const int32_t logical = xcd * eighth + (xcd * over >> 3) + (blockIdx.x >> 3);
+    if (logical >= (xcd + 1) * eighth + ((xcd + 1) * over >> 3)) return;
     attn_item<D, PARTIAL, ROPEQ, MAPPED>(p, logical, hg, lds_k, lds_v);
 }
 
@@ -544,12 +548,14 @@ hipError_t launch_attn_bf16(const AttnParams &p, int32_t D, bool partial, int32_
     // its items into runs.  Runs of many blocks weigh the same and keep a block's keys in one L2 (65 K tokens in blocks of
     // 1024, 8/1 heads: 224 us, 302 dealt out).  Where one region fills the runs the first has its long rows and the last its
     // short ones (dense attention over 16 K tokens x 28/4 heads: 165 against 57 ms of workgroup time), and the XCDs take the
-    // items in turn instead: 2152 -> 1852 us, 8 K tokens 544 -> 420, 8 K x 14/2 heads x 64 226 -> 139, two blocks of 3000
-    // x 28/4 1.20 times.  The lines: between two XCDs from 0.9 of a run on (1.13 times at 0.98, 0.97 at 0.79), between
-    // more from three runs on (1.31 times at 3.2, 0.88 to 1.07 at 2).
+    // items in turn instead: 2171 -> 1656 us, 8 K tokens 555 -> 421, 2 K 45.3 -> 39.8, 8 K x 14/2 heads x 64 233 -> 137, two
+    // blocks of 3000 x 28/4 1.20 times.  The lines: between two XCDs from 0.9 of a run on (1.13 times at 0.98, 0.97 at 0.79),
+    // between more from three runs on (1.31 times at 3.2, 0.88 to 1.07 at 2); and only where some compute unit has two
+    // workgroups (280 of 28/4 heads 25.5 -> 24.2 us; 224 of 16/2 heads 29.3 -> 30.3).
+    const int32_t n_logical = p.n_items * hg.wgs_per_item * (together ? p.n_kv_heads : p.n_q_heads);
     hg.deal_runs = 1;
     hg.deal_len = p.n_items;
-    if (!partial && together && p.n_kv_heads < 8 && 8 % p.n_kv_heads == 0) {
+    if (!partial && n_logical > compute_units && together && p.n_kv_heads < 8 && 8 % p.n_kv_heads == 0) {
         const int32_t runs = 8 / p.n_kv_heads;
         const int64_t region = (int64_t)p.max_region_items * runs;  // against n_items: in runs
         if (p.n_items >= runs && (runs == 2 ? 10 * region >= 9 * (int64_t)p.n_items : region >= 3 * (int64_t)p.n_items)) {
@@ -557,7 +563,6 @@ hipError_t launch_attn_bf16(const AttnParams &p, int32_t D, bool partial, int32_
             hg.deal_len = p.n_items / runs;
         }
     }
-    const int32_t n_logical = p.n_items * hg.wgs_per_item * (together ? p.n_kv_heads : p.n_q_heads);
     const dim3 grid((n_logical + 7) / 8 * 8), block(256);
 #define PEVLM_ATTN_LAUNCH(DD, PP, RR)                                                                             \
     do {                                                                                                          \

@@ -448,7 +448,7 @@ struct HeadGroups {
     int32_t wgs_per_item;     // workgroups of 128 (row, head) pairs per item and group
     int32_t groups_inside;    // groups that an item's workgroups run over before the next item (1: the next item comes first)
     int32_t step_rows, step_heads;  // the pairs that one wavefront-wide load covers, as rows and heads
-    int32_t deal_runs, deal_len;    // items dealt in turn over deal_runs runs of deal_len, the few others last (1: in order)
+    int32_t deal_runs, deal_len;    // items dealt in turn over deal_runs runs of deal_len, the few others between them (1: in order)
 };
 
 struct StreamParams {

@@ -283,10 +283,11 @@ def test_head_maps_against_the_default_map(Hq, Hkv, D):
 
 @pytest.mark.parametrize("Hkv", [1, 2, 4])
 @pytest.mark.parametrize("seqs", [[(0, 900, 900, 0)], [(0, 1024, 1024, 3)], [(0, 1100, 1100, 0)], [(130, 1500, 1700, 5)], [(40, 700, 1400, 0)],
-                                  [(0, 60, 60, 0), (0, 2000, 2000, 7)], [(0, 200, 5000, 0)]])
+                                  [(0, 60, 60, 0), (0, 2000, 2000, 7)], [(0, 200, 5000, 0)],
+                                  [(0, 8500, 8500, 0)], [(0, 9100, 9100, 0)]])
 def test_items_dealt_over_xcds(Hkv, seqs):
-    """One region that fills the runs of the XCDs on a KV head (7 to 18 items over 2, 4 or 8 runs, remainders among them), and
-    layouts on the other side of the rule: every row once, with the bits of the streaming kernel, folded calls too."""
+    """One region that fills the runs of the XCDs on a KV head (7 to 72 items over 2, 4 or 8 runs, remainders among them; from
+    257 workgroups on they are dealt), and layouts on the other side of the rule: every row once, with the bits of the streaming kernel, folded calls too."""
     lay, heads = P.Layout.from_seqs(seqs), P.Heads(3 * Hkv, Hkv, 128, "bf16")
     gen = torch.Generator(device=DEV).manual_seed(9)
     q, k, v = (torch.randn(lay.total_tokens, h, 128, device=DEV, dtype=torch.bfloat16, generator=gen) for h in (3 * Hkv, Hkv, Hkv))
