@@ -11,6 +11,7 @@
 #include <mutex>
 
 #include "common.h"
+#include "rope_math.h"
 
 namespace pevlm {
 
@@ -1021,9 +1022,27 @@ static pevlm_status query_impl(const void *q, const void *k, const void *v, void
     float *rope_tab = (float *)(ws + plan.off_rope);
     const bool inlined = fill_inline_items(layout, 2, plan.n_items * heads->n_q_heads, plan.tile_rows, plan.num_splits,
                                            (int32_t)plan.total_q, sel, &p.inline_items);
+    p.q = q; p.k = k; p.v = v;
+    p.rope_tab = fuse_rope ? rope_tab : nullptr;
+    p.rope_compact_rows = fuse_rope ? (int32_t)plan.total_q : 0;
+    p.part_acc = acc;
+    p.part_ml = ml;
+    p.items = items;
+    p.n_items = (int32_t)plan.n_items;
+    p.max_item_rows = max_query_rows(layout, plan.tile_rows);
+    p.num_splits = plan.num_splits;
+    p.n_q_heads = heads->n_q_heads;
+    p.n_kv_heads = heads->n_kv_heads;
+    p.scale = scale_of(heads);
+    // a single split is the whole softmax: the attention kernel writes the rows itself and nothing is merged
+    const bool partial = plan.num_splits > 1;
+    p.out = out;
+    p.lse = lse;
+    const bool short_question = heads->dtype == PEVLM_BF16 && partial && is_short_question(p, compute_units());
+    const bool own_angles = fuse_rope && short_question && inlined && !ax.pos_ids && p.max_item_rows <= kAngleRows;
     int32_t item_offset = 0, qrow_base = 0;
     for (int32_t s0 = 0; s0 < layout->num_seqs; s0 += kMaxSeqsPerLaunch) {
-        if (inlined && !fuse_rope) break;
+        if (inlined && (!fuse_rope || own_angles)) break;
         SeqTable tab;
         int32_t n = std::min(kMaxSeqsPerLaunch, layout->num_seqs - s0);
         fill_table(layout, s0, n, pos_offset, &tab, sel);
@@ -1045,24 +1064,23 @@ static pevlm_status query_impl(const void *q, const void *k, const void *v, void
         }
         item_offset += tab.item_base[n];
     }
-    p.q = q; p.k = k; p.v = v;
-    p.rope_tab = fuse_rope ? rope_tab : nullptr;
-    p.rope_compact_rows = fuse_rope ? (int32_t)plan.total_q : 0;
-    p.part_acc = acc;
-    p.part_ml = ml;
-    p.items = items;
-    p.n_items = (int32_t)plan.n_items;
-    p.max_item_rows = max_query_rows(layout, plan.tile_rows);
-    p.num_splits = plan.num_splits;
-    p.n_q_heads = heads->n_q_heads;
-    p.n_kv_heads = heads->n_kv_heads;
-    p.scale = scale_of(heads);
-    // a single split is the whole softmax: the attention kernel writes the rows itself and nothing is merged
-    const bool partial = plan.num_splits > 1;
-    p.out = out;
-    p.lse = lse;
-    hipError_t e = heads->dtype == PEVLM_BF16 ? launch_attn_bf16(p, heads->head_dim, partial, compute_units(), hs)
-                                              : launch_attn_f32(p, heads->head_dim, partial, compute_units(), hs);
+    hipError_t e;
+    if (short_question) {
+        RopeAngles angles;
+        if (own_angles) {
+            SeqTable tab;
+            fill_table(layout, 0, layout->num_seqs, pos_offset, &tab, sel);
+            for (int32_t i = 0; i < layout->num_seqs; ++i) {
+                tab.qrow_base[i] = qrow_base;
+                qrow_base += tab.query[i];
+            }
+            question_angles(tab, heads->head_dim, rope_base, &angles);
+        }
+        e = launch_attn_bf16_question(p, heads->head_dim, own_angles ? &angles : nullptr, hs);
+    } else {
+        e = heads->dtype == PEVLM_BF16 ? launch_attn_bf16(p, heads->head_dim, partial, compute_units(), hs)
+                                       : launch_attn_f32(p, heads->head_dim, partial, compute_units(), hs);
+    }
     if (e != hipSuccess) return hip_fail(e, "query split launch");
     if (!partial) return PEVLM_OK;
     MergeParams m;

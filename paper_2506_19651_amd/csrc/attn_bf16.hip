@@ -529,13 +529,6 @@ hipError_t launch_attn_bf16(const AttnParams &p, int32_t D, bool partial, int32_
         if (p.heads.head_order[i] != i || p.heads.kv_of_q[i] != i / G) identity = false;
     }
     const bool together = uniform && (identity || G <= 64);
-    // The kernel for short questions takes a compute unit per (KV head, split), so there must not be more of those.  Up to 128
-    // pairs a workgroup of four wavefronts has one too (16 rows x 28/4 heads over 65 K keys, 24 / 48 / 64 splits: 56.2 -> 51.2,
-    // 40.9 -> 36.3, 38.6 -> 36.3 us; 1 row 50.8 -> 46.5, 34.3 -> 32.2, 31.3 -> 31.9); above that it has two, which need not
-    // share a compute unit while there are few (20 rows, 192 of 256 compute units 49.8 -> 45.9, 128 48.3 -> 57.5).
-    const int32_t n_question = p.n_items * p.n_kv_heads, pairs = p.max_item_rows * G;
-    if (partial && identity && pairs <= 32 * kQuestionWaves && n_question <= compute_units && (pairs <= 128 || 4 * n_question >= 3 * compute_units))
-        return launch_attn_bf16_question(p, D, stream);
     HeadGroups hg;
     hg.heads_per_group = together ? G : 1;
     hg.group_rcp = reciprocal_of(hg.heads_per_group);

@@ -19,6 +19,9 @@ namespace {
 constexpr int NW = kQuestionWaves;
 constexpr int NST = 3;
 
+// where the rotation of the queries comes from
+constexpr int kRotated = 0, kTable = 1, kAngles = 2;
+
 template <int NL>
 struct QuestionLoads {
     const void *base;
@@ -28,8 +31,8 @@ struct QuestionLoads {
 };
 }  // namespace
 
-template <int D, bool ROPEQ>
-__global__ __launch_bounds__(NW * 64, 2) void attn_bf16_question_kernel(AttnParams p, int32_t n_logical, uint32_t group_rcp)
+template <int D, int ROPE>
+__global__ __launch_bounds__(NW * 64, 2) void attn_bf16_question_kernel(AttnParams p, int32_t n_logical, uint32_t group_rcp, RopeAngles angles)
 {
     using C = TileCfg<D>;
     constexpr int KT = C::KT, ROWB = C::ROWB, CH = C::CH, KSTEPS = C::KSTEPS, DBLK = C::DBLK;
@@ -108,7 +111,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_question_kernel(AttnPara
         for (int j = 0; j < NL; ++j) ld.issue(j);
     };
 
-    f32x4 rope_cs[ROPEQ ? KSTEPS / 2 : 1][4];
+    f32x4 rope_cs[ROPE != kRotated ? KSTEPS / 2 : 1][4];
     if (n_tiles > 0) {
         set_loads(ldk, K, false, lds_k_addr, 0, 0);
         burst(ldk);
@@ -127,20 +130,41 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_question_kernel(AttnPara
             load_lds_16_base(qbase, (uint32_t)((r * Hq + pair - r * G) * ROWB + (((lane % CH) ^ (rl & (CH - 1))) << 4)), slice_addr + j * 1024);
         }
     }
-    if (ROPEQ) {
-        const int64_t entry = it.reserved % p.rope_compact_rows + row_in_item;
-        const f32x4 *tab = reinterpret_cast<const f32x4 *>(p.rope_tab + entry * D) + g32 * 4;
+    auto read_table = [&](const float *table, int64_t entry) {
+        const f32x4 *tab = reinterpret_cast<const f32x4 *>(table + entry * D) + g32 * 4;
 #pragma unroll
         for (int kk = 0; kk < KSTEPS / 2; ++kk)
 #pragma unroll
             for (int j = 0; j < 4; ++j) rope_cs[kk][j] = tab[kk * 8 + j];
+    };
+    if (ROPE == kTable) read_table(p.rope_tab, it.reserved % p.rope_compact_rows + row_in_item);
+    if (ROPE == kAngles) {
+        // The item's (cos, sin) pairs, as the table kernel forms them, into the stages of V(1) and V(2) while the first tiles
+        // are under way: a launch before this one takes 4.7 us (20 rows x 28/4 heads over 65 K keys, the call 48.3 -> 46.0).
+        static_assert(kAngleRows * D * 4 <= 2 * TILEB, "the stages of V(1) and V(2) hold the pairs");
+        float2 *const table = reinterpret_cast<float2 *>(lds_v + TILEB);
+        const int32_t first_row = it.reserved % p.rope_compact_rows, i = tid % (D / 2);
+        const double inv_freq = angles.freq.inv_freq[i];
+        int32_t s = 0;
+        while (s + 1 < angles.num_seqs && first_row >= angles.first[s + 1]) ++s;
+        const int32_t pos0 = first_row - angles.first[s] + angles.pos[s];
+        for (int32_t r = tid / (D / 2); r < it.q_rows; r += NW * 64 / (D / 2)) {
+            float2 cs;
+            rope_cos_sin<false>((double)(pos0 + r), inv_freq, cs.x, cs.y);
+            table[r * (D / 2) + i] = cs;
+        }
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     asm volatile("" ::: "memory");
+    if (ROPE == kAngles) {
+        __syncthreads();
+        read_table(reinterpret_cast<const float *>(lds_v + TILEB), row_in_item);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read before the next barrier, behind which V(1) is loaded
+    }
     bf16x8 qf[KSTEPS];
 #pragma unroll
     for (int kk = 0; kk < KSTEPS; ++kk) qf[kk] = *reinterpret_cast<const bf16x8 *>(slice + l32 * ROWB + (((kk * 2 + g32) ^ (l32 & (CH - 1))) << 4));
-    if (ROPEQ) {
+    if (ROPE != kRotated) {
 #pragma unroll
         for (int kk = 0; kk < KSTEPS / 2; ++kk) {
             const f32x4 *cs = rope_cs[kk];
@@ -276,15 +300,35 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_question_kernel(AttnPara
     }
 }
 
-hipError_t launch_attn_bf16_question(const AttnParams &p, int32_t D, hipStream_t stream)
+// This kernel takes a compute unit per (KV head, split), so there must not be more of those.  Up to 128 pairs a workgroup
+// of the one-item kernel has one too (16 rows x 28/4 heads over 65 K keys, 24 / 48 / 64 splits: 56.2 -> 51.2, 40.9 -> 36.3,
+// 38.6 -> 36.3 us; 1 row 50.8 -> 46.5, 34.3 -> 32.2, 31.3 -> 31.9); above that it has two, which need not share
+// a compute unit while there are few (20 rows, 192 of 256 compute units 49.8 -> 45.9, 128 48.3 -> 57.5).
+bool is_short_question(const AttnParams &p, int32_t compute_units)
 {
+    if (p.n_q_heads % p.n_kv_heads != 0) return false;
+    const int32_t G = p.n_q_heads / p.n_kv_heads, pairs = p.max_item_rows * G;
+    for (int32_t i = 0; i < p.n_q_heads; ++i)
+        if (p.heads.head_order[i] != i || p.heads.kv_of_q[i] != i / G) return false;
+    const int64_t wgs = (int64_t)p.n_items * p.n_kv_heads;
+    return pairs <= 32 * kQuestionWaves && wgs <= compute_units && (pairs <= 128 || 4 * wgs >= 3 * (int64_t)compute_units);
+}
+
+hipError_t launch_attn_bf16_question(const AttnParams &p, int32_t D, const RopeAngles *angles, hipStream_t stream)
+{
+    static const RopeAngles none = {};
     const int32_t n_logical = p.n_items * p.n_kv_heads;
     const dim3 grid((n_logical + 7) / 8 * 8), block(NW * 64);
     const uint32_t rcp = reciprocal_of(p.n_q_heads / p.n_kv_heads);
-    const bool rope = p.rope_tab != nullptr;
-    const auto kernel = D == 128 ? (rope ? attn_bf16_question_kernel<128, true> : attn_bf16_question_kernel<128, false>)
-                                 : (rope ? attn_bf16_question_kernel<64, true> : attn_bf16_question_kernel<64, false>);
-    hipLaunchKernelGGL(kernel, grid, block, 0, stream, p, n_logical, rcp);
+#define PEVLM_QUESTION_LAUNCH(DD)                                                                                                       \
+    do {                                                                                                                                \
+        if (angles) hipLaunchKernelGGL((attn_bf16_question_kernel<DD, kAngles>), grid, block, 0, stream, p, n_logical, rcp, *angles);    \
+        else if (p.rope_tab) hipLaunchKernelGGL((attn_bf16_question_kernel<DD, kTable>), grid, block, 0, stream, p, n_logical, rcp, none); \
+        else hipLaunchKernelGGL((attn_bf16_question_kernel<DD, kRotated>), grid, block, 0, stream, p, n_logical, rcp, none);             \
+    } while (0)
+    if (D == 128) PEVLM_QUESTION_LAUNCH(128);
+    else PEVLM_QUESTION_LAUNCH(64);
+#undef PEVLM_QUESTION_LAUNCH
     return hipGetLastError();
 }
 

@@ -441,6 +441,8 @@ struct AttnParams {
     HeadTable heads;
 };
 
+struct RopeAngles;
+
 // how the bf16 kernel deals the query heads out over workgroups
 struct HeadGroups {
     int32_t heads_per_group;  // query heads taken together (those of a KV head, or 1 where the groups differ)
@@ -543,8 +545,11 @@ hipError_t launch_fp8_quantise(const void *q, const void *k, const void *v, int6
 hipError_t launch_attn_fp8(const Fp8Params &p, int32_t D, hipStream_t stream);
 hipError_t launch_attn_f32(const AttnParams &p, int32_t D, bool partial, int32_t compute_units, hipStream_t stream);
 hipError_t launch_attn_bf16(const AttnParams &p, int32_t D, bool partial, int32_t compute_units, hipStream_t stream);  // p.rope_tab selects the fused variant
-// partials of a question whose (row, head) pairs of a KV head fit one workgroup, default head map
-hipError_t launch_attn_bf16_question(const AttnParams &p, int32_t D, hipStream_t stream);
+// partials of a question whose (row, head) pairs of a KV head fit one workgroup (is_short_question), default head map;
+// angles: the query rotation without a table, for items of up to kAngleRows rows
+bool is_short_question(const AttnParams &p, int32_t compute_units);
+hipError_t launch_attn_bf16_question(const AttnParams &p, int32_t D, const RopeAngles *angles, hipStream_t stream);
+void question_angles(const SeqTable &tab, int32_t D, double rope_base, RopeAngles *angles);
 hipError_t launch_merge(const MergeParams &p, hipStream_t stream);
 hipError_t launch_probe_mfma(float *sink, int32_t workgroups, int32_t iters, hipStream_t stream);
 hipError_t launch_probe_copy(void *dst, const void *src, int64_t bytes, hipStream_t stream);
@@ -554,6 +559,7 @@ hipError_t launch_probe_tile_loop(float *sink, const void *kv, int32_t n_tiles, 
 constexpr int32_t kTileRowsF32 = 16;   // query rows per work item of the fp32 kernels
 constexpr int32_t kTileRowsBf16 = 128; // query rows per work item of the bf16 MFMA kernels
 constexpr int32_t kQuestionWaves = 8;  // wavefronts (32 (row, head) pairs each) of the kernel for short questions
+constexpr int32_t kAngleRows = 64;     // rows whose (cos, sin) pairs fit two tile stages of that kernel
 constexpr int32_t kKeyTile = 64;       // keys staged per step by the bf16 and fp8 kernels
 constexpr int32_t kFp8TileRows = 128;  // query rows per work item of the fp8 kernel
 

@@ -194,6 +194,18 @@ static RopeRows rope_rows(const SeqTable &tab, bool question)
     return r;
 }
 
+void question_angles(const SeqTable &tab, int32_t D, double rope_base, RopeAngles *angles)
+{
+    static_assert(kInlineSeqs <= 4, "RopeAngles holds the sequences of a call without a list");
+    const RopeRows rows = rope_rows(tab, true);
+    angles->freq = frequencies(D, rope_base);
+    angles->num_seqs = rows.num_seqs;
+    for (int32_t s = 0; s < rows.num_seqs; ++s) {
+        angles->first[s] = rows.first[s];
+        angles->pos[s] = rows.pos[s];
+    }
+}
+
 hipError_t launch_rope_table(float *table, bool question, const SeqTable &tab, int32_t D, double rope_base,
                              int32_t entry_begin, int32_t entry_end, const int32_t *pos3, int64_t T, int32_t sec0, int32_t sec01,
                              hipStream_t stream)

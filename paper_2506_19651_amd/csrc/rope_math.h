@@ -12,6 +12,13 @@ struct RopeFreq {
     double inv_freq[64];  // rope_base^(-2i/D), i < D/2
 };
 
+// What the angles of a batch's question rows follow from, as they are counted over a few sequences
+struct RopeAngles {
+    RopeFreq freq;
+    int32_t num_seqs;
+    int32_t first[4], pos[4];  // of each sequence: first question row, its position
+};
+
 // cos / sin of pos * inv_freq: the angle is formed in fp64 and reduced to [-pi, pi] before the fp32
 // (bf16 tensors) or fp64 (fp32 tensors) sine and cosine.
 template <bool WIDE>

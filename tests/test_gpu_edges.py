@@ -393,6 +393,8 @@ def test_fp32_groups_of_heads(oracle, Hq, Hkv, D, seqs, splits):
     (8, 2, 64, [(1, 64, 1000, 32), (0, 100, 0, 31), (5, 50, 5000, 1)], 9),  # 128 pairs; sequences of 1 to 80 tiles, in a batch
     (14, 2, 128, [(256, 1024, 20000, 36)], 64),                             # 252 of 256 pairs, half of the compute units: the other kernel
     (28, 4, 128, [(256, 1024, 20000, 36)], 64),                             # ... all of them
+    (12, 4, 128, [(0, 512, 4000, 64), (0, 0, 0, 0), (7, 64, 900, 65)], 20),  # as many rows as angles go without a table, and one more
+    (4, 2, 64, [(3, 512, 2000, 64), (0, 64, 0, 0), (7, 64, 900, 3)], 30),
     (16, 8, 64, [(30, 700, 9000, 128)], 32),                                # 256 pairs, 128 rows of the diagonal: two tiles of it
     (64, 1, 128, [(0, 512, 3000, 4)] * 5, 50),                              # 256 pairs of a wide group; more sequences than kernel arguments hold
 ])
@@ -412,7 +414,7 @@ def test_short_questions(Hq, Hkv, D, seqs, splits, call):
         kk, vv = (k, v) if hmap is None else (k.flip(1).contiguous(), v.flip(1).contiguous())
         out, lse = torch.full_like(q, 7.0), torch.full((lay.total_tokens, Hq), 7.0, device=DEV)
         if call == "rope":
-            P.pevlm_query_attn_rope(q, kk, vv, out, lay, heads, 1.0e6, num_splits=splits, lse=lse)
+            P.pevlm_query_attn_rope(q, kk, vv, out, lay, heads, 1.0e6, pos_offset=[70 * i for i in range(len(seqs))], num_splits=splits, lse=lse)
         elif call == "window":
             P.pevlm_query_attn_window(q, kk, vv, out, lay, heads, [2] * len(seqs), num_splits=splits, lse=lse)
         else:
