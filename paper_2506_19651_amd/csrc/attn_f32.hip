@@ -592,21 +592,25 @@ struct F32Shares {
 // Logical workgroup ids run over (KV head, batch of items, unit of the KV head's query heads), and every XCD (workgroup b
 // runs on XCD b % 8) gets one contiguous run of them, so that its L2 holds the keys it works on.  Items
 // are taken last first (the later tiles of a block are the longer ones), and where several XCDs share a KV
-// head, every `stride`-th item in turn, so that each gets as many long ones.  Units: one head each, or (GROUP) 128 (row, head) pairs.
+// head, every `stride`-th item in turn, so that each gets as many long ones.  The runs start at eighths of the ids (rounded
+// up to a common length, a KV head's longest items ended up on the XCD of the one before: one region of 1100 rows x 28/4
+// heads, 69 batches, 166 us, 120 now; 2000 x 14/2 heads x 64 124 and 94).  Units: one head each, or (GROUP) 128 (row, head) pairs.
 template <int D, bool PARTIAL, bool GROUP>
 __global__ __launch_bounds__(256, 2) void attn_f32_kernel(AttnParams p, int32_t n_logical, F32Shares gs)
 {
     __shared__ __attribute__((aligned(1024))) std::conditional_t<GROUP, F32GroupShared<D>, F32Shared<D>> sh;
-    const int32_t per_xcd = gridDim.x >> 3;
+    const int32_t xcd = blockIdx.x & 7, eighth = n_logical >> 3, over = n_logical & 7;
+    const int32_t first = xcd * eighth + (xcd * over >> 3), per_xcd = (xcd + 1) * eighth + ((xcd + 1) * over >> 3) - first;
     int32_t place = blockIdx.x >> 3;
+    if (place >= per_xcd) return;
     const int32_t layer = place / gs.cus_per_xcd;  // the compute units get their first workgroups in layers: a long and a short one
     if (GROUP && layer == 1) place = gs.cus_per_xcd + min(2 * gs.cus_per_xcd, per_xcd) - 1 - place;
-    const int32_t logical = (int32_t)(blockIdx.x & 7) * per_xcd + place;
-    if (logical >= n_logical) return;
+    const int32_t logical = first + place;
     const int32_t u = logical % gs.units, outer = logical / gs.units;  // outer: (group of units, item or items)
     const int32_t group = outer / gs.n_batches, j = outer % gs.n_batches;
-    const int32_t full = gs.n_batches / gs.stride * gs.stride;  // dealt out in `stride` runs; the few others come last
-    const int32_t batch = gs.n_batches - 1 - (j < full ? j % (full / gs.stride) * gs.stride + j / (full / gs.stride) : j);
+    // dealt out in `stride` runs, run r from ceil(r n / stride) on; a left-over one, of the shortest, goes where two XCDs meet in it
+    const int32_t run = j * gs.stride / gs.n_batches, start = (run * gs.n_batches + gs.stride - 1) / gs.stride, len = gs.n_batches / gs.stride;
+    const int32_t batch = gs.n_batches - 1 - (j - start < len ? (j - start) * gs.stride + run : len * (gs.stride - run) + start);
     auto item = [&](int32_t idx) {
         if (!p.inline_items.mode) return p.items[idx];
         const pevlm_work_item it = inline_item(p.inline_items, idx);
