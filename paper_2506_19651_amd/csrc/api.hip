@@ -219,6 +219,21 @@ static int32_t max_region_rows(const pevlm_layout *lay, const Restrict &r)
     }
     return n;
 }
+// half items between the middle of the list and the first item of the region that it lies in
+static int32_t middle_half_items(const pevlm_layout *lay, const Restrict &r, int32_t n_items, int32_t tile_rows)
+{
+    int32_t idx = n_items / 2;
+    for (int32_t s = 0; s < lay->num_seqs; ++s) {
+        const int32_t S = lay->sink_len[s], C = lay->ctx_len[s], B = C > 0 ? lay->block_len[s] : 1, first = r.first_block ? r.first_block[s] : 0;
+        const int32_t n = prefill_items_of_seq_sel(S, B, C, tile_rows, first, r.num_blocks ? r.num_blocks[s] : blocks_of(lay, s), r.with_sink);
+        if (idx < n) {
+            const pevlm_work_item it = prefill_item_sel(lay->cu_seqlens[s], S, B, C, tile_rows, first, r.with_sink, idx, s);
+            return (it.q_start - it.diag_start) / tile_rows * 2 + n_items % 2;
+        }
+        idx -= n;
+    }
+    return 0;
+}
 static int32_t max_query_rows(const pevlm_layout *lay, int32_t tile_rows)
 {
     return std::min(tile_rows, *std::max_element(lay->query_len, lay->query_len + lay->num_seqs));
@@ -818,6 +833,7 @@ static pevlm_status prefill_impl(const void *q, const void *k, const void *v, vo
     const int32_t region_rows = max_region_rows(layout, sel);
     p.max_item_rows = std::min(region_rows, tile_rows);
     p.max_region_items = ceil_div(region_rows, tile_rows);
+    p.middle_half_items = middle_half_items(layout, sel, p.n_items, tile_rows);
     p.num_splits = 1;
     p.n_q_heads = heads->n_q_heads;
     p.n_kv_heads = heads->n_kv_heads;

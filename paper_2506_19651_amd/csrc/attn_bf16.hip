@@ -541,17 +541,22 @@ hipError_t launch_attn_bf16(const AttnParams &p, int32_t D, bool partial, int32_
     // its items into runs.  Runs of many blocks weigh the same and keep a block's keys in one L2 (65 K tokens in blocks of
     // 1024, 8/1 heads: 224 us, 302 dealt out).  Where one region fills the runs the first has its long rows and the last its
     // short ones (dense attention over 16 K tokens x 28/4 heads: 165 against 57 ms of workgroup time), and the XCDs take the
-    // items in turn instead: 2171 -> 1656 us, 8 K tokens 555 -> 421, 2 K 45.3 -> 39.8, 8 K x 14/2 heads x 64 233 -> 137, two
-    // blocks of 3000 x 28/4 1.20 times.  The lines: between two XCDs from 0.9 of a run on (1.13 times at 0.98, 0.97 at 0.79),
-    // between more from three runs on (1.31 times at 3.2, 0.88 to 1.07 at 2); and only where some compute unit has two
-    // workgroups (280 of 28/4 heads 25.5 -> 24.2 us; 224 of 16/2 heads 29.3 -> 30.3).
+    // items in turn instead: 2171 -> 1656 us, 8 K tokens 555 -> 421, 2 K 45.3 -> 39.8, 8 K x 14/2 heads x 64 233 -> 137.
+    // The lines.  Some compute unit has two workgroups (280 of 28/4 heads 25.5 -> 24.2 us; 224 of 16/2 heads 29.3 -> 30.3).
+    // Between more than two XCDs the longest region has three runs (16/2 heads, blocks of 3136, 3.2 runs: 66.0 -> 58.2 us;
+    // 2.0 runs 0.89 to 1.27 times).  Between two it has nearly a run and they meet in its later part, so that one of
+    // them would take its longest rows last (28/4 heads, blocks of 2048: a sink of 256 and two blocks 99 -> 73, one block and
+    // 1700 rows 69 -> 52; meeting where a block starts, two blocks 65.0 and 67.5 dealt, in its first rows 65.0 and 70.3).
+    // Where all workgroups are resident at once the order matters less (16/4 heads x 64: 1.06 runs 30.8 -> 34.6, 1.15 31.7 -> 29.3).
     const int32_t n_logical = p.n_items * hg.wgs_per_item * (together ? p.n_kv_heads : p.n_q_heads);
     hg.deal_runs = 1;
     hg.deal_len = p.n_items;
     if (!partial && n_logical > compute_units && together && p.n_kv_heads < 8 && 8 % p.n_kv_heads == 0) {
         const int32_t runs = 8 / p.n_kv_heads;
-        const int64_t region = (int64_t)p.max_region_items * runs;  // against n_items: in runs
-        if (p.n_items >= runs && (runs == 2 ? 10 * region >= 9 * (int64_t)p.n_items : region >= 3 * (int64_t)p.n_items)) {
+        const int64_t region = (int64_t)p.max_region_items * runs, n = p.n_items;  // region / n: in runs
+        const bool late = 5 * (int64_t)p.middle_half_items >= 4 * (int64_t)p.max_region_items;
+        const bool pays = runs > 2 ? region >= 3 * n : late && (n_logical > 2 * compute_units ? 10 * region >= 9 * n : 20 * region >= 23 * n);
+        if (p.n_items >= runs && pays) {
             hg.deal_runs = runs;
             hg.deal_len = p.n_items / runs;
         }

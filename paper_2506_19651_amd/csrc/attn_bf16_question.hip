@@ -1,11 +1,11 @@
-// Split-KV attention of a short question for gfx950 (CDNA4), bf16: the (row, head) pairs of one KV head fit one workgroup, and what
-// bounds the call is how fast the keys and values come from HBM (20 rows x 28/4 heads over 65 K keys: 135 MB, 9 GFLOP).
+// Split-KV attention of a short question for gfx950 (CDNA4), bf16: the (row, head) pairs of one KV head fit one workgroup.
 //
 // Same work items, tile arithmetic and partials as the one-item kernel (attn_bf16.hip), bit for bit, under another schedule.
-// That one has a tile and a half under way per workgroup of 4 wavefronts, and where every compute unit has one item of its own,
-// or two workgroups that read the same keys, each tile waits for memory (2.0 us of a tile's 2.1 here).  This one has one workgroup of
-// 8 wavefronts to a compute unit, three LDS stages per tensor, K two tiles and V one and a half ahead of the arithmetic: 64 KB
-// under way, and the keys are staged once for up to 256 pairs.
+// That one has a tile and a half under way per workgroup of 4 wavefronts, and above 128 pairs two workgroups that read the same
+// keys.  This one has one workgroup of 8 wavefronts to a compute unit, three LDS stages per tensor, K two tiles and V one and a
+// half ahead of the arithmetic: 64 KB under way, and the keys are staged once for up to 256 pairs.  Attention and merge,
+// 65 K keys: 20 rows x 28/4 heads 46.1 -> 41.8 us, x 32/8 60.9 -> 53.3, 36 rows x 32/8 76.4 -> 71.3.  What bounds it now: the 140
+// pairs of 20 rows x 7 heads are five wavefronts on four SIMDs, 2 us a tile; 16 rows (four) take 36.3 us.
 //
 // Waits.  Loads into LDS complete in issue order per wavefront, and every wavefront issues the same number in every tile
 // (past the last tile the last one again, into a stage that nobody reads): the top of a tile waits until only those of the

@@ -429,6 +429,7 @@ struct AttnParams {
     pevlm_work_item *items;         // read, or (inline_items.mode != 0) written by the workgroups of the first head
     int32_t n_items, max_item_rows; // items, rows of the longest of them
     int32_t max_region_items;       // block prefill: items of the longest sink or block
+    int32_t middle_half_items;      // block prefill: half items from the start of a sink or block to the middle of the list
     int32_t num_splits;             // question: splits of the keys (1 for block prefill)
     int32_t n_q_heads, n_kv_heads;
     float scale;                    // softmax scale

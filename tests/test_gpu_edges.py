@@ -361,7 +361,7 @@ def test_shares_of_the_streaming_kernel(Hq, Hkv, seqs):
     (32, 16, 128, [(0, 70, 1200, 40)], 40),            # 2 heads, two or four items together, short blocks
     (56, 8, 64, [(7, 60, 100, 17)] * 6, 7),            # a list that is read
     (28, 4, 64, [(0, 1100, 1100, 5)], 3),              # 69 items over two XCDs
-    (14, 2, 64, [(0, 2080, 2080, 0)], 0),              # 130 over four
+    (14, 2, 64, [(0, 2080, 2080, 1)], 5),              # 130 over four
 ])
 def test_fp32_groups_of_heads(oracle, Hq, Hkv, D, seqs, splits):
     """The fp32 kernel that takes all heads of a group: column and key remainders, items joined inside a region and not across
