@@ -582,6 +582,19 @@ static int32_t splits_of_short_questions(const pevlm_layout *lay, const pevlm_he
     return min_keys >= (max_pairs <= 128 ? 512 : 768) * cuts ? (int32_t)n : 0;
 }
 
+// keys of the longest of a question's splits (with a window: the sink's apart)
+static int32_t longest_split(const pevlm_layout *lay, int32_t num_splits, const Restrict &sel)
+{
+    int32_t n = 0;
+    for (int32_t s = 0; s < lay->num_seqs; ++s) {
+        if (lay->query_len[s] == 0) continue;
+        const bool windowed = sel.window_blocks != nullptr;
+        const int32_t keys = windowed ? window_keys(lay, s, sel) : lay->cu_seqlens[s + 1] - lay->cu_seqlens[s];
+        n = std::max(n, split_len_of_seq(keys, windowed ? num_splits - 1 : num_splits, kKeyTile));
+    }
+    return n;
+}
+
 static int32_t auto_splits(const pevlm_layout *lay, const pevlm_heads *h, const Restrict &sel = Restrict(), bool short_rule = true)
 {
     const bool f32 = h->dtype == PEVLM_F32, windowed = sel.window_blocks != nullptr;
@@ -1054,7 +1067,7 @@ static pevlm_status query_impl(const void *q, const void *k, const void *v, void
     const bool partial = plan.num_splits > 1;
     p.out = out;
     p.lse = lse;
-    const bool short_question = heads->dtype == PEVLM_BF16 && partial && is_short_question(p, compute_units());
+    const bool short_question = heads->dtype == PEVLM_BF16 && partial && is_short_question(p, longest_split(layout, plan.num_splits, sel), compute_units());
     const bool own_angles = fuse_rope && short_question && inlined && !ax.pos_ids && p.max_item_rows <= kAngleRows;
     int32_t item_offset = 0, qrow_base = 0;
     for (int32_t s0 = 0; s0 < layout->num_seqs; s0 += kMaxSeqsPerLaunch) {

@@ -303,9 +303,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_question_kernel(AttnPara
 // This kernel takes a compute unit per (KV head, split), so there must not be more of those.  Up to 128 pairs a workgroup
 // of the one-item kernel has one too (16 rows x 28/4 heads over 65 K keys, 24 / 48 / 64 splits: 56.2 -> 51.2, 40.9 -> 36.3,
 // 38.6 -> 36.3 us; 1 row 50.8 -> 46.5, 34.3 -> 32.2, 31.3 -> 31.9); above that it has two, which need not share
-// a compute unit while there are few (20 rows, 192 of 256 compute units 49.8 -> 45.9, 128 48.3 -> 57.5).
-bool is_short_question(const AttnParams &p, int32_t compute_units)
+// a compute unit while there are few (20 rows, 192 of 256 compute units 49.8 -> 45.9, 128 48.3 -> 57.5).  Short splits do not
+// make up for its longer start: 8 rows x 14/2 heads x 64, 10 tiles a split 16.7 -> 16.9, 5 tiles 14.6 -> 15.7; 28/4 heads, 13
+// tiles 24.7 -> 23.2, 5 20.4 -> 20.7; the line is 8.
+bool is_short_question(const AttnParams &p, int32_t split_keys, int32_t compute_units)
 {
+    if (split_keys < 512) return false;
     if (p.n_q_heads % p.n_kv_heads != 0) return false;
     const int32_t G = p.n_q_heads / p.n_kv_heads, pairs = p.max_item_rows * G;
     for (int32_t i = 0; i < p.n_q_heads; ++i)

@@ -548,7 +548,7 @@ hipError_t launch_attn_f32(const AttnParams &p, int32_t D, bool partial, int32_t
 hipError_t launch_attn_bf16(const AttnParams &p, int32_t D, bool partial, int32_t compute_units, hipStream_t stream);  // p.rope_tab selects the fused variant
 // partials of a question whose (row, head) pairs of a KV head fit one workgroup (is_short_question), default head map;
 // angles: the query rotation without a table, for items of up to kAngleRows rows
-bool is_short_question(const AttnParams &p, int32_t compute_units);
+bool is_short_question(const AttnParams &p, int32_t split_keys, int32_t compute_units);  // split_keys: of the longest split
 hipError_t launch_attn_bf16_question(const AttnParams &p, int32_t D, const RopeAngles *angles, hipStream_t stream);
 void question_angles(const SeqTable &tab, int32_t D, double rope_base, RopeAngles *angles);
 hipError_t launch_merge(const MergeParams &p, hipStream_t stream);

@@ -390,15 +390,16 @@ def test_fp32_groups_of_heads(oracle, Hq, Hkv, D, seqs, splits):
 
 
 @pytest.mark.parametrize("Hq,Hkv,D,seqs,splits", [
-    (3, 3, 128, [(0, 64, 0, 1)], 64),                                       # one pair, one key, empty splits
-    (7, 1, 128, [(65, 128, 300, 18)], 13),                                  # 126 of 128 pairs; key ranges of part of a tile
+    (3, 3, 128, [(0, 64, 0, 1), (0, 512, 9000, 1)], 16),                    # one pair; one key and empty splits beside long ones
+    (7, 1, 128, [(65, 128, 300, 18), (9, 1000, 8000, 18)], 13),             # 126 of 128 pairs; key ranges of part of a tile
     (8, 2, 64, [(1, 64, 1000, 32), (0, 100, 0, 31), (5, 50, 5000, 1)], 9),  # 128 pairs; sequences of 1 to 80 tiles, in a batch
-    (14, 2, 128, [(256, 1024, 20000, 36)], 64),                             # 252 of 256 pairs, half of the compute units: the other kernel
-    (28, 4, 128, [(256, 1024, 20000, 36)], 64),                             # ... all of them
-    (12, 4, 128, [(0, 512, 4000, 64), (0, 0, 0, 0), (7, 64, 900, 65)], 20),  # as many rows as angles go without a table, and one more
-    (4, 2, 64, [(3, 512, 2000, 64), (0, 64, 0, 0), (7, 64, 900, 3)], 30),
-    (16, 8, 64, [(30, 700, 9000, 128)], 32),                                # 256 pairs, 128 rows of the diagonal: two tiles of it
-    (64, 1, 128, [(0, 512, 3000, 4)] * 5, 50),                              # 256 pairs of a wide group; more sequences than kernel arguments hold
+    (14, 2, 128, [(256, 1024, 36000, 36)], 64),                             # 252 of 256 pairs, half of the compute units: the other kernel
+    (28, 4, 128, [(256, 1024, 36000, 36)], 64),                             # ... all of them
+    (28, 4, 128, [(256, 1024, 30000, 36)], 64),                             # ... and splits below the line: the other kernel
+    (12, 4, 128, [(0, 512, 15000, 64), (0, 0, 0, 0), (7, 64, 900, 65)], 28),  # more rows than angles go without a table
+    (4, 2, 64, [(3, 512, 16000, 64), (0, 64, 0, 0), (7, 64, 900, 3)], 30),    # as many
+    (16, 8, 64, [(30, 700, 17000, 128)], 32),                               # 256 pairs, 128 rows of the diagonal: two tiles of it
+    (64, 1, 128, [(0, 512, 26000, 4)] + [(0, 512, 3000, 4)] * 4, 50),       # 256 pairs of a wide group; more sequences than kernel arguments hold
 ])
 @pytest.mark.parametrize("call", ["plain", "rope", "window", "bad"])
 def test_short_questions(Hq, Hkv, D, seqs, splits, call):
@@ -418,7 +419,7 @@ def test_short_questions(Hq, Hkv, D, seqs, splits, call):
         if call == "rope":
             P.pevlm_query_attn_rope(q, kk, vv, out, lay, heads, 1.0e6, pos_offset=[70 * i for i in range(len(seqs))], num_splits=splits, lse=lse)
         elif call == "window":
-            P.pevlm_query_attn_window(q, kk, vv, out, lay, heads, [2] * len(seqs), num_splits=splits, lse=lse)
+            P.pevlm_query_attn_window(q, kk, vv, out, lay, heads, [30] * len(seqs), num_splits=splits, lse=lse)
         else:
             P.pevlm_query_attn(q, kk, vv, out, lay, heads, num_splits=splits, lse=lse)
         res.append((out.view(torch.int16), lse.view(torch.int32)))
