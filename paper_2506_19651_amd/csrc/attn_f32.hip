@@ -103,10 +103,11 @@ __device__ __forceinline__ bool store_rows(const AttnParams &p, const pevlm_work
     return true;
 }
 
-// The same four rows with plain multiply-adds, over the keys that a row sees and no others: one row after the other, lanes
-// over the keys for the scores and over head_dim for the values.  Taken where infinite or invalid numbers are about.
+// Rows [first, end) of the item's, four to a wavefront, with plain multiply-adds over the keys that a row sees and no others: one
+// row after the other, lanes over the keys for the scores and over head_dim for the values.  Taken where infinite or invalid
+// numbers are about.
 template <int D, bool PARTIAL>
-__device__ __forceinline__ void attn_f32_rows(const AttnParams &p, const pevlm_work_item &it, int32_t h, int32_t g, F32Row<D> *rows)
+__device__ __forceinline__ void attn_f32_rows(const AttnParams &p, const pevlm_work_item &it, int32_t first, int32_t end, int32_t h, int32_t g, F32Row<D> *rows)
 {
     constexpr int DV = D / 64;
     const int32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -118,7 +119,7 @@ __device__ __forceinline__ void attn_f32_rows(const AttnParams &p, const pevlm_w
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
-    for (int32_t rr = wave * kRowsPerWave; rr < it.q_rows && rr < (wave + 1) * kRowsPerWave; ++rr) {
+    for (int32_t rr = max(first, wave * kRowsPerWave); rr < end && rr < (wave + 1) * kRowsPerWave; ++rr) {
         const int32_t row = it.q_start + rr;
         exchanged();
         for (int c = 0; c < DV; ++c) q_s[lane + 64 * c] = Q[((int64_t)row * Hq + h) * D + lane + 64 * c];
@@ -559,7 +560,11 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
         }
     if (live && wrong != 0.f) atomicOr(&sh.left[my_pair % G / 32], 1u << (my_pair % G % 32));
     const int64_t slot = (int64_t)((PARTIAL ? it.reserved : it.q_start) + my_pair / G) * Hq + my_head;
-    if (live && g32 == 0) {
+    barrier();
+    // A row that is done again, by any wavefront, is not stored here: nothing would order the two stores.
+    auto again = [&](int32_t j) { return (sh.left[j / 32] >> (j % 32) & 1) != 0; };
+    const bool keep = live && !again(my_pair % G);
+    if (keep && g32 == 0) {
         if (PARTIAL) {
             p.part_ml[slot * 2] = m;
             p.part_ml[slot * 2 + 1] = l;
@@ -567,17 +572,17 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
             p.lse[slot] = m * p.scale + logf(l);
         }
     }
-    barrier();
     constexpr int LPR = D / 4;
 #pragma unroll
     for (int j = 0; j < 32; j += 64 / LPR) {
         const int32_t c = j + lane / LPR, c_slot_lo = __shfl((int32_t)(uint32_t)slot, c), c_slot_hi = __shfl((int32_t)(slot >> 32), c);
         const int64_t row = ((int64_t)c_slot_hi << 32) | (uint32_t)c_slot_lo;
-        if (col0 + c < n_pairs)
+        if (__shfl((int32_t)keep, c))
             *reinterpret_cast<f32x4 *>((PARTIAL ? p.part_acc : (float *)p.out) + row * D + lane % LPR * 4) = *reinterpret_cast<const f32x4 *>(&sh.o[wave * 32 + c][lane % LPR * 4]);
     }
-    for (int32_t j = 0; j < G; ++j)
-        if (sh.left[j / 32] >> (j % 32) & 1) attn_f32_rows<D, PARTIAL>(p, it, p.heads.head_order[g * G + j], g, sh.row);
+    for (int32_t j = 0; j < G; ++j)  // the workgroup's own rows of head j: those of its pairs
+        if (again(j))
+            attn_f32_rows<D, PARTIAL>(p, it, max(0, ceil_div(pair0 - j, G)), ceil_div(min(pair0 + kGroupColumns, n_pairs) - j, G), p.heads.head_order[g * G + j], g, sh.row);
 }
 
 }  // namespace
@@ -636,7 +641,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(AttnParams p, int32_t 
     } else {
         const pevlm_work_item it = item(batch);
         const int32_t h = p.heads.head_order[group * gs.units + u], g = p.heads.kv_of_q[h];
-        if (attn_f32_single<D, PARTIAL>(p, it, h, g, u, sh)) attn_f32_rows<D, PARTIAL>(p, it, h, g, sh.row);
+        if (attn_f32_single<D, PARTIAL>(p, it, h, g, u, sh)) attn_f32_rows<D, PARTIAL>(p, it, 0, it.q_rows, h, g, sh.row);
     }
 }
 

@@ -58,6 +58,29 @@ def test_fp32_groups_of_heads_with_bad_keys(oracle, Hq, Hkv, D, where):
     assert (np.abs(got[fine] - want[fine]) <= 1e-5 * np.maximum(1.0, np.abs(want[fine]))).all()
 
 
+@pytest.mark.parametrize("Hq,Hkv,D", [(72, 8, 64), (64, 4, 64), (96, 2, 128)])
+def test_fp32_wide_groups_with_bad_keys(oracle, Hq, Hkv, D):
+    """Groups of 9, 16 and 48 heads, whose items are dealt out over several workgroups (an item's 16 rows, over the ends of
+    them): a row that is done again is stored once, by the workgroup that has it.  Right against the oracle, lse too, and the same
+    bits whatever the buffers held before."""
+    seqs = [(21, 100, 430, 37)]
+    w = W.Workload("bad_f32w", 43, "f32", Hq, Hkv, D, 1.0e4, seqs, 1.0)
+    data = W.generate(w)
+    for i, t in enumerate([20, 121, 160, 351, 457, 487]):
+        data["v"][t, i % Hkv, (5 * i) % D] = [np.nan, np.inf, -np.inf, 3.4e38][i % 4]
+    r = run_path(w, data, num_splits=11, want_lse=True)
+    got, lse = to_host_f32(r["out"]), to_host_f32(r["lse"])
+    want, want_lse = oracle.forward(data["q"], data["k"], data["v"], oracle_layout(oracle, w), w.rope_base)
+    fine = np.isfinite(want)
+    assert 0.2 < fine.mean() < 1.0
+    assert np.array_equal(np.isfinite(got), fine)
+    assert (np.abs(got[fine] - want[fine]) <= 1e-5 * np.maximum(1.0, np.abs(want[fine]))).all()
+    assert np.abs(lse - want_lse).max() <= 1e-4  # scores are finite
+    once = run_path(w, data, num_splits=11, want_lse=True, poison=False)
+    for name in ("out", "lse"):
+        assert torch.equal(r[name].nan_to_num(9.0), once[name].nan_to_num(9.0))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("splits", [1, 2, 9, 64])
