@@ -18,7 +18,7 @@
 //
 // A key that a row must not see enters its value MFMAs with the weight 0, which hides every finite value but not an
 // infinite or invalid one (nor one that overflows its first bf16 part).  Such a value leaves a NaN in the row, so rows that do
-// not come out finite are done again over the keys that they see and no others (attn_f32_rows).
+// not come out finite are done again over the keys that they see and no others (attn_f32_row).
 #include <algorithm>
 #include <type_traits>
 
@@ -39,7 +39,7 @@ template <int D>
 struct F32Shared {
     float ml[NW][kRows][2];           // per wavefront and row: maximum of the raw scores, sum of the weights
     float o[NW][kRows][D + 4];        // values of every wavefront, scaled to the common maximum
-    F32Row<D> row[NW];                // attn_f32_rows
+    F32Row<D> row[NW];                // attn_f32_row
 };
 
 // exp(d * scale) for c = scale * log2(e): two instructions where expf takes twelve.  The product is rounded once, as the argument
@@ -103,72 +103,69 @@ __device__ __forceinline__ bool store_rows(const AttnParams &p, const pevlm_work
     return true;
 }
 
-// Rows [first, end) of the item's, four to a wavefront, with plain multiply-adds over the keys that a row sees and no others: one
-// row after the other, lanes over the keys for the scores and over head_dim for the values.  Taken where infinite or invalid
-// numbers are about.
+// Row rr of an item by one wavefront, with plain multiply-adds over the keys that the row sees and no others: lanes over the keys
+// for the scores and over head_dim for the values.  Taken where infinite or invalid numbers are about.
 template <int D, bool PARTIAL>
-__device__ __forceinline__ void attn_f32_rows(const AttnParams &p, const pevlm_work_item &it, int32_t first, int32_t end, int32_t h, int32_t g, F32Row<D> *rows)
+__device__ __forceinline__ void attn_f32_row(const AttnParams &p, const pevlm_work_item &it, int32_t rr, int32_t h, int32_t g, F32Row<D> &own)
 {
     constexpr int DV = D / 64;
-    const int32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t lane = threadIdx.x & 63;
     const int32_t Hq = p.n_q_heads, Hkv = p.n_kv_heads;
     const float *Q = (const float *)p.q, *K = (const float *)p.k, *V = (const float *)p.v;
-    float *const q_s = rows[wave].q, *const w_s = rows[wave].w;
+    float *const q_s = own.q, *const w_s = own.w;
     auto exchanged = [] {  // what a lane has written to the wavefront's own LDS is read by its other lanes
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
-    for (int32_t rr = max(first, wave * kRowsPerWave); rr < end && rr < (wave + 1) * kRowsPerWave; ++rr) {
-        const int32_t row = it.q_start + rr;
-        exchanged();
-        for (int c = 0; c < DV; ++c) q_s[lane + 64 * c] = Q[((int64_t)row * Hq + h) * D + lane + 64 * c];
-        exchanged();
-        float m = -INFINITY, l = 0.f, acc[DV];
-        for (int c = 0; c < DV; ++c) acc[c] = 0.f;
-        for (int seg = 0; seg < 2; ++seg) {
-            const int32_t start = seg == 0 ? it.full_start : it.diag_start;
-            const int32_t n = seg == 0 ? it.full_len : (row - start + 1 < it.diag_len ? row - start + 1 : it.diag_len);
-            for (int32_t k0 = 0; k0 < n; k0 += 64) {
-                const int32_t j = k0 + lane, cnt = n - k0 < 64 ? n - k0 : 64;
-                float s = -INFINITY;
-                if (j < n) {
-                    const f32x4 *kp = reinterpret_cast<const f32x4 *>(K + ((int64_t)(start + j) * Hkv + g) * D);
-                    s = 0.f;
-                    for (int d = 0; d < D / 4; ++d) {
-                        const f32x4 x = kp[d];
-                        s += q_s[4 * d] * x[0] + q_s[4 * d + 1] * x[1] + q_s[4 * d + 2] * x[2] + q_s[4 * d + 3] * x[3];
-                    }
+    const int32_t row = it.q_start + rr;
+    exchanged();
+    for (int c = 0; c < DV; ++c) q_s[lane + 64 * c] = Q[((int64_t)row * Hq + h) * D + lane + 64 * c];
+    exchanged();
+    float m = -INFINITY, l = 0.f, acc[DV];
+    for (int c = 0; c < DV; ++c) acc[c] = 0.f;
+    for (int seg = 0; seg < 2; ++seg) {
+        const int32_t start = seg == 0 ? it.full_start : it.diag_start;
+        const int32_t n = seg == 0 ? it.full_len : (row - start + 1 < it.diag_len ? row - start + 1 : it.diag_len);
+        for (int32_t k0 = 0; k0 < n; k0 += 64) {
+            const int32_t j = k0 + lane, cnt = n - k0 < 64 ? n - k0 : 64;
+            float s = -INFINITY;
+            if (j < n) {
+                const f32x4 *kp = reinterpret_cast<const f32x4 *>(K + ((int64_t)(start + j) * Hkv + g) * D);
+                s = 0.f;
+                for (int d = 0; d < D / 4; ++d) {
+                    const f32x4 x = kp[d];
+                    s += q_s[4 * d] * x[0] + q_s[4 * d + 1] * x[1] + q_s[4 * d + 2] * x[2] + q_s[4 * d + 3] * x[3];
                 }
-                float mx = s;
-                for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-                const float m_new = fmaxf(m, mx);
-                const float w = j < n ? expf((s - m_new) * p.scale) : 0.f;
-                const float alpha = expf((m - m_new) * p.scale);  // m = -inf gives 0
-                float sum = w;
-                for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-                l = l * alpha + sum;
-                for (int c = 0; c < DV; ++c) acc[c] *= alpha;
-                m = m_new;
-                exchanged();
-                w_s[lane] = w;
-                exchanged();
-                for (int32_t jj = 0; jj < cnt; ++jj) {
-                    const float *vp = V + ((int64_t)(start + k0 + jj) * Hkv + g) * D;
-                    for (int c = 0; c < DV; ++c) acc[c] += w_s[jj] * vp[lane + 64 * c];
-                }
+            }
+            float mx = s;
+            for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+            const float m_new = fmaxf(m, mx);
+            const float w = j < n ? expf((s - m_new) * p.scale) : 0.f;
+            const float alpha = expf((m - m_new) * p.scale);  // m = -inf gives 0
+            float sum = w;
+            for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+            l = l * alpha + sum;
+            for (int c = 0; c < DV; ++c) acc[c] *= alpha;
+            m = m_new;
+            exchanged();
+            w_s[lane] = w;
+            exchanged();
+            for (int32_t jj = 0; jj < cnt; ++jj) {
+                const float *vp = V + ((int64_t)(start + k0 + jj) * Hkv + g) * D;
+                for (int c = 0; c < DV; ++c) acc[c] += w_s[jj] * vp[lane + 64 * c];
             }
         }
-        const int64_t slot = ((int64_t)(PARTIAL ? it.reserved + rr : row)) * Hq + h;
-        float *const dst = (PARTIAL ? p.part_acc : (float *)p.out) + slot * D;
-        for (int c = 0; c < DV; ++c) dst[lane + 64 * c] = PARTIAL ? acc[c] : acc[c] * (1.f / l);
-        if (lane == 0) {
-            if (PARTIAL) {
-                p.part_ml[slot * 2] = m;
-                p.part_ml[slot * 2 + 1] = l;
-            } else if (p.lse) {
-                p.lse[slot] = m * p.scale + logf(l);
-            }
+    }
+    const int64_t slot = ((int64_t)(PARTIAL ? it.reserved + rr : row)) * Hq + h;
+    float *const dst = (PARTIAL ? p.part_acc : (float *)p.out) + slot * D;
+    for (int c = 0; c < DV; ++c) dst[lane + 64 * c] = PARTIAL ? acc[c] : acc[c] * (1.f / l);
+    if (lane == 0) {
+        if (PARTIAL) {
+            p.part_ml[slot * 2] = m;
+            p.part_ml[slot * 2 + 1] = l;
+        } else if (p.lse) {
+            p.lse[slot] = m * p.scale + logf(l);
         }
     }
 }
@@ -337,7 +334,6 @@ union F32GroupShared {
     struct {
         float o[kGroupColumns][D + 4];  // rows on their way out
         F32Row<D> row[NW];
-        uint32_t left[kMaxHeads / 32];  // heads whose rows are to be done again
     };
 };
 static_assert(2 * sizeof(F32GroupShared<128>) <= 160 * 1024, "two workgroups on a compute unit");
@@ -543,8 +539,6 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
     asm volatile("" : "+v"(out_lane));
     const int32_t my_pair = min(col0 + (out_lane & 31), n_pairs - 1), my_head = p.heads.head_order[g * G + my_pair % G];
     l += other_half(l);
-    if (tid < kMaxHeads / 32) sh.left[tid] = 0u;
-    barrier();
     const bool live = col0 + l32 < n_pairs;
     const float inv = PARTIAL ? 1.f : 1.f / l;
     float wrong = 0.f;  // stays 0 while every value is finite
@@ -558,13 +552,11 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
             for (int j = 0; j < 4; ++j) wrong = fmaf(x[j], 0.f, wrong);
             *reinterpret_cast<f32x4 *>(&sh.o[wave * 32 + l32][b * 32 + i4 * 8 + g32 * 4]) = x;
         }
-    if (live && wrong != 0.f) atomicOr(&sh.left[my_pair % G / 32], 1u << (my_pair % G % 32));
+    // Columns whose rows are to be done again: by this wavefront, and not stored before.
+    const uint64_t marked = __ballot(live && wrong != 0.f);
+    uint32_t again = (uint32_t)(marked | marked >> 32);
     const int64_t slot = (int64_t)((PARTIAL ? it.reserved : it.q_start) + my_pair / G) * Hq + my_head;
-    barrier();
-    // A row that is done again, by any wavefront, is not stored here: nothing would order the two stores.
-    auto again = [&](int32_t j) { return (sh.left[j / 32] >> (j % 32) & 1) != 0; };
-    const bool keep = live && !again(my_pair % G);
-    if (keep && g32 == 0) {
+    if (live && g32 == 0 && !(again >> l32 & 1)) {
         if (PARTIAL) {
             p.part_ml[slot * 2] = m;
             p.part_ml[slot * 2 + 1] = l;
@@ -572,17 +564,19 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
             p.lse[slot] = m * p.scale + logf(l);
         }
     }
+    barrier();
     constexpr int LPR = D / 4;
 #pragma unroll
     for (int j = 0; j < 32; j += 64 / LPR) {
         const int32_t c = j + lane / LPR, c_slot_lo = __shfl((int32_t)(uint32_t)slot, c), c_slot_hi = __shfl((int32_t)(slot >> 32), c);
         const int64_t row = ((int64_t)c_slot_hi << 32) | (uint32_t)c_slot_lo;
-        if (__shfl((int32_t)keep, c))
+        if (col0 + c < n_pairs && !(again >> c & 1))
             *reinterpret_cast<f32x4 *>((PARTIAL ? p.part_acc : (float *)p.out) + row * D + lane % LPR * 4) = *reinterpret_cast<const f32x4 *>(&sh.o[wave * 32 + c][lane % LPR * 4]);
     }
-    for (int32_t j = 0; j < G; ++j)  // the workgroup's own rows of head j: those of its pairs
-        if (again(j))
-            attn_f32_rows<D, PARTIAL>(p, it, max(0, ceil_div(pair0 - j, G)), ceil_div(min(pair0 + kGroupColumns, n_pairs) - j, G), p.heads.head_order[g * G + j], g, sh.row);
+    for (; again; again &= again - 1) {
+        const int32_t pair = col0 + __builtin_ctz(again);
+        attn_f32_row<D, PARTIAL>(p, it, pair / G, p.heads.head_order[g * G + pair % G], g, sh.row[wave]);
+    }
 }
 
 }  // namespace
@@ -641,7 +635,10 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(AttnParams p, int32_t 
     } else {
         const pevlm_work_item it = item(batch);
         const int32_t h = p.heads.head_order[group * gs.units + u], g = p.heads.kv_of_q[h];
-        if (attn_f32_single<D, PARTIAL>(p, it, h, g, u, sh)) attn_f32_rows<D, PARTIAL>(p, it, 0, it.q_rows, h, g, sh.row);
+        if (attn_f32_single<D, PARTIAL>(p, it, h, g, u, sh)) {  // the wavefront's four rows, of which none was stored
+            const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+            for (int32_t rr = wave * kRowsPerWave; rr < it.q_rows && rr < (wave + 1) * kRowsPerWave; ++rr) attn_f32_row<D, PARTIAL>(p, it, rr, h, g, sh.row[wave]);
+        }
     }
 }
 

@@ -58,6 +58,38 @@ def test_fp32_groups_of_heads_with_bad_keys(oracle, Hq, Hkv, D, where):
     assert (np.abs(got[fine] - want[fine]) <= 1e-5 * np.maximum(1.0, np.abs(want[fine]))).all()
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,seqs,splits", [
+    (32, 8, 128, [(100, 500, 1400, 70)], 24),   # 4 heads: two items together, 4 of 5 in the question
+    (48, 16, 64, [(33, 100, 870, 50)], 12),     # 3 heads: two
+    (16, 8, 64, [(56, 500, 3010, 110)], 40),    # 2 heads: four in the prefill and the question, ends of three, two and one
+    (32, 16, 128, [(0, 70, 1200, 40)], 40),     # 2 heads: short blocks
+])
+@pytest.mark.parametrize("where", ["value", "key", "largest"])
+def test_fp32_joined_items_with_bad_keys(oracle, Hq, Hkv, D, seqs, splits, where):
+    """The same where a workgroup takes several items of 16 rows at once: a bad key or value in every stretch of 16 rows of
+    a sink, a block and the question, so that rows of each of the joined items do and do not see one; the largest finite values, which
+    overflow their first bf16 plane, in the rows of all of them."""
+    w = W.Workload("bad_f32j", 44, "f32", Hq, Hkv, D, 1.0e4, seqs, 1.0)
+    data = W.generate(w)
+    S, B, C, Q = seqs[0]
+    bad = [(t, t // 16 % Hkv) for t in range(S - 1 if S else 0, S)]  # the sink's last key alone: blocks and question see the sink
+    for start, n in [(S + b, min(B, C - b)) for b in range(0, C, B)] + [(S + C, Q)]:
+        g = start % Hkv  # one KV head to a region: the others' rows stay as they are
+        bad += [(start + r, g) for r in (18, 33, 50, n - 2) if r < n and start != S]
+    x = data["k" if where == "key" else "v"]
+    for i, (t, g) in enumerate(bad):
+        x[t, g, (5 * i) % D] = np.nan if where == "key" else (3.399e38 if where == "largest" else [np.nan, np.inf, -np.inf][i % 3])
+    r = run_path(w, data, num_splits=splits, want_lse=True)
+    got, lse = to_host_f32(r["out"]), to_host_f32(r["lse"])
+    want, want_lse = oracle.forward(data["q"], data["k"], data["v"], oracle_layout(oracle, w), w.rope_base)
+    fine = np.isfinite(want)
+    assert 0.2 < fine.mean() < 1.0 or where == "largest" and fine.all()
+    assert np.array_equal(np.isfinite(got), fine)
+    assert (np.abs(got[fine] - want[fine]) <= 1e-5 * np.maximum(1.0, np.abs(want[fine]))).all()
+    both = np.isfinite(want_lse)
+    assert np.array_equal(np.isfinite(lse), both) and np.abs(lse[both] - want_lse[both]).max() <= 1e-4
+
+
 @pytest.mark.parametrize("Hq,Hkv,D", [(72, 8, 64), (64, 4, 64), (96, 2, 128)])
 def test_fp32_wide_groups_with_bad_keys(oracle, Hq, Hkv, D):
     """Groups of 9, 16 and 48 heads, whose items are dealt out over several workgroups (an item's 16 rows, over the ends of
