@@ -109,7 +109,8 @@ template <int D, bool PARTIAL>
 __device__ __forceinline__ void attn_f32_row(const AttnParams &p, const pevlm_work_item &it, int32_t rr, int32_t h, int32_t g, F32Row<D> &own)
 {
     constexpr int DV = D / 64;
-    const int32_t lane = threadIdx.x & 63;
+    int32_t lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));  // nothing of this is formed ahead of the tile loop, whose registers are full
     const int32_t Hq = p.n_q_heads, Hkv = p.n_kv_heads;
     const float *Q = (const float *)p.q, *K = (const float *)p.k, *V = (const float *)p.v;
     float *const q_s = own.q, *const w_s = own.w;
@@ -537,9 +538,10 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
     // another: the registers are full through the loop.
     int32_t out_lane = lane;
     asm volatile("" : "+v"(out_lane));
-    const int32_t my_pair = min(col0 + (out_lane & 31), n_pairs - 1), my_head = p.heads.head_order[g * G + my_pair % G];
+    const int32_t out32 = out_lane & 31, half = out_lane >> 5;
+    const int32_t my_pair = min(col0 + out32, n_pairs - 1), my_head = p.heads.head_order[g * G + my_pair % G];
     l += other_half(l);
-    const bool live = col0 + l32 < n_pairs;
+    const bool live = col0 + out32 < n_pairs;
     const float inv = PARTIAL ? 1.f : 1.f / l;
     float wrong = 0.f;  // stays 0 while every value is finite
 #pragma unroll
@@ -550,13 +552,13 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
             x *= inv;
 #pragma unroll
             for (int j = 0; j < 4; ++j) wrong = fmaf(x[j], 0.f, wrong);
-            *reinterpret_cast<f32x4 *>(&sh.o[wave * 32 + l32][b * 32 + i4 * 8 + g32 * 4]) = x;
+            *reinterpret_cast<f32x4 *>(&sh.o[wave * 32 + out32][b * 32 + i4 * 8 + half * 4]) = x;
         }
     // Columns whose rows are to be done again: by this wavefront, and not stored before.
     const uint64_t marked = __ballot(live && wrong != 0.f);
     uint32_t again = (uint32_t)(marked | marked >> 32);
     const int64_t slot = (int64_t)((PARTIAL ? it.reserved : it.q_start) + my_pair / G) * Hq + my_head;
-    if (live && g32 == 0 && !(again >> l32 & 1)) {
+    if (live && half == 0 && !(again >> out32 & 1)) {
         if (PARTIAL) {
             p.part_ml[slot * 2] = m;
             p.part_ml[slot * 2 + 1] = l;
@@ -568,10 +570,10 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
     constexpr int LPR = D / 4;
 #pragma unroll
     for (int j = 0; j < 32; j += 64 / LPR) {
-        const int32_t c = j + lane / LPR, c_slot_lo = __shfl((int32_t)(uint32_t)slot, c), c_slot_hi = __shfl((int32_t)(slot >> 32), c);
+        const int32_t c = j + out_lane / LPR, c_slot_lo = __shfl((int32_t)(uint32_t)slot, c), c_slot_hi = __shfl((int32_t)(slot >> 32), c);
         const int64_t row = ((int64_t)c_slot_hi << 32) | (uint32_t)c_slot_lo;
         if (col0 + c < n_pairs && !(again >> c & 1))
-            *reinterpret_cast<f32x4 *>((PARTIAL ? p.part_acc : (float *)p.out) + row * D + lane % LPR * 4) = *reinterpret_cast<const f32x4 *>(&sh.o[wave * 32 + c][lane % LPR * 4]);
+            *reinterpret_cast<f32x4 *>((PARTIAL ? p.part_acc : (float *)p.out) + row * D + out_lane % LPR * 4) = *reinterpret_cast<const f32x4 *>(&sh.o[wave * 32 + c][out_lane % LPR * 4]);
     }
     for (; again; again &= again - 1) {
         const int32_t pair = col0 + __builtin_ctz(again);
