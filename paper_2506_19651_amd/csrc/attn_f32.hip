@@ -173,7 +173,8 @@ __device__ __forceinline__ void attn_f32_row(const AttnParams &p, const pevlm_wo
 
 // One head on 16 columns: lane % 16 is the row, lane / 16 the k index; step j of group i of Q K^T contracts
 // head_dim 16 i + 4 kq + j, the lane's score v of a block of 16 keys is that of key 4 kq + v, row r of
-// block 4 hh + b of O^T is head_dim 64 hh + 4 r + b.
+// block 4 hh + b of O^T is head_dim 64 hh + 4 r + b.  A score is two sums over half of head_dim each: one sum has a third more
+// error in the output (28/4 heads x 128, blocks of 333: 2.2e-7 and 3.2e-7; 14/2 x 64 1.9e-7 and 2.6e-7) and takes as long.
 template <int D, bool PARTIAL>
 __device__ __forceinline__ int32_t attn_f32_single(const AttnParams &p, const pevlm_work_item &it, int32_t h, int32_t g, int32_t u, F32Shared<D> &sh)
 {
@@ -213,13 +214,17 @@ __device__ __forceinline__ int32_t attn_f32_single(const AttnParams &p, const pe
             if (b < nblk) {
                 const int32_t key = b * 16 + r16 < last ? b * 16 + r16 : last;
                 const float *kp = K + ((int64_t)(k0 + key) * Hkv + g) * D + 4 * kq;
-                f32x4 a[KI];
+                f32x4 a[KI], s2 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int i = 0; i < KI; ++i) a[i] = *reinterpret_cast<const f32x4 *>(kp + 16 * i);
 #pragma unroll
                 for (int i = 0; i < KI; ++i)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) s[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j], qf[i][j], s[b], 0, 0, 0);
+                    for (int j = 0; j < 4; j += 2) {
+                        s[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j], qf[i][j], s[b], 0, 0, 0);
+                        s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j + 1], qf[i][j + 1], s2, 0, 0, 0);
+                    }
+                s[b] += s2;
             }
         }
         // ---- weights: this lane holds keys 16 b + 4 kq + v of its row

@@ -389,6 +389,38 @@ def test_fp32_groups_of_heads(oracle, Hq, Hkv, D, seqs, splits):
     assert outs[0].any() and (outs[0] - outs[1]).abs().max() <= F32_TOL
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,seq,splits,tol", [
+    (28, 4, 128, (100, 333, 500, 40), 4, 4.6e-7),  # the two-head kernel of before had 4.65e-7, one sum a score 6.5e-7
+    (14, 2, 64, (77, 333, 900, 21), 4, 3.5e-7),    # 3.53e-7, 4.96e-7
+    (2, 1, 64, (32, 16, 64, 8), 1, 2.9e-7),        # (one head then too) 3.1e-7
+    (4, 1, 128, (64, 300, 1500, 64), 6, 5.0e-7),   # 6.7e-7
+    (28, 4, 128, (256, 1024, 2048, 64), 16, 3.9e-7),  # all heads of a group: 5.6e-7
+])
+def test_fp32_distance_to_64_bits(Hq, Hkv, D, seq, splits, tol):
+    """Relative 2-norm of the error over all rows, scores of standard deviation 2: no more than the fp32 matrix instructions of two heads
+    a workgroup had.  The limit lies between what two sums a score measure (10 to 15 % below it) and what one does."""
+    lay, heads = P.Layout.from_seqs([seq]), P.Heads(Hq, Hkv, D, "f32")
+    S, B, C, Q = seq
+    T = S + C + Q
+    gen = torch.Generator().manual_seed(15)
+    q, k, v = (torch.randn(T, h, D, generator=gen) for h in (Hq, Hkv, Hkv))
+    q *= 2.0
+    i = torch.arange(T)
+    region = torch.where(i < S, -1, torch.where(i < S + C, (i - S) // B, T))
+    sees = (i[None, :] <= i[:, None]) & ((region[None, :] == region[:, None]) | (region[None, :] == -1) | (region[:, None] == T))
+    want = torch.zeros(T, Hq, D, dtype=torch.float64)
+    for h in range(Hq):
+        s = q[:, h].double() @ k[:, h * Hkv // Hq].double().T / D ** 0.5
+        want[:, h] = torch.softmax(s.masked_fill(~sees, float("-inf")), dim=-1) @ v[:, h * Hkv // Hq].double()
+    dev = [x.to(DEV) for x in (q, k, v)]
+    out = torch.full((T, Hq, D), float("nan"), device=DEV)
+    P.pevlm_block_prefill_attn(*dev, out, lay, heads)
+    P.pevlm_query_attn(*dev, out, lay, heads, num_splits=splits)
+    err = float((out.cpu().double() - want).norm() / want.norm())
+    print(err)
+    assert err <= tol
+
+
 @pytest.mark.parametrize("Hq,Hkv,D,seqs,splits", [
     (3, 3, 128, [(0, 64, 0, 1), (0, 512, 9000, 1)], 16),                    # one pair; one key and empty splits beside long ones
     (7, 1, 128, [(65, 128, 300, 18), (9, 1000, 8000, 18)], 13),             # 126 of 128 pairs; key ranges of part of a tile
