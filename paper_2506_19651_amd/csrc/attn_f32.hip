@@ -37,8 +37,8 @@ struct F32Row {  // a wavefront's query row and weights of 64 keys
 };
 template <int D>
 struct F32Shared {
-    float ml[NW][kRows][2];           // per wavefront and row: maximum of the raw scores, sum of the weights
-    float o[NW][kRows][D + 4];        // values of every wavefront, scaled to the common maximum
+    float ml[NW][kRows][2];           // per first tile of a wavefront, and row: maximum of the raw scores, sum of the weights
+    float o[NW][kRows][D + 4];        // values of each, scaled to the common maximum
     F32Row<D> row[NW];                // attn_f32_row
 };
 
@@ -54,8 +54,8 @@ __device__ __forceinline__ float other_half(float x)  // the value of lane ^ 32
 // a lane's sum of weights reaches this bound: they are not negative, so each stays below it, and an overflow is seen.
 constexpr float kSumBound = 256.f;
 // The wavefronts of a workgroup take its tiles in turn, wavefront 0 not always first: it sits on the same SIMD in every
-// workgroup, and where the tiles do not divide by four that one had the most to do.  The row decides, so that a row's
-// result does not depend on the launch.
+// workgroup, and where the tiles do not divide by four that one had the most to do.  What a wavefront brings to the join goes by
+// its first tile's number, so that a row's result does not depend on who came first, on the row's place in the batch for one.
 __device__ __forceinline__ int32_t first_tile(const pevlm_work_item &it, int32_t u, int32_t wave) { return (wave + u + (it.q_start >> 4) + (it.q_start >> 7)) % NW; }
 
 // Rows of one head: the wavefronts' values in sh.o, already scaled to
@@ -200,7 +200,8 @@ __device__ __forceinline__ int32_t attn_f32_single(const AttnParams &p, const pe
 #pragma unroll
     for (int b = 0; b < 4 * VH; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float c_log2 = p.scale * 1.4426950408889634f;
-    for (int32_t t = first_tile(it, u, wave); t < n_tiles; t += NW) {
+    const int32_t turn = first_tile(it, u, wave);
+    for (int32_t t = turn; t < n_tiles; t += NW) {
         const bool causal = t >= n_full;
         const int32_t k0 = causal ? it.diag_start + (t - n_full) * KT : it.full_start + t * KT;
         const int32_t kend = causal ? it.diag_start + it.diag_len : it.full_start + it.full_len;
@@ -282,8 +283,8 @@ __device__ __forceinline__ int32_t attn_f32_single(const AttnParams &p, const pe
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
     if (kq == 0) {
-        sh.ml[wave][r16][0] = m;
-        sh.ml[wave][r16][1] = l;
+        sh.ml[turn][r16][0] = m;
+        sh.ml[turn][r16][1] = l;
     }
     __syncthreads();
     float M = -INFINITY;
@@ -294,7 +295,7 @@ __device__ __forceinline__ int32_t attn_f32_single(const AttnParams &p, const pe
     for (int hh = 0; hh < VH; ++hh)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-            *reinterpret_cast<f32x4 *>(&sh.o[wave][r16][64 * hh + 16 * kq + 4 * v]) =
+            *reinterpret_cast<f32x4 *>(&sh.o[turn][r16][64 * hh + 16 * kq + 4 * v]) =
                 f32x4{o[4 * hh][v] * f, o[4 * hh + 1][v] * f, o[4 * hh + 2][v] * f, o[4 * hh + 3][v] * f};
     __syncthreads();
     return store_rows<D, PARTIAL>(p, it, h, sh) ? 0 : 1;

@@ -421,6 +421,23 @@ def test_fp32_distance_to_64_bits(Hq, Hkv, D, seq, splits, tol):
     assert err <= tol
 
 
+@pytest.mark.parametrize("Hq,Hkv,D", [(2, 1, 64), (3, 3, 128), (4, 2, 128)])
+@pytest.mark.parametrize("before", [3, 16, 37, 100])
+def test_fp32_rows_do_not_depend_on_their_place_in_the_batch(Hq, Hkv, D, before):
+    """One head at a time: a sequence alone and behind another one of any length, the same bits, question and lse too."""
+    seq, gen = (21, 100, 330, 37), torch.Generator(device=DEV).manual_seed(16)
+    T = sum(seq) - seq[1]
+    q, k, v = (torch.randn(T + before, h, D, device=DEV, generator=gen) for h in (Hq, Hkv, Hkv))
+    heads, res = P.Heads(Hq, Hkv, D, "f32"), []
+    for seqs in ([seq], [(0, 8, before, 0), seq]):
+        lay, x = P.Layout.from_seqs(seqs), [t[before if len(seqs) == 1 else 0:].clone() for t in (q, k, v)]
+        out, lse = torch.zeros_like(x[0]), torch.zeros(lay.total_tokens, Hq, device=DEV)
+        P.pevlm_block_prefill_attn(*x, out, lay, heads, lse=lse)
+        P.pevlm_query_attn(*x, out, lay, heads, num_splits=3, lse=lse)
+        res.append((out[-T:].view(torch.int32), lse[-T:].view(torch.int32)))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+
+
 @pytest.mark.parametrize("Hq,Hkv,D,seqs,splits", [
     (3, 3, 128, [(0, 64, 0, 1), (0, 512, 9000, 1)], 16),                    # one pair; one key and empty splits beside long ones
     (7, 1, 128, [(65, 128, 300, 18), (9, 1000, 8000, 18)], 13),             # 126 of 128 pairs; key ranges of part of a tile
