@@ -302,9 +302,15 @@ __device__ __forceinline__ int32_t attn_f32_single(const AttnParams &p, const pe
 }
 
 // ---------------------------------------------------------------- all heads of a KV group, on bf16 matrix instructions
-// Every fp32 value is the sum of three bf16 ones, to the last bit: x = x1 + x2 + x3, each the rounding of what the ones before
-// leave, each at most 2^-9 of the one before.  A product is then x1 y1 + (x1 y2 + x2 y1) + (x1 y3 + x2 y2 + x3 y1), bf16
-// products that are exact in fp32, but for 2^-26 of it.
+// An fp32 value is the sum of three bf16 ones, to the last bit: x = x1 + x2 + x3, each the rounding of what the ones before
+// leave, each at most 2^-8 of the one before.  A product is then x1 y1 + (x1 y2 + x2 y1) + (x1 y3 + x2 y2 + x3 y1), bf16
+// products that are exact in fp32, but for x2 y3 + x3 y2 + x3 y3: 2^-23 of it at most, 2^-27 root mean square.
+//
+// x3 reaches down to the last bit of x, which bf16 does not hold as a normal number where x is below 2^-103.  Values and weights are
+// therefore taken kLift times as large, down to the smallest denormal (what then overflows does not come out finite).  Of keys
+// below 2^-103 up to 2^-126 is lost, which takes a query above kLargeQuery to be seen in a score; such rows, and those of a query
+// with numbers below kSmallQuery, are done again from the fp32 values.
+constexpr float kLift = 0x1p24f, kSmallQuery = 0x1p-100f, kLargeQuery = 0x1p80f;
 struct Planes {
     u32x4 x[3];  // eight values each
 };
@@ -397,7 +403,7 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
         for (int j = 0; j < NCH; ++j) {
             const int32_t r = srow + j * (THREADS / CH);
             const int32_t at = r * ROWB + ((ch ^ (is_v ? (r & VSW) << 2 : r & (CH - 1))) << 4);
-            const Planes x = split8(raw[j][0], raw[j][1]);
+            const Planes x = is_v ? split8(raw[j][0] * kLift, raw[j][1] * kLift) : split8(raw[j][0], raw[j][1]);
 #pragma unroll
             for (int n = 0; n < 3; ++n) *reinterpret_cast<u32x4 *>(planes[n] + at) = x.x[n];
         }
@@ -417,17 +423,28 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
 
     // ---- queries: planes 1 and 2 in registers, plane 3 in LDS
     u32x4 q1[KS], q2[KS];
+    const float c_log2 = p.scale * 1.4426950408889634f;
+    uint64_t extreme;
     if (n_tiles > 0) load_raw(p.k, 0);
     {
         const int32_t head = p.heads.head_order[g * G + min(col0 + l32, n_pairs - 1) % G];
         const f32x4 *q = reinterpret_cast<const f32x4 *>((const float *)p.q + ((int64_t)my_row * Hq + head) * D + 8 * g32);
+        uint32_t least = 0xffffffffu;  // twice the bits of the smallest number but 0, less one
+        float most = 0.f;
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
             const Planes x = split8(q[kk * 4], q[kk * 4 + 1]);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float a = q[kk * 4 + j / 4][j % 4];
+                least = min(least, (__float_as_uint(a) << 1) - 1u);
+                most = fmaxf(most, fabsf(a));
+            }
             q1[kk] = x.x[0];
             q2[kk] = x.x[1];
             sh.q3[wave][kk][lane] = x.x[2];
         }
+        extreme = __ballot(least < (__float_as_uint(kSmallQuery) << 1) - 1u || !(most * c_log2 < kLargeQuery));
     }
     if (n_tiles > 0) {
         stage(sh.k, false);
@@ -436,7 +453,6 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
     barrier();
 
     float m = -INFINITY, l = 0.f;
-    const float c_log2 = p.scale * 1.4426950408889634f;
     f32x16 o[DBLK];
 #pragma unroll
     for (int b = 0; b < DBLK; ++b)
@@ -513,8 +529,8 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
             Planes w8[2];
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks)
-                w8[ks] = split8(f32x4{w[8 * ks], w[8 * ks + 1], w[8 * ks + 2], w[8 * ks + 3]},
-                                f32x4{w[8 * ks + 4], w[8 * ks + 5], w[8 * ks + 6], w[8 * ks + 7]});
+                w8[ks] = split8(f32x4{w[8 * ks], w[8 * ks + 1], w[8 * ks + 2], w[8 * ks + 3]} * kLift,
+                                f32x4{w[8 * ks + 4], w[8 * ks + 5], w[8 * ks + 6], w[8 * ks + 7]} * kLift);
 #pragma unroll
             for (int b = 0; b < DBLK; ++b) {
                 f32x16 sum = zero;
@@ -548,7 +564,7 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
     const int32_t my_pair = min(col0 + out32, n_pairs - 1), my_head = p.heads.head_order[g * G + my_pair % G];
     l += other_half(l);
     const bool live = col0 + out32 < n_pairs;
-    const float inv = PARTIAL ? 1.f : 1.f / l;
+    const float inv = (PARTIAL ? 1.f : 1.f / l) * (1.f / (kLift * kLift));
     float wrong = 0.f;  // stays 0 while every value is finite
 #pragma unroll
     for (int b = 0; b < DBLK; ++b)
@@ -561,7 +577,7 @@ __device__ __forceinline__ void attn_f32_group(const AttnParams &p, const pevlm_
             *reinterpret_cast<f32x4 *>(&sh.o[wave * 32 + out32][b * 32 + i4 * 8 + half * 4]) = x;
         }
     // Columns whose rows are to be done again: by this wavefront, and not stored before.
-    const uint64_t marked = __ballot(live && wrong != 0.f);
+    const uint64_t marked = __ballot(live && wrong != 0.f) | (extreme & __ballot(live));
     uint32_t again = (uint32_t)(marked | marked >> 32);
     const int64_t slot = (int64_t)((PARTIAL ? it.reserved : it.q_start) + my_pair / G) * Hq + my_head;
     if (live && half == 0 && !(again >> out32 & 1)) {

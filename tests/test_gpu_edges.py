@@ -389,6 +389,31 @@ def test_fp32_groups_of_heads(oracle, Hq, Hkv, D, seqs, splits):
     assert outs[0].any() and (outs[0] - outs[1]).abs().max() <= F32_TOL
 
 
+def attention_in_64_bits(q, k, v, seq):
+    """Rows of one sequence (rotated operands on the CPU), on the device and in 64 bits."""
+    S, B, C, _Q = seq
+    T, Hq, D = q.shape
+    i = torch.arange(T, device=DEV)
+    region = torch.where(i < S, -1, torch.where(i < S + C, (i - S) // B, T))
+    sees = (i[None, :] <= i[:, None]) & ((region[None, :] == region[:, None]) | (region[None, :] == -1) | (region[:, None] == T))
+    q, k, v = (x.to(DEV).double() for x in (q, k, v))
+    want = torch.zeros(T, Hq, D, dtype=torch.float64, device=DEV)
+    for h in range(Hq):
+        g = h * k.shape[1] // Hq
+        w = torch.softmax((q[:, h] @ k[:, g].T / D ** 0.5).masked_fill(~sees, float("-inf")), dim=-1)
+        want[:, h] = w @ v[:, g]
+    return want
+
+
+def fp32_attention(q, k, v, seq, splits):
+    lay, heads = P.Layout.from_seqs([seq]), P.Heads(q.shape[1], k.shape[1], q.shape[2], "f32")
+    dev = [x.to(DEV) for x in (q, k, v)]
+    out = torch.full_like(dev[0], float("nan"))
+    P.pevlm_block_prefill_attn(*dev, out, lay, heads)
+    P.pevlm_query_attn(*dev, out, lay, heads, num_splits=splits)
+    return out.double()
+
+
 @pytest.mark.parametrize("Hq,Hkv,D,seq,splits,tol", [
     (28, 4, 128, (100, 333, 500, 40), 4, 4.6e-7),  # the two-head kernel of before had 4.65e-7, one sum a score 6.5e-7
     (14, 2, 64, (77, 333, 900, 21), 4, 3.5e-7),    # 3.53e-7, 4.96e-7
@@ -399,26 +424,45 @@ def test_fp32_groups_of_heads(oracle, Hq, Hkv, D, seqs, splits):
 def test_fp32_distance_to_64_bits(Hq, Hkv, D, seq, splits, tol):
     """Relative 2-norm of the error over all rows, scores of standard deviation 2: no more than the fp32 matrix instructions of two heads
     a workgroup had.  The limit lies between what two sums a score measure (10 to 15 % below it) and what one does."""
-    lay, heads = P.Layout.from_seqs([seq]), P.Heads(Hq, Hkv, D, "f32")
-    S, B, C, Q = seq
-    T = S + C + Q
     gen = torch.Generator().manual_seed(15)
-    q, k, v = (torch.randn(T, h, D, generator=gen) for h in (Hq, Hkv, Hkv))
+    q, k, v = (torch.randn(sum(seq) - seq[1], h, D, generator=gen) for h in (Hq, Hkv, Hkv))
     q *= 2.0
-    i = torch.arange(T)
-    region = torch.where(i < S, -1, torch.where(i < S + C, (i - S) // B, T))
-    sees = (i[None, :] <= i[:, None]) & ((region[None, :] == region[:, None]) | (region[None, :] == -1) | (region[:, None] == T))
-    want = torch.zeros(T, Hq, D, dtype=torch.float64)
-    for h in range(Hq):
-        s = q[:, h].double() @ k[:, h * Hkv // Hq].double().T / D ** 0.5
-        want[:, h] = torch.softmax(s.masked_fill(~sees, float("-inf")), dim=-1) @ v[:, h * Hkv // Hq].double()
-    dev = [x.to(DEV) for x in (q, k, v)]
-    out = torch.full((T, Hq, D), float("nan"), device=DEV)
-    P.pevlm_block_prefill_attn(*dev, out, lay, heads)
-    P.pevlm_query_attn(*dev, out, lay, heads, num_splits=splits)
-    err = float((out.cpu().double() - want).norm() / want.norm())
+    want = attention_in_64_bits(q, k, v, seq)
+    err = float((fp32_attention(q, k, v, seq, splits) - want).norm() / want.norm())
     print(err)
     assert err <= tol
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(56, 8, 64), (64, 16, 128)])
+@pytest.mark.parametrize("q_exp,k_exp,v_exp", [(0, 0, -112), (0, 0, -118), (0, 0, -126), (0, 0, 100), (0, 0, 123), (112, -112, 0), (-112, 112, 0), (-60, 60, -60)])
+def test_fp32_groups_of_heads_over_all_magnitudes(Hq, Hkv, D, q_exp, k_exp, v_exp):
+    """Operands whose bf16 parts would not all be normal numbers, and ones that leave no room for a power of two: as exact as others.
+    The limit is that of the test before for scores of deviation 1, twice it for rows that are done again one by one."""
+    seq, gen = (37, 150, 480, 70), torch.Generator().manual_seed(17)
+    q, k, v = (torch.randn(sum(seq) - seq[1], h, D, generator=gen) for h in (Hq, Hkv, Hkv))
+    tensors = [(x * 2.0 ** e, e) for x, e in ((q, q_exp), (k, k_exp), (v, v_exp))]
+    want = attention_in_64_bits(*(x.double() * 2.0 ** -e for x, e in tensors), seq)  # of what the denormals among them hold
+    got = fp32_attention(*(x for x, _e in tensors), seq, 13) * 2.0 ** -v_exp
+    if v_exp == -126:  # results about 2^-126: a step of the smallest denormal, 2^-23 here, beside the largest error of the others
+        assert float((got - want).abs().max()) <= 2.0 ** -23 + 1e-6
+    else:
+        err = float((got - want).norm() / want.norm())
+        print(err)
+        assert err <= 6e-7
+
+
+def test_fp32_groups_of_heads_with_vanishing_weights_of_large_values():
+    """A key whose weight is 2^-118 to 2^-125 of the largest and whose value is 2^103, beside values of 2^-17: a good part of the
+    result.  The weight's own error is its exponent's, 86 x 2^-24; a weight in fewer bits than fp32 has would be seen."""
+    Hq, Hkv, D, seq, gen = 56, 8, 64, (37, 150, 480, 70), torch.Generator().manual_seed(18)
+    T = sum(seq) - seq[1]
+    q, k, v = (torch.randn(T, h, D, generator=gen) for h in (Hq, Hkv, Hkv))
+    q[:, :, 0], k[:, :, 0], k[0, :, 1:], k[0, :, 0] = 8.0, 0.0, 0.0, -82.0
+    v[:, :, 5] = 2.0 ** -17 * (1.0 + torch.rand(T, Hkv, generator=gen))
+    v[0, :, 5] = 1.999 * 2.0 ** 102
+    want = attention_in_64_bits(q, k, v, seq)[1:, :, 5]
+    got = fp32_attention(q, k, v, seq, 13)[1:, :, 5]
+    assert float(((got - want) / want).abs().max()) <= 2e-5
 
 
 @pytest.mark.parametrize("Hq,Hkv,D", [(2, 1, 64), (3, 3, 128), (4, 2, 128)])
