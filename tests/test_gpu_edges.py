@@ -493,6 +493,7 @@ def test_fp32_rows_do_not_depend_on_their_place_in_the_batch(Hq, Hkv, D, before)
     (4, 2, 64, [(3, 512, 16000, 64), (0, 64, 0, 0), (7, 64, 900, 3)], 30),    # as many
     (16, 8, 64, [(30, 700, 17000, 128)], 32),                               # 256 pairs, 128 rows of the diagonal: two tiles of it
     (64, 1, 128, [(0, 512, 26000, 4)] + [(0, 512, 3000, 4)] * 4, 50),       # 256 pairs of a wide group; more sequences than kernel arguments hold
+    (16, 2, 64, [(0, 512, 11000, 16)] + [(5, 64, 700 + i, 16 - i) for i in range(5)], 20),  # more sequences, two KV heads
 ])
 @pytest.mark.parametrize("call", ["plain", "rope", "window", "bad"])
 def test_short_questions(Hq, Hkv, D, seqs, splits, call):
@@ -516,4 +517,29 @@ def test_short_questions(Hq, Hkv, D, seqs, splits, call):
         else:
             P.pevlm_query_attn(q, kk, vv, out, lay, heads, num_splits=splits, lse=lse)
         res.append((out.view(torch.int16), lse.view(torch.int32)))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+
+
+@pytest.mark.parametrize("Hq,D,seqs,splits", [
+    (7, 128, [(65, 128, 300, 18), (9, 1000, 8000, 18)], 13),
+    (64, 128, [(0, 512, 26000, 4)] + [(0, 512, 3000, 4)] * 4, 50),
+    (32, 64, [(3, 512, 16000, 8), (0, 64, 0, 0), (7, 64, 900, 3)], 60),
+])
+@pytest.mark.parametrize("call", ["plain", "rope", "window"])
+def test_short_questions_of_one_kv_head(Hq, D, seqs, splits, call):
+    """One KV head has no other head map: the one-item kernel takes its heads as the second half of a call with two KV heads
+    under a map that swaps them."""
+    lay, gen = P.Layout.from_seqs(seqs), torch.Generator(device=DEV).manual_seed(19)
+    q, k, v = (torch.randn(lay.total_tokens, h, D, device=DEV, dtype=torch.bfloat16, generator=gen) for h in (2 * Hq, 2, 2))
+    res = []
+    for heads, x, kk, vv in ((P.Heads(Hq, 1, D, "bf16"), *(t.contiguous() for t in (q[:, Hq:], k[:, :1], v[:, :1]))),
+                             (P.Heads(2 * Hq, 2, D, "bf16", kv_head_of_q=[1] * Hq + [0] * Hq), q, k, v)):
+        out, lse = torch.full_like(x, 7.0), torch.full((lay.total_tokens, x.shape[1]), 7.0, device=DEV)
+        if call == "rope":
+            P.pevlm_query_attn_rope(x, kk, vv, out, lay, heads, 1.0e6, pos_offset=[70 * i for i in range(len(seqs))], num_splits=splits, lse=lse)
+        elif call == "window":
+            P.pevlm_query_attn_window(x, kk, vv, out, lay, heads, [30] * len(seqs), num_splits=splits, lse=lse)
+        else:
+            P.pevlm_query_attn(x, kk, vv, out, lay, heads, num_splits=splits, lse=lse)
+        res.append((out[:, -Hq:].contiguous().view(torch.int16), lse[:, -Hq:].contiguous().view(torch.int32)))
     assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
