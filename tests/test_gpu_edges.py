@@ -522,8 +522,8 @@ def test_short_questions(Hq, Hkv, D, seqs, splits, call):
 
 @pytest.mark.parametrize("Hq,D,seqs,splits", [
     (7, 128, [(65, 128, 300, 18), (9, 1000, 8000, 18)], 13),
-    (64, 128, [(0, 512, 26000, 4)] + [(0, 512, 3000, 4)] * 4, 50),
-    (32, 64, [(3, 512, 16000, 8), (0, 64, 0, 0), (7, 64, 900, 3)], 60),
+    (64, 128, [(0, 900, 26000, 4)] + [(0, 512, 3000, 4)] * 4, 50),
+    (16, 64, [(3, 1200, 34000, 8), (0, 64, 0, 0), (7, 64, 900, 3)], 60),
 ])
 @pytest.mark.parametrize("call", ["plain", "rope", "window"])
 def test_short_questions_of_one_kv_head(Hq, D, seqs, splits, call):
