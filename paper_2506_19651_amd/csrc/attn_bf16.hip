@@ -296,32 +296,10 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
 #pragma unroll
     for (int kk = 0; kk < KSTEPS; ++kk)
         qf[kk] = *reinterpret_cast<const bf16x8 *>(wave_slice + l32 * ROWB + (((kk * 2 + g32) ^ (l32 & (CH - 1))) << 4));
-    if (ROPEQ) {
-        // this lane holds dims kk*16 + g32*8 + e of its row: pair index i < D/2 in qf[kk], its partner
-        // i + D/2 in qf[kk + KSTEPS/2]
-#pragma unroll
-        for (int kk = 0; kk < KSTEPS / 2; ++kk) {
-            const f32x4 *cs = rope_cs[kk];
-            const u32x4 lo = __builtin_bit_cast(u32x4, qf[kk]), hi = __builtin_bit_cast(u32x4, qf[kk + KSTEPS / 2]);
-            u32x4 rl, rh;
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const float a0 = __uint_as_float(lo[w] << 16), a1 = __uint_as_float(lo[w] & 0xffff0000u);
-                const float b0 = __uint_as_float(hi[w] << 16), b1 = __uint_as_float(hi[w] & 0xffff0000u);
-                float r0, r1, t0, t1;
-                rope_rotate(a0, b0, cs[w][0], cs[w][1], r0, t0);
-                rope_rotate(a1, b1, cs[w][2], cs[w][3], r1, t1);
-                rl[w] = rope_pack_bf16(r0, r1);
-                rh[w] = rope_pack_bf16(t0, t1);
-            }
-            qf[kk] = __builtin_bit_cast(bf16x8, rl);
-            qf[kk + KSTEPS / 2] = __builtin_bit_cast(bf16x8, rh);
-        }
-    }
+    if constexpr (ROPEQ) rotate_query(qf, rope_cs);
 
     // m_ref: reference maximum of this lane's row in base-2 units, c_log2 * score (-inf: none yet)
     float m_ref = -INFINITY, l_run = 0.f;
-#define PEVLM_MREF ((m_ref == -INFINITY) ? 0.f : m_ref)
     f32x16 o[DBLK];
 #pragma unroll
     for (int b = 0; b < DBLK; ++b)
@@ -334,32 +312,6 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
         if ((k0 + KT > kend) || (causal && (k0 + KT - 1 > wr_lo)))                        \
             mask_tile(s, k0, kend, causal, my_row, g32);                                  \
     } while (0)
-    // The weights of a tile are first formed against the reference maximum the row already has.
-    // Only if a lane's weights may have reached 2^kRescaleStep (or a row has no reference yet) is the
-    // row maximum of the tile computed, the reference raised, o and l scaled down and the tile's weights formed
-    // again: weights stay below 2^kRescaleStep, which fp32 sums and bf16 weights carry without loss,
-    // and on almost every tile the vector ALU only does exp2, convert and sum.  A row is raised for its own weights
-    // only: its result does not depend on which rows share its wavefront, which the two prefill kernels, the calls with
-    // RoPE folded in and a prefill in pieces choose differently.
-#define PEVLM_FIX_REFERENCE()                                                                         \
-    do {                                                                                              \
-        const int32_t up_ = sum_reached_step(psum) || m_ref == -INFINITY;                             \
-        if (__any(up_)) {                                                                             \
-            const float mx = row_max(s) * c_log2;                                                     \
-            const bool has = m_ref != -INFINITY;                                                      \
-            const float m_new = up_ | __shfl_xor(up_, 32) ? fmaxf(m_ref, mx) : m_ref;                   \
-            const float alpha = has ? __builtin_amdgcn_exp2f(m_ref - m_new) : 1.f;                    \
-            m_ref = m_new;                                                                            \
-            psum = 0.f;                                                                               \
-            weights(s, c_log2, PEVLM_MREF, psum, pf);                                                 \
-            if (__any(has)) { /* rows without a reference have o = l = 0 */                          \
-                l_run = rounded_product(l_run, alpha);                                                \
-                _Pragma("unroll") for (int b = 0; b < DBLK; ++b)                                      \
-                    _Pragma("unroll") for (int i = 0; i < 16; ++i) o[b][i] *= alpha;                  \
-            }                                                                                         \
-        }                                                                                             \
-    } while (0)
-
     f32x16 s[2];
     u32x4 pf[4];  // weights of the last tile whose scores are known, bf16 pairs
     float psum;
@@ -376,7 +328,7 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
         PEVLM_TILE_RANGE(0, k0, kend, causal);
         PEVLM_MASK(k0, kend, causal);
         psum = 0.f;  // no row has a reference yet: the first tile always takes the exact path
-        PEVLM_FIX_REFERENCE();
+        raise_reference(s, c_log2, m_ref, l_run, psum, pf, o);
         l_run += psum;
         for (int32_t t = 1; t < n_w; ++t) {
             // top of tile t as in PEVLM_TOP, but K(t+1) and V(t) are fetched piecewise between the
@@ -398,8 +350,8 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
             PEVLM_MASK(k0, kend, causal);
             // values of tile t-1 (matrix cores) under the weights of tile t (vector ALU)
             psum = 0.f;
-            pv_prev_weights_cur<D, NLD>(tv, L, pf, o, s, c_log2, PEVLM_MREF, psum, ldv, vfirst);
-            PEVLM_FIX_REFERENCE();
+            pv_prev_weights_cur<D, NLD>(tv, L, pf, o, s, c_log2, reference_of(m_ref), psum, ldv, vfirst);
+            raise_reference(s, c_log2, m_ref, l_run, psum, pf, o);
             l_run += psum;
         }
     }
@@ -450,19 +402,7 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
     if (PARTIAL) {
         if (!pair_valid) return;
         const int64_t slot = ((int64_t)it.reserved + out_row) * Hq + out_head;
-        float *acc = p.part_acc + slot * D;
-#pragma unroll
-        for (int b = 0; b < DBLK; ++b)
-#pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4) {
-                const int32_t d = b * 32 + i4 * 8 + g32 * 4;
-                f32x4 v4 = {o[b][i4 * 4], o[b][i4 * 4 + 1], o[b][i4 * 4 + 2], o[b][i4 * 4 + 3]};
-                *reinterpret_cast<f32x4 *>(acc + d) = v4;
-            }
-        if (g32 == 0) {
-            p.part_ml[slot * 2] = m_ref / c_log2;  // back to raw score units (-inf stays)
-            p.part_ml[slot * 2 + 1] = l_tot;
-        }
+        store_partial(p, slot, o, g32, m_ref, c_log2, l_tot);
     } else {
         // O^T fragments -> wave-private LDS slice (row-major bf16, swizzled), then whole-row 16-byte
         // stores.  The slice lies in the stage the last tile does not use: a wavefront may still be

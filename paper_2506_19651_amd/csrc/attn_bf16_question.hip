@@ -11,7 +11,6 @@
 // (past the last tile the last one again, into a stage that nobody reads): the top of a tile waits until only those of the
 // tile before are outstanding.
 #include "attn_bf16_tile.h"
-#include "rope_math.h"
 
 namespace pevlm {
 
@@ -164,26 +163,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_question_kernel(AttnPara
     bf16x8 qf[KSTEPS];
 #pragma unroll
     for (int kk = 0; kk < KSTEPS; ++kk) qf[kk] = *reinterpret_cast<const bf16x8 *>(slice + l32 * ROWB + (((kk * 2 + g32) ^ (l32 & (CH - 1))) << 4));
-    if (ROPE != kRotated) {
-#pragma unroll
-        for (int kk = 0; kk < KSTEPS / 2; ++kk) {
-            const f32x4 *cs = rope_cs[kk];
-            const u32x4 lo = __builtin_bit_cast(u32x4, qf[kk]), hi = __builtin_bit_cast(u32x4, qf[kk + KSTEPS / 2]);
-            u32x4 rl, rh;
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const float a0 = __uint_as_float(lo[w] << 16), a1 = __uint_as_float(lo[w] & 0xffff0000u);
-                const float b0 = __uint_as_float(hi[w] << 16), b1 = __uint_as_float(hi[w] & 0xffff0000u);
-                float r0, r1, t0, t1;
-                rope_rotate(a0, b0, cs[w][0], cs[w][1], r0, t0);
-                rope_rotate(a1, b1, cs[w][2], cs[w][3], r1, t1);
-                rl[w] = rope_pack_bf16(r0, r1);
-                rh[w] = rope_pack_bf16(t0, t1);
-            }
-            qf[kk] = __builtin_bit_cast(bf16x8, rl);
-            qf[kk + KSTEPS / 2] = __builtin_bit_cast(bf16x8, rh);
-        }
-    }
+    if constexpr (ROPE != kRotated) rotate_query(qf, rope_cs);
 
     const float c_log2 = p.scale * 1.4426950408889634f;
     float m_ref = -INFINITY, l_run = 0.f, psum = 0.f;
@@ -193,31 +173,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_question_kernel(AttnPara
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[b][i] = 0.f;
     u32x4 pf[4];
-    auto mref = [&] { return m_ref == -INFINITY ? 0.f : m_ref; };
     auto mask = [&](int32_t t) {
         int32_t k0, kend;
         const bool causal = tile_range(t, k0, kend);
         if ((k0 + KT > kend) || (causal && (k0 + KT - 1 > wr_lo))) mask_tile(s, k0, kend, causal, my_row, g32);
-    };
-    // as in the one-item kernel: a row's reference maximum is raised for its own weights only
-    auto fix_reference = [&] {
-        const int32_t up = sum_reached_step(psum) || m_ref == -INFINITY;
-        if (__any(up)) {
-            const float mx = row_max(s) * c_log2;
-            const bool has = m_ref != -INFINITY;
-            const float m_new = up | __shfl_xor(up, 32) ? fmaxf(m_ref, mx) : m_ref;
-            const float alpha = has ? __builtin_amdgcn_exp2f(m_ref - m_new) : 1.f;
-            m_ref = m_new;
-            psum = 0.f;
-            weights(s, c_log2, mref(), psum, pf);
-            if (__any(has)) {
-                l_run = rounded_product(l_run, alpha);
-#pragma unroll
-                for (int b = 0; b < DBLK; ++b)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) o[b][i] *= alpha;
-            }
-        }
     };
     const auto next = [](int32_t st) { return st + 1 < NST ? st + 1 : 0; };
     const auto before = [](int32_t st) { return st > 0 ? st - 1 : NST - 1; };
@@ -243,7 +202,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_question_kernel(AttnPara
         qk_tile<D, false, NL>(lds_k, L, qf, s, ldk, [] {}, [] {});
         mask(0);
         psum = 0.f;
-        fix_reference();
+        raise_reference(s, c_log2, m_ref, l_run, psum, pf, o);
         l_run += psum;
         for (int32_t t = 1; t < n_w; ++t) {
             st = next(st);
@@ -253,8 +212,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_question_kernel(AttnPara
             qk_tile<D, true, NL>(lds_k + st * TILEB, L, qf, s, ldk, [&] { prepare(t, st); }, [&] { first_v<D>(tv, L, vfirst); });
             mask(t);
             psum = 0.f;
-            pv_prev_weights_cur<D, NL>(tv, L, pf, o, s, c_log2, mref(), psum, ldv, vfirst);
-            fix_reference();
+            pv_prev_weights_cur<D, NL>(tv, L, pf, o, s, c_log2, reference_of(m_ref), psum, ldv, vfirst);
+            raise_reference(s, c_log2, m_ref, l_run, psum, pf, o);
             l_run += psum;
         }
     }
@@ -286,18 +245,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_question_kernel(AttnPara
     if (out_pair >= n_pairs) return;
     const int32_t out_row = div_by(out_pair, group_rcp);
     const int64_t slot = ((int64_t)it.reserved + out_row) * Hq + g * G + out_pair - out_row * G;
-    float *acc = p.part_acc + slot * D;
-#pragma unroll
-    for (int b = 0; b < DBLK; ++b)
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-            const f32x4 v4 = {o[b][i4 * 4], o[b][i4 * 4 + 1], o[b][i4 * 4 + 2], o[b][i4 * 4 + 3]};
-            *reinterpret_cast<f32x4 *>(acc + b * 32 + i4 * 8 + g32 * 4) = v4;
-        }
-    if (g32 == 0) {
-        p.part_ml[slot * 2] = m_ref / c_log2;  // back to raw score units (-inf stays)
-        p.part_ml[slot * 2 + 1] = l_tot;
-    }
+    store_partial(p, slot, o, g32, m_ref, c_log2, l_tot);
 }
 
 // This kernel takes a compute unit per (KV head, split), so there must not be more of those.  Up to 128 pairs a workgroup

@@ -252,31 +252,10 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
     u32x4 pf[4];
     float m_ref = -INFINITY, l_run = 0.f, psum = 0.f;
     const float c_log2 = p.scale * 1.4426950408889634f;
-#define PEVLM_MREF ((m_ref == -INFINITY) ? 0.f : m_ref)
     // slot of the item being computed / of the item whose last value tile and output are pending
     int32_t q_start = 0, q_rows = 0, head = 0;
     int32_t pend = 0, pend_vs = 0, pend_q_start = 0, pend_q_rows = 0, pend_head = 0;
     int32_t q_age = 3;  // tiles since this wavefront last issued a query prefetch (>= 3: it has landed)
-
-    // same check-after-the-fact reference maximum as the one-item kernel
-#define PEVLM_FIX_REFERENCE()                                                                         \
-    do {                                                                                              \
-        const int32_t up_ = sum_reached_step(psum) || m_ref == -INFINITY;                             \
-        if (__any(up_)) {                                                                             \
-            const float mx = row_max(s) * c_log2;                                                     \
-            const bool has = m_ref != -INFINITY;                                                      \
-            const float m_new = up_ | __shfl_xor(up_, 32) ? fmaxf(m_ref, mx) : m_ref;                   \
-            const float alpha = has ? __builtin_amdgcn_exp2f(m_ref - m_new) : 1.f;                    \
-            m_ref = m_new;                                                                            \
-            psum = 0.f;                                                                               \
-            weights(s, c_log2, PEVLM_MREF, psum, pf);                                             \
-            if (__any(has)) {                                                                         \
-                l_run = rounded_product(l_run, alpha);                                                \
-                _Pragma("unroll") for (int b = 0; b < DBLK; ++b)                                      \
-                    _Pragma("unroll") for (int i = 0; i < 16; ++i) o[b][i] *= alpha;                  \
-            }                                                                                         \
-        }                                                                                             \
-    } while (0)
 
     // last value tile of a finished slot (V stage pend_vs), normalisation, rows out through the slice
 #define PEVLM_FINISH_PENDING()                                                                        \
@@ -440,7 +419,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
             qk_tile<D, false, NL>(lds_k + ks * TILEB, L, qf, s, ldk, [] {}, [] {});
             if ((k0 + KT > kend) || (causal && (k0 + KT - 1 > wr_lo))) mask_tile(s, k0, kend, causal, my_row, g32);
             psum = 0.f;
-            PEVLM_FIX_REFERENCE();
+            raise_reference(s, c_log2, m_ref, l_run, psum, pf, o);
             l_run += psum;
         }
         if (n_w <= 1) PEVLM_END_OF_COMPUTE(ord);
@@ -461,8 +440,8 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_stream_kernel(StreamParams p
                 [&] { first_v<D>(tv, L, vfirst); });
             if ((k0 + KT > kend) || (causal && (k0 + KT - 1 > wr_lo))) mask_tile(s, k0, kend, causal, my_row, g32);
             psum = 0.f;
-            pv_prev_weights_cur<D, NL>(tv, L, pf, o, s, c_log2, PEVLM_MREF, psum, ldv, vfirst);
-            PEVLM_FIX_REFERENCE();
+            pv_prev_weights_cur<D, NL>(tv, L, pf, o, s, c_log2, reference_of(m_ref), psum, ldv, vfirst);
+            raise_reference(s, c_log2, m_ref, l_run, psum, pf, o);
             l_run += psum;
             if (t == n_w - 1) PEVLM_END_OF_COMPUTE(ord);
             PEVLM_NEXT_TILE();

@@ -3,6 +3,7 @@
 // online softmax.  Shared by the one-item-per-workgroup kernel and the streaming kernel.
 #pragma once
 #include "bf16_device.h"
+#include "rope_math.h"
 
 namespace pevlm {
 
@@ -176,6 +177,80 @@ __device__ __forceinline__ float rounded_product(float a, float b)
 {
 #pragma clang fp contract(off)
     return a * b;
+}
+
+// The weights of a tile are first formed against the reference maximum the row already has (m_ref, base-2 units; -inf: none yet).
+// Only if a lane's weights may have reached 2^kRescaleStep (or a row has no reference yet) is the
+// row maximum of the tile computed, the reference raised, o and l scaled down and the tile's weights formed
+// again: weights stay below 2^kRescaleStep, which fp32 sums and bf16 weights carry without loss,
+// and on almost every tile the vector ALU only does exp2, convert and sum.  A row is raised for its own weights
+// only: its result does not depend on which rows share its wavefront, which the kernels, the calls with
+// RoPE folded in and a prefill in pieces choose differently.
+__device__ __forceinline__ float reference_of(float m_ref) { return m_ref == -INFINITY ? 0.f : m_ref; }
+template <int DBLK>
+__device__ __forceinline__ void raise_reference(const f32x16 (&s)[2], float c_log2, float &m_ref, float &l_run, float &psum, u32x4 (&pf)[4],
+                                                f32x16 (&o)[DBLK])
+{
+    const int32_t up = sum_reached_step(psum) || m_ref == -INFINITY;
+    if (__any(up)) {
+        const float mx = row_max(s) * c_log2;
+        const bool has = m_ref != -INFINITY;
+        const float m_new = up | __shfl_xor(up, 32) ? fmaxf(m_ref, mx) : m_ref;
+        const float alpha = has ? __builtin_amdgcn_exp2f(m_ref - m_new) : 1.f;
+        m_ref = m_new;
+        psum = 0.f;
+        weights(s, c_log2, reference_of(m_ref), psum, pf);
+        if (__any(has)) {
+            l_run = rounded_product(l_run, alpha);
+#pragma unroll
+            for (int b = 0; b < DBLK; ++b)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[b][i] *= alpha;
+        }
+    }
+}
+
+// A lane's query fragments turned by its row's (cos, sin) pairs, with pevlm_rope_seq's arithmetic: it holds dims
+// kk*16 + g32*8 + e of its row, pair index i < D/2 in qf[kk], its partner i + D/2 in qf[kk + KSTEPS/2]
+template <int KSTEPS>
+__device__ __forceinline__ void rotate_query(bf16x8 (&qf)[KSTEPS], const f32x4 (&rope_cs)[KSTEPS / 2][4])
+{
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS / 2; ++kk) {
+        const f32x4 *cs = rope_cs[kk];
+        const u32x4 lo = __builtin_bit_cast(u32x4, qf[kk]), hi = __builtin_bit_cast(u32x4, qf[kk + KSTEPS / 2]);
+        u32x4 rl, rh;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float a0 = __uint_as_float(lo[w] << 16), a1 = __uint_as_float(lo[w] & 0xffff0000u);
+            const float b0 = __uint_as_float(hi[w] << 16), b1 = __uint_as_float(hi[w] & 0xffff0000u);
+            float r0, r1, t0, t1;
+            rope_rotate(a0, b0, cs[w][0], cs[w][1], r0, t0);
+            rope_rotate(a1, b1, cs[w][2], cs[w][3], r1, t1);
+            rl[w] = rope_pack_bf16(r0, r1);
+            rh[w] = rope_pack_bf16(t0, t1);
+        }
+        qf[kk] = __builtin_bit_cast(bf16x8, rl);
+        qf[kk + KSTEPS / 2] = __builtin_bit_cast(bf16x8, rh);
+    }
+}
+
+// A lane's share of a (row, head) pair of a split: unnormalised values, maximum and sum
+template <int DBLK>
+__device__ __forceinline__ void store_partial(const AttnParams &p, int64_t slot, const f32x16 (&o)[DBLK], int32_t g32, float m_ref, float c_log2, float l_tot)
+{
+    float *acc = p.part_acc + slot * (DBLK * 32);
+#pragma unroll
+    for (int b = 0; b < DBLK; ++b)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+            const f32x4 v4 = {o[b][i4 * 4], o[b][i4 * 4 + 1], o[b][i4 * 4 + 2], o[b][i4 * 4 + 3]};
+            *reinterpret_cast<f32x4 *>(acc + b * 32 + i4 * 8 + g32 * 4) = v4;
+        }
+    if (g32 == 0) {
+        p.part_ml[slot * 2] = m_ref / c_log2;  // back to raw score units (-inf stays)
+        p.part_ml[slot * 2 + 1] = l_tot;
+    }
 }
 
 // O^T += V^T P^T for a staged V tile (16 MFMAs per 32 values of head_dim ... 4 k-steps x DBLK blocks)
