@@ -61,14 +61,14 @@ def prefill_work(layout: Layout, heads: Heads):
     return n_wg, n_tiles
 
 
-_XCDS, _DEALT_ROUNDS, _DEALT_ITEMS, _DEALT_WGS, _DEALT_SEQS, _EVEN_SHARE = 8, 4, 4096, 32, 48, 28
+_XCDS, _DEALT_ROUNDS, _DEALT_ITEMS, _DEALT_WGS, _DEALT_SEQS, _EVEN_SHARE = 8, 4, 4096, 32, 48, 18
 
 
 def stream_shares(tiles, num_seqs: int, compute_units: int = 256):
     """The library's own assignment of a stream-item list (key tiles of each item) to workgroups: one array of item
     numbers per workgroup, in its order.  Runs of the list per XCD are cut by cost, 7 an item and 3 a tile; inside a run
-    the items go round by round to the workgroups, as listed where that is even enough, else ranked by cost there and
-    back, the last rounds' sorted and to the least loads."""
+    the items go round by round to the workgroups, as listed where that is even enough over all of them, else ranked by cost
+    there and back, the last rounds' sorted and to the least loads."""
     import numpy as np
 
     n, wgs = len(tiles), min(max(compute_units // _XCDS, 1), _DEALT_WGS)
@@ -79,14 +79,13 @@ def stream_shares(tiles, num_seqs: int, compute_units: int = 256):
     dealt = num_seqs <= _DEALT_SEQS and wgs == _DEALT_WGS and max(np.diff(first)) <= _DEALT_ITEMS
     if not dealt:
         first = [n * x // _XCDS for x in range(_XCDS + 1)]
+    listed = [np.arange(lo + w, hi, wgs) for lo, hi in zip(first[:-1], first[1:]) for w in range(wgs)]
+    most = max((int(cost[i].sum()) for i in listed), default=0)
+    if not dealt or most * len(listed) * _EVEN_SHARE <= total * (_EVEN_SHARE + 1):
+        return listed
     shares = []
     for lo, hi in zip(first[:-1], first[1:]):
         c, m = cost[lo:hi], hi - lo
-        listed = [np.arange(lo + w, hi, wgs) for w in range(wgs)]
-        most = max((int(cost[i].sum()) for i in listed), default=0)
-        if not dealt or most * wgs * _EVEN_SHARE <= int(c.sum()) * (_EVEN_SHARE + 1):
-            shares += listed
-            continue
         plain = max(0, -(-m // wgs) - _DEALT_ROUNDS) * wgs
         mine, load = [[] for _ in range(wgs)], np.zeros(wgs, np.int64)
         for r0 in range(0, plain, wgs):

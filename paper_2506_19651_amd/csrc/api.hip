@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <numeric>
 
 #include "common.h"
 #include "rope_math.h"
@@ -287,9 +288,12 @@ static bool stream_kernel_applies(const pevlm_layout *lay, const pevlm_heads *h)
 }
 
 // It deals whole items out to one resident workgroup per compute unit; with only a few items per
-// workgroup the shares come out too uneven, and the one-item-per-workgroup kernel (two small workgroups
-// per compute unit, dispatched as slots free up) finishes sooner.  So it does on regions far longer
-// than any block the method uses (a dense causal attention written as one block: measured 8 % faster at
+// workgroup a last item weighs too much, and the one-item-per-workgroup kernel (two small workgroups
+// per compute unit, dispatched as slots free up) finishes sooner (32/8 heads, blocks of 565 over 1.6 K tokens 24 us and 18.6; of 634
+// over 3.8 K 38 and 39).  From 9 to 12 items per compute unit the two are within 5 % of one another either way (28/4 heads, blocks
+// of 256, 9.5 items: 163 and 159 us; of 1024, 10.4: 269 and 277; of 392, 11.7: 272 and 268); above the streaming kernel takes
+// 0.88 to 0.97 of the other's time, but for 28/4 heads in blocks of 128 and 196 (1.02 to 1.08).  The other one is faster, too, on regions
+// far longer than any block the method uses (a dense causal attention written as one block: measured 8 % faster at
 // 64K rows), where the key stream of an item no longer stays in the L2 of its XCD.  64-wide heads always
 // go to the one-item kernel: it fits three wavefronts on a SIMD there, resident workgroups with three stages per
 // tensor two (98K tokens x 14 heads in blocks of 1024: 341 us against 362, of 3136: 695 against 758, of 128: 185 against 207).
@@ -315,19 +319,60 @@ static int64_t count_stream_items(const pevlm_layout *lay, const pevlm_heads *h,
     return n;
 }
 
-// First item of every XCD: the list cut into kXcds runs that take the same time, to within an item.
-static void cut_by_cost(const SeqTable &tab, int32_t G, int32_t Hkv, StreamShares *sh)
+struct StreamRegions {  // `count` regions of R rows by KV heads, each with the same items
+    int32_t R, full_len, count, items;
+    int64_t cost;
+};
+
+// Whether the items of a list are dealt by length (StreamShares) or taken as listed: the latter where it leaves no
+// workgroup more than 1/kEvenShare above the mean.  Dealing evens the loads but takes a round's workgroups apart, which costs most where
+// an item is short (28/4 heads, blocks of 196 over 34 K tokens, most load 1.047 of the mean: 272 us as listed, 281 dealt), and the
+// builder's time.  Dealt / listed over 79 layouts (28/4 and 32/8 heads, 22 K to 100 K tokens, blocks of 128 to 6100), by the
+// most load as listed: up to 1.055 of the mean 0.95 to 1.06, 1.007 on average; to 1.08 0.95 to 1.01, 0.987; to 1.13 0.94 to 1.03, 0.985;
+// above 0.71 to 1.01, 0.92.  The lengths of a run of equal regions repeat, and so do the workgroups that listed ones fall to:
+// one period is looked at, 224 items of 28/4 heads in blocks of 1024 (3 us of host time with the cut; 18 us for 100 K tokens in blocks of
+// 3136, which run for 3 ms).
+constexpr int32_t kEvenShare = 18;
+static bool worth_dealing(const StreamRegions *list, int32_t n, int64_t total, int32_t G, const StreamShares &sh)
 {
-    struct Regions {  // `count` regions of R rows, each Hkv times the same items
-        int32_t R, full_len, count, items;
-        int64_t cost;
-    };
+    constexpr int32_t W = kMaxWgsPerXcd, kMaxItems = 512;
+    int64_t load[kXcds][W] = {};
+    int32_t at = 0;  // items before list[r]
+    for (int32_t r = 0; r < n; ++r) {
+        const int32_t P = list[r].items, end = at + list[r].count * P;
+        if (P > kMaxItems) return true;
+        int32_t cost[kMaxItems];
+        for (int32_t j = 0; j < P; ++j) cost[j] = stream_item_cost(list[r].R, list[r].full_len, G, j);
+        const int32_t period = P / std::gcd(P, W) * W;
+        for (int32_t x = 0; x < kXcds; ++x) {
+            const int32_t lo = std::max(at, sh.first[x]), m = std::min(end, sh.first[x + 1]) - lo;
+            if (m <= 0) continue;
+            int32_t j = (lo - at) % P, w = (lo - sh.first[x]) % W;
+            const int64_t times = m / period;
+            const int32_t once_more = m % period;
+            for (int32_t t = 0; t < std::min(m, period); ++t) {
+                load[x][w] += cost[j] * (times + (t < once_more ? 1 : 0));
+                j = j + 1 < P ? j + 1 : 0;
+                w = w + 1 < W ? w + 1 : 0;
+            }
+        }
+        at = end;
+    }
+    int64_t most = 0;
+    for (const auto &xcd : load) most = std::max(most, *std::max_element(xcd, xcd + W));
+    return most * (kXcds * W) * kEvenShare > total * (kEvenShare + 1);
+}
+
+// First item of every XCD: the list cut into kXcds runs that take the same time, to within an item.  Returns whether the
+// items are to be dealt.
+static bool cut_by_cost(const SeqTable &tab, int32_t G, int32_t Hkv, StreamShares *sh)
+{
     const auto cost_of = [&](int32_t R, int32_t full_len) {
         int64_t c = 0;
         for (int32_t j = 0, n = stream_items_of_region(R, G); j < n; ++j) c += stream_item_cost(R, full_len, G, j);
         return c;
     };
-    Regions list[3 * kMaxSeqsPerLaunch];
+    StreamRegions list[3 * kMaxSeqsPerLaunch];
     int32_t n = 0;
     int64_t total = 0;
     const auto add = [&](int32_t R, int32_t full_len, int32_t count) {
@@ -361,6 +406,7 @@ static void cut_by_cost(const SeqTable &tab, int32_t G, int32_t Hkv, StreamShare
         before += all;
     }
     for (; x <= kXcds; ++x) sh->first[x] = at;
+    return worth_dealing(list, n, total, G, *sh);
 }
 
 static int32_t compute_units();
@@ -771,7 +817,7 @@ static pevlm_status prefill_impl(const void *q, const void *k, const void *v, vo
         const int32_t G = heads->n_q_heads / heads->n_kv_heads;
         StreamParams sp;
         sp.shares.wgs = std::min(std::max(compute_units() / kXcds, 1), kMaxWgsPerXcd);
-        bool whole = layout->num_seqs <= kMaxSeqsPerLaunch && sp.shares.wgs == kMaxWgsPerXcd;  // one chunk: its builder sees the whole list
+        bool whole = layout->num_seqs <= kMaxSeqsPerLaunch && sp.shares.wgs == kMaxWgsPerXcd, deal = false;  // one chunk: its builder sees the whole list
         int32_t offset = 0;
         for (int32_t s0 = 0; s0 < layout->num_seqs; s0 += kMaxSeqsPerLaunch) {
             SeqTable tab;
@@ -781,12 +827,12 @@ static pevlm_status prefill_impl(const void *q, const void *k, const void *v, vo
                 tab.item_base[i + 1] = tab.item_base[i] + stream_items_of_seq(tab.sink[i], tab.block[i], tab.ctx[i], G, heads->n_kv_heads,
                                                                               tab.sel_first[i], tab.sel_count[i], tab.sel_sink);
             if (s0 == 0) {
-                if (whole) cut_by_cost(tab, G, heads->n_kv_heads, &sp.shares);
+                if (whole) deal = cut_by_cost(tab, G, heads->n_kv_heads, &sp.shares);
                 for (int32_t x = 0; x < kXcds; ++x) whole = whole && sp.shares.first[x + 1] - sp.shares.first[x] <= kDealtItems;
                 if (!whole) for (int32_t x = 0; x <= kXcds; ++x) sp.shares.first[x] = (int32_t)(n_stream * x / kXcds);
             }
             if (tab.item_base[n] > 0) {
-                hipError_t e = launch_build_stream_items(tab, G, heads->n_kv_heads, p.heads, sitems, offset, sp.shares, order, whole, hs);
+                hipError_t e = launch_build_stream_items(tab, G, heads->n_kv_heads, p.heads, sitems, offset, sp.shares, order, whole && deal, hs);
                 if (e != hipSuccess) return hip_fail(e, "stream-item builder launch");
             }
             offset += tab.item_base[n];

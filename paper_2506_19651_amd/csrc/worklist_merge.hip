@@ -51,12 +51,8 @@ struct DealtSeq {
     DealtRegion region[3];
 };
 
-// The order of one XCD's items (one workgroup): as listed where that leaves no workgroup more than 1/kEvenShare above the mean (a
-// round's workgroups then stay closer together: 100 K tokens in blocks of 392, most load 1.02 of the mean, 1228 us as
-// listed and 1250 dealt), else as StreamShares says.  Keys are all different: equal
-// costs go by their place.
+// The order of one XCD's items (one workgroup), as StreamShares says.  Keys are all different: equal costs go by their place.
 constexpr int32_t kDealThreads = 512;
-constexpr int32_t kEvenShare = 28;
 // keys v[0 .. N) above mine; a short loop, since what is fetched of a kernel that runs once costs more than its cycles
 template <int N>
 __device__ __forceinline__ int32_t keys_above(const uint32_t *v, uint32_t mine)
@@ -76,7 +72,7 @@ __device__ __forceinline__ void deal_stream_items(const SeqTable &tab, int32_t G
 {
     constexpr int32_t W = kMaxWgsPerXcd, TAIL = kDealtRounds * W;
     __shared__ __attribute__((aligned(16))) uint32_t key[kDealtItems];  // cost * 2^7 + 127 - place % 128
-    __shared__ __attribute__((aligned(16))) uint32_t tail[TAIL], load[W], listed[W];  // load: sum of costs * 2^5 + workgroup
+    __shared__ __attribute__((aligned(16))) uint32_t tail[TAIL], load[W];  // load: sum of costs * 2^5 + workgroup
     __shared__ DealtSeq seqs[kMaxSeqsPerLaunch];
     __shared__ uint2 sorted[TAIL];  // (item, cost)
     const int32_t tid = threadIdx.x, lo = sh.first[xcd], n = sh.first[xcd + 1] - lo;
@@ -95,10 +91,7 @@ __device__ __forceinline__ void deal_stream_items(const SeqTable &tab, int32_t G
         d.last = d.blocks + (count > 0 ? (count - 1) * d.region[1].items * Hkv : 0);
         seqs[tid] = d;
     }
-    if (tid < W) {
-        load[tid] = (uint32_t)tid;
-        listed[tid] = 0u;
-    }
+    if (tid < W) load[tid] = (uint32_t)tid;
     __syncthreads();
     for (int32_t i = tid; i < n; i += kDealThreads) {
         const int32_t idx = lo + i;
@@ -109,19 +102,8 @@ __device__ __forceinline__ void deal_stream_items(const SeqTable &tab, int32_t G
         const DealtRegion r = d.region[in_sink ? 0 : (in_last ? 2 : 1)];
         const uint32_t c = stream_item_cost(r.R, r.full_len, G, (idx - (in_sink ? d.base : (in_last ? d.last : d.blocks))) % r.items);
         key[i] = (c << 7) + (uint32_t)(127 - i % 128);
-        atomicAdd(&listed[i % W], c);
     }
     __syncthreads();
-    uint32_t sum = 0u, most = 0u;
-#pragma unroll 4
-    for (int32_t w = 0; w < W; ++w) {
-        sum += listed[w];
-        most = listed[w] > most ? listed[w] : most;
-    }
-    if ((uint64_t)most * W * kEvenShare <= (uint64_t)sum * (kEvenShare + 1)) {
-        for (int32_t i = tid; i < rounds * W; i += kDealThreads) seg[i % W * rounds + i / W] = i < n ? lo + i : -1;
-        return;
-    }
     const int32_t t0 = plain * W, m = n - t0;  // at most TAIL items are left
     if (tid < TAIL) tail[tid] = tid < m ? key[t0 + tid] : (uint32_t)tid;
     for (int32_t i = tid; i < t0; i += kDealThreads) {
@@ -147,7 +129,7 @@ __device__ __forceinline__ void deal_stream_items(const SeqTable &tab, int32_t G
 }
 
 // Same for the stream items of the bf16 streaming block-prefill kernel (item_base counts stream items) and their order: the
-// first kXcds workgroups deal it out if the chunk is the whole list, otherwise every thread lists its own item.
+// first kXcds workgroups deal it out where that pays (the chunk is then the whole list), otherwise every thread lists its own item.
 __global__ __launch_bounds__(kDealThreads) void build_stream_items_kernel(SeqTable tab, int32_t G, int32_t Hkv, HeadTable heads,
                                                                           pevlm_stream_item *items, int32_t item_offset, StreamShares shares,
                                                                           int32_t *order, int32_t dealers)
@@ -175,9 +157,9 @@ __global__ __launch_bounds__(kDealThreads) void build_stream_items_kernel(SeqTab
 }
 
 hipError_t launch_build_stream_items(const SeqTable &tab, int32_t G, int32_t Hkv, const HeadTable &heads, pevlm_stream_item *items,
-                                     int32_t item_offset, const StreamShares &shares, int32_t *order, bool whole, hipStream_t stream)
+                                     int32_t item_offset, const StreamShares &shares, int32_t *order, bool deal, hipStream_t stream)
 {
-    const int32_t total = tab.item_base[tab.num_seqs], dealers = whole ? kXcds : 0;
+    const int32_t total = tab.item_base[tab.num_seqs], dealers = deal ? kXcds : 0;
     hipLaunchKernelGGL(build_stream_items_kernel, dim3(dealers + (total + kDealThreads - 1) / kDealThreads), dim3(kDealThreads), 0, stream, tab, G, Hkv,
                        heads, items, item_offset, shares, order, dealers);
     return hipGetLastError();

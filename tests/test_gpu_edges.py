@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import paper_2506_19651_amd as P
+from paper_2506_19651_amd import cost_model
 import workloads as W
 from gpu_util import DEV, error_stats, layout_heads, oracle_layout, run_path, to_device, to_host_f32
 
@@ -348,6 +349,40 @@ def test_shares_of_the_streaming_kernel(Hq, Hkv, seqs):
         if mine and dealt:
             load = np.where(seg >= 0, cost[seg], 0).sum(axis=1)
             assert load.max() <= max(1.04 * load.mean(), load.mean() + cost[first[x]:first[x + 1]].max())
+
+
+@pytest.mark.parametrize("Hq,Hkv,seqs", [
+    (28, 4, [(196, 196, 33712, 0)]),                               # 7 items a head, even as listed
+    (32, 8, [(196, 196, 33712, 0)]),                               # 4, four workgroups of 32 always the longest
+    (28, 4, [(256, 1024, 32768, 0)]),                              # 28
+    (16, 8, [(392, 3136, 50000, 0)]),                              # 25 and a short last block
+    (14, 2, [(256, 1024, 256 * f, 0) for f in (33, 97, 41, 63)]),  # runs that end in another sequence
+    (6, 2, [(5, 64, 300 + 40 * i, 3) for i in range(48)]),         # as many sequences as a table holds
+    (12, 2, [(0, 640, 12800, 0), (700, 64, 0, 5), (0, 33, 1000, 0)]),
+])
+def test_items_are_dealt_where_listed_ones_come_out_uneven(Hq, Hkv, seqs):
+    """The rule looks at one period of a run of equal regions: as the loads of all listed items added up."""
+    lay, heads = P.Layout.from_seqs(seqs), P.Heads(Hq, Hkv, 128, "bf16")
+    q, k, v = (torch.zeros(lay.total_tokens, h, 128, device=DEV, dtype=torch.bfloat16) for h in (Hq, Hkv, Hkv))
+    ws = torch.zeros(P.pevlm_block_prefill_workspace_bytes(lay, heads), dtype=torch.uint8, device=DEV)
+    prev = P.pevlm_set_prefill_kernel("stream")
+    try:
+        P.pevlm_block_prefill_attn(q, k, v, torch.empty_like(q), lay, heads, workspace=ws)
+        tiles = np.array([it.n_tiles for it in P.pevlm_prefill_stream_items_host(lay, heads)])
+    finally:
+        P.pevlm_set_prefill_kernel(prev)
+    n, cus = len(tiles), torch.cuda.get_device_properties(0).multi_processor_count
+    shares = cost_model.stream_shares(tiles, len(seqs), cus)
+    order = ws.cpu().numpy()[(n * 160 + 255) // 256 * 256:].view(np.int32)
+    at = 0
+    for x in range(8):
+        mine = shares[x * (cus // 8):(x + 1) * (cus // 8)]
+        count = sum(len(i) for i in mine)
+        rounds = -(-count // len(mine))
+        for w, want in enumerate(mine):
+            got = order[at + x * len(mine) + w * rounds:][:rounds]
+            assert np.array_equal(tiles[got[got >= 0]], tiles[want]), (x, w)  # equal ones may stand for each other
+        at += count
 
 
 @pytest.mark.parametrize("Hq,Hkv,D,seqs,splits", [
