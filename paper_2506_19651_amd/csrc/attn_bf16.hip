@@ -69,7 +69,7 @@ __device__ __forceinline__ void attn_item(const AttnParams &p, int32_t logical, 
     // ends on short items has a shorter tail; where the items are dealt, the XCDs that share a group
     // take them in turn
     int32_t in_order = rest % p.n_items;
-    if (hg.deal_runs > 1) {
+    if (!PARTIAL && hg.deal_runs > 1) {
         // run r has the positions from ceil(r n / runs) on; what is left over goes, a shortest item each, where two XCDs
         // meet inside an item
         const int32_t run = in_order * hg.deal_runs / p.n_items, start = (run * p.n_items + hg.deal_runs - 1) / hg.deal_runs;
