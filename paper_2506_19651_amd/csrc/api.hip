@@ -832,7 +832,7 @@ static pevlm_status prefill_impl(const void *q, const void *k, const void *v, vo
                 if (!whole) for (int32_t x = 0; x <= kXcds; ++x) sp.shares.first[x] = (int32_t)(n_stream * x / kXcds);
             }
             if (tab.item_base[n] > 0) {
-                hipError_t e = launch_build_stream_items(tab, G, heads->n_kv_heads, p.heads, sitems, offset, sp.shares, order, whole && deal, hs);
+                hipError_t e = launch_build_stream_items(tab, G, heads->n_kv_heads, p.heads, sitems, offset, sp.shares, order, whole, deal, hs);
                 if (e != hipSuccess) return hip_fail(e, "stream-item builder launch");
             }
             offset += tab.item_base[n];

@@ -531,9 +531,9 @@ hipError_t launch_rope_table(float *table, bool question, const SeqTable &tab, i
                              hipStream_t stream);
 hipError_t launch_rope_mrope(void *q, void *k, int64_t T, int32_t Hq, int32_t Hkv, int32_t D, bool bf16, double rope_base,
                              const int32_t *pos3, int32_t sec0, int32_t sec01, float *table, hipStream_t stream);
-// the list's items of one chunk of sequences, and their order: dealt by length (the chunk is the whole list) or as listed
+// the list's items of one chunk of sequences, and their order: as listed or (the chunk is the whole list) dealt by length
 hipError_t launch_build_stream_items(const SeqTable &tab, int32_t G, int32_t Hkv, const HeadTable &heads, pevlm_stream_item *items,
-                                     int32_t item_offset, const StreamShares &shares, int32_t *order, bool deal, hipStream_t stream);
+                                     int32_t item_offset, const StreamShares &shares, int32_t *order, bool whole, bool deal, hipStream_t stream);
 // block-prefill rows of bf16 tensors from a stream-item list, 8 * shares.wgs workgroups of 8 wavefronts
 hipError_t launch_attn_bf16_stream(const StreamParams &p, int32_t D, hipStream_t stream);
 hipError_t launch_fp8_setup(const SeqTable &tab, const Fp8TileBases &bases, const Fp8ItemBases &items_of, pevlm_work_item *key_tiles,

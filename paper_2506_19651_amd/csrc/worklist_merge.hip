@@ -51,7 +51,8 @@ struct DealtSeq {
     DealtRegion region[3];
 };
 
-// The order of one XCD's items (one workgroup), as StreamShares says.  Keys are all different: equal costs go by their place.
+// The order of one XCD's items (one workgroup), as StreamShares says where they are dealt.  Keys are all different: equal costs go by
+// their place.
 constexpr int32_t kDealThreads = 512;
 // keys v[0 .. N) above mine; a short loop, since what is fetched of a kernel that runs once costs more than its cycles
 template <int N>
@@ -68,7 +69,7 @@ __device__ __forceinline__ int32_t keys_above(const uint32_t *v, uint32_t mine)
     }
     return rank;
 }
-__device__ __forceinline__ void deal_stream_items(const SeqTable &tab, int32_t G, int32_t Hkv, const StreamShares &sh, int32_t xcd, int32_t *order)
+__device__ __forceinline__ void deal_stream_items(const SeqTable &tab, int32_t G, int32_t Hkv, const StreamShares &sh, int32_t xcd, int32_t *order, int32_t deal)
 {
     constexpr int32_t W = kMaxWgsPerXcd, TAIL = kDealtRounds * W;
     __shared__ __attribute__((aligned(16))) uint32_t key[kDealtItems];  // cost * 2^7 + 127 - place % 128
@@ -78,6 +79,10 @@ __device__ __forceinline__ void deal_stream_items(const SeqTable &tab, int32_t G
     const int32_t tid = threadIdx.x, lo = sh.first[xcd], n = sh.first[xcd + 1] - lo;
     const int32_t rounds = ceil_div(n, W), plain = rounds > kDealtRounds ? rounds - kDealtRounds : 0;  // rounds dealt there and back
     int32_t *const seg = order + share_segment(sh, xcd);
+    if (!deal) {
+        for (int32_t i = tid; i < rounds * W; i += kDealThreads) seg[i % W * rounds + i / W] = i < n ? lo + i : -1;
+        return;
+    }
     const int32_t num_seqs = tab.num_seqs;
     if (tid < num_seqs) {
         const int32_t S = tab.sink[tid], B = tab.block[tid], C = tab.ctx[tid], first = tab.sel_first[tid], count = C > 0 ? tab.sel_count[tid] : 0;
@@ -129,13 +134,14 @@ __device__ __forceinline__ void deal_stream_items(const SeqTable &tab, int32_t G
 }
 
 // Same for the stream items of the bf16 streaming block-prefill kernel (item_base counts stream items) and their order: the
-// first kXcds workgroups deal it out where that pays (the chunk is then the whole list), otherwise every thread lists its own item.
+// first kXcds workgroups list it or deal it out if the chunk is the whole list, otherwise every thread lists its own item (the 12.7 K items
+// of 100 K tokens in blocks of 392, by the threads 10.6 us).
 __global__ __launch_bounds__(kDealThreads) void build_stream_items_kernel(SeqTable tab, int32_t G, int32_t Hkv, HeadTable heads,
                                                                           pevlm_stream_item *items, int32_t item_offset, StreamShares shares,
-                                                                          int32_t *order, int32_t dealers)
+                                                                          int32_t *order, int32_t dealers, int32_t deal)
 {
     if ((int32_t)blockIdx.x < dealers) {
-        deal_stream_items(tab, G, Hkv, shares, blockIdx.x, order);
+        deal_stream_items(tab, G, Hkv, shares, blockIdx.x, order, deal);
         return;
     }
     int32_t i = ((int32_t)blockIdx.x - dealers) * kDealThreads + threadIdx.x;
@@ -157,11 +163,11 @@ __global__ __launch_bounds__(kDealThreads) void build_stream_items_kernel(SeqTab
 }
 
 hipError_t launch_build_stream_items(const SeqTable &tab, int32_t G, int32_t Hkv, const HeadTable &heads, pevlm_stream_item *items,
-                                     int32_t item_offset, const StreamShares &shares, int32_t *order, bool deal, hipStream_t stream)
+                                     int32_t item_offset, const StreamShares &shares, int32_t *order, bool whole, bool deal, hipStream_t stream)
 {
-    const int32_t total = tab.item_base[tab.num_seqs], dealers = deal ? kXcds : 0;
+    const int32_t total = tab.item_base[tab.num_seqs], dealers = whole ? kXcds : 0;
     hipLaunchKernelGGL(build_stream_items_kernel, dim3(dealers + (total + kDealThreads - 1) / kDealThreads), dim3(kDealThreads), 0, stream, tab, G, Hkv,
-                       heads, items, item_offset, shares, order, dealers);
+                       heads, items, item_offset, shares, order, dealers, (int32_t)deal);
     return hipGetLastError();
 }
 
