@@ -49,7 +49,9 @@ typedef enum {
 } pevlm_status;
 
 typedef enum {
-    PEVLM_F32 = 0,  /* fp32 storage and arithmetic (fp32 matrix cores; the numerical anchor)       */
+    PEVLM_F32 = 0,  /* fp32 storage, products and sums: the numerical anchor.  Products on the fp32 matrix cores, or on
+                       the bf16 ones over operands split exactly into three parts, of which six of the nine part products are
+                       taken; either way no further from the same attention in 64 bits than fp32 products are */
     PEVLM_BF16 = 1  /* bf16 storage, bf16 MFMA with fp32 accumulation and fp32 softmax             */
 } pevlm_dtype;
 

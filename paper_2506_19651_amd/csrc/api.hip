@@ -473,9 +473,11 @@ static QueryPlan carve_query(int64_t tiles, int64_t total_q, const pevlm_heads *
 
 // Split count when the caller leaves it to the library.
 //
-// fp32: splits_of_f32 (64 question rows x 28/4 heads over 2.4 K keys: 36 us at 16 splits, 51 at 9); where that does not go,
-// workgroups (16 rows x two heads x split) are brought as close as possible to one or two full rounds of 2 x CUs from below,
-// with at least 256 keys per split.
+// fp32: splits_of_f32 (64 question rows x 28/4 heads over 2.4 K keys: 36 us at 16 splits, 51 at 9); where that does not go, pairs
+// of workgroups (16 rows x one head x split) are brought as close as possible to one or two full rounds of 2 x CUs from below,
+// with at least 256 keys per split.  That is the count of a kernel that took two heads a workgroup, and scratch sizes follow from it;
+// a workgroup has one head now, and more splits are faster (64 rows x 32/8 heads over 2.4 K keys 51 us at its 8, 39 at 24; 16 rows 23
+// at 9, 21 at 16; 21 rows x 14/2 heads x 64 over 1 K keys 15 at 3, 11 at 8).
 //
 // bf16: the count with the least predicted time.  A workgroup (128 (row, head) pairs x split) takes 6 us plus a
 // time per key tile that depends on how full the compute units are, workgroups run in rounds of two per

@@ -4,12 +4,12 @@
 //
 // attn_f32_group, where it gives every compute unit a workgroup: all heads of a KV group together, 128 (row, head) columns to a
 // workgroup of 4 wavefronts, on the bf16 matrix instructions: every fp32 value is split into three bf16 ones that add up to it
-// exactly, and six of their nine products are taken (the others are below 2^-26 of the whole).  Six bf16 instructions take 192
-// cycles where the fp32 ones take 512, and leave the vector ALU its cycles.  K and V are split once per workgroup, on their way
-// into LDS.  Prefill of 2304 rows (sink 256, two blocks of 1024) x 28/4 heads x 128: 272 us on the fp32 instructions (two heads
-// x 16 rows, 56 % of the time matrix instructions, every wavefront loading its own keys), 180 now; 20.7 K rows 2350 -> 1360 us,
-// 1.2 PFLOP/s of bf16 products.  Distance to the same attention in 64 bits 1.8e-7, 2.9e-7 before.  Bound: the bf16 matrix
-// instructions, and with few workgroups their unequal lengths.
+// exactly, and six of their nine products are taken (the others come to 2^-27 of the product, root mean square).  Six bf16
+// instructions take 192 cycles where the fp32 ones take 512, and leave the vector ALU its cycles.  K and V are split once per
+// workgroup, on their way into LDS.  Prefill of 2304 rows (sink 256, two blocks of 1024) x 28/4 heads x 128: 261 us on the fp32
+// instructions (two heads x 16 rows, 56 % of the time matrix instructions, every wavefront loading its own keys), 170 now; 20.7 K
+// rows 2350 -> 1360 us, 1.2 PFLOP/s of bf16 products.  Distance to the same attention in 64 bits 1.8e-7, 2.9e-7 before.  Bound: the
+// bf16 matrix instructions, and with few workgroups their unequal lengths.
 //
 // attn_f32_single elsewhere: one head on 16 columns of v_mfma_f32_16x16x4_f32; the 4 wavefronts take the item's key tiles in turn,
 // each with an online softmax of its own, and are joined at the end by the log-sum-exp identity, so that an item of a few
@@ -17,8 +17,8 @@
 // contraction and of the output rows is free, and is chosen so that a lane feeds 4 MFMA steps from one 16-byte load.
 //
 // A key that a row must not see enters its value MFMAs with the weight 0, which hides every finite value but not an
-// infinite or invalid one (nor one that overflows its first bf16 part).  Such a value leaves a NaN in the row, so rows that do
-// not come out finite are done again over the keys that they see and no others (attn_f32_row).
+// infinite or invalid one (nor one that overflows its first bf16 part, from 2^104 on).  Such a value leaves a NaN in the row, so
+// rows that do not come out finite are done again over the keys that they see and no others (attn_f32_row).
 #include <algorithm>
 #include <type_traits>
 
@@ -42,8 +42,9 @@ struct F32Shared {
     F32Row<D> row[NW];                // attn_f32_row
 };
 
-// exp(d * scale) for c = scale * log2(e): two instructions where expf takes twelve.  The product is rounded once, as the argument
-// of expf was.
+// exp(d * scale) for c = scale * log2(e): two instructions where expf takes twelve.  c and the product are rounded where expf's
+// argument was rounded once; the outputs' distance to 64 bits does not show it (28/4 heads x 384 rows 2.894e-7, 2.889e-7 with expf; 2/1 x
+// 104 rows 1.900e-7, 1.901e-7; 4/1 x 1.9 K rows 3.446e-7, 3.453e-7).
 __device__ __forceinline__ float weight_of(float d, float c) { return __builtin_amdgcn_exp2f(d * c); }
 __device__ __forceinline__ float other_half(float x)  // the value of lane ^ 32
 {
@@ -303,8 +304,8 @@ __device__ __forceinline__ int32_t attn_f32_single(const AttnParams &p, const pe
 
 // ---------------------------------------------------------------- all heads of a KV group, on bf16 matrix instructions
 // An fp32 value is the sum of three bf16 ones, to the last bit: x = x1 + x2 + x3, each the rounding of what the ones before
-// leave, each at most 2^-8 of the one before.  A product is then x1 y1 + (x1 y2 + x2 y1) + (x1 y3 + x2 y2 + x3 y1), bf16
-// products that are exact in fp32, but for x2 y3 + x3 y2 + x3 y3: 2^-23 of it at most, 2^-27 root mean square.
+// leave; the second is at most 2^-8 of x, the third 2^-17.  A product is then x1 y1 + (x1 y2 + x2 y1) + (x1 y3 + x2 y2 + x3 y1), bf16
+// products that are exact in fp32, but for x2 y3 + x3 y2 + x3 y3: 2^-24 of it at most, 2^-27 root mean square.
 //
 // x3 reaches down to the last bit of x, which bf16 does not hold as a normal number where x is below 2^-103.  Values and weights are
 // therefore taken kLift times as large, down to the smallest denormal (what then overflows does not come out finite).  Of keys

@@ -19,8 +19,10 @@ struct RopeRows {
 // Pair indices of a lane.  Two: 64 lanes take two tokens of 128-wide heads, 4 bytes each in bf16.  With eight (16 bytes) the eight
 // sines and cosines in a row are 8 KB of instructions, and a launch too small to run them more than a few times on a compute unit
 // waits for them to be fetched (about 0.37 us a KB); large launches are not faster for it.  us, eight / two: 104 tokens x
-// 28/4 heads 4.1 / 2.9 (fp32 5.6 / 3.3), 1152 5.7 / 5.0, 16 K 42.0 / 40.5, 66 K 222.5 / 211.6; 66 K x 32/8 heads 290 / 258; 3.3 K x
-// 32/8 heads 10.4 / 11.3.
+// 28/4 heads 4.1 / 2.9 (fp32 5.6 / 3.3), 1152 5.7 / 5.0, 16 K 42.0 / 40.5, 66 K 222.5 / 211.6; 66 K x 32/8 heads 290 / 258.  Passes over
+// the same 26 to 42 MB, which the L2s then hold, can be slower with two (32/8 heads, 2.5 K tokens 8.3 / 9.3, 3.3 K 11.1 / 11.6, 4.1 K 13.3 /
+// 14.9; 3.7 K 12.4 / 12.1): it depends on which XCD had the rows last.  On rows that come from further off two are faster at every size
+// (2.5 K 15.2 / 13.5, 3.3 K 18.2 / 17.5, 4.1 K 21.8 / 19.7), so there is no rule for it.
 constexpr int kPairsPerLane = 2;
 // a lane's values of one half of a row, as they lie in memory
 template <bool BF16>
