@@ -230,12 +230,13 @@ __host__ __device__ inline pevlm_stream_item stream_item(int32_t start, int32_t 
 // meets the same lengths again and again, since a region's items rise in length and come at a fixed stride: most and mean
 // load of 64 K tokens in blocks of 1024 x 28/4 heads 779 and 703 us, of four ragged videos 1.09 of the mean.  So the items
 // of a round are ranked by length and dealt there and back, and those of the last kDealtRounds rounds, sorted, go
-// round by round to the workgroups with the least load: 1.015 and 1.01 of the mean, 1.02 over other layouts.
+// round by round to the workgroups with the least load: 1.015 and 1.01 of the mean, 1.02 over other layouts.  Lists that are even
+// enough by themselves are taken in their order.
 // ------------------------------------------------------------------------------------------
 constexpr int32_t kXcds = 8;
 constexpr int32_t kMaxWgsPerXcd = 32;
 constexpr int32_t kDealtRounds = 4;
-constexpr int32_t kDealtItems = 4096;  // an XCD's share of a longer list is not dealt: 128 items a workgroup even out by themselves
+constexpr int32_t kDealtItems = 4096;  // costs that fit LDS: an XCD's share of a longer list stays as listed, even or not
 struct StreamShares {
     int32_t wgs;               // workgroups of an XCD
     int32_t first[kXcds + 1];  // first item of each XCD
